@@ -107,7 +107,9 @@ def csrc_sha1():
 VARIANT_NAME = {0: "k_group<2,2,2>", 1: "k_group<1,4,2>", 2: "k_group<1,2,2>", 3: "k_group<1,2,4>"}
 # pointwise kernels by item shape
 PW_NAME = {0: "k_pw<2,2,6,2>", 1: "k_pw<1,1,8,4>", 2: "k_pw_sk", 3: "k_pwb<2,2>", 4: "k_pwb<1,4>"}
-PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>"}
+PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>", 17: "k_skc<1,2,4,true>",
+            18: "k_skc<1,4,3,true>", 19: "k_skc<2,4,3,true>"}
+SKC_NAME = {16: "k_skc<1,1,4>", 17: "k_skc<1,2,4>", 18: "k_skc<1,4,3>", 19: "k_skc<2,4,3>"}
 DW_NAME = {0: "k_dw<1>", 1: "k_dw<2>"}
 C3_NAME = {0: "k_c3b<2,32,2>", 1: "k_c3b<2,64,2>", 2: "k_c3b<1,32,2>", 3: "k_c3b<1,64,2>", 4: "k_c3b<2,32,4>"}
 
@@ -188,6 +190,8 @@ def group_accounting(net, batch, session):
             kname = "k_dwpw<%d>" % cfg["variant"]
         elif cfg["kind"] == 7:
             kname = "k_dwt<%d>" % (cfg["variant"] + 1)
+        elif cfg["kind"] == 10 and cfg["variant"] in SKC_NAME:
+            kname = SKC_NAME[cfg["variant"]]
         elif cfg["kind"] == 10:
             kname = "k_c3s<%d,%d,%d>" % (1 if cfg["variant"] >= 8 else 9, net["layers"][f]["stride"],
                                          2 if info["tile_h"] * info["tile_w"] > 32 else 1)

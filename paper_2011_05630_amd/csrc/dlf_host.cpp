@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <limits>
 #include <memory>
 #include <mutex>
@@ -155,7 +156,7 @@ dlf_status pack_and_upload(Layer& L)
 // Fusion groups
 // ------------------------------------------------------------------------------------------
 
-enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12 };
+enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13 };
 
 struct TileCfg {
     int th, tw;      // tile of the group's final output tensor
@@ -185,7 +186,7 @@ struct GroupPlan {
     DlfDwPwArgs dp;
     DlfDwtArgs dt;
     DlfDwsArgs ds;
-    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn;
+    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn; DlfSkcArgs sk;
 };
 
 const int VAR_FC[DLF_NUM_VARIANTS] = {2, 1, 1, 1};
@@ -238,6 +239,8 @@ const int64_t C_PWB_BLOCK = 4000;           // block form, per round of two bloc
 const int64_t PWB_BYTES_PER_CYCLE = 28;     // rate at which a CU takes operand fragments in (block form of the pointwise kernel)
 const int64_t PW_BYTES_PER_CYCLE = 25;      // ... the per-wave forms, the 1x1 phase of the depthwise tile kernel, the FC kernel
 const int64_t C_PW_SK = 2000;               // split-K: exchange of partial sums through LDS
+const int64_t C_PW_SK_ONE = 100;            // ... with no more items than CUs: the whole item ...
+const int64_t C_PW_SK_STEP = 143;           // ... and per K step of it
 const int64_t C_PW_RES = 1000;              // residual loads
 const int64_t PW_HBM_BYTES_PER_CYCLE = 2000;
 // block 3x3 kernel: per work item (first stages of the ring, epilogue), per LDS stage of 16 input
@@ -300,6 +303,9 @@ const int64_t C_C3S_STEP = 128;
 const int64_t C_C3S_STEP_BIG = 215;
 const int64_t C_C3S_BIG_BYTES = 3 << 20;
 const int64_t C_C3S_RED = 1500;
+const int64_t C3S_SMALL_ITEMS = 128;
+const int64_t C_C3S_SMALL = 1200;
+const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_EPI = 2500;
 // the fused 3x3 -> 1x1 kernel for small maps: per work item (decode, first loads), bytes per cycle of
 // its LDS intake, cycles per MFMA of a SIMD, per K step of the first layer's weight ring (requests
@@ -318,6 +324,13 @@ const int64_t C_BN_PIXEL = 245;
 const int64_t C_BN_CHANNEL = 150;
 const int64_t C_BN_LAST = 5000;              // ... less without the last layer
 const int64_t C3PW_OVERLAP_PCT = 60;         // two workgroups per CU: what a further round of items adds, in per cent of an item
+
+// split-K convolution kernel: a launch of one round trip, then the rate at which a CU takes operands in
+// (49 bytes per cycle for a workgroup alone on its CU, 34 if it gathers 32 pixels; several share the
+// first-level cache and its path to L2 and get 28 or 25 together).  Fitted to 10 layer shapes at batch 1, 2 and 4 in chains of 12 layers.
+const int64_t C_SKC_ITEM = -900;
+const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
+const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
 
 struct StageSpec {   // one stage, before tiling
     int layer;
@@ -793,7 +806,9 @@ uint64_t pw_shape_cost_ps(const Layer& L, int batch, int budget, int shape)
     }
     const int64_t step = std::max(C_PW_STEP[shape], std::min(items_cu, W) * C_PW_STEP_WAVE[shape]);
     const int64_t ks = PW_KSPLIT[shape];
-    const int64_t item = C_PW_ITEM + (L.nsteps / ks) * step + (ks > 1 ? C_PW_SK : 0) + has_res * C_PW_RES;
+    int64_t item = C_PW_ITEM + (L.nsteps / ks) * step + (ks > 1 ? C_PW_SK : 0) + has_res * C_PW_RES;
+    // split-K with one item per CU at most: measured 5.3 / 6.4 / 8.5 us at K = 256 / 512 / 1024
+    if (ks > 1 && items_cu <= 1) item = C_PW_SK_ONE + L.nsteps * C_PW_SK_STEP + has_res * C_PW_RES;
     // ... and never faster than the CU takes in the operand fragments of its items
     const int64_t stream = items_cu * L.nsteps * (FCs + FPs) * 1024 / PW_BYTES_PER_CYCLE;
     const int64_t compute = std::max(((items_cu + W - 1) / W) * item, stream);
@@ -1199,7 +1214,12 @@ uint64_t c3s_cost_ps(const Layer& L, int batch, int budget, const DlfC3sArgs& cs
                              (cs.tp > 32 ? 4 : 3) / 4 +        // one pixel block: half the MFMAs, the same weights
 
                          (cs.ksplit > 1 ? C_C3S_RED : 0) + C_C3S_EPI + (L.d.residual_from >= 0 ? C_PW_RES : 0);
-    const int64_t compute = C_LAT + rounds * item;
+    int64_t compute = C_LAT + rounds * item;
+    // half of the chip's CUs or fewer: the launch's fixed part is short and the K loop runs at the
+    // rate a CU takes eight waves' weights in (183 cycles per step: 45 bytes per cycle), not at the
+    // chip's matrix rate (256 channels at 14 x 14, batch 1 - 8: 8.3 - 8.5 us; 512 at 7 x 7: 11.4)
+    if (nitems <= (cs.taps == 9 ? C3S_SMALL_ITEMS : C3S_SMALL_ITEMS / 2) && rounds == 1)
+        compute = C_C3S_SMALL + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE + (int64_t)(cs.nsteps / cs.ksplit) * C_C3S_STEP_SMALL;
     const int64_t m = (int64_t)batch * L.out_h * L.out_w;
     const int64_t bytes = (int64_t)batch * L.in_h * L.in_w * L.d.cin * 2 + m * L.d.cout * 2 * (L.d.residual_from >= 0 ? 2 : 1) +
                           (int64_t)L.ncb * L.nsteps * 1024;
@@ -1419,6 +1439,84 @@ bool bneck_choose(const Layer& A, const Layer& B, const Layer& P, int batch, int
     return found;
 }
 
+// ---- split-K convolution for outputs of few pixels ----
+
+// Testing hook: mode 0 = by modelled cost, 1 = wherever it applies, 2 = never; shape >= 0 fixes the
+// item's shape, waves > 0 the waves per workgroup.
+struct SkcForce { int mode, shape, waves; };
+SkcForce g_skc_force = {0, -1, 0};
+const int SKC_TP[DLF_SKC_SHAPES] = {1, 1, 1, 2};        // 16-pixel blocks of an item
+const int SKC_TC[DLF_SKC_SHAPES] = {1, 2, 4, 4};        // 16-channel blocks of an item
+
+// A convolution the kernel can run, alone or with the 2x2 pool behind it, or a fully connected layer.
+bool skc_layer_ok(const Layer& L, int batch)
+{
+    const dlf_layer_desc& d = L.d;
+    if (d.op != DLF_CONV || L.im2col || L.rowfold) return false;
+    if ((d.cin % 32) != 0 || (d.cout % 4) != 0 || d.kh * d.kw > DLF_SKC_MAX_TAPS) return false;
+    if ((int64_t)L.ncb * L.nsteps * 1024 >= (int64_t)1 << 31) return false;
+    if ((int64_t)batch * L.in_h * L.in_w * L.in_c * 2 >= (int64_t)1 << 31) return false;
+    // items, pixels and rows are divided as 32-bit products
+    const int64_t m = (int64_t)batch * L.out_h * L.out_w;
+    return m <= 1 << 17 && m * std::max(L.out_h, L.out_w) < (int64_t)1 << 31 && m * d.cout * 2 < (int64_t)1 << 31;
+}
+
+void skc_fill(const Layer& L, const Layer* proj, int pool2, int batch, int shape, int waves, DlfSkcArgs& sk)
+{
+    memset(&sk, 0, sizeof sk);
+    sk.w = L.d_w; sk.bias = L.d_bias;
+    sk.in_bytes = (uint32_t)((int64_t)batch * L.in_h * L.in_w * L.in_c * 2);
+    sk.h = L.in_h; sk.w_ = L.in_w; sk.oh = L.out_h; sk.ow = L.out_w; sk.cin = L.d.cin; sk.cout = L.d.cout; sk.ncb = L.ncb;
+    sk.kw = L.d.kw; sk.kh = L.d.kh; sk.stride = L.d.stride; sk.pad = L.d.pad; sk.act = L.d.act; sk.pool2 = pool2;
+    sk.nk = L.nsteps / 2;
+    if (proj) {
+        sk.w2 = proj->d_w; sk.bias2 = proj->d_bias;
+        sk.in2_bytes = (uint32_t)((int64_t)batch * proj->in_h * proj->in_w * proj->in_c * 2);
+        sk.nk2 = proj->nsteps / 2; sk.cin2 = proj->d.cin; sk.stride2 = proj->d.stride; sk.h2 = proj->in_h; sk.w2_ = proj->in_w;
+    }
+    sk.m = batch * L.out_h * L.out_w;
+    sk.n_pg = ceil_div(sk.m, 16 * SKC_TP[shape]);
+    sk.n_cg = ceil_div(L.d.cout, 16 * SKC_TC[shape]);
+    // Waves per workgroup: four, two for short K (measured at 1, 2, 4, 8: K of 8 or 16 steps 0.2 us
+    // faster on two waves than on four, 64 steps and more 0.5 - 2 us slower; eight never pay: the
+    // operands' path into the CU is the limit, not the number of loads in flight).
+    sk.nw = waves > 0 ? waves : sk.nk + sk.nk2 <= 16 ? 2 : 4;
+    while (sk.nw > 1 && sk.nw / 2 >= sk.nk + sk.nk2) sk.nw /= 2;
+    sk.ksw = ceil_div(sk.nk + sk.nk2, sk.nw);
+    sk.pw = pool2 ? L.out_w / 2 : L.out_w;
+    sk.ph = pool2 ? L.out_h / 2 : L.out_h;
+    auto magic = [](int d) { return 0xFFFFFFFFu / (unsigned)d + 1u; };
+    sk.n_cg_m = magic(sk.n_cg); sk.pw_m = magic(sk.pw); sk.ph_m = magic(sk.ph);
+    sk.taps_m = magic(L.d.kh * L.d.kw); sk.kw_m = magic(L.d.kw);
+}
+
+uint64_t skc_cost_ps(const DlfSkcArgs& sk, int shape, int budget)
+{
+    const int64_t items = (int64_t)sk.n_pg * sk.n_cg;
+    const int64_t bytes = (int64_t)(sk.nk + sk.nk2) * (SKC_TP[shape] + SKC_TC[shape]) * 1024;
+    int64_t intake = bytes / SKC_BYTES_PER_CYCLE[shape];
+    if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
+    int64_t cycles = C_LAUNCH + C_SKC_ITEM + intake;
+    // The kernel is for launches of at most about one item per CU.  Beyond that the models of the
+    // kernels it competes with are too high (single layers on the fused-group kernel by up to 6 us), so
+    // it has to be ahead by a third there.
+    if (items > budget) cycles = cycles * 4 / 3;
+    return (uint64_t)(cycles * PS_PER_CYCLE);
+}
+
+bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, DlfSkcArgs& best, int& shape, uint64_t& cost)
+{
+    bool found = false;
+    for (int sh = 0; sh < DLF_SKC_SHAPES; ++sh) {
+        if (g_skc_force.shape >= 0 && sh != g_skc_force.shape) continue;
+        DlfSkcArgs sk;
+        skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
+        const uint64_t c = skc_cost_ps(sk, sh, budget);
+        if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
+    }
+    return found;
+}
+
 // ---- depthwise + 1x1 kernel for maps of many channels and few pixels ----
 
 bool dws_eligible(const dlf_net_s& net, int first, int last, int batch)
@@ -1513,9 +1611,8 @@ uint64_t fc_cost_ps(const Layer& L, int batch, int& ksplit)
     return best;
 }
 
-dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
-                      GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
-                      const C3Force* c3_force = nullptr)
+dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
+                            GroupPlan& g, const TileCfg* force_tc, int pw_mode, const C3Force* c3_force)
 {
     const TileCfg& force = force_tc ? *force_tc : g_force;
     const int pwm = pw_mode >= 0 ? pw_mode : g_pw_mode;
@@ -1864,6 +1961,54 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     return DLF_OK;
 }
 
+// The group on the cheapest kernel: the one of make_group_tiled, or the split-K convolution kernel.
+dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
+                      GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
+                      const C3Force* c3_force = nullptr)
+{
+    const dlf_status s = make_group_tiled(net, batch, first, last, budget, max_lds, g, force_tc, pw_mode, c3_force);
+    // a caller or a testing hook that names another kernel's form gets that kernel
+    const bool named = force_tc || pw_mode > 0 || c3_force || g_force.th > 0 || g_pw_mode != 0 || g_c3_force.mode != 0 ||
+                       g_c3_force.shape >= 0 || g_dw_mode != 0;
+    if (g_skc_force.mode == 2 || (named && g_skc_force.mode == 0)) return s;
+    if (first < 0 || last >= (int)net.L.size() || first > last || budget <= 0 || last > first + 1) return s;
+    const Layer& L0 = net.L[first];
+    const Layer* conv = nullptr;
+    const Layer* proj = nullptr;
+    int pool2 = 0;
+    if (pw2_eligible(net, first, last, batch)) {
+        conv = &net.L[last];
+        proj = &L0;
+    } else {
+        std::vector<StageSpec> specs;
+        std::string why;
+        int kind;
+        if (!group_stages(net, first, last, specs, kind, why) || kind != GK_GROUP || specs.size() != 1) return s;
+        conv = &L0;
+        pool2 = specs[0].pool2;
+    }
+    if (!skc_layer_ok(*conv, batch) || (proj && !skc_layer_ok(*proj, batch))) return s;
+    DlfSkcArgs sk;
+    int shape = 0;
+    uint64_t cost = 0;
+    if (!skc_choose(*conv, proj, pool2, batch, budget, sk, shape, cost)) return s;
+    if (s == DLF_OK && g_skc_force.mode != 1 && g.cost <= cost) return s;
+    g = GroupPlan();
+    g.first = first; g.last = last; g.budget = budget;
+    g.in_layer = conv->src;
+    if (proj) { g.res_layer = proj->src; g.res_stage = 0; }
+    else if (conv->d.residual_from >= 0) { g.res_layer = conv->d.residual_from; g.res_stage = 0; }
+    g.sk = sk;
+    g.kind = GK_SKC;
+    g.cost = cost;
+    g.variant = shape;
+    g.occ = 1;
+    g.grid = sk.n_pg * sk.n_cg;
+    g.th = 1; g.tw = 16 * SKC_TP[shape];
+    g.lds_bytes = sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024;
+    return DLF_OK;
+}
+
 }  // namespace
 
 struct dlf_plan_s {
@@ -2170,25 +2315,20 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
         // cost[f][l][b] for every contiguous range and budget; infeasible = no entry
         const uint64_t INF = std::numeric_limits<uint64_t>::max();
         const int nb = (int)budgets.size();
-        std::vector<GroupPlan> table((size_t)n * n * nb);
-        std::vector<char> ok((size_t)n * n * nb, 0);
+        // (a range that cannot be a group does not end the scan: longer ranges starting at the same
+        // layer may still be, e.g. conv + pool + conv)
+        std::deque<GroupPlan> table;                               // the groups that exist ...
+        std::vector<int> at((size_t)n * n * nb, -1);               // ... and where a range's group is
         auto idx = [&](int f, int l, int b) { return ((size_t)f * n + l) * nb + b; };
         for (int f = 0; f < n; ++f)
-            for (int l = f; l < n; ++l) {
-                bool any = false;
+            for (int l = f; l < n; ++l)
                 for (int b = 0; b < nb; ++b) {
-                    GroupPlan gp;
-                    if (make_group(*net, batch, f, l, budgets[b], max_lds, gp) == DLF_OK) {
-                        table[idx(f, l, b)] = gp;
-                        ok[idx(f, l, b)] = 1;
-                        any = true;
-                    }
+                    table.emplace_back();
+                    if (make_group(*net, batch, f, l, budgets[b], max_lds, table.back()) == DLF_OK)
+                        at[idx(f, l, b)] = (int)table.size() - 1;
+                    else
+                        table.pop_back();
                 }
-                if (!any && l > f) {
-                    // a range that cannot be a group: longer ranges starting at f may still be
-                    // (e.g. conv + pool + conv), so keep scanning
-                }
-            }
         // best[i] = best plan for the suffix starting at layer i under the total order
         // (cost, number of groups, group_last lexicographic, budgets lexicographic)
         struct Sfx { uint64_t cost; int ngroups; std::vector<int> lasts, buds; bool valid; };
@@ -2199,10 +2339,10 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
             for (int l = i; l < n; ++l) {
                 if (!best[l + 1].valid) continue;
                 for (int b = 0; b < nb; ++b) {
-                    if (!ok[idx(i, l, b)]) continue;
+                    if (at[idx(i, l, b)] < 0) continue;
                     Sfx c;
                     c.valid = true;
-                    c.cost = table[idx(i, l, b)].cost + best[l + 1].cost;
+                    c.cost = table[at[idx(i, l, b)]].cost + best[l + 1].cost;
                     c.ngroups = 1 + best[l + 1].ngroups;
                     c.lasts.push_back(l);
                     c.lasts.insert(c.lasts.end(), best[l + 1].lasts.begin(), best[l + 1].lasts.end());
@@ -2226,7 +2366,7 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
             const int last = best[0].lasts[g];
             int bi = 0;
             for (int b = 0; b < nb; ++b) if (budgets[b] == best[0].buds[g]) { bi = b; break; }
-            groups.push_back(table[idx(first, last, bi)]);
+            groups.push_back(table[at[idx(first, last, bi)]]);
             first = last + 1;
         }
     } else if (o.mode == DLF_TUNER_GREEDY) {
@@ -2364,8 +2504,10 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
 {
     if (!plan || g < 0 || g >= (int)plan->G.size()) return fail(DLF_ERR_INVALID_ARG, "bad group index");
     const GroupPlan& G = plan->G[g];
-    if (kind) *kind = G.kind;
-    if (variant) *variant = G.variant;
+    // the split-K convolution is reported as a form of the small-map kernel, with a projection as
+    // one of the two-operand kind
+    if (kind) *kind = G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
+    if (variant) *variant = G.kind != GK_SKC ? G.variant : 16 + G.variant;
     if (nslices) *nslices = G.kind == GK_GROUP ? G.ga.nslices : 1;
     if (slice_c) *slice_c = G.kind == GK_GROUP ? G.ga.slice_c : 0;
     if (stream0) *stream0 = G.kind == GK_GROUP ? G.ga.stream0 : 0;
@@ -2391,6 +2533,12 @@ void dlf_debug_depthwise_tile(int32_t wx, int32_t rw) { g_dwt_force = DwtForce{w
 void dlf_debug_block3x3_mode(int32_t mode, int32_t shape, int32_t th, int32_t tw)
 {
     g_c3_force = C3Force{(mode >= 0 && mode <= 2) ? mode : 0, shape, th, tw};
+}
+
+void dlf_debug_small_mode(int32_t mode, int32_t shape, int32_t waves)
+{
+    g_skc_force = SkcForce{(mode >= 0 && mode <= 2) ? mode : 0, shape < DLF_SKC_SHAPES ? shape : -1,
+                           waves == 1 || waves == 2 || waves == 4 || waves == 8 ? waves : 0};
 }
 
 void dlf_debug_force_ksplit(int32_t ksplit) { g_force.ksplit = ksplit > 0 ? ksplit : 1; }
@@ -2485,6 +2633,15 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
         DlfBnArgs bn = G.bn;
         bn.in = in; bn.out = out;
         e = dlf_launch_bneck(&bn, G.grid, G.lds_bytes, stream);
+    } else if (G.kind == GK_SKC) {
+        DlfSkcArgs sk = G.sk;
+        sk.in = in; sk.out = out;
+        if (G.res_stage >= 0) {
+            if (!res) return fail(DLF_ERR_INVALID_ARG, "group [%d,%d] needs its second operand", G.first, G.last);
+            if (sk.nk2 > 0) sk.in2 = res;
+            else sk.res = res;
+        }
+        e = dlf_launch_skc ? dlf_launch_skc(&sk, G.variant, stream) : (int)hipErrorInvalidDeviceFunction;
     } else if (G.kind == GK_DWS) {
         DlfDwsArgs ds = G.ds;
         ds.in = in; ds.out = out;

@@ -363,6 +363,34 @@ struct DlfBnArgs {
     int32_t nsl;          // slices of the last layer's channels: ceil(ncb2 / 8)
 };
 
+// One convolution (any filter of up to 25 taps, any stride; optionally with the 2x2 max pool behind
+// it folded in, a residual operand, or a second 1x1 operand pair added before the activation), or a
+// fully connected layer, for outputs so small that the latency of one workgroup is the launch: a
+// workgroup of `nw` waves computes 16 * TP pixels x 16 * TC channels, each wave over its own share of
+// K with all of its operands requested at once; the partial sums meet in LDS.
+#define DLF_SKC_SHAPES 4             // (TP, TC): 0 = (1, 1), 1 = (1, 2), 2 = (1, 4), 3 = (2, 4)
+#define DLF_SKC_MAX_TAPS 25
+struct DlfSkcArgs {
+    const void* in;       // [batch][h][w][cin] fp16
+    const void* in2;      // second operand pair: [batch][h2][w2][cin2] fp16, or null
+    const void* res;      // residual operand, output shape, or null
+    void* out;            // [batch][oh][ow][cout] fp16 ([batch][oh/2][ow/2][cout] with pool2)
+    const void* w;        // packed fragments, K step = (32-channel chunk, tap, half)
+    const void* w2;       // packed fragments of the second pair
+    const float* bias;    // padded to ncb * 32
+    const float* bias2;   // ... of the second pair
+    uint32_t in_bytes, in2_bytes, res_bytes;  // sizes of the tensors read (below 2 GiB each)
+    int32_t h, w_, oh, ow, cin, cout, ncb;
+    int32_t kw, kh, stride, pad, act, pool2;
+    int32_t nk, nk2;      // 32-channel K steps of the first / second pair (cin / 32 * taps, cin2 / 32)
+    int32_t cin2, stride2, h2, w2_;
+    int32_t m;            // output pixels; with pool2 the convolution pixels of the pooled windows, window by window
+    int32_t n_pg, n_cg;   // groups of 16 * TP pixels, of 16 * TC channels
+    int32_t nw, ksw;      // waves per workgroup (1, 2, 4 or 8), K steps per wave
+    int32_t pw, ph;       // columns and rows of the map `m` counts (of pooled pixels with pool2)
+    uint32_t n_cg_m, pw_m, ph_m, taps_m, kw_m;   // reciprocals for division by n_cg, pw, ph, kh * kw, kw
+};
+
 struct DlfGapArgs {
     const void* x;        // [batch][hw][c]
     void* y;              // [batch][c]
@@ -390,6 +418,8 @@ int dlf_launch_dws(const DlfDwsArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_c3s(const DlfC3sArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_c3pw(const DlfC3PwArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, void* stream);
+// (weak: a host-only build of the planner, which launches nothing, links without it)
+__attribute__((weak)) int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream);
 int dlf_kernels_init(void);
 // Attaches a start / stop event pair (hipEvent_t, either may be null) to this thread's next launch.
 void dlf_next_launch_events(void* start, void* stop);

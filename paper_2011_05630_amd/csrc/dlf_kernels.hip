@@ -4051,6 +4051,182 @@ __global__ __launch_bounds__(256) void k_fc_fin(const DlfFcArgs a)
     }
 }
 
+// Convolutions of few outputs: the layers of small batches, where the other kernels' launches last two or
+// three times what an empty one does because few workgroups walk a long K each (256 -> 256 3x3 at 14 x 14,
+// batch 1: 16 workgroups, 8.3 us; 1024 -> 256 1x1: 16 workgroups, 8.5 us; a launch that reads and writes
+// one value takes 4.1).
+//
+// Work item = 16 * TP pixels x 16 * TC channels, one workgroup of up to four waves, an item per CU where the
+// layer has that many; K is dealt to the waves in contiguous shares of 32-channel steps, each wave keeps D
+// steps' operands in flight, and the partial sums meet in LDS.  No operand passes through LDS: the waves
+// share none.  What bounds an item is the CU's vector-memory path: it takes in (TP + TC) KiB per step at
+// 49 bytes per cycle of 2.15 GHz (of the path's 64), so the planner prices the shapes by that.  Deeper
+// rings (up to 18 steps) and 8 or 16 waves were measured and are slower: the loads beyond a share cost
+// issue slots though they fetch nothing, a workgroup of 16 waves takes 0.5 us longer to start, and streaming
+// hints on the weights cost 0.3 - 2 us (the second item of an XCD finds them in its L2).
+// Measured at batch 1 (us per layer in a chain of 12, before -> after): 256 -> 256 3x3 at 14 x 14 8.3 -> 5.4;
+// 512 -> 512 3x3 at 7 x 7 11.6 -> 7.2, at 14 x 14 11.4 -> 8.4; 128 -> 128 3x3 at 28 x 28 8.7 -> 4.7; 1x1 pairs
+// 256 -> 1024 -> 256 at 14 x 14 6.6 -> 4.1, 512 -> 2048 -> 512 at 7 x 7 6.8 -> 4.5.
+//
+// v_mfma_f32_16x16x32_f16: its "A" operand is half of the rows of two consecutive packed 32-channel
+// fragments (runs of 256 bytes), its "B" operand 64 contiguous bytes of each of 16 pixels, gathered
+// through a buffer resource whose range check supplies the padding.
+template <int TP, int TC, int D, bool P2>
+__global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
+{
+    constexpr int P = 16 * TP, C = 16 * TC;
+    float* const part = (float*)lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q = lane >> 4;
+    // channel groups fastest: an XCD (item % 8) keeps to few groups' weights
+    const int pg = div_by((int)blockIdx.x, a.n_cg_m), cg = (int)blockIdx.x - pg * a.n_cg;
+    const int taps = a.kh * a.kw, nkt = P2 ? a.nk + a.nk2 : a.nk;
+    const int k0 = wave * a.ksw, k1 = min(k0 + a.ksw, nkt);
+
+    // what the thread adds at the end: the bias of its four channels (the same in every turn of the last
+    // loop, whose stride is a multiple of C / 4) and its first pixel's residual
+    const int rc = cg * C + tid % (C / 4) * 4, rcc = min(rc, a.ncb * 32 - 4), rp0 = pg * P + tid / (C / 4);
+    f4v bv = *(const f4v*)(a.bias + rcc);
+    if (P2) bv += *(const f4v*)(a.bias2 + rcc);
+    const half_t* const rsrc = (const half_t*)a.res + min(rc, a.cout - 4);
+    u2v rv = {0, 0};
+    if (a.res != nullptr) rv = *(const u2v*)(rsrc + (size_t)min(rp0, a.m - 1) * a.cout);
+
+    f4v acc[TC][TP];
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+#pragma unroll
+        for (int p = 0; p < TP; ++p) acc[c][p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+
+    if (k0 < k1) {
+        const i32x4 rin = make_rsrc(a.in, a.in_bytes);
+        const i32x4 rw = make_rsrc(a.w, (unsigned)a.ncb * (unsigned)a.nk * 2048u);
+        i32x4 rin2 = rin, rw2 = rw;
+        if (P2) {
+            rin2 = make_rsrc(a.in2, a.in2_bytes);
+            rw2 = make_rsrc(a.w2, (unsigned)a.ncb * (unsigned)a.nk2 * 2048u);
+        }
+        // "A": 16 channels = half a 32-channel block; lane (row r16, K quarter q)
+        int aoff[TC];
+        unsigned cb[TC];
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+            const int sc = cg * TC + c;
+            cb[c] = (unsigned)min(sc >> 1, a.ncb - 1);
+            aoff[c] = (q >> 1) * 1024 + ((q & 1) * 32 + (sc & 1) * 16 + r16) * 16;
+        }
+        // "B": the lane's pixel: byte offset of its first tap, a bit per tap inside the image
+        int boff[TP], boff2[TP];
+        unsigned mask[TP];
+#pragma unroll
+        for (int p = 0; p < TP; ++p) {
+            const int pi = pg * P + p * 16 + r16;
+            const int px = a.pool2 ? pi >> 2 : pi;
+            const int row = div_by(px, a.pw_m), n = div_by(row, a.ph_m);
+            int ox = px - row * a.pw, oy = row - n * a.ph;
+            if (a.pool2) { oy = 2 * oy + ((pi >> 1) & 1); ox = 2 * ox + (pi & 1); }
+            const int iy = oy * a.stride - a.pad, ix = ox * a.stride - a.pad;
+            boff[p] = ((n * a.h + iy) * a.w_ + ix) * a.cin * 2 + q * 16;
+            unsigned cols = 0, mk = 0;
+            for (int t = 0; t < a.kw; ++t) cols |= (unsigned)(ix + t >= 0 && ix + t < a.w_) << t;
+            for (int t = 0; t < a.kh; ++t) mk |= (iy + t >= 0 && iy + t < a.h) ? cols << (t * a.kw) : 0u;
+            mask[p] = pi < a.m ? mk : 0u;
+            boff2[p] = 0;
+            if (P2) boff2[p] = pi < a.m ? ((n * a.h2 + oy * a.stride2) * a.w2_ + ox * a.stride2) * a.cin2 * 2 + q * 16 : DLF_OOB;
+        }
+        h8 A[D][TC], B[D][TP];
+        // The requests of a wave run through its share of K in order; what names the next one is
+        // kept as running scalars: the step, its tap, the tap's column, the tap's byte offset, the
+        // chunk's.  (Finding them by division cost two dozen scalar instructions and four branches a step.)
+        int s_ = k0, tap, tx, toff, coff;
+        {
+            const int s1 = P2 && k0 >= a.nk ? 0 : k0, chunk = div_by(s1, a.taps_m);
+            tap = s1 - chunk * taps;
+            const int ty = div_by(tap, a.kw_m);
+            tx = tap - ty * a.kw;
+            toff = (ty * a.w_ + tx) * a.cin * 2;
+            coff = chunk * 64;
+        }
+        const int step_x = a.cin * 2, step_y = (a.w_ - a.kw) * a.cin * 2;
+        // next step into ring slot d; beyond the wave's share nothing is fetched (out of range: zeros)
+        auto request = [&](int d) __attribute__((always_inline)) {
+            const bool ok = s_ < k1, second = P2 && s_ >= a.nk;
+            const int s1 = second ? s_ - a.nk : s_;
+            const i32x4 rwx = second ? rw2 : rw;
+#pragma unroll
+            for (int c = 0; c < TC; ++c)
+                A[d][c] = __builtin_bit_cast(h8, raw_buffer_load_x4(rwx, ok ? aoff[c] : DLF_OOB,
+                                                                    (int)((cb[c] * (unsigned)(second ? a.nk2 : a.nk) + (unsigned)s1) * 2048u), 0));
+            if (P2) {
+                const i32x4 rinx = second ? rin2 : rin;
+                const unsigned bit = ok ? 1u << tap : 0u;
+#pragma unroll
+                for (int p = 0; p < TP; ++p) {
+                    const int b1 = (mask[p] & bit) ? boff[p] + toff : DLF_OOB, b2 = ok ? boff2[p] : DLF_OOB;
+                    B[d][p] = __builtin_bit_cast(h8, raw_buffer_load_x4(rinx, second ? b2 : b1, second ? s1 * 64 : coff, 0));
+                }
+            } else {
+                const unsigned bit = ok ? 1u << tap : 0u;
+#pragma unroll
+                for (int p = 0; p < TP; ++p)
+                    B[d][p] = __builtin_bit_cast(h8, raw_buffer_load_x4(rin, (mask[p] & bit) ? boff[p] + toff : DLF_OOB, coff, 0));
+            }
+            ++s_; ++tap; ++tx; toff += step_x;
+            if (tx == a.kw) { tx = 0; toff += step_y; }
+            if (tap == taps) { tap = 0; toff = 0; coff += 64; }
+        };
+        auto multiply = [&](int d) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < TC; ++c)
+#pragma unroll
+                for (int p = 0; p < TP; ++p)
+                    acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], B[d][p], acc[c][p], 0, 0, 0);
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) request(d);
+        for (int s = k0; s + D < k1; s += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                multiply(d);
+                request(d);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) multiply(d);
+    }
+
+    // partial sums: [wave][pixel][channel]; lane (pixel r16, channels 4q .. 4q + 3)
+    float* const mine = part + wave * (P * C);
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+#pragma unroll
+        for (int p = 0; p < TP; ++p) *(f4v*)(mine + (p * 16 + r16) * C + c * 16 + q * 4) = acc[c][p];
+    __syncthreads();
+    // 4 channels of one pixel per thread and turn; the order of the waves' sums is fixed
+    const unsigned lo = act_lo(a.act), hi = act_hi(a.act);
+    for (int e = tid; e < P * C / 4; e += a.nw * 64) {
+        const int rp = pg * P + e / (C / 4);
+        if (a.res != nullptr && e != tid) rv = *(const u2v*)(rsrc + (size_t)min(rp, a.m - 1) * a.cout);
+        f4v sum = bv;
+        for (int w = 0; w < a.nw; ++w) sum += *(const f4v*)(part + w * (P * C) + e * 4);
+        u2v o = {cvt_pk(sum.x, sum.y), cvt_pk(sum.z, sum.w)};
+        if (a.res != nullptr) { o.x = pk_add(o.x, rv.x); o.y = pk_add(o.y, rv.y); }
+        o.x = pk_min(pk_max(o.x, lo), hi);
+        o.y = pk_min(pk_max(o.y, lo), hi);
+        size_t opix = (size_t)rp;
+        bool store = rp < a.m && rc < a.cout;
+        if (a.pool2) {       // the four pixels of a window are C / 4 lanes apart in the same wave
+            o.x = pk_max(o.x, (unsigned)__shfl_xor((int)o.x, C / 4));
+            o.y = pk_max(o.y, (unsigned)__shfl_xor((int)o.y, C / 4));
+            o.x = pk_max(o.x, (unsigned)__shfl_xor((int)o.x, C / 2));
+            o.y = pk_max(o.y, (unsigned)__shfl_xor((int)o.y, C / 2));
+            opix >>= 2;
+            store = store && (rp & 3) == 0;
+        }
+        if (store) *(u2v*)((half_t*)a.out + opix * a.cout + rc) = o;
+    }
+}
+
 // Global average pooling: fp32 sum over H*W, mean, fp16.
 __global__ __launch_bounds__(256) void k_gap(const DlfGapArgs a)
 {
@@ -4426,6 +4602,18 @@ extern "C" int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, voi
     if (lds_bytes != (int)DLF_BN_LDS_BYTES(a->rp, a->tp, a->cin0) || lds_bytes > 160 * 1024) return (int)hipErrorInvalidValue;
     void (*const kern)(DlfBnArgs) = a->cin0 == 64 ? k_bneck<64> : (a->cin0 == 128 ? k_bneck<128> : (a->cin0 == 256 ? k_bneck<256> : k_bneck<512>));
     launch(kern, dim3(grid), dim3(DLF_BN_WAVES * 64), (size_t)lds_bytes, (hipStream_t)stream, *a);
+    return (int)hipGetLastError();
+}
+
+extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
+{
+    static void (*const k[2][DLF_SKC_SHAPES])(const DlfSkcArgs) = {
+        {k_skc<1, 1, 4, false>, k_skc<1, 2, 4, false>, k_skc<1, 4, 3, false>, k_skc<2, 4, 3, false>},
+        {k_skc<1, 1, 4, true>, k_skc<1, 2, 4, true>, k_skc<1, 4, 3, true>, k_skc<2, 4, 3, true>}};
+    static const int px[DLF_SKC_SHAPES] = {16, 16, 16, 32}, ch[DLF_SKC_SHAPES] = {16, 32, 64, 64};
+    if (shape < 0 || shape >= DLF_SKC_SHAPES || (a->nw != 1 && a->nw != 2 && a->nw != 4 && a->nw != 8)) return (int)hipErrorInvalidValue;
+    launch(k[a->nk2 > 0 ? 1 : 0][shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * px[shape] * ch[shape] * 4,
+           (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
 

@@ -1,0 +1,63 @@
+"""GPU parity of the split-K convolution kernel for outputs of few pixels, forced through its
+testing hook, against the CPU oracle: every item shape, the numbers of waves K is dealt to, filters,
+strides, ragged pixel and channel groups, residual operand, folded pool and projection pair."""
+import pytest
+
+from synth import nets, gen
+from gpu_util import compare, announce
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(net, batch, lasts, shape, waves, kinds):
+    from oracle import oracle as o
+    from paper_2011_05630_amd import binding as B
+    from paper_2011_05630_amd.runner import Session
+    x, ws, bs = gen.make_params(net, batch, 21, residual_gain=1.0)
+    ref = o.run_net(net, x, ws, bs)
+    B.dlf_debug_small_mode(1, shape, waves)
+    try:
+        s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=list(lasts), group_budget=[256] * len(lasts))
+    finally:
+        B.dlf_debug_small_mode(0)
+    try:
+        cfg = [B.dlf_plan_group_config(s.plan, g) for g in range(len(lasts))]
+        assert [(c["kind"], c["variant"]) for c in cfg] == [(k, 16 + shape) for k in kinds], cfg
+        got = s.run_numpy(x)
+    finally:
+        s.close()
+    compare(got, ref, "shape %d waves %d" % (shape, waves))
+
+
+def _mk(layers, h, w, c):
+    return dict(name="t", layers=layers, in_h=h, in_w=w, in_c=c, input_dist="normal")
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+@pytest.mark.parametrize("k,cin,cout,stride,h,w,batch", [
+    (1, 32, 4, 1, 1, 1, 1),          # one K step, one pixel, the smallest channel count
+    (1, 2048, 40, 1, 7, 5, 3),       # long K, a channel group that is mostly padding
+    (3, 64, 100, 1, 9, 13, 2),       # channels that end inside a 16-channel block
+    (3, 32, 64, 2, 15, 8, 3),        # odd map, stride 2
+    (5, 96, 36, 1, 6, 7, 2),         # 25 taps, an odd number of 32-channel chunks
+    (3, 512, 72, 1, 3, 3, 4)])       # every pixel at an edge, pixels of several images in one group
+def test_single_layer(shape, k, cin, cout, stride, h, w, batch):
+    announce("small", shape, k, cin, cout, stride, h, w, batch)
+    for waves in (0, 1, 2, 4, 8):
+        _run(_mk([nets.conv(cin, cout, k, stride, k // 2, "relu6" if cout == 40 else "relu")], h, w, cin), batch, [0], shape, waves, [10])
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+def test_residual_pool_and_projection(shape):
+    announce("small residual / pool / projection", shape)
+    # the residual operand of several turns of the reducing threads (two waves), ragged pixels
+    _run(_mk([nets.conv(64, 160, 1, 1, 0, "relu"), nets.conv(160, 160, 3, 1, 1, "relu", residual_from=0)], 7, 9, 64),
+         2, [0, 1], shape, 2, [10, 10])
+    # the 2x2 max pool behind the layer: windows of several images in one pixel group, a negative bias
+    _run(_mk([nets.conv(64, 72, 3, 1, 1, "none"), nets.maxpool(72, 2, 2, 0)], 6, 10, 64), 3, [1], shape, 0, [10])
+    # projection shortcut and last 1x1 layer as one group, both strides
+    for stride, hw in ((1, 6), (2, 11)):
+        layers = [nets.conv(64, 64, 1, 1, 0, "relu"), nets.conv(64, 32, 1, 1, 0, "relu"), nets.conv(32, 32, 3, stride, 1, "relu"),
+                  nets.conv(64, 136, 1, stride, 0, "none", input_from=0),
+                  nets.conv(32, 136, 1, 1, 0, "relu", input_from=2, residual_from=3)]
+        _run(_mk(layers, hw, hw + 2, 64), 3, [0, 1, 2, 4], shape, 0, [10, 10, 10, 8])
