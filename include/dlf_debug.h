@@ -58,7 +58,9 @@ void dlf_debug_depthwise_tile(int32_t wx, int32_t rw);
  * kernel for a 3x3 layer (128 or 256 channels in and out) with a 1x1 layer behind it as one group
  * (th, tw > 0 then fix the tile the map is cut into equal parts for: at most 8 x 16 pixels), 7 = the
  * kernel for a whole bottleneck block (1x1 to 64 channels, 3x3, 1x1; th, tw as for 6, at most 64
- * pixels); a shape
+ * pixels), 8 .. 13 = the block kernel with its weights in registers (channels x pixels and input channels at a
+ * time: 128 x 224 and 64, 128 x 128 and 64, 64 x 448 and 64, 64 x 256 and 64, 128 x 224 and 32, 64 x 448 and
+ * 32); a shape
  * that cannot be laid out falls back to the fused-group kernel.  Mode 2 keeps such a pair of layers
  * on the fused-group kernel as well.
  * Process-wide, not thread-safe. */

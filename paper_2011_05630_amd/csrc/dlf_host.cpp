@@ -156,7 +156,7 @@ dlf_status pack_and_upload(Layer& L)
 // Fusion groups
 // ------------------------------------------------------------------------------------------
 
-enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13 };
+enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13, GK_C3R = 14 };
 
 struct TileCfg {
     int th, tw;      // tile of the group's final output tensor
@@ -250,6 +250,15 @@ const int64_t C_C3_SHORT_K = 6000;          // per item when K has fewer than 8 
 const int64_t C3_MMA_TENTHS = 15;
 const int64_t C3_BYTES_PER_CYCLE = 27;
 const int64_t C3_SHALLOW_RING = 300;        // per stage when the weight ring has two stages only
+// ... with the weights in registers: the first block of activations and the last epilogue of a CU (by shape:
+// pixels of a wave's part), what a further item adds to its multiplies where two workgroups share the CU, cycles of a
+// SIMD per matrix cycle in hundredths with one workgroup and with two.  Fitted to 19 layer shapes (64 - 512
+// channels, 14 - 224 pixels, batch 1 - 32), every shape and tile forced in turn.
+const int64_t C_C3R_EDGE[DLF_C3R_SHAPES] = {7000, 4000, 9000, 6000, 7000, 9000};
+const int64_t C_C3R_ITEM[DLF_C3R_SHAPES] = {4000, 2000, 6500, 3500, 4000, 6500};
+const int64_t C3R_MMA_ALONE[DLF_C3R_SHAPES] = {160, 140, 160, 150, 160, 160};
+const int64_t C3R_MMA_SHARED = 142;
+const int64_t C3R_FEW_ITEMS = 128;      // ... a launch of at most so many items leaves half of the chip idle
 
 // streaming depthwise kernel: per work item (decode, weights, first rows of the window), per output
 // row of a wave (about a hundred vector instructions; the waves of a SIMD share its issue slots),
@@ -964,6 +973,98 @@ bool c3_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C3
             }
         }
     return found;
+}
+
+// ---- the block kernel with the weights in registers (k_c3r) ----
+
+const int C3R_NCBW[DLF_C3R_SHAPES] = {4, 4, 2, 2, 4, 2};      // 32-channel blocks of a workgroup
+const int C3R_FP[DLF_C3R_SHAPES] = {7, 4, 7, 4, 7, 7};        // 32-pixel blocks of a wave
+const int C3R_ACH[DLF_C3R_SHAPES] = {64, 64, 64, 64, 32, 32}; // input channels of an activation block
+const int C3R_NA[DLF_C3R_SHAPES] = {10, 6, 17, 11, 6, 9};     // activation requests of a wave per block
+const int C3R_HOOK = DLF_C3_SHAPES + 3;                       // first shape number of the testing hook
+
+bool c3r_build(int pool2, int cin, int shape, int th, int tw, int max_lds, C3Cfg& c, int& pw, int& vw)
+{
+    if (shape < 0 || shape >= DLF_C3R_SHAPES) return false;
+    const int ach = C3R_ACH[shape];
+    if (th < 1 || tw < 2 || th * tw > 32 * C3R_FP[shape] * (DLF_C3R_WAVES / C3R_NCBW[shape]) || (cin % ach) != 0) return false;
+    if (pool2 && (((th | tw) & 1) != 0 || tw < 4)) return false;
+    // rows of the halo region and of the index the parts are permuted by: see the kernel
+    pw = ach == 64 ? tw + 2 : tw + 4;
+    vw = pool2 ? tw + ((8 - tw) & 15) : tw;
+    c.shape = shape; c.th = th; c.tw = tw;
+    c.npxh = (th + 2) * pw;
+    c.na_i = ceil_div(c.npxh, 512 / ach);
+    c.lpw_a = C3R_NA[shape];
+    if (c.na_i > DLF_C3R_WAVES * c.lpw_a) return false;
+    c.nst = std::min(2, cin / ach);
+    c.lds_bytes = std::max(c.nst * c.na_i * 1024, (int)DLF_C3R_EPI_BYTES);
+    return c.lds_bytes <= max_lds;
+}
+
+uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3Cfg& c)
+{
+    const int64_t tiles = (int64_t)batch * ceil_div(L.out_h, c.th) * ceil_div(L.out_w, c.tw);
+    const int64_t items = tiles * ceil_div(L.ncb, C3R_NCBW[c.shape]);
+    const int64_t items_cu = (items + budget - 1) / budget;
+    const int64_t mma = (int64_t)L.nsteps * C3R_FP[c.shape] * MFMA_CYCLES;
+    const int64_t has_res = L.d.residual_from >= 0 ? 1 : 0;
+    const int64_t edge = C_C3R_EDGE[c.shape] + has_res * C_PW_RES;
+    // two workgroups on a CU: the first loads and the epilogue of one run under the other's multiplies
+    const int64_t compute = items_cu > 1 && 160 * 1024 / c.lds_bytes >= 2
+                                ? edge + items_cu * (mma * C3R_MMA_SHARED / 100 + C_C3R_ITEM[c.shape] + has_res * C_PW_RES)
+                                : items_cu * (mma * C3R_MMA_ALONE[c.shape] / 100 + edge);
+    const int64_t m = (int64_t)batch * L.out_h * L.out_w;
+    const int64_t bytes = m * L.d.cin * 2 + (pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
+    const int64_t mem = bytes / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
+    int64_t cycles = C_LAUNCH + std::max(compute, mem);
+    // With most of the chip idle a split of K is the better kernel, and the model of the fused-group kernel's is too
+    // high there (256 channels at 56 x 56 with the pool, batch 1, 56 items: 12.8 us, modelled 18.3, here 15.2)
+    if (items <= C3R_FEW_ITEMS) cycles = cycles * 4 / 3;
+    return (uint64_t)(cycles * PS_PER_CYCLE);
+}
+
+// Cheapest shape and tile (ties: the fewest work items, then as in c3_choose; 8 x 28 tiles of a 56 x 56 map take
+// 3 % less time than 7 x 28, the matrix pipes' power being the limit).
+bool c3r_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost)
+{
+    bool found = false;
+    int64_t items = 0;
+    for (int shape = 0; shape < DLF_C3R_SHAPES; ++shape)
+        for (int th : TILE_H) {
+            if (th > L.out_h && th != TILE_H[0] && (th - L.out_h) >= 4) continue;
+            for (int tw : TILE_W) {
+                if (tw > L.out_w && tw != TILE_W[0] && (tw - L.out_w) >= 4) continue;
+                C3Cfg c;
+                int pw, vw;
+                if (!c3r_build(pool2, L.d.cin, shape, th, tw, max_lds, c, pw, vw)) continue;
+                const uint64_t cc = c3r_cost_ps(L, pool2, batch, budget, c);
+                const int64_t n = (int64_t)ceil_div(L.out_h, th) * ceil_div(L.out_w, tw) * ceil_div(L.ncb, C3R_NCBW[shape]);
+                if (!found || cc < cost || (cc == cost && n < items)) { found = true; cost = cc; best = c; items = n; }
+            }
+        }
+    return found;
+}
+
+// Kernel arguments of a layer on k_c3b (reg = false) or k_c3r, without the pointers; returns the grid.
+int c3_fill(const Layer& L, int pool2, int batch, int budget, int act, bool reg, const C3Cfg& cc, DlfC3Args& ca)
+{
+    memset(&ca, 0, sizeof ca);
+    ca.batch = batch; ca.h = L.out_h; ca.w_ = L.out_w; ca.cin = L.d.cin; ca.cout = L.d.cout;
+    ca.ncb = L.ncb; ca.nsteps = L.nsteps; ca.act = act; ca.pool2 = pool2;
+    ca.th = cc.th; ca.tw = cc.tw;
+    ca.tiles_y = ceil_div(L.out_h, cc.th); ca.tiles_x = ceil_div(L.out_w, cc.tw);
+    ca.n_cg = ceil_div(L.ncb, reg ? C3R_NCBW[cc.shape] : 2 * C3_WC[cc.shape]);
+    ca.ntiles = batch * ca.tiles_y * ca.tiles_x;
+    ca.nitems = ca.n_cg * ca.ntiles;
+    ca.npxh = cc.npxh; ca.na_i = cc.na_i; ca.lpw_a = cc.lpw_a; ca.nst = cc.nst;
+    int occ = 1;
+    if (reg) {
+        C3Cfg again;
+        c3r_build(pool2, L.d.cin, cc.shape, cc.th, cc.tw, 160 * 1024, again, ca.pw, ca.vw);
+        occ = std::min(2, 160 * 1024 / cc.lds_bytes);
+    }
+    return std::max(8, std::min(budget * occ, ceil_div(ca.nitems, 8) * 8) / 8 * 8);
 }
 
 // ---- streaming depthwise kernel (one depthwise 3x3 layer, pad 1, stride 1 or 2) ----
@@ -1898,34 +1999,36 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
         }
     }
     if (c3f.mode != 2 && (force.th <= 0 || c3f.mode == 1) && c3f.shape != DLF_C3_SHAPES && c3_eligible(net, specs, batch)) {
-        C3Cfg cc;
-        uint64_t c3c = 0;
+        C3Cfg cc, cr;
+        uint64_t c3c = 0, crc = 0;
         const int pool2 = specs[0].pool2;
-        bool have;
-        if (c3f.shape >= 0) {
+        bool have, reg = false;
+        int pw, vw;
+        if (c3f.shape >= C3R_HOOK) {
+            have = reg = c3r_build(pool2, L0.d.cin, c3f.shape - C3R_HOOK, c3f.th, c3f.tw, max_lds, cc, pw, vw);
+            if (have) c3c = c3r_cost_ps(L0, pool2, batch, budget, cc);
+        } else if (c3f.shape >= 0) {
             have = c3_build(pool2, L0.d.cin, c3f.shape, c3f.th, c3f.tw, max_lds, cc);
             if (have) c3c = c3_cost_ps(L0, pool2, batch, budget, cc);
         } else {
             have = c3_choose(L0, pool2, batch, budget, max_lds, cc, c3c);
+            // (not considered while a testing hook or a caller names another kernel's form)
+            const bool named = (force_tc && force_tc->th > 0) || pwm != 0 || g_force.th > 0 || g_dw_mode != 0;
+            if (!named && c3r_choose(L0, pool2, batch, budget, max_lds, cr, crc) && (!have || crc < c3c)) {
+                have = reg = true;
+                cc = cr;
+                c3c = crc;
+            }
         }
         if (have && have_c3s && c3sc < c3c) have = false;       // the small-map kernel is cheaper: decided below
         if (have && (!tiled || c3f.mode == 1 || c3c < cost)) {
             DlfC3Args& ca = g.ca;
-            memset(&ca, 0, sizeof ca);
+            g.grid = c3_fill(L0, pool2, batch, budget, L0.d.act, reg, cc, ca);
             ca.w = L0.d_w; ca.bias = L0.d_bias;
-            ca.batch = batch; ca.h = L0.out_h; ca.w_ = L0.out_w; ca.cin = L0.d.cin; ca.cout = L0.d.cout;
-            ca.ncb = L0.ncb; ca.nsteps = L0.nsteps; ca.act = L0.d.act; ca.pool2 = pool2;
-            ca.th = cc.th; ca.tw = cc.tw;
-            ca.tiles_y = ceil_div(L0.out_h, cc.th); ca.tiles_x = ceil_div(L0.out_w, cc.tw);
-            ca.n_cg = ceil_div(L0.ncb, 2 * C3_WC[cc.shape]);
-            ca.ntiles = batch * ca.tiles_y * ca.tiles_x;
-            ca.nitems = ca.n_cg * ca.ntiles;
-            ca.npxh = cc.npxh; ca.na_i = cc.na_i; ca.lpw_a = cc.lpw_a; ca.nst = cc.nst;
-            g.kind = GK_C3;
+            g.kind = reg ? GK_C3R : GK_C3;
             g.cost = c3c;
             g.variant = cc.shape;
-            g.occ = 1;
-            g.grid = std::max(8, std::min(budget, ceil_div(ca.nitems, 8) * 8) / 8 * 8);
+            g.occ = reg ? std::min(2, 160 * 1024 / cc.lds_bytes) : 1;
             g.th = cc.th; g.tw = cc.tw;
             g.lds_bytes = cc.lds_bytes;
             if (L0.d.residual_from >= 0) { g.res_layer = L0.d.residual_from; g.res_stage = 0; }
@@ -2506,8 +2609,9 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
     const GroupPlan& G = plan->G[g];
     // the split-K convolution is reported as a form of the small-map kernel, with a projection as
     // one of the two-operand kind
-    if (kind) *kind = G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
-    if (variant) *variant = G.kind != GK_SKC ? G.variant : 16 + G.variant;
+    // ..., the block kernel with the weights in registers as a form of the block kernel
+    if (kind) *kind = G.kind == GK_C3R ? GK_C3 : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
+    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R ? G.variant : 16 + G.variant;
     if (nslices) *nslices = G.kind == GK_GROUP ? G.ga.nslices : 1;
     if (slice_c) *slice_c = G.kind == GK_GROUP ? G.ga.slice_c : 0;
     if (stream0) *stream0 = G.kind == GK_GROUP ? G.ga.stream0 : 0;
@@ -2650,14 +2754,15 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
         DlfDwPwArgs dp = G.dp;
         dp.in = in; dp.out = out;
         e = dlf_launch_dwpw(&dp, G.variant, G.grid, stream);
-    } else if (G.kind == GK_C3) {
+    } else if (G.kind == GK_C3 || G.kind == GK_C3R) {
         DlfC3Args ca = G.ca;
         ca.in = in; ca.out = out;
         if (G.res_stage >= 0) {
             if (!res) return fail(DLF_ERR_INVALID_ARG, "group [%d,%d] needs its residual operand", G.first, G.last);
             ca.res = res;
         }
-        e = dlf_launch_c3(&ca, G.variant, G.grid, G.lds_bytes, stream);
+        if (G.kind == GK_C3) e = dlf_launch_c3(&ca, G.variant, G.grid, G.lds_bytes, stream);
+        else e = dlf_launch_c3r ? dlf_launch_c3r(&ca, G.variant, 0, G.grid, G.lds_bytes, stream) : (int)hipErrorInvalidDeviceFunction;
     } else {
         DlfGroupArgs ga = G.ga;
         ga.in = in; ga.out = out;
@@ -2976,6 +3081,7 @@ static dlf_status static_workspace(char** base)
 struct dlf_i8conv_s {
     int ksize = 3;
     bool small_map = false;      // runs on the small-map kernel (cs), else on a block kernel (ca / wa)
+    bool reg = false;            // ... the 3x3 block kernel with the weights in registers
     DlfC3Args ca;
     DlfPwArgs wa;
     DlfC3sArgs cs;
@@ -3036,7 +3142,7 @@ dlf_status dlf_i8conv_create(int32_t batch, int32_t h, int32_t w, int32_t cin, i
     DlfC3sArgs cs;
     uint64_t cost_s = 0;
     bool have_s = false;
-    if (c3s_cin_ok(L.d.cin) && !(g_c3_force.shape >= 0 && g_c3_force.shape < DLF_C3_SHAPES)) {
+    if (c3s_cin_ok(L.d.cin) && (g_c3_force.shape < 0 || g_c3_force.shape == DLF_C3_SHAPES)) {
         if (g_c3_force.shape == DLF_C3_SHAPES && g_c3_force.th > 0) {
             have_s = c3s_build(L, batch, g_c3_force.th, 0, 0, 160 * 1024, cs, pool);
             if (!have_s) return fail(DLF_ERR_INFEASIBLE, "the forced split of K does not fit this layer");
@@ -3047,7 +3153,11 @@ dlf_status dlf_i8conv_create(int32_t batch, int32_t h, int32_t w, int32_t cin, i
             uint64_t other = UINT64_MAX;
             C3Cfg c2;
             if (ksize == 1) other = pw_shape_cost_ps(L, batch, budget, pw_shape_ok(L, 3) ? 3 : 4);
-            else if (!c3_choose(L, pool, batch, budget, 160 * 1024, c2, other)) other = UINT64_MAX;
+            else {
+                if (!c3_choose(L, pool, batch, budget, 160 * 1024, c2, other)) other = UINT64_MAX;
+                uint64_t reg = 0;
+                if (c3r_choose(L, pool, batch, budget, 160 * 1024, c2, reg)) other = std::min(other, reg);
+            }
             if (other <= cost_s) have_s = false;
         }
     } else if (g_c3_force.shape == DLF_C3_SHAPES) {
@@ -3075,22 +3185,23 @@ dlf_status dlf_i8conv_create(int32_t batch, int32_t h, int32_t w, int32_t cin, i
         l->grid = std::max(8, std::min(budget * 2, ceil_div(wa.nitems, 8) * 8) / 8 * 8);
         l->th = 1; l->tw = 32 * PW_FP[shape];
     } else {
-    if (g_c3_force.shape >= 0 && g_c3_force.shape < DLF_C3_SHAPES) {      // testing hook: shape and tile as given
+    int pw, vw;
+    if (g_c3_force.shape >= C3R_HOOK) {                                   // testing hook: shape and tile as given
+        l->reg = true;
+        if (!c3r_build(pool, L.d.cin, g_c3_force.shape - C3R_HOOK, g_c3_force.th, g_c3_force.tw, 160 * 1024, cc, pw, vw))
+            return fail(DLF_ERR_INFEASIBLE, "the forced shape and tile do not fit this layer");
+    } else if (g_c3_force.shape >= 0 && g_c3_force.shape < DLF_C3_SHAPES) {
         if (!c3_build(pool, L.d.cin, g_c3_force.shape, g_c3_force.th, g_c3_force.tw, 160 * 1024, cc))
             return fail(DLF_ERR_INFEASIBLE, "the forced shape and tile do not fit this layer");
-    } else if (!c3_choose(L, pool, batch, budget, 160 * 1024, cc, cost))
-        return fail(DLF_ERR_INFEASIBLE, "no tile of the block kernel fits this layer");
-    DlfC3Args& ca = l->ca;
-    ca.batch = batch; ca.h = h; ca.w_ = w; ca.cin = cin / 2; ca.cout = cout;
-    ca.ncb = L.ncb; ca.nsteps = L.nsteps; ca.act = relu ? 1 : 0; ca.pool2 = pool;
-    ca.th = cc.th; ca.tw = cc.tw;
-    ca.tiles_y = ceil_div(h, cc.th); ca.tiles_x = ceil_div(w, cc.tw);
-    ca.n_cg = ceil_div(L.ncb, 2 * C3_WC[cc.shape]);
-    ca.ntiles = batch * ca.tiles_y * ca.tiles_x;
-    ca.nitems = ca.n_cg * ca.ntiles;
-    ca.npxh = cc.npxh; ca.na_i = cc.na_i; ca.lpw_a = cc.lpw_a; ca.nst = cc.nst;
+    } else {
+        C3Cfg cr;
+        uint64_t crc = 0;
+        const bool have = c3_choose(L, pool, batch, budget, 160 * 1024, cc, cost);
+        if (c3r_choose(L, pool, batch, budget, 160 * 1024, cr, crc) && (!have || crc < cost)) { l->reg = true; cc = cr; }
+        else if (!have) return fail(DLF_ERR_INFEASIBLE, "no tile of the block kernel fits this layer");
+    }
+    l->grid = c3_fill(L, pool, batch, budget, relu ? 1 : 0, l->reg, cc, l->ca);
     l->shape = cc.shape;
-    l->grid = std::max(8, std::min(budget, ceil_div(ca.nitems, 8) * 8) / 8 * 8);
     l->lds_bytes = cc.lds_bytes;
     l->th = cc.th; l->tw = cc.tw;
     }
@@ -3119,8 +3230,10 @@ dlf_status dlf_i8conv_info(const dlf_i8conv_t* l, int32_t* th, int32_t* tw, int3
     if (!l) return fail(DLF_ERR_INVALID_ARG, "dlf_i8conv_info: null layer");
     if (th) *th = l->th;
     if (tw) *tw = l->tw;
-    if (shape) *shape = l->shape;
-    if (grid) *grid = l->grid;
+    // the block kernel with its weights in registers: the block shape of its channels and activation block; workgroups
+    // that share a CU count once
+    if (shape) *shape = !l->reg ? l->shape : (C3R_NCBW[l->shape] == 4 ? 0 : 2) + (C3R_ACH[l->shape] == 64 ? 1 : 0);
+    if (grid) *grid = !l->reg ? l->grid : std::max(8, l->grid / std::min(2, 160 * 1024 / l->lds_bytes) / 8 * 8);
     if (op_count) *op_count = l->ops;
     return DLF_OK;
 }
@@ -3146,7 +3259,8 @@ dlf_status dlf_i8conv_run(const dlf_i8conv_t* l, const void* in_dev, void* out_d
     } else {
         DlfC3Args ca = l->ca;
         ca.in = in_dev; ca.out = out_dev;
-        e = dlf_launch_c3_i8(&ca, l->shape, l->grid, l->lds_bytes, hip_stream);
+        if (!l->reg) e = dlf_launch_c3_i8(&ca, l->shape, l->grid, l->lds_bytes, hip_stream);
+        else e = dlf_launch_c3r ? dlf_launch_c3r(&ca, l->shape, 1, l->grid, l->lds_bytes, hip_stream) : (int)hipErrorInvalidDeviceFunction;
     }
     if (e != 0) return fail(DLF_ERR_HIP, "launch of the int8 layer failed: %s", hipGetErrorString((hipError_t)e));
     return DLF_OK;

@@ -152,7 +152,17 @@ struct DlfC3Args {
     int32_t nst;          // stages in the weight ring (2 .. 4)
     // quantised form only (int8 tensors, `cin` = byte pairs per pixel, `act` != 0 = ReLU):
     const float* scale;   // requantisation scale per output channel, padded to ncb*32
+    // k_c3r only (n_cg counts groups of 32 * NCBW channels, nst is the number of activation buffers):
+    int32_t pw, vw;       // pixels per halo row in LDS, and per row of the index the parts are permuted by
 };
+
+// The same layer with the weights in registers (k_c3r): a workgroup of four waves computes 32 * NCBW output
+// channels x up to 32 * FP * (4 / NCBW) pixels, ACH input channels at a time, NA activation requests per wave
+// and block.  Shapes (NCBW, FP, ACH, NA): 0 = (4, 7, 64, 10), 1 = (4, 4, 64, 6), 2 = (2, 7, 64, 17),
+// 3 = (2, 4, 64, 11), 4 = (4, 7, 32, 6), 5 = (2, 7, 32, 9).
+#define DLF_C3R_WAVES 4
+#define DLF_C3R_SHAPES 6
+#define DLF_C3R_EPI_BYTES (DLF_C3R_WAVES * 32 * 40 * 2)   // transpose buffers of the epilogue
 
 // Depthwise 3x3 convolution (pad 1, stride 1 or 2) as a streaming kernel without LDS or barriers:
 // a wave owns 64 consecutive 16-byte vectors (8 channels each) of the output rows of a strip and
@@ -409,6 +419,8 @@ int dlf_launch_fc(const DlfFcArgs* a, void* stream);
 int dlf_launch_gap(const DlfGapArgs* a, void* stream);
 int dlf_launch_pw(const DlfPwArgs* a, int shape, int grid, void* stream);
 int dlf_launch_c3(const DlfC3Args* a, int shape, int grid, int lds_bytes, void* stream);
+// (weak, as dlf_launch_skc below) `i8`: the quantised form
+__attribute__((weak)) int dlf_launch_c3r(const DlfC3Args* a, int shape, int i8, int grid, int lds_bytes, void* stream);
 int dlf_launch_pw_i8(const DlfPwArgs* a, int shape, int grid, void* stream);
 int dlf_launch_c3_i8(const DlfC3Args* a, int shape, int grid, int lds_bytes, void* stream);
 int dlf_launch_dw(const DlfDwArgs* a, int grid, void* stream);

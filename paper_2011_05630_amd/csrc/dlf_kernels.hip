@@ -2251,6 +2251,327 @@ __global__ __launch_bounds__(DLF_C3_WAVES * 64, 1) void k_c3b(const DlfC3Args a)
     }
 }
 
+// Direct-to-LDS load through a buffer resource: lane l's 16 bytes at voff + soff to dst + 16 l, zeros where voff
+// lies beyond the tensor.
+__device__ __forceinline__ void dma16b(__amdgpu_buffer_rsrc_t r, half_t* dst, unsigned voff, int soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, 0);
+}
+// v += by (uniform), in place.  Written as an instruction: the compiler would form the values of all steps of a
+// loop body ahead of it, in registers there are not.
+__device__ __forceinline__ void step_v(int& v, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(v) : "s"(by)); }
+
+// 3x3 convolution, stride 1, pad 1 (with the 2x2 max pool behind it, or a residual operand), for maps that
+// give every CU a whole item: the block kernel with the weights in registers.  A workgroup of FOUR waves, one
+// per SIMD, computes 32 * NCBW channels x a th x tw tile; a wave owns one 32-channel block and FP 32-pixel
+// blocks (NCBW = 4: all waves share the tile's pixels; NCBW = 2: two groups of pixels).  Two workgroups share
+// a CU where there are enough items: one's first loads and epilogue run under the other's multiplies.
+// What bounds k_c3b and is gone here:
+//   - lanes without a pixel: a tile of 196 pixels filled 6.1 of its 8 pixel blocks, 392 filled 12.25 of 16; seven
+//     blocks take 196 or 224 pixels (7 x 28, 8 x 28, 7 x 32, 14 x 16);
+//   - LDS bandwidth: both operands went through LDS, one 1 KiB read per MFMA and 1.4 times that with the
+//     conflicts of a block that spans a row break.  Weights come from L2 straight into a register ring of nine
+//     K steps (a wave's fragments are one contiguous stream; 4 KiB per 7 * 32 matrix cycles and CU), which
+//     leaves one read per MFMA of FP, without conflicts (below);
+//   - barriers: LDS holds activations only, so a block is ACH = 64 (or 32) input channels x nine taps, 36 (18)
+//     K steps between two barriers instead of nine.
+// Activations: two buffers (one if K is a single block) of the tile's halo region, filled by 16-byte direct
+// loads; the byte offsets of a lane's NA requests are formed once per item and stay in registers, pixels
+// outside the image hold an offset beyond the tensor (the range check writes zeros: the padding).  Block
+// b + 1 is requested one load per K step over the first NA steps of block b, always NA of them (surplus ones
+// repeat the last): loads retire in order, so the requests behind them are a constant.
+// Bank conflicts: part q of the halo pixel (r, c) lies at q ^ ((r * vw + c) >> SH), rows of `pw` pixels.  LDS serves
+// 16 lanes per cycle; with vw = tw the permutation runs through consecutive integers for consecutive tile
+// pixels whatever the tap and across row breaks, and pw = tw + 2 (128-byte pixels) or tw + 4 (64-byte pixels)
+// keeps the pixels' own bank halves (quarters) in step: no conflicts for any tile (a count over all tiles;
+// with the halo index in the permutation 1.4 cycles per read at 28-wide tiles, 2 with the pool's quads).  The
+// pool's order (2x2 windows in quads) wants the rows of a window 8 parts apart: vw = 8 mod 16.
+// Fragment reads are a ring of FP registers, each refilled for the next K step behind the MFMA that used it, and
+// waited for by count (see k_c3b), two pixel blocks at a time: a wave alone on its SIMD issues one instruction per
+// matrix instruction's eight passes, so what stands beside the MFMAs (4.2 instructions each, 8 in the first form) is
+// what bounds the kernel where every CU has one item only; with two the matrix pipes' power does.  I8: the
+// quantised form, as in k_c3b.
+// Measured against k_c3b and the fused-group kernel (fp16, random operands): 256 -> 256 at 56 x 56, batch 8: 36.4 ->
+// 31.4 us, batch 16: 62.2 -> 54 (1.10 PFLOP/s); 512 -> 512 at 28 x 28, batch 16: 62.7 -> 55.4; 128 -> 128 at 112 x 112:
+// 67.9 -> 57; 64 -> 64 at 224 x 224: 96.6 -> 69.5, with the pool 89 -> 62; VGG-16 batch 16 703 -> 648 us, its body
+// in int8 396 -> 330 us.
+template <int NCBW, int FP, int ACH, int NA, bool I8>
+__global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a)
+{
+    using acc_t = typename AccOf<I8>::type;
+    static_assert(NCBW == 2 || NCBW == 4, "channel blocks of a workgroup");
+    static_assert(ACH == 32 || ACH == 64, "activation block: 64 or 128 bytes per pixel");
+    constexpr int LPP = ACH / 8, PPI = 64 / LPP;     // lanes (16-byte parts) per pixel, pixels per load
+    constexpr int SH = LPP == 8 ? 1 : 2;
+    constexpr int STEPS = 18 * (ACH / 32);           // K steps of a block, in the order the weights are packed
+    constexpr int D = 9;                             // weight ring: divides STEPS
+    constexpr int PM = (LPP - 1) << 4, US = 4 - SH;  // the permuted part as a byte offset: (u << US) & PM
+    static_assert(NA + D <= STEPS, "the block's requests are older than the last D weight requests");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const int cbw = wave & (NCBW - 1), pg = NCBW == 4 ? 0 : wave >> 1;
+    const int pw = a.pw, npxh = a.npxh, na_i = a.na_i;
+    const int buf_bytes = na_i * 1024;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) half_t*)lds;
+    const int NB = a.cin / ACH;
+    const unsigned pw_m = div_magic(pw);             // (both divisors are above 1: a division is the product)
+    const unsigned tw_m = div_magic(a.pool2 ? a.tw >> 1 : a.tw);
+    const int npix = a.th * a.tw;
+    const half_t* resp = (const half_t*)a.res;
+    const int act_epi = resp != nullptr ? 0 : a.act;
+    const unsigned lo_e = act_lo(act_epi), hi_e = act_hi(act_epi);
+    const unsigned lo_r = act_lo(a.act), hi_r = act_hi(a.act);
+    const int per_xcd = (a.nitems + 7) >> 3;
+    const unsigned lane16 = (unsigned)lane * 16u;
+
+    // the lane's pixels: byte address of the halo pixel under tap (0, 0), and its permutation index
+    int hb[FP], uu[FP];
+#pragma unroll
+    for (int p = 0; p < FP; ++p) {
+        int pix = (pg * FP + p) * 32 + l32;
+        pix = pix < npix ? pix : 0;                  // surplus lanes compute a result nobody stores
+        int ry, rx;
+        pix_to_rc(pix, a.tw, tw_m, a.pool2, ry, rx);
+        hb[p] = (int)lds0 + (ry * pw + rx) * (ACH * 2) + (lhi << 4);
+        uu[p] = (ry * a.vw + rx) << US;
+    }
+    // from filter row to filter row the two step by uniform amounts, in place; a column is an immediate offset
+    // of the read and a constant in the permutation, the K half and the 32-channel chunk are bits 5 and 6
+    const int hb_row = pw * (ACH * 2), uu_row = a.vw << US;
+    const int hb_back = -2 * hb_row, uu_back = -2 * uu_row;
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)a.in, 0, (int)((unsigned)(a.batch * a.h * a.w_) * (unsigned)a.cin * 2u), 0x00020000);
+    const i32x4 rwt = make_rsrc(a.w, 0xffffffffu);
+
+    for (int li = blockIdx.x >> 3; li < per_xcd; li += gridDim.x >> 3) {
+        const int item = (blockIdx.x & 7) * per_xcd + li;
+        if (item >= a.nitems) break;
+        const int cg = item / a.ntiles;
+        int t_ = item - cg * a.ntiles;
+        const int tx = t_ % a.tiles_x;
+        t_ /= a.tiles_x;
+        const int ty = t_ % a.tiles_y, n = t_ / a.tiles_y;
+        const int ty0 = ty * a.th, tx0 = tx * a.tw;
+        // (the lane number, opaque: what is derived from it below is formed per item, not kept in registers
+        // or scratch memory through the K loop)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int cb = cg * NCBW + cbw;
+        const int cbc = min(cb, a.ncb - 1);          // a block beyond the layer: computed again, not stored
+
+        f4v bias[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if constexpr (!I8) bias[q] = *(const f4v*)(a.bias + cbc * 32 + q * 8 + lhi * 4);
+        // request i of the wave: load j = wave + 4 i (a surplus one repeats the last) covers PPI halo pixels x LPP parts
+        unsigned vo[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int hpx = min(wave + DLF_C3R_WAVES * i, na_i - 1) * PPI + ln / LPP;
+            unsigned off = DLF_OOB;
+            const int hy = (int)__umulhi((unsigned)hpx, pw_m), hx = hpx - hy * pw;
+            const int gy = ty0 - 1 + hy, gx = tx0 - 1 + hx;
+            if (hpx < npxh && gy >= 0 && gy < a.h && gx >= 0 && gx < a.w_)
+                off = (unsigned)(((n * a.h + gy) * a.w_ + gx) * a.cin) * 2u;
+            const int u = (hy * a.vw + hx) >> SH;
+            vo[i] = off + (unsigned)(((ln ^ u) & (LPP - 1)) << 4);
+        }
+        auto request_a = [&](int i, int b) __attribute__((always_inline)) {
+            half_t* dst = lds + ((b & 1) * na_i + min(wave + DLF_C3R_WAVES * i, na_i - 1)) * 512;
+            dma16b(rin, dst, vo[i], b * (ACH * 2));
+        };
+        const unsigned wo = (unsigned)(cbc * a.nsteps) * 1024u;
+        h8 ar[D];
+        // K step `step` of the block whose fragments start at `wb` (four steps share a scalar offset)
+        auto request_w = [&](int slot, unsigned wb, int step) __attribute__((always_inline)) {
+            ar[slot] = wfrag(rwt, (int)lane16 + (step & 3) * 1024, wb + (unsigned)(step >> 2) * 4096u);
+        };
+#pragma unroll
+        for (int i = 0; i < NA; ++i) request_a(i, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < D; ++d) request_w(d, wo, d);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt<D>();                             // the first block has landed
+        asm volatile("s_barrier" ::: "memory");
+        acc_t acc[FP];
+#pragma unroll
+        for (int p = 0; p < FP; ++p)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                if constexpr (I8) acc[p][q] = 0;
+                else acc[p][q] = bias[q >> 2][q & 3];
+            }
+
+        auto block = [&](int b, const bool more) __attribute__((always_inline)) {     // (more: a constant, once inlined)
+            const unsigned wb = wo + (unsigned)b * (STEPS * 1024);
+            h8 bq[FP];
+            int xa[FP];
+#pragma unroll
+            for (int p = 0; p < FP; ++p) {
+                xa[p] = (uu[p] & PM) ^ hb[p];
+                bq[p] = lds_read16<0>((unsigned)xa[p]);
+            }
+            static_for<0, STEPS>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                constexpr int jn = j + 1, tapn = (jn % 18) >> 1, hn = jn & 1, dxn = tapn % 3;
+                static_for<0, FP>([&](auto pc) __attribute__((always_inline)) {
+                    constexpr int p = decltype(pc)::value;
+                    // (one wait for two pixel blocks; the reads behind the pair's second may be outstanding)
+                    if constexpr ((p & 1) == 0 && p + 1 < FP) lds_arrive2<jn < STEPS ? FP - 2 : FP - 2 - p>(bq[p], bq[p + 1]);
+                    else if constexpr ((p & 1) == 0) lds_arrive1<jn < STEPS ? FP - 1 : 0>(bq[p]);
+                    if constexpr (I8)
+                        acc[p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, ar[j % D]),
+                                                                       __builtin_bit_cast(i32x4, bq[p]), acc[p], 0, 0, 0);
+                    else
+                        acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ar[j % D], bq[p], acc[p], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (jn < STEPS) {
+                        if constexpr (hn == 0) {
+                            if constexpr (dxn == 0) {
+                                step_v(hb[p], tapn == 0 ? hb_back + 64 : hb_row);
+                                step_v(uu[p], tapn == 0 ? uu_back : uu_row);
+                            }
+                            xa[p] = ((uu[p] + (dxn << US)) & PM) ^ hb[p];
+                        } else
+                            xa[p] ^= 32;
+                        bq[p] = lds_read16<dxn * (ACH * 2)>((unsigned)xa[p]);
+                    } else {
+                        step_v(hb[p], hb_back - (STEPS / 18 - 1) * 64 + ((b & 1) ? -buf_bytes : more ? buf_bytes : 0));
+                        step_v(uu[p], uu_back);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if (more || j + D < STEPS) request_w(j % D, wb, j + D);
+                if (more && j < NA) request_a(j, b + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            // the next block has landed (its requests are older than the ring's), and everyone is done with this one
+            if (more) wait_vmcnt<D>();
+            asm volatile("s_barrier" ::: "memory");
+        };
+#pragma unroll 1
+        for (int b = 0; b < NB - 1; ++b) block(b, true);
+        block(NB - 1, false);
+
+        // Epilogue: a pass per pixel block through the wave's transpose buffer (in the activation buffers, which
+        // nobody reads any more)
+        const int oh = a.pool2 ? a.h >> 1 : a.h, ow = a.pool2 ? a.w_ >> 1 : a.w_;
+        const int otw = a.pool2 ? a.tw >> 1 : a.tw;
+        const int oy0 = a.pool2 ? ty0 >> 1 : ty0, ox0 = a.pool2 ? tx0 >> 1 : tx0;
+        const int onpix = a.pool2 ? npix >> 2 : npix;
+        const int rows = a.pool2 ? 8 : 32;           // output pixels of a pass
+        if constexpr (I8) {
+            unsigned char* const tb8 = (unsigned char*)lds + wave * 1024;
+            signed char* const out8 = (signed char*)a.out;
+            const float lo = a.act != 0 ? 0.0f : -128.0f;
+            const bool pool = a.pool2 != 0;
+            f4v sv[4], bv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sv[q] = *(const f4v*)(a.scale + cbc * 32 + q * 8 + lhi * 4);
+                bv[q] = *(const f4v*)(a.bias + cbc * 32 + q * 8 + lhi * 4);
+            }
+            // rows of 32 bytes: 16-byte part c of row r at c ^ (r / 4) % 2, dword d of a part at d ^ (r / 8) % 4 (as in k_c3s)
+            const int wrow = pool ? l32 >> 2 : l32;
+            const int part = ln & 1, pl = ln >> 1;
+            const int cc = cb * 32 + part * 16;
+#pragma unroll
+            for (int p = 0; p < FP; ++p) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float tv[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float t = requant_biased(acc[p][q * 4 + r], sv[q][r], bv[q][r], lo);
+                        if (pool) {
+                            t = __builtin_fmaxf(t, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0xB1, 0xF, 0xF, true)));
+                            t = __builtin_fmaxf(t, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, t), 0x4E, 0xF, 0xF, true)));
+                        }
+                        tv[r] = t;
+                    }
+                    const unsigned u = pack_low_bytes(tv[0], tv[1], tv[2], tv[3]);
+                    if (!pool || (l32 & 3) == 0)
+                        *(unsigned*)(tb8 + wrow * 32 + ((((q >> 1) ^ (wrow >> 2)) & 1) << 4) + (((((q & 1) * 2 + lhi) ^ (wrow >> 3)) & 3) << 2)) = u;
+                }
+                __builtin_amdgcn_wave_barrier();
+                const u4v v = *(const u4v*)(tb8 + pl * 32 + (((part ^ (pl >> 2)) & 1) << 4));
+                const int k = pl >> 3;
+                const u4v v1 = (k & 1) ? u4v{v.y, v.x, v.w, v.z} : v;
+                const u4v v2 = (k & 2) ? u4v{v1.z, v1.w, v1.x, v1.y} : v1;
+                const int opix = (pg * FP + p) * rows + pl;
+                const int ry = (int)__umulhi((unsigned)opix, tw_m), rx = opix - ry * otw;
+                const int gy = oy0 + ry, gx = ox0 + rx;
+                if (pl < rows && opix < onpix && gy < oh && gx < ow && cc < a.cout)
+                    *(u4v*)(out8 + ((size_t)((n * oh + gy) * ow + gx) * a.cout + cc)) = v2;
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            constexpr int ROW = 32 + 8;
+            half_t* const tb = lds + wave * (32 * ROW);
+            half_t* const outp = (half_t*)a.out;
+            const int part = ln & 3, prow = ln >> 2;
+            const int cc = cb * 32 + part * 8;
+            // where the lane stores in a pass (32-bit element offset, or none); the residual vectors there are
+            // requested two passes at a time (a load behind a store waits for the store as well)
+            auto where = [&](int p, int i, unsigned& go) __attribute__((always_inline)) {
+                const int row = i * 16 + prow;
+                const int opix = (pg * FP + p) * rows + row;
+                const int ry = (int)__umulhi((unsigned)opix, tw_m), rx = opix - ry * otw;
+                const int gy = oy0 + ry, gx = ox0 + rx;
+                go = (unsigned)(((n * oh + gy) * ow + gx) * a.cout + cc);
+                return row < rows && opix < onpix && gy < oh && gx < ow && cc < a.cout;
+            };
+            u4v rv[2][2];
+#pragma unroll
+            for (int p = 0; p < FP; ++p) {
+                if ((p & 1) == 0 && resp != nullptr) {
+#pragma unroll
+                    for (int k = p; k < FP && k < p + 2; ++k)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            unsigned go;
+                            const bool ok = where(k, i, go);
+                            rv[k & 1][i] = *(const u4v*)(resp + (ok ? go : 0u));
+                        }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    unsigned u0 = cvt_pk(acc[p][q * 4 + 0], acc[p][q * 4 + 1]);
+                    unsigned u1 = cvt_pk(acc[p][q * 4 + 2], acc[p][q * 4 + 3]);
+                    if (a.pool2) {
+                        u0 = quad_max_pk(u0);
+                        u1 = quad_max_pk(u1);
+                    }
+                    u0 = pk_min(pk_max(u0, lo_e), hi_e);
+                    u1 = pk_min(pk_max(u1, lo_e), hi_e);
+                    const u2v uv = {u0, u1};
+                    if (!a.pool2) *(u2v*)(tb + l32 * ROW + q * 8 + lhi * 4) = uv;
+                    else if ((l32 & 3) == 0) *(u2v*)(tb + (l32 >> 2) * ROW + q * 8 + lhi * 4) = uv;
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    unsigned go;
+                    if (where(p, i, go)) {
+                        u4v v = *(const u4v*)(tb + (i * 16 + prow) * ROW + part * 8);
+                        if (resp != nullptr) {
+                            v.x = pk_min(pk_max(pk_add(v.x, rv[p & 1][i].x), lo_r), hi_r);
+                            v.y = pk_min(pk_max(pk_add(v.y, rv[p & 1][i].y), lo_r), hi_r);
+                            v.z = pk_min(pk_max(pk_add(v.z, rv[p & 1][i].z), lo_r), hi_r);
+                            v.w = pk_min(pk_max(pk_add(v.w, rv[p & 1][i].w), lo_r), hi_r);
+                        }
+                        *(u4v*)(outp + go) = v;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        // the transpose buffers lie where the next item's first block goes
+        if (li + (int)(gridDim.x >> 3) < per_xcd) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+}
+
 // ---- buffer loads: a tensor behind a buffer resource, so that the hardware's range check turns the
 // loads of padding positions into zeros (an offset beyond the tensor returns 0: no branch, no
 // select).  Offsets are bytes; DLF_OOB is an offset no tensor reaches (the host keeps tensors
@@ -4312,8 +4633,26 @@ static c3_kernel_t c3_kernel_i8(int shape)
     }
 }
 
+template <bool I8> static c3_kernel_t c3r_kernel(int shape)
+{
+    switch (shape) {
+    case 0: return k_c3r<4, 7, 64, 10, I8>;
+    case 1: return k_c3r<4, 4, 64, 6, I8>;
+    case 2: return k_c3r<2, 7, 64, 17, I8>;
+    case 3: return k_c3r<2, 4, 64, 11, I8>;
+    case 4: return k_c3r<4, 7, 32, 6, I8>;
+    case 5: return k_c3r<2, 7, 32, 9, I8>;
+    default: return nullptr;
+    }
+}
+
 extern "C" int dlf_kernels_init(void)
 {
+    for (int v = 0; v < 2 * DLF_C3R_SHAPES; ++v) {
+        hipError_t e = hipFuncSetAttribute((const void*)((v & 1) ? c3r_kernel<true>(v >> 1) : c3r_kernel<false>(v >> 1)),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return (int)e;
+    }
     for (int v = 0; v < 2 * DLF_NUM_VARIANTS; ++v) {
         group_kernel_t k = group_kernel(v >> 1, (v & 1) != 0);
         if (k == nullptr) continue;
@@ -4370,6 +4709,17 @@ extern "C" int dlf_launch_c3(const DlfC3Args* a, int shape, int grid, int lds_by
     c3_kernel_t k = c3_kernel(shape);
     if (k == nullptr || grid < 8 || (grid & 7) != 0 || lds_bytes <= 0) return (int)hipErrorInvalidValue;
     launch(k, dim3(grid), dim3(DLF_C3_WAVES * 64), (size_t)lds_bytes, (hipStream_t)stream, *a);
+    return (int)hipGetLastError();
+}
+
+extern "C" int dlf_launch_c3r(const DlfC3Args* a, int shape, int i8, int grid, int lds_bytes, void* stream)
+{
+    c3_kernel_t k = i8 != 0 ? c3r_kernel<true>(shape) : c3r_kernel<false>(shape);
+    if (k == nullptr || grid < 8 || (grid & 7) != 0 || lds_bytes < (int)DLF_C3R_EPI_BYTES || lds_bytes < a->nst * a->na_i * 1024 ||
+        a->pw < a->tw + 2 || (a->pool2 != 0 && ((a->th | a->tw) & 1) != 0) ||
+        (i8 != 0 && (a->scale == nullptr || a->res != nullptr || (a->cout & 15) != 0)))
+        return (int)hipErrorInvalidValue;
+    launch(k, dim3(grid), dim3(DLF_C3R_WAVES * 64), (size_t)lds_bytes, (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
 
