@@ -189,7 +189,7 @@ def group_accounting(net, batch, session):
         elif cfg["kind"] == 5:
             kname = DW_NAME[cfg["variant"]]
         elif cfg["kind"] == 6:
-            kname = "k_dwpw<%d>" % cfg["variant"]
+            kname = "k_dwpw<%d>" % cfg["variant"] if cfg["variant"] < 16 else "k_skd<%d>" % (2 << (cfg["variant"] - 16))
         elif cfg["kind"] == 7:
             kname = "k_dwt<%d>" % (cfg["variant"] + 1)
         elif cfg["kind"] == 10 and cfg["variant"] in SKC_NAME:

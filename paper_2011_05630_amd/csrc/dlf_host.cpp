@@ -156,7 +156,7 @@ dlf_status pack_and_upload(Layer& L)
 // Fusion groups
 // ------------------------------------------------------------------------------------------
 
-enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13, GK_C3R = 14 };
+enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13, GK_C3R = 14, GK_SKD = 15 };
 
 struct TileCfg {
     int th, tw;      // tile of the group's final output tensor
@@ -186,7 +186,7 @@ struct GroupPlan {
     DlfDwPwArgs dp;
     DlfDwtArgs dt;
     DlfDwsArgs ds;
-    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn; DlfSkcArgs sk;
+    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn; DlfSkcArgs sk; DlfSkdArgs sd;
 };
 
 const int VAR_FC[DLF_NUM_VARIANTS] = {2, 1, 1, 1};
@@ -258,7 +258,7 @@ const int64_t C_C3R_EDGE[DLF_C3R_SHAPES] = {7000, 4000, 9000, 6000, 7000, 9000};
 const int64_t C_C3R_ITEM[DLF_C3R_SHAPES] = {4000, 2000, 6500, 3500, 4000, 6500};
 const int64_t C3R_MMA_ALONE[DLF_C3R_SHAPES] = {160, 140, 160, 150, 160, 160};
 const int64_t C3R_MMA_SHARED = 142;
-const int64_t C3R_FEW_ITEMS = 128;      // ... a launch of at most so many items leaves half of the chip idle
+const int64_t C3R_FEW_ITEMS = 128;
 
 // streaming depthwise kernel: per work item (decode, weights, first rows of the window), per output
 // row of a wave (about a hundred vector instructions; the waves of a SIMD share its issue slots),
@@ -315,6 +315,7 @@ const int64_t C_C3S_RED = 1500;
 const int64_t C3S_SMALL_ITEMS = 128;
 const int64_t C_C3S_SMALL = 1200;
 const int64_t C_C3S_STEP_SMALL = 183;
+const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
 const int64_t C_C3S_EPI = 2500;
 // the fused 3x3 -> 1x1 kernel for small maps: per work item (decode, first loads), bytes per cycle of
 // its LDS intake, cycles per MFMA of a SIMD, per K step of the first layer's weight ring (requests
@@ -338,8 +339,28 @@ const int64_t C3PW_OVERLAP_PCT = 60;         // two workgroups per CU: what a fu
 // (49 bytes per cycle for a workgroup alone on its CU, 34 if it gathers 32 pixels; several share the
 // first-level cache and its path to L2 and get 28 or 25 together).  Fitted to 10 layer shapes at batch 1, 2 and 4 in chains of 12 layers.
 const int64_t C_SKC_ITEM = -900;
+const int64_t SKC_FEW_ITEMS = 128;
 const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
 const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
+
+// depthwise + 1x1 pair for outputs of few pixels: a whole launch of one item per CU (at least; by shape; per 32-channel step
+// of K), and what a further item per CU adds.  Fitted to MobileNet-v1's nine pairs at batch 1, 2 and 4 in chains of six.
+const int64_t C_SKD_LEAST = 10800;
+const int64_t C_SKD_ITEM[DLF_SKD_SHAPES] = {7000, 7800};
+const int64_t C_SKD_STEP = 565;
+const int64_t C_SKD_ROUND = 700;
+const int64_t C_SKD_ROUND_STEP = 700;
+// ... and on the same pairs the other depthwise kernels in launches that leave places free (C_LAUNCH holds most of
+// such a launch's round trips; in per cent): the tile kernel with one tile per CU at most (5.0 - 7.4 us, 11 - 14
+// without this), the small-map kernel with one item (8.5 / 10.6 / 13.4 / 17.8, 14.7 -
+// 25.2; batch 18 10.0 and 13.1, 15.8 and 18.8), a streaming layer
+// of one item per SIMD (4.4 - 6.0, 8.0)
+const int64_t DWT_ONE_PCT = 30;
+const int64_t DWT_ONE_BYTES = 5 << 20;
+const int64_t DWS_SMALL_BYTES = 8 << 20;
+const int64_t DWS_SMALL_PCT = 92;
+const int64_t C_DWS_SMALL = 8000;
+const int64_t DW_ONE_PCT = 30;
 
 struct StageSpec {   // one stage, before tiling
     int layer;
@@ -1018,9 +1039,10 @@ uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3C
     const int64_t bytes = m * L.d.cin * 2 + (pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
     const int64_t mem = bytes / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
     int64_t cycles = C_LAUNCH + std::max(compute, mem);
-    // With most of the chip idle a split of K is the better kernel, and the model of the fused-group kernel's is too
-    // high there (256 channels at 56 x 56 with the pool, batch 1, 56 items: 12.8 us, modelled 18.3, here 15.2)
-    if (items <= C3R_FEW_ITEMS) cycles = cycles * 4 / 3;
+    // With half of the chip idle (counted in items of 128 channels x 128 pixels, all of them used) a split of K is the better
+    // kernel, and the model of the fused-group kernel's is too high there (256 channels at 56 x 56 with the pool, batch
+    // 1: 12.8 us, modelled 18.3, here 15.2)
+    if (m * L.ncb <= C3R_FEW_ITEMS * 4 * 128) cycles = cycles * 4 / 3;
     return (uint64_t)(cycles * PS_PER_CYCLE);
 }
 
@@ -1103,8 +1125,9 @@ uint64_t dw_cost_ps(const Layer& L, int batch, int budget, const DlfDwArgs& da)
     const int64_t rows = std::min<int64_t>(L.out_h, L.d.stride == 1 ? DLF_DW_ROWS1 : DLF_DW_ROWS2);
     // the items of a CU are dealt to its four SIMDs; a SIMD's waves share its instruction issue
     const int64_t items_simd = ((int64_t)da.nitems + (int64_t)budget * 4 - 1) / ((int64_t)budget * 4);
-    const int64_t compute = C_LAT + items_simd * (C_DW_ITEM / (DW_WAVES_PER_CU / 4) + rows * C_DW_ROW);
+    int64_t compute = C_LAT + items_simd * (C_DW_ITEM / (DW_WAVES_PER_CU / 4) + rows * C_DW_ROW);
     const int64_t bytes = (int64_t)da.in_bytes + (int64_t)batch * L.out_h * L.out_w * L.out_c * 2 + (int64_t)L.cin_pad * 22;
+    if (items_simd <= 1 && bytes <= DWS_SMALL_BYTES) compute = compute * DW_ONE_PCT / 100;
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
 }
@@ -1205,10 +1228,11 @@ uint64_t dwt_cost_ps(const Layer& D, const Layer& P, int batch, int budget, cons
     const int64_t conc = std::min<int64_t>(occ, tiles_cu);
     // ... but not the rate at which the CU takes in the weight fragments every tile streams anew
     const int64_t intake = tiles_cu * ((int64_t)dt.ncb * dt.npg * dt.nsteps * 1024) / PW_BYTES_PER_CYCLE;
-    const int64_t compute = C_LAT + std::max(tiles_cu * tile / conc, intake);
+    int64_t compute = C_LAT + std::max(tiles_cu * tile / conc, intake);
     const int64_t m = (int64_t)batch * D.out_h * D.out_w;
     const int64_t bytes = (int64_t)batch * D.in_h * D.in_w * D.in_c * 2 + m * P.d.cout * 2 +
                           (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
+    if (tiles_cu <= 1 && bytes <= DWT_ONE_BYTES) compute = std::max(compute * DWT_ONE_PCT / 100, intake);
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
 }
@@ -1320,7 +1344,7 @@ uint64_t c3s_cost_ps(const Layer& L, int batch, int budget, const DlfC3sArgs& cs
     // rate a CU takes eight waves' weights in (183 cycles per step: 45 bytes per cycle), not at the
     // chip's matrix rate (256 channels at 14 x 14, batch 1 - 8: 8.3 - 8.5 us; 512 at 7 x 7: 11.4)
     if (nitems <= (cs.taps == 9 ? C3S_SMALL_ITEMS : C3S_SMALL_ITEMS / 2) && rounds == 1)
-        compute = C_C3S_SMALL + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE + (int64_t)(cs.nsteps / cs.ksplit) * C_C3S_STEP_SMALL;
+        compute = C_C3S_SMALL + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE + (int64_t)(cs.nsteps / cs.ksplit) * (nitems > C3S_SMALL_ITEMS / 2 && cs.ksplit < 4 ? C_C3S_STEP_HALF : C_C3S_STEP_SMALL);
     const int64_t m = (int64_t)batch * L.out_h * L.out_w;
     const int64_t bytes = (int64_t)batch * L.in_h * L.in_w * L.d.cin * 2 + m * L.d.cout * 2 * (L.d.residual_from >= 0 ? 2 : 1) +
                           (int64_t)L.ncb * L.nsteps * 1024;
@@ -1596,8 +1620,12 @@ uint64_t skc_cost_ps(const DlfSkcArgs& sk, int shape, int budget)
     const int64_t items = (int64_t)sk.n_pg * sk.n_cg;
     const int64_t bytes = (int64_t)(sk.nk + sk.nk2) * (SKC_TP[shape] + SKC_TC[shape]) * 1024;
     int64_t intake = bytes / SKC_BYTES_PER_CYCLE[shape];
+    // the taps of a 3x3 filter meet in the first-level cache, a long 1x1 row does not (2048 channels, 240 items: 12 us)
+    if (shape == 3 && sk.kh * sk.kw == 1 && items > SKC_FEW_ITEMS) intake = bytes / SKC_SHARED_BYTES_PER_CYCLE[shape];
     if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
     int64_t cycles = C_LAUNCH + C_SKC_ITEM + intake;
+    // 32 pixels x 64 channels on nearly every CU: 15 - 20 % above the fit (64 -> 64 3x3 at 32 x 32, batch 7, 224 items: 6.2 us, not 5.3)
+    if (shape == 3 && items <= budget && items * 4 > (int64_t)budget * 3) cycles = cycles * 5 / 4;
     // The kernel is for launches of at most about one item per CU.  Beyond that the models of the
     // kernels it competes with are too high (single layers on the fused-group kernel by up to 6 us), so
     // it has to be ahead by a third there.
@@ -1614,6 +1642,62 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
         skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
         const uint64_t c = skc_cost_ps(sk, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
+    }
+    return found;
+}
+
+// ---- depthwise + 1x1 pair for outputs of few pixels ----
+
+// Testing hook: as SkcForce.
+SkcForce g_skd_force = {0, -1, 0};
+const int SKD_TC[DLF_SKD_SHAPES] = {2, 4};          // 16-channel blocks of an item
+
+bool skd_eligible(const dlf_net_s& net, int first, int last, int batch)
+{
+    if (!dwpw_eligible(net, first, last, batch)) return false;
+    const Layer& P = net.L[last];
+    // items, pixels and rows are divided as 32-bit products
+    const int64_t m = (int64_t)batch * P.out_h * P.out_w;
+    return m <= 1 << 17 && m * std::max(P.out_h, P.out_w) < (int64_t)1 << 31 && (int64_t)P.ncb * P.nsteps * 1024 < (int64_t)1 << 31 &&
+           net.L[first].d.cin <= 2048;                             // (the weights' place in LDS)
+}
+
+void skd_fill(const Layer& D, const Layer& P, int batch, int shape, int waves, DlfSkdArgs& sd)
+{
+    memset(&sd, 0, sizeof sd);
+    sd.wdw = D.d_w; sd.bdw = D.d_bias; sd.wpw = P.d_w; sd.bpw = P.d_bias;
+    sd.in_bytes = (uint32_t)((int64_t)batch * D.in_h * D.in_w * D.in_c * 2);
+    sd.h = D.in_h; sd.w_ = D.in_w; sd.c = D.d.cin; sd.cpad = D.cin_pad; sd.oh = D.out_h; sd.ow = D.out_w; sd.stride = D.d.stride;
+    sd.act_dw = D.d.act; sd.act_pw = P.d.act; sd.cout = P.d.cout; sd.ncb = P.ncb; sd.nk = D.d.cin / 32;
+    sd.m = batch * D.out_h * D.out_w;
+    sd.n_pg = ceil_div(sd.m, 16);
+    sd.n_cg = ceil_div(P.d.cout, 16 * SKD_TC[shape]);
+    // two waves, four from 8 steps on (measured at 1, 2 and 4: 256 channels 8.2 / 6.2 / 6.1 us, 512 11.8 / 8.4 / 7.5, 1024
+    // 20.5 / 12.6 / 11.7; at 128 channels 7.3 / 7.6 / 9.3)
+    sd.nw = waves > 0 ? std::min(waves, DLF_SKD_MAX_WAVES) : sd.nk >= 8 ? 4 : 2;
+    while (sd.nw > 1 && sd.nw / 2 >= sd.nk) sd.nw /= 2;
+    sd.ksw = ceil_div(sd.nk, sd.nw);
+    auto magic = [](int d) { return 0xFFFFFFFFu / (unsigned)d + 1u; };
+    sd.n_cg_m = magic(sd.n_cg); sd.ow_m = magic(sd.ow); sd.oh_m = magic(sd.oh);
+}
+
+uint64_t skd_cost_ps(const DlfSkdArgs& sd, int shape, int budget)
+{
+    const int64_t items = (int64_t)sd.n_pg * sd.n_cg;
+    const int64_t rounds = (items + budget - 1) / budget;
+    const int64_t cycles = std::max(C_SKD_LEAST, C_SKD_ITEM[shape] + sd.nk * C_SKD_STEP) + (rounds - 1) * (C_SKD_ROUND + sd.nk * C_SKD_ROUND_STEP);
+    return (uint64_t)(cycles * PS_PER_CYCLE);
+}
+
+bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, DlfSkdArgs& best, int& shape, uint64_t& cost)
+{
+    bool found = false;
+    for (int sh = 0; sh < DLF_SKD_SHAPES; ++sh) {
+        if (g_skd_force.shape >= 0 && sh != g_skd_force.shape) continue;
+        DlfSkdArgs sd;
+        skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
+        const uint64_t c = skd_cost_ps(sd, sh, budget);
+        if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }
     return found;
 }
@@ -1669,10 +1753,11 @@ uint64_t dws_cost_ps(const Layer& D, const Layer& P, int batch, int budget, cons
     const int64_t item = C_DWS_ITEM + (int64_t)ds.rp * ds.c * 2 / DWS_BYTES_PER_CYCLE + exposed + dw + std::max(mma, intake) +
                          (int64_t)ds.cbw * C_DWS_EPI;
     const int64_t nitems = (int64_t)ds.ntiles * ds.nsl;
-    const int64_t compute = C_LAT + ((nitems + budget - 1) / budget) * item;
+    int64_t compute = C_LAT + ((nitems + budget - 1) / budget) * item;
     const int64_t m = (int64_t)batch * D.out_h * D.out_w;
     const int64_t bytes = (int64_t)batch * D.in_h * D.in_w * D.in_c * 2 + m * P.d.cout * 2 +
                           (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
+    if (nitems <= budget && bytes <= DWS_SMALL_BYTES) compute = std::max<int64_t>(0, compute * DWS_SMALL_PCT / 100 - C_DWS_SMALL);
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
 }
@@ -2073,9 +2158,28 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     // a caller or a testing hook that names another kernel's form gets that kernel
     const bool named = force_tc || pw_mode > 0 || c3_force || g_force.th > 0 || g_pw_mode != 0 || g_c3_force.mode != 0 ||
                        g_c3_force.shape >= 0 || g_dw_mode != 0;
-    if (g_skc_force.mode == 2 || (named && g_skc_force.mode == 0)) return s;
+    if (named && g_skc_force.mode != 1 && g_skd_force.mode != 1) return s;
     if (first < 0 || last >= (int)net.L.size() || first > last || budget <= 0 || last > first + 1) return s;
     const Layer& L0 = net.L[first];
+    if (g_skd_force.mode != 2 && !(named && g_skd_force.mode == 0) && last == first + 1 && skd_eligible(net, first, last, batch)) {
+        DlfSkdArgs sd;
+        int shape = 0;
+        uint64_t cost = 0;
+        if (!skd_choose(L0, net.L[last], batch, budget, sd, shape, cost)) return s;
+        if (s == DLF_OK && g_skd_force.mode != 1 && g.cost <= cost) return s;
+        g = GroupPlan();
+        g.first = first; g.last = last; g.budget = budget;
+        g.in_layer = L0.src;
+        g.sd = sd;
+        g.kind = GK_SKD;
+        g.cost = cost;
+        g.variant = shape;
+        g.occ = 1;
+        g.grid = sd.n_pg * sd.n_cg;
+        g.th = 1; g.tw = 16;
+        g.lds_bytes = DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw);
+        return DLF_OK;
+    }
     const Layer* conv = nullptr;
     const Layer* proj = nullptr;
     int pool2 = 0;
@@ -2090,6 +2194,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
         conv = &L0;
         pool2 = specs[0].pool2;
     }
+    if (g_skc_force.mode == 2 || (named && g_skc_force.mode == 0)) return s;
     if (!skc_layer_ok(*conv, batch) || (proj && !skc_layer_ok(*proj, batch))) return s;
     DlfSkcArgs sk;
     int shape = 0;
@@ -2610,8 +2715,9 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
     // the split-K convolution is reported as a form of the small-map kernel, with a projection as
     // one of the two-operand kind
     // ..., the block kernel with the weights in registers as a form of the block kernel
-    if (kind) *kind = G.kind == GK_C3R ? GK_C3 : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
-    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R ? G.variant : 16 + G.variant;
+    // ..., the depthwise pair for few pixels as a form of the register kernel
+    if (kind) *kind = G.kind == GK_C3R ? GK_C3 : G.kind == GK_SKD ? GK_DWPW : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
+    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R && G.kind != GK_SKD ? G.variant : 16 + G.variant;
     if (nslices) *nslices = G.kind == GK_GROUP ? G.ga.nslices : 1;
     if (slice_c) *slice_c = G.kind == GK_GROUP ? G.ga.slice_c : 0;
     if (stream0) *stream0 = G.kind == GK_GROUP ? G.ga.stream0 : 0;
@@ -2643,6 +2749,12 @@ void dlf_debug_small_mode(int32_t mode, int32_t shape, int32_t waves)
 {
     g_skc_force = SkcForce{(mode >= 0 && mode <= 2) ? mode : 0, shape < DLF_SKC_SHAPES ? shape : -1,
                            waves == 1 || waves == 2 || waves == 4 || waves == 8 ? waves : 0};
+}
+
+void dlf_debug_small_pair_mode(int32_t mode, int32_t shape, int32_t waves)
+{
+    g_skd_force = SkcForce{(mode >= 0 && mode <= 2) ? mode : 0, shape < DLF_SKD_SHAPES ? shape : -1,
+                           waves == 1 || waves == 2 || waves == 4 ? waves : 0};
 }
 
 void dlf_debug_force_ksplit(int32_t ksplit) { g_force.ksplit = ksplit > 0 ? ksplit : 1; }
@@ -2746,6 +2858,10 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
             else sk.res = res;
         }
         e = dlf_launch_skc ? dlf_launch_skc(&sk, G.variant, stream) : (int)hipErrorInvalidDeviceFunction;
+    } else if (G.kind == GK_SKD) {
+        DlfSkdArgs sd = G.sd;
+        sd.in = in; sd.out = out;
+        e = dlf_launch_skd ? dlf_launch_skd(&sd, G.variant, stream) : (int)hipErrorInvalidDeviceFunction;
     } else if (G.kind == GK_DWS) {
         DlfDwsArgs ds = G.ds;
         ds.in = in; ds.out = out;

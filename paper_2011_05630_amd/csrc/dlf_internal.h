@@ -401,6 +401,28 @@ struct DlfSkcArgs {
     uint32_t n_cg_m, pw_m, ph_m, taps_m, kw_m;   // reciprocals for division by n_cg, pw, ph, kh * kw, kw
 };
 
+// A depthwise 3x3 layer and the 1x1 layer behind it for outputs of few pixels (k_skd): a workgroup of `nw` waves
+// computes 16 pixels x 16 * TC channels, each wave over its own share of the depthwise layer's channels.
+#define DLF_SKD_SHAPES 2             // TC = 2, 4
+#define DLF_SKD_MAX_WAVES 4
+// partial sums, and each wave's depthwise weights and biases (9 halfs and a float per channel of its share)
+#define DLF_SKD_LDS_BYTES(NW, C, KSW) ((NW) * (16 * (C) * 4 + (KSW) * 32 * 22))
+struct DlfSkdArgs {
+    const void* in;       // [batch][h][w][c] fp16
+    void* out;            // [batch][oh][ow][cout] fp16
+    const void* wdw;      // depthwise weights [9][cpad] fp16 (tap-major)
+    const float* bdw;     // depthwise bias [cpad]
+    const void* wpw;      // pointwise weights, packed fragments
+    const float* bpw;     // pointwise bias, padded to ncb * 32
+    uint32_t in_bytes;    // size of the input tensor (below 2 GiB)
+    int32_t h, w_, c, cpad, oh, ow, stride, act_dw, act_pw;
+    int32_t cout, ncb, nk;          // nk: 32-channel steps = c / 32
+    int32_t m;            // output pixels = batch * oh * ow
+    int32_t n_pg, n_cg;   // groups of 16 pixels, of 16 * TC channels
+    int32_t nw, ksw;      // waves per workgroup (1, 2 or 4), steps per wave
+    uint32_t n_cg_m, ow_m, oh_m;    // reciprocals for division by n_cg, ow, oh
+};
+
 struct DlfGapArgs {
     const void* x;        // [batch][hw][c]
     void* y;              // [batch][c]
@@ -432,6 +454,7 @@ int dlf_launch_c3pw(const DlfC3PwArgs* a, int grid, int lds_bytes, void* stream)
 int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, void* stream);
 // (weak: a host-only build of the planner, which launches nothing, links without it)
 __attribute__((weak)) int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream);
+__attribute__((weak)) int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream);
 int dlf_kernels_init(void);
 // Attaches a start / stop event pair (hipEvent_t, either may be null) to this thread's next launch.
 void dlf_next_launch_events(void* start, void* stop);

@@ -4548,6 +4548,139 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
     }
 }
 
+// A depthwise 3x3 layer (pad 1, stride 1 or 2) and the 1x1 layer behind it for outputs of few pixels: the pairs of
+// MobileNet-style networks at small batch, which k_dwt / k_dws need more pixels for.
+// Built as k_skc: work item = 16 pixels x 16 * TC channels of the 1x1 layer, K -- the depthwise layer's channels -- dealt to
+// the waves in shares of 32-channel steps, partial sums in LDS.  In a step a lane computes the depthwise result of its pixel
+// and 8 channels in registers (nine 16-byte loads through a buffer resource whose range check supplies the padding, the
+// order of sums and the rounding of k_dw): that is the MFMA "B" operand as it stands.  Every channel group computes it
+// again: 72 multiply-adds a step.  What bounds an item is the CU's vector-memory path, (9 + TC) KiB a step; the depthwise
+// weights and biases of a share go through LDS (fetched per step they were 11 KiB more: 512 -> 512 channels at 14 x 14 8.3 ->
+// 7.5 us).  Operands of step s + 1 are requested ahead of the arithmetic of step s; three or four steps at a time is slower
+// (8.5 us: requests beyond a share cost the path what real ones do).
+// Batch 1 against the faster of k_dwt and k_dws: 256 -> 256 at 28 x 28 7.3 -> 6.1 us, 256 -> 512 stride 2 8.6 -> 5.6, 512 -> 512 at
+// 14 x 14 10.6 -> 7.5, 512 -> 1024 stride 2 13.5 -> 7.4; on the maps in front k_dwt is ahead (128 at 56 x 56: 5.2 against 6.6).
+template <int TC>
+__global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs a)
+{
+    constexpr int P = 16, C = 16 * TC;
+    float* const part = (float*)lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q = lane >> 4;
+    const int pg = div_by((int)blockIdx.x, a.n_cg_m), cg = (int)blockIdx.x - pg * a.n_cg;
+    const int k0 = wave * a.ksw, k1 = min(k0 + a.ksw, a.nk);
+    const int rc = cg * C + tid % (C / 4) * 4;
+    const f4v bv = *(const f4v*)(a.bpw + min(rc, a.ncb * 32 - 4));
+    f4v acc[TC];
+#pragma unroll
+    for (int c = 0; c < TC; ++c) acc[c] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+
+    if (k0 < k1) {
+        const i32x4 rin = make_rsrc(a.in, a.in_bytes);
+        const i32x4 rwp = make_rsrc(a.wpw, (unsigned)a.ncb * (unsigned)a.nk * 2048u);
+        const i32x4 rwd = make_rsrc(a.wdw, 9u * (unsigned)a.cpad * 2u);
+        const i32x4 rbd = make_rsrc(a.bdw, (unsigned)a.cpad * 4u);
+        int aoff[TC];
+        unsigned cb[TC];
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+            const int sc = cg * TC + c;
+            cb[c] = (unsigned)min(sc >> 1, a.ncb - 1);
+            aoff[c] = (q >> 1) * 1024 + ((q & 1) * 32 + (sc & 1) * 16 + r16) * 16;
+        }
+        // the lane's pixel: byte offsets of its nine taps' 16 bytes of the first step, or out of range
+        int voff[9];
+        {
+            const int px = pg * P + r16;
+            const int row = div_by(px, a.ow_m), n = div_by(row, a.oh_m);
+            const int ox = px - row * a.ow, oy = row - n * a.oh;
+            const int iy = oy * a.stride - 1, ix = ox * a.stride - 1;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int y = iy + t / 3, x = ix + t % 3;
+                const bool ok = px < a.m && y >= 0 && y < a.h && x >= 0 && x < a.w_;
+                voff[t] = ok ? ((n * a.h + y) * a.w_ + x) * a.c * 2 + q * 16 : DLF_OOB;
+            }
+        }
+        const unsigned lo_d = act_lo(a.act_dw), hi_d = act_hi(a.act_dw);
+        u4v x[2][9];
+        h8 A[2][TC];
+        // the share's depthwise weights [tap][channel] and biases, in the wave's own part of LDS: a vector of them serves
+        // sixteen pixels, and requested per step the eleven would take more of the CU's path than the inputs
+        half_t* const wl = (half_t*)(part + a.nw * (P * C)) + wave * (a.ksw * 32 * 11);
+        const int row = a.ksw * 4, nparts = 9 * row, n = nparts + 2 * row;
+        const unsigned row_m = div_magic(row);
+        auto weight = [&](int i) __attribute__((always_inline)) {      // 16-byte part i: nine rows of weights, two of biases
+            const int t = (int)__umulhi((unsigned)i, row_m), r = i - t * row;
+            const int wo = i < nparts && k0 * 4 + r < a.nk * 4 ? (t * a.cpad + k0 * 32 + r * 8) * 2 : DLF_OOB;
+            const int bo = i >= nparts && i < n && k0 * 8 + (i - nparts) < a.nk * 8 ? k0 * 128 + (i - nparts) * 16 : DLF_OOB;
+            const u4v v = __builtin_bit_cast(u4v, raw_buffer_load_x4(rwd, wo, 0, 0)), u = __builtin_bit_cast(u4v, raw_buffer_load_x4(rbd, bo, 0, 0));
+            return v | u;
+        };
+        u4v wv[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) wv[i] = weight(i * 64 + lane);
+        // (a step beyond the share fetches nothing: out of range, zeros)
+        auto request = [&](int s, int d) __attribute__((always_inline)) {
+            const bool ok = s < k1;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) x[d][t] = __builtin_bit_cast(u4v, raw_buffer_load_x4(rin, ok ? voff[t] : DLF_OOB, s * 64, 0));
+#pragma unroll
+            for (int c = 0; c < TC; ++c)
+                A[d][c] = __builtin_bit_cast(h8, raw_buffer_load_x4(rwp, ok ? aoff[c] : DLF_OOB, (int)((cb[c] * (unsigned)a.nk + (unsigned)s) * 2048u), 0));
+        };
+        auto multiply = [&](int s, int d) __attribute__((always_inline)) {
+            const half_t* const ws = wl + (s - k0) * 32 + q * 8;
+            const float* const bs = (const float*)(wl + 9 * a.ksw * 32) + (s - k0) * 32 + q * 8;
+            const f4v b0 = *(const f4v*)bs, b1 = *(const f4v*)(bs + 4);
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = b0[j]; v[j + 4] = b1[j]; }
+#pragma unroll
+            for (int t = 0; t < 9; ++t) dw_tap(v, x[d][t], *(const u4v*)(ws + t * a.ksw * 32));
+            u4v hv;
+            hv.x = pk_min(pk_max(cvt_pk(v[0], v[1]), lo_d), hi_d);
+            hv.y = pk_min(pk_max(cvt_pk(v[2], v[3]), lo_d), hi_d);
+            hv.z = pk_min(pk_max(cvt_pk(v[4], v[5]), lo_d), hi_d);
+            hv.w = pk_min(pk_max(cvt_pk(v[6], v[7]), lo_d), hi_d);
+#pragma unroll
+            for (int c = 0; c < TC; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], __builtin_bit_cast(h8, hv), acc[c], 0, 0, 0);
+        };
+        request(k0, 0);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i * 64 + lane < n) *(u4v*)(wl + (i * 64 + lane) * 8) = wv[i];
+        for (int i = 192 + lane; i < n; i += 64) *(u4v*)(wl + i * 8) = weight(i);
+        __builtin_amdgcn_wave_barrier();
+        for (int s = k0; s < k1; s += 2) {
+            request(s + 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(s, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 >= k1) break;
+            request(s + 2, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(s + 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // partial sums: [wave][pixel][channel], as in k_skc
+    float* const mine = part + wave * (P * C);
+#pragma unroll
+    for (int c = 0; c < TC; ++c) *(f4v*)(mine + r16 * C + c * 16 + q * 4) = acc[c];
+    __syncthreads();
+    const unsigned lo = act_lo(a.act_pw), hi = act_hi(a.act_pw);
+    for (int e = tid; e < P * C / 4; e += a.nw * 64) {
+        const int rp = pg * P + e / (C / 4);
+        f4v sum = bv;
+        for (int i = 0; i < a.nw; ++i) sum += *(const f4v*)(part + i * (P * C) + e * 4);
+        const u2v o = {pk_min(pk_max(cvt_pk(sum.x, sum.y), lo), hi), pk_min(pk_max(cvt_pk(sum.z, sum.w), lo), hi)};
+        if (rp < a.m && rc < a.cout) *(u2v*)((half_t*)a.out + (size_t)rp * a.cout + rc) = o;
+    }
+}
+
 // Global average pooling: fp32 sum over H*W, mean, fp16.
 __global__ __launch_bounds__(256) void k_gap(const DlfGapArgs a)
 {
@@ -4963,6 +5096,16 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
     static const int px[DLF_SKC_SHAPES] = {16, 16, 16, 32}, ch[DLF_SKC_SHAPES] = {16, 32, 64, 64};
     if (shape < 0 || shape >= DLF_SKC_SHAPES || (a->nw != 1 && a->nw != 2 && a->nw != 4 && a->nw != 8)) return (int)hipErrorInvalidValue;
     launch(k[a->nk2 > 0 ? 1 : 0][shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * px[shape] * ch[shape] * 4,
+           (hipStream_t)stream, *a);
+    return (int)hipGetLastError();
+}
+
+extern "C" int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream)
+{
+    static void (*const k[DLF_SKD_SHAPES])(const DlfSkdArgs) = {k_skd<2>, k_skd<4>};
+    if (DLF_SKD_LDS_BYTES(a->nw, 64, a->ksw) > 64 * 1024) return (int)hipErrorInvalidValue;
+    if (shape < 0 || shape >= DLF_SKD_SHAPES || a->ksw < 1 || a->nw < 1 || a->nw > DLF_SKD_MAX_WAVES || (a->nw & (a->nw - 1)) != 0) return (int)hipErrorInvalidValue;
+    launch(k[shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), DLF_SKD_LDS_BYTES(a->nw, 32 << shape, a->ksw),
            (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
