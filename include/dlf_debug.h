@@ -60,7 +60,7 @@ void dlf_debug_depthwise_tile(int32_t wx, int32_t rw);
  * kernel for a whole bottleneck block (1x1 to 64 channels, 3x3, 1x1; th, tw as for 6, at most 64
  * pixels), 8 .. 13 = the block kernel with its weights in registers (channels x pixels and input channels at a
  * time: 128 x 224 and 64, 128 x 128 and 64, 64 x 448 and 64, 64 x 256 and 64, 128 x 224 and 32, 64 x 448 and
- * 32); a shape
+ * 32), 14 = shape 10 with a first 3x3 layer of at most three input and 64 output channels in front, as one group; a shape
  * that cannot be laid out falls back to the fused-group kernel.  Mode 2 keeps such a pair of layers
  * on the fused-group kernel as well.
  * Process-wide, not thread-safe. */

@@ -259,6 +259,7 @@ const int64_t C_C3R_ITEM[DLF_C3R_SHAPES] = {4000, 2000, 6500, 3500, 4000, 6500};
 const int64_t C3R_MMA_ALONE[DLF_C3R_SHAPES] = {160, 140, 160, 150, 160, 160};
 const int64_t C3R_MMA_SHARED = 142;
 const int64_t C3R_FEW_ITEMS = 128;
+const int64_t C_C3R_STEM = 4000;             // an item's layer in front
 
 // streaming depthwise kernel: per work item (decode, weights, first rows of the window), per output
 // row of a wave (about a hundred vector instructions; the waves of a SIMD share its issue slots),
@@ -1064,6 +1065,43 @@ bool c3r_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C
                 const int64_t n = (int64_t)ceil_div(L.out_h, th) * ceil_div(L.out_w, tw) * ceil_div(L.ncb, C3R_NCBW[shape]);
                 if (!found || cc < cost || (cc == cost && n < items)) { found = true; cost = cc; best = c; items = n; }
             }
+        }
+    return found;
+}
+
+// Two 3x3 stride-1 layers, the first of 64 channels on an image of at most three channels, the second (with the pool behind it)
+// of any number: the first computed for the halo region of the second's tiles.
+bool c3r_stem_eligible(const dlf_net_s& net, const std::vector<StageSpec>& specs, int batch)
+{
+    if (specs.size() != 2 || specs[0].kind != DLF_ST_CONV || specs[1].kind != DLF_ST_CONV || specs[0].pool2) return false;
+    const Layer& A = net.L[specs[0].layer];
+    const Layer& B = net.L[specs[1].layer];
+    const dlf_layer_desc& d = A.d;
+    if (d.op != DLF_CONV || d.kh != 3 || d.kw != 3 || d.stride != 1 || d.pad != 1 || d.residual_from >= 0 || !A.im2col || A.rowfold) return false;
+    if (9 * d.cin > 32 || d.cout != 64 || A.nsteps != 2 || (int64_t)batch * A.in_h * A.in_w * A.in_c >= (int64_t)1 << 31) return false;
+    const std::vector<StageSpec> second(1, specs[1]);
+    return c3_eligible(net, second, batch) && B.d.cin == 64 && B.d.residual_from < 0;
+}
+
+bool c3r_stem_choose(const Layer& A, const Layer& B, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost, int fth = 0, int ftw = 0)
+{
+    bool found = false;
+    for (int th : TILE_H)
+        for (int tw : TILE_W) {
+            if (fth > 0 && (th != fth || tw != ftw)) continue;
+            if (fth <= 0 && ((th > B.out_h && (th - B.out_h) >= 4) || (tw > B.out_w && (tw - B.out_w) >= 4))) continue;
+            C3Cfg c;
+            int pw, vw;
+            if (!c3r_build(pool2, 64, DLF_C3R_STEM_SHAPE, th, tw, max_lds, c, pw, vw)) continue;
+            c.lds_bytes = std::max(c.na_i * 1024 + DLF_C3R_STEM_BYTES(th, tw, A.d.cin), (int)DLF_C3R_EPI_BYTES);
+            if (c.lds_bytes > max_lds) continue;
+            const int64_t items = (int64_t)batch * ceil_div(B.out_h, th) * ceil_div(B.out_w, tw) * ceil_div(B.ncb, C3R_NCBW[DLF_C3R_STEM_SHAPE]);
+            const int64_t items_cu = (items + budget - 1) / budget;
+            uint64_t cc = c3r_cost_ps(B, pool2, batch, budget, c) + (uint64_t)(items_cu * C_C3R_STEM * PS_PER_CYCLE);
+            // (half of the chip idle, in items of 64 channels x 512 pixels: as in c3r_cost_ps; VGG-16 batch 1 17.4 us, the
+            // fused-group kernel 15.1)
+            if ((int64_t)batch * B.out_h * B.out_w * B.ncb <= C3R_FEW_ITEMS * 2 * 512) cc = cc * 4 / 3;
+            if (!found || cc < cost) { found = true; cost = cc; best = c; }
         }
     return found;
 }
@@ -2120,6 +2158,28 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
             return DLF_OK;
         }
     }
+    // a first layer of few channels and the 3x3 layer behind it: shape C3R_HOOK + DLF_C3R_SHAPES of the testing hook
+    if (c3f.mode != 2 && (c3f.shape < 0 || c3f.shape == C3R_HOOK + DLF_C3R_SHAPES) && !(force_tc && force_tc->th > 0) && pwm == 0 &&
+        g_force.th <= 0 && g_dw_mode == 0 && c3r_stem_eligible(net, specs, batch)) {
+        const Layer& B = net.L[specs[1].layer];
+        const int pool2 = specs[1].pool2;
+        C3Cfg cc;
+        uint64_t c = 0;
+        const bool forced = c3f.shape >= 0;
+        if (c3r_stem_choose(L0, B, pool2, batch, budget, max_lds, cc, c, forced ? c3f.th : 0, forced ? c3f.tw : 0) && (!tiled || c3f.mode == 1 || c < cost)) {
+            DlfC3Args& ca = g.ca;
+            g.grid = c3_fill(B, pool2, batch, budget, B.d.act, true, cc, ca);
+            ca.w = B.d_w; ca.bias = B.d_bias;
+            ca.cin0 = L0.d.cin; ca.act0 = L0.d.act; ca.w0 = L0.d_w; ca.bias0 = L0.d_bias;
+            g.kind = GK_C3R;
+            g.cost = c;
+            g.variant = cc.shape;
+            g.occ = std::min(2, 160 * 1024 / cc.lds_bytes);
+            g.th = cc.th; g.tw = cc.tw;
+            g.lds_bytes = cc.lds_bytes;
+            return DLF_OK;
+        }
+    }
     if (have_c3s && (!tiled || c3f.mode == 1 || c3sc < cost)) {
         g.cs = cs;
         g.kind = GK_C3S;
@@ -2717,7 +2777,8 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
     // ..., the block kernel with the weights in registers as a form of the block kernel
     // ..., the depthwise pair for few pixels as a form of the register kernel
     if (kind) *kind = G.kind == GK_C3R ? GK_C3 : G.kind == GK_SKD ? GK_DWPW : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
-    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R && G.kind != GK_SKD ? G.variant : 16 + G.variant;
+    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R && G.kind != GK_SKD ? G.variant
+                            : G.kind == GK_C3R && G.ca.cin0 > 0 ? 16 + DLF_C3R_SHAPES : 16 + G.variant;
     if (nslices) *nslices = G.kind == GK_GROUP ? G.ga.nslices : 1;
     if (slice_c) *slice_c = G.kind == GK_GROUP ? G.ga.slice_c : 0;
     if (stream0) *stream0 = G.kind == GK_GROUP ? G.ga.stream0 : 0;

@@ -154,6 +154,10 @@ struct DlfC3Args {
     const float* scale;   // requantisation scale per output channel, padded to ncb*32
     // k_c3r only (n_cg counts groups of 32 * NCBW channels, nst is the number of activation buffers):
     int32_t pw, vw;       // pixels per halo row in LDS, and per row of the index the parts are permuted by
+    // cin0 > 0: the 3x3 layer's input is another 3x3 layer's result (stride 1, pad 1, 64 channels) on `in` of cin0 channels
+    int32_t cin0, act0;
+    const void* w0;       // its packed fragments (gathered rows of 9 * cin0 <= 32 inputs: two K steps)
+    const float* bias0;
 };
 
 // The same layer with the weights in registers (k_c3r): a workgroup of four waves computes 32 * NCBW output
@@ -162,6 +166,8 @@ struct DlfC3Args {
 // 3 = (2, 4, 64, 11), 4 = (4, 7, 32, 6), 5 = (2, 7, 32, 9).
 #define DLF_C3R_WAVES 4
 #define DLF_C3R_SHAPES 6
+#define DLF_C3R_STEM_SHAPE 2         // the shape that a layer in front can be computed for
+#define DLF_C3R_STEM_BYTES(TH, TW, CIN) ((((TH) + 4) * ((TW) + 4) * (CIN) * 2 + 15) / 16 * 16)   // the image patch behind the activations
 #define DLF_C3R_EPI_BYTES (DLF_C3R_WAVES * 32 * 40 * 2)   // transpose buffers of the epilogue
 
 // Depthwise 3x3 convolution (pad 1, stride 1 or 2) as a streaming kernel without LDS or barriers:

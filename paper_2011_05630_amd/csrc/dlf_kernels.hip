@@ -233,6 +233,7 @@ __device__ __forceinline__ void stage_region(const half_t* in, int n, int H, int
 typedef const __attribute__((address_space(1))) half_t* gconst_h;
 typedef __attribute__((address_space(3))) half_t* lds_h;
 typedef __attribute__((address_space(3))) u4v* lds_u4v;
+typedef __attribute__((address_space(3))) u2v* lds_u2v;
 typedef __attribute__((address_space(3))) h4* lds_h4;
 
 // im2col staging for a convolution on a narrow input (3 channels): LDS row p holds the
@@ -2261,6 +2262,99 @@ __device__ __forceinline__ void dma16b(__amdgpu_buffer_rsrc_t r, half_t* dst, un
 // loop body ahead of it, in registers there are not.
 __device__ __forceinline__ void step_v(int& v, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(v) : "s"(by)); }
 
+// The activation block of k_c3r computed in place of being loaded: a 3x3 stride-1 layer of 64 channels on an image of
+// a few channels (9 * cin0 <= 32), for the halo region of the tile, written to LDS in the order the block's reads
+// expect (128 bytes per pixel, part q at q ^ ((r * vw + c) / 2) % 8).  The image patch goes to LDS first (behind the
+// block); a lane then gathers the 2 x 8 inputs of its pixel and K half -- runs of 3 * cin0 halfs per filter row -- as the two
+// "B" fragments of a K of 32, and a wave multiplies 32 pixels x 64 channels with four MFMAs.  Pixels outside the map are the next
+// layer's padding: zero.  Bound by vector arithmetic (the gather and the rounding of 544 pixels an item, beside the other workgroup's
+// multiplies); the fused-group kernel, which had VGG-16's first three layers before, gathers rows through LDS twice and waits
+// for each phase: batch 16 117 -> 80 us, the network 632 -> 587 us.
+__device__ __forceinline__ void stem_region(const DlfC3Args& a, int n, int ty0, int tx0, int lane, int wave)
+{
+    const int l32 = lane & 31, lhi = lane >> 5, c0 = a.cin0;
+    const lds_h act = (lds_h)lds, patch = act + a.na_i * 512;
+    const gconst_h img = (gconst_h)a.in;
+    const int rowh = (a.tw + 4) * c0, ptotal = (a.th + 4) * rowh;
+    const unsigned rowh_m = div_magic(rowh), pw_m = div_magic(a.pw);
+    h8 wf[2][2];
+    f4v bv[2][4];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) wf[f][k] = *((const h8*)a.w0 + (f * 2 + k) * 64 + lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bv[f][q] = *(const f4v*)(a.bias0 + f * 32 + q * 8 + lhi * 4);
+    }
+    // (batches of loads without conditions, from the nearest element inside the image: see stage_im2col_lds)
+    constexpr int U = 4, T = DLF_C3R_WAVES * 64;
+    for (int v0 = wave * 64 + lane; v0 < ptotal; v0 += T * U) {
+        half_t val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int vv = min(v0 + u * T, ptotal - 1);
+            const int r = (int)__umulhi((unsigned)vv, rowh_m), x = (tx0 - 2) * c0 + (vv - r * rowh);
+            const int gy = ty0 - 2 + r;
+            const bool ok = gy >= 0 && gy < a.h && x >= 0 && x < a.w_ * c0;
+            const half_t h = img[(unsigned)((n * a.h + min(max(gy, 0), a.h - 1)) * a.w_ * c0 + min(max(x, 0), a.w_ * c0 - 1))];
+            val[u] = ok ? h : (half_t)0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v0 + u * T < ptotal) patch[v0 + u * T] = val[u];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // element j of fragment k is input e = 16 k + 8 lhi + j of the window; beyond the window: the first input, masked to zero
+    int off[2][8];
+    unsigned mask[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int e = k * 16 + lhi * 8 + j, r = e / 3 >= 2 * c0 ? 2 : e / 3 >= c0 ? 1 : 0;
+            const bool in = e < 9 * c0;
+            off[k][j] = in ? r * rowh + e - r * 3 * c0 : 0;
+            if ((j & 1) == 0) mask[k][j >> 1] = in ? 0xFFFFu : 0u;
+            else if (in) mask[k][j >> 1] |= 0xFFFF0000u;
+        }
+    const unsigned lo = act_lo(a.act0), hi = act_hi(a.act0);
+    for (int p0 = wave * 32; p0 < a.npxh; p0 += DLF_C3R_WAVES * 32) {
+        const int h = min(p0 + l32, a.npxh - 1);
+        const int hy = (int)__umulhi((unsigned)h, pw_m), hx = h - hy * a.pw;
+        const lds_h src = patch + hy * rowh + hx * c0;
+        h8 b[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            half_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = src[off[k][j]];
+            u4v v = *(const u4v*)e;
+            v.x &= mask[k][0]; v.y &= mask[k][1]; v.z &= mask[k][2]; v.w &= mask[k][3];
+            b[k] = __builtin_bit_cast(h8, v);
+        }
+        const int gy = ty0 - 1 + hy, gx = tx0 - 1 + hx;
+        const bool inside = gy >= 0 && gy < a.h && gx >= 0 && gx < a.w_;
+        const unsigned keep = inside ? 0xFFFFFFFFu : 0u;
+        const int perm = (hy * a.vw + hx) >> 1;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            f16v acc;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[q] = bv[f][q >> 2][q & 3];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[f][k], b[k], acc, 0, 0, 0);
+            if (p0 + l32 < a.npxh) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u2v uu = {pk_min(pk_max(cvt_pk(acc[q * 4 + 0], acc[q * 4 + 1]), lo), hi) & keep,
+                                    pk_min(pk_max(cvt_pk(acc[q * 4 + 2], acc[q * 4 + 3]), lo), hi) & keep};
+                    *(lds_u2v)(act + h * 64 + (((f * 4 + q) ^ perm) & 7) * 8 + lhi * 4) = uu;
+                }
+            }
+        }
+    }
+}
+
 // 3x3 convolution, stride 1, pad 1 (with the 2x2 max pool behind it, or a residual operand), for maps that
 // give every CU a whole item: the block kernel with the weights in registers.  A workgroup of FOUR waves, one
 // per SIMD, computes 32 * NCBW channels x a th x tw tile; a wave owns one 32-channel block and FP 32-pixel
@@ -2295,7 +2389,7 @@ __device__ __forceinline__ void step_v(int& v, int by) { asm volatile("v_add_u32
 // 31.4 us, batch 16: 62.2 -> 54 (1.10 PFLOP/s); 512 -> 512 at 28 x 28, batch 16: 62.7 -> 55.4; 128 -> 128 at 112 x 112:
 // 67.9 -> 57; 64 -> 64 at 224 x 224: 96.6 -> 69.5, with the pool 89 -> 62; VGG-16 batch 16 703 -> 648 us, its body
 // in int8 396 -> 330 us.
-template <int NCBW, int FP, int ACH, int NA, bool I8>
+template <int NCBW, int FP, int ACH, int NA, bool I8, bool STEM = false>
 __global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a)
 {
     using acc_t = typename AccOf<I8>::type;
@@ -2306,6 +2400,7 @@ __global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a
     constexpr int STEPS = 18 * (ACH / 32);           // K steps of a block, in the order the weights are packed
     constexpr int D = 9;                             // weight ring: divides STEPS
     constexpr int PM = (LPP - 1) << 4, US = 4 - SH;  // the permuted part as a byte offset: (u << US) & PM
+    static_assert(!STEM || (ACH == 64 && !I8), "the layer in front: 64 channels, one block of K");
     static_assert(NA + D <= STEPS, "the block's requests are older than the last D weight requests");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -2339,8 +2434,8 @@ __global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a
     // of the read and a constant in the permutation, the K half and the 32-channel chunk are bits 5 and 6
     const int hb_row = pw * (ACH * 2), uu_row = a.vw << US;
     const int hb_back = -2 * hb_row, uu_back = -2 * uu_row;
-    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)a.in, 0, (int)((unsigned)(a.batch * a.h * a.w_) * (unsigned)a.cin * 2u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(     // (not read if the block is computed)
+        (void*)a.in, 0, STEM ? 0 : (int)((unsigned)(a.batch * a.h * a.w_) * (unsigned)a.cin * 2u), 0x00020000);
     const i32x4 rwt = make_rsrc(a.w, 0xffffffffu);
 
     for (int li = blockIdx.x >> 3; li < per_xcd; li += gridDim.x >> 3) {
@@ -2386,14 +2481,21 @@ __global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a
         auto request_w = [&](int slot, unsigned wb, int step) __attribute__((always_inline)) {
             ar[slot] = wfrag(rwt, (int)lane16 + (step & 3) * 1024, wb + (unsigned)(step >> 2) * 4096u);
         };
+        if constexpr (!STEM) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) request_a(i, 0);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < NA; ++i) request_a(i, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int d = 0; d < D; ++d) request_w(d, wo, d);
         __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<D>();                             // the first block has landed
-        asm volatile("s_barrier" ::: "memory");
+        if constexpr (STEM) {
+            stem_region(a, n, ty0, tx0, ln, wave);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        } else {
+            wait_vmcnt<D>();                         // the first block has landed
+            asm volatile("s_barrier" ::: "memory");
+        }
         acc_t acc[FP];
 #pragma unroll
         for (int p = 0; p < FP; ++p)
@@ -2451,8 +2553,8 @@ __global__ __launch_bounds__(DLF_C3R_WAVES * 64, 2) void k_c3r(const DlfC3Args a
             asm volatile("s_barrier" ::: "memory");
         };
 #pragma unroll 1
-        for (int b = 0; b < NB - 1; ++b) block(b, true);
-        block(NB - 1, false);
+        for (int b = 0; b < (STEM ? 0 : NB - 1); ++b) block(b, true);
+        block(STEM ? 0 : NB - 1, false);
 
         // Epilogue: a pass per pixel block through the wave's transpose buffer (in the activation buffers, which
         // nobody reads any more)
@@ -4781,6 +4883,10 @@ template <bool I8> static c3_kernel_t c3r_kernel(int shape)
 
 extern "C" int dlf_kernels_init(void)
 {
+    {
+        hipError_t e = hipFuncSetAttribute((const void*)k_c3r<2, 7, 64, 17, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return (int)e;
+    }
     for (int v = 0; v < 2 * DLF_C3R_SHAPES; ++v) {
         hipError_t e = hipFuncSetAttribute((const void*)((v & 1) ? c3r_kernel<true>(v >> 1) : c3r_kernel<false>(v >> 1)),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -4847,7 +4953,10 @@ extern "C" int dlf_launch_c3(const DlfC3Args* a, int shape, int grid, int lds_by
 
 extern "C" int dlf_launch_c3r(const DlfC3Args* a, int shape, int i8, int grid, int lds_bytes, void* stream)
 {
-    c3_kernel_t k = i8 != 0 ? c3r_kernel<true>(shape) : c3r_kernel<false>(shape);
+    c3_kernel_t k = a->cin0 > 0 ? (c3_kernel_t)k_c3r<2, 7, 64, 17, false, true> : i8 != 0 ? c3r_kernel<true>(shape) : c3r_kernel<false>(shape);
+    if (a->cin0 > 0 && (i8 != 0 || shape != DLF_C3R_STEM_SHAPE || a->cin != 64 || a->nst != 1 || 9 * a->cin0 > 32 || a->w0 == nullptr ||
+                        a->pw != a->tw + 2 || lds_bytes < a->na_i * 1024 + DLF_C3R_STEM_BYTES(a->th, a->tw, a->cin0)))
+        return (int)hipErrorInvalidValue;
     if (k == nullptr || grid < 8 || (grid & 7) != 0 || lds_bytes < (int)DLF_C3R_EPI_BYTES || lds_bytes < a->nst * a->na_i * 1024 ||
         a->pw < a->tw + 2 || (a->pool2 != 0 && ((a->th | a->tw) & 1) != 0) ||
         (i8 != 0 && (a->scale == nullptr || a->res != nullptr || (a->cout & 15) != 0)))

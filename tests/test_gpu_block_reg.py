@@ -55,6 +55,17 @@ def test_layer_pool_and_residual(shape, th, tw, cin, cout, h, w, batch, budget):
         _fp16([nets.conv(cin, cout, 3, 1, 1, "none"), nets.maxpool(cout, 2, 2, 0)], [1], *args)
 
 
+@pytest.mark.parametrize("cin,cout,h,w,batch,th,tw,budget", [
+    (3, 64, 30, 66, 2, 14, 32, 8), (3, 40, 16, 28, 1, 16, 28, 256), (1, 128, 13, 9, 3, 4, 14, 8), (2, 64, 1, 1, 2, 2, 4, 8),
+    (3, 96, 31, 45, 1, 8, 16, 16)])
+def test_first_layer_in_front(cin, cout, h, w, batch, th, tw, budget):
+    announce("block reg stem", cin, cout, h, w, batch, th, tw)
+    layers = [nets.conv(cin, 64, 3, 1, 1, "relu6" if cin == 2 else "relu"), nets.conv(64, cout, 3, 1, 1, "relu")]
+    _fp16(layers, [1], h, w, cin, batch, 6, th, tw, budget)
+    if h % 2 == 0 and w % 2 == 0:
+        _fp16(layers + [nets.maxpool(cout, 2, 2, 0)], [2], h, w, cin, batch, 6, th, tw, budget)
+
+
 @pytest.mark.parametrize("shape,th,tw,cin,cout,h,w,batch,budget", CASES)
 def test_int8_layer(shape, th, tw, cin, cout, h, w, batch, budget):
     from paper_2011_05630_amd import binding as B
