@@ -315,6 +315,7 @@ const int64_t C_C3S_BIG_BYTES = 3 << 20;
 const int64_t C_C3S_RED = 1500;
 const int64_t C3S_SMALL_ITEMS = 128;
 const int64_t C_C3S_SMALL = 1200;
+const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
 const int64_t C_C3S_EPI = 2500;
@@ -358,7 +359,7 @@ const int64_t C_SKD_ROUND_STEP = 700;
 // of one item per SIMD (4.4 - 6.0, 8.0)
 const int64_t DWT_ONE_PCT = 30;
 const int64_t DWT_ONE_BYTES = 5 << 20;
-const int64_t DWS_SMALL_BYTES = 8 << 20;
+const int64_t DWS_SMALL_BYTES = 10 << 20;
 const int64_t DWS_SMALL_PCT = 92;
 const int64_t C_DWS_SMALL = 8000;
 const int64_t DW_ONE_PCT = 30;
@@ -1378,6 +1379,9 @@ uint64_t c3s_cost_ps(const Layer& L, int batch, int budget, const DlfC3sArgs& cs
 
                          (cs.ksplit > 1 ? C_C3S_RED : 0) + C_C3S_EPI + (L.d.residual_from >= 0 ? C_PW_RES : 0);
     int64_t compute = C_LAT + rounds * item;
+    // one round of items that share K four ways: most of its round trips are in C_LAUNCH already (512 channels at 5 x 5, batch 26:
+    // 11.7 and 10.0 us, 16 without this; 9.3 at 11 x 11, batch 15, 12.6)
+    if (rounds == 1 && cs.ksplit == 4) compute -= C_C3S_ONE;
     // half of the chip's CUs or fewer: the launch's fixed part is short and the K loop runs at the
     // rate a CU takes eight waves' weights in (183 cycles per step: 45 bytes per cycle), not at the
     // chip's matrix rate (256 channels at 14 x 14, batch 1 - 8: 8.3 - 8.5 us; 512 at 7 x 7: 11.4)
