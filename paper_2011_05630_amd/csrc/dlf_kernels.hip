@@ -2377,7 +2377,7 @@ __device__ __forceinline__ void stem_region(const DlfC3Args& a, int n, int ty0, 
 // Bank conflicts: part q of the halo pixel (r, c) lies at q ^ ((r * vw + c) >> SH), rows of `pw` pixels.  LDS serves
 // 16 lanes per cycle; with vw = tw the permutation runs through consecutive integers for consecutive tile
 // pixels whatever the tap and across row breaks, and pw = tw + 2 (128-byte pixels) or tw + 4 (64-byte pixels)
-// keeps the pixels' own bank halves (quarters) in step: no conflicts for any tile (a count over all tiles;
+// keeps the pixels' own bank halves (quarters) in step: no conflicts in the K loop's reads (counted over the tiles in use;
 // with the halo index in the permutation 1.4 cycles per read at 28-wide tiles, 2 with the pool's quads).  The
 // pool's order (2x2 windows in quads) wants the rows of a window 8 parts apart: vw = 8 mod 16.
 // Fragment reads are a ring of FP registers, each refilled for the next K step behind the MFMA that used it, and
