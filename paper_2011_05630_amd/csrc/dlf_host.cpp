@@ -1623,10 +1623,14 @@ bool skc_layer_ok(const Layer& L, int batch)
     if ((d.cin % 32) != 0 || (d.cout % 4) != 0 || d.kh * d.kw > DLF_SKC_MAX_TAPS) return false;
     if ((int64_t)L.ncb * L.nsteps * 1024 >= (int64_t)1 << 31) return false;
     if ((int64_t)batch * L.in_h * L.in_w * L.in_c * 2 >= (int64_t)1 << 31) return false;
-    // items, pixels and rows are divided as 32-bit products
+    // pixels and rows are divided as 32-bit products (items: skc_choose)
     const int64_t m = (int64_t)batch * L.out_h * L.out_w;
     return m <= 1 << 17 && m * std::max(L.out_h, L.out_w) < (int64_t)1 << 31 && m * d.cout * 2 < (int64_t)1 << 31;
 }
+
+// The split-K kernels find an item's pixel group as a 32-bit product (div_by): exact while item * n_cg < 2^32.  Layers of
+// more than half a million output channels reach that.
+bool sk_items_ok(int n_pg, int n_cg) { return (int64_t)n_pg * n_cg * n_cg < (int64_t)1 << 32; }
 
 void skc_fill(const Layer& L, const Layer* proj, int pool2, int batch, int shape, int waves, DlfSkcArgs& sk)
 {
@@ -1682,6 +1686,7 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
         if (g_skc_force.shape >= 0 && sh != g_skc_force.shape) continue;
         DlfSkcArgs sk;
         skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
+        if (!sk_items_ok(sk.n_pg, sk.n_cg)) continue;
         const uint64_t c = skc_cost_ps(sk, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
     }
@@ -1698,7 +1703,7 @@ bool skd_eligible(const dlf_net_s& net, int first, int last, int batch)
 {
     if (!dwpw_eligible(net, first, last, batch)) return false;
     const Layer& P = net.L[last];
-    // items, pixels and rows are divided as 32-bit products
+    // pixels and rows are divided as 32-bit products (items: skd_choose)
     const int64_t m = (int64_t)batch * P.out_h * P.out_w;
     return m <= 1 << 17 && m * std::max(P.out_h, P.out_w) < (int64_t)1 << 31 && (int64_t)P.ncb * P.nsteps * 1024 < (int64_t)1 << 31 &&
            net.L[first].d.cin <= 2048;                             // (the weights' place in LDS)
@@ -1738,6 +1743,7 @@ bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, DlfSkdArg
         if (g_skd_force.shape >= 0 && sh != g_skd_force.shape) continue;
         DlfSkdArgs sd;
         skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
+        if (!sk_items_ok(sd.n_pg, sd.n_cg)) continue;
         const uint64_t c = skd_cost_ps(sd, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }

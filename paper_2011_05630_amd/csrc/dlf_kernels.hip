@@ -5203,6 +5203,7 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
         {k_skc<1, 1, 4, false>, k_skc<1, 2, 4, false>, k_skc<1, 4, 3, false>, k_skc<2, 4, 3, false>},
         {k_skc<1, 1, 4, true>, k_skc<1, 2, 4, true>, k_skc<1, 4, 3, true>, k_skc<2, 4, 3, true>}};
     static const int px[DLF_SKC_SHAPES] = {16, 16, 16, 32}, ch[DLF_SKC_SHAPES] = {16, 32, 64, 64};
+    if ((int64_t)a->n_pg * a->n_cg * a->n_cg >= (int64_t)1 << 32) return (int)hipErrorInvalidValue;      // div_by of an item
     if (shape < 0 || shape >= DLF_SKC_SHAPES || (a->nw != 1 && a->nw != 2 && a->nw != 4 && a->nw != 8)) return (int)hipErrorInvalidValue;
     launch(k[a->nk2 > 0 ? 1 : 0][shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * px[shape] * ch[shape] * 4,
            (hipStream_t)stream, *a);
@@ -5212,6 +5213,7 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
 extern "C" int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream)
 {
     static void (*const k[DLF_SKD_SHAPES])(const DlfSkdArgs) = {k_skd<2>, k_skd<4>};
+    if ((int64_t)a->n_pg * a->n_cg * a->n_cg >= (int64_t)1 << 32) return (int)hipErrorInvalidValue;      // div_by of an item
     if (DLF_SKD_LDS_BYTES(a->nw, 64, a->ksw) > 64 * 1024) return (int)hipErrorInvalidValue;
     if (shape < 0 || shape >= DLF_SKD_SHAPES || a->ksw < 1 || a->nw < 1 || a->nw > DLF_SKD_MAX_WAVES || (a->nw & (a->nw - 1)) != 0) return (int)hipErrorInvalidValue;
     launch(k[shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), DLF_SKD_LDS_BYTES(a->nw, 32 << shape, a->ksw),

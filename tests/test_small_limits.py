@@ -1,0 +1,63 @@
+"""Limits of the split-K kernels for outputs of few pixels (a single convolution, and a depthwise layer with the 1x1
+layer behind it), as plans show them on the CPU."""
+import random
+
+import numpy as np
+import pytest
+
+from synth import nets
+from paper_2011_05630_amd import binding as B
+
+# items of a shape, pixels x channels (shape = variant - 16)
+CONV_ITEM = {0: (16, 16), 1: (16, 32), 2: (16, 64), 3: (32, 64)}
+PAIR_ITEM = {0: (16, 32), 1: (16, 64)}
+
+
+def _plan(layers, h, w, batch, budget=256, max_lds=0):
+    """-> (group configuration, pixels) of the layers as one group."""
+    n = B.dlf_net_create(layers, h, w, layers[0]["cin"])
+    try:
+        p = B.dlf_plan(n, batch, mode=B.TUNER_MANUAL, group_last=[len(layers) - 1], group_budget=[budget], max_lds_bytes=max_lds)
+        cfg = B.dlf_plan_group_config(p, 0)
+        B.dlf_plan_destroy(p)
+        oh, ow = B.dlf_net_layer_info(n, len(layers) - 1)[:2]
+    finally:
+        B.dlf_net_destroy(n)
+    return cfg, batch * oh * ow
+
+
+def _items_divide_exactly(m, cout, item):
+    n_pg, n_cg = -(-m // item[0]), -(-cout // item[1])
+    if n_cg == 1:
+        return True
+    items = np.arange(n_pg * n_cg, dtype=np.uint64)
+    magic = np.uint64(0xFFFFFFFF // n_cg + 1)                       # the kernels' div_by
+    return bool(np.all((items * magic) >> np.uint64(32) == items // np.uint64(n_cg)))
+
+
+def test_items_of_many_channels_are_divided_exactly():
+    """Layers of up to 2^20 output channels: a kernel that finds its pixel group by a 32-bit product is planned only
+    where that product is exact for every item."""
+    rng = random.Random(7)
+    cases = [(32, 905432, 44, 20), (64, 561244, 64, 16), (32, 1 << 20, 40, 24)]
+    cases += [(32 * rng.randint(1, 4), 4 * rng.randint(1 << 16, 1 << 18), rng.randint(2, 48), rng.randint(2, 48)) for _ in range(20)]
+    seen = 0
+    for cin, cout, h, w in cases:
+        try:
+            cfg, m = _plan([nets.conv(cin, cout, 1, 1, 0, "relu")], h, w, 1)
+        except B.DlfError:
+            continue
+        if cfg["kind"] == 10 and cfg["variant"] >= 16:
+            seen += 1
+            assert _items_divide_exactly(m, cout, CONV_ITEM[cfg["variant"] - 16]), (cin, cout, h, w, cfg)
+    for shape in (0, 1):
+        B.dlf_debug_small_pair_mode(1, shape, 0)
+        try:
+            for c, cout, h, w in ((32, 905432, 44, 20), (32, 1 << 20, 40, 25), (64, 40000, 9, 9)):
+                cfg, m = _plan([nets.dwconv(c, 3, 1, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")], h, w, 1)
+                if cfg["kind"] == 6 and cfg["variant"] >= 16:
+                    seen += 1
+                    assert _items_divide_exactly(m, cout, PAIR_ITEM[shape]), (c, cout, h, w, cfg)
+        finally:
+            B.dlf_debug_small_pair_mode(0)
+    assert seen >= 4, seen
