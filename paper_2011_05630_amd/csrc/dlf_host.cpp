@@ -1628,9 +1628,15 @@ bool skc_layer_ok(const Layer& L, int batch)
     return m <= 1 << 17 && m * std::max(L.out_h, L.out_w) < (int64_t)1 << 31 && m * d.cout * 2 < (int64_t)1 << 31;
 }
 
-// The split-K kernels find an item's pixel group as a 32-bit product (div_by): exact while item * n_cg < 2^32.  Layers of
-// more than half a million output channels reach that.
-bool sk_items_ok(int n_pg, int n_cg) { return (int64_t)n_pg * n_cg * n_cg < (int64_t)1 << 32; }
+// The split-K kernels launch a workgroup per item, so a layer of more items than budget x occupancy is not theirs.  (A
+// loop over items costs every launch 3 - 8 %: 256 -> 256 3x3 at 14 x 14 5.6 -> 6.2 us, and at 784 items of 32 channels 4.3 -> 6.0.)
+// They find an item's pixel group as a 32-bit product (div_by): exact while item * n_cg < 2^32.
+const int SK_OCC = 2;
+bool sk_items_ok(int n_pg, int n_cg, int budget)
+{
+    const int64_t items = (int64_t)n_pg * n_cg;
+    return items <= (int64_t)budget * SK_OCC && items * n_cg < (int64_t)1 << 32;
+}
 
 void skc_fill(const Layer& L, const Layer* proj, int pool2, int batch, int shape, int waves, DlfSkcArgs& sk)
 {
@@ -1686,7 +1692,7 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
         if (g_skc_force.shape >= 0 && sh != g_skc_force.shape) continue;
         DlfSkcArgs sk;
         skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
-        if (!sk_items_ok(sk.n_pg, sk.n_cg)) continue;
+        if (!sk_items_ok(sk.n_pg, sk.n_cg, budget)) continue;
         const uint64_t c = skc_cost_ps(sk, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
     }
@@ -1743,7 +1749,7 @@ bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, DlfSkdArg
         if (g_skd_force.shape >= 0 && sh != g_skd_force.shape) continue;
         DlfSkdArgs sd;
         skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
-        if (!sk_items_ok(sd.n_pg, sd.n_cg)) continue;
+        if (!sk_items_ok(sd.n_pg, sd.n_cg, budget)) continue;
         const uint64_t c = skd_cost_ps(sd, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }
@@ -2244,7 +2250,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
         g.kind = GK_SKD;
         g.cost = cost;
         g.variant = shape;
-        g.occ = 1;
+        g.occ = SK_OCC;
         g.grid = sd.n_pg * sd.n_cg;
         g.th = 1; g.tw = 16;
         g.lds_bytes = DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw);
@@ -2280,7 +2286,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     g.kind = GK_SKC;
     g.cost = cost;
     g.variant = shape;
-    g.occ = 1;
+    g.occ = SK_OCC;
     g.grid = sk.n_pg * sk.n_cg;
     g.th = 1; g.tw = 16 * SKC_TP[shape];
     g.lds_bytes = sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024;

@@ -37,14 +37,15 @@ def _items_divide_exactly(m, cout, item):
 
 def test_items_of_many_channels_are_divided_exactly():
     """Layers of up to 2^20 output channels: a kernel that finds its pixel group by a 32-bit product is planned only
-    where that product is exact for every item."""
+    where that product is exact for every item.  (A budget far above the chip's: the number of workgroups is no limit.)"""
+    budget = 1 << 20
     rng = random.Random(7)
     cases = [(32, 905432, 44, 20), (64, 561244, 64, 16), (32, 1 << 20, 40, 24)]
     cases += [(32 * rng.randint(1, 4), 4 * rng.randint(1 << 16, 1 << 18), rng.randint(2, 48), rng.randint(2, 48)) for _ in range(20)]
     seen = 0
     for cin, cout, h, w in cases:
         try:
-            cfg, m = _plan([nets.conv(cin, cout, 1, 1, 0, "relu")], h, w, 1)
+            cfg, m = _plan([nets.conv(cin, cout, 1, 1, 0, "relu")], h, w, 1, budget)
         except B.DlfError:
             continue
         if cfg["kind"] == 10 and cfg["variant"] >= 16:
@@ -54,10 +55,44 @@ def test_items_of_many_channels_are_divided_exactly():
         B.dlf_debug_small_pair_mode(1, shape, 0)
         try:
             for c, cout, h, w in ((32, 905432, 44, 20), (32, 1 << 20, 40, 25), (64, 40000, 9, 9)):
-                cfg, m = _plan([nets.dwconv(c, 3, 1, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")], h, w, 1)
+                cfg, m = _plan([nets.dwconv(c, 3, 1, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")], h, w, 1, budget)
                 if cfg["kind"] == 6 and cfg["variant"] >= 16:
                     seen += 1
                     assert _items_divide_exactly(m, cout, PAIR_ITEM[shape]), (c, cout, h, w, cfg)
         finally:
             B.dlf_debug_small_pair_mode(0)
     assert seen >= 4, seen
+
+
+def _split_k_groups(net, batch, **plan):
+    """-> [(workgroups, budget, item shape, group configuration)] of the plan's groups on the split-K kernels."""
+    h = B.dlf_net_create(net["layers"], net["in_h"], net["in_w"], net["in_c"])
+    p = B.dlf_plan(h, batch, **plan)
+    out = []
+    for g, info in enumerate(B.dlf_plan_groups(p)):
+        cfg = B.dlf_plan_group_config(p, g)
+        if cfg["variant"] < 16 or cfg["kind"] not in (6, 8, 10):
+            continue
+        item = (PAIR_ITEM if cfg["kind"] == 6 else CONV_ITEM)[cfg["variant"] - 16]
+        last = info["last"]
+        if net["layers"][last]["op"] == "maxpool":
+            last -= 1                                              # items count the convolution's pixels
+        oh, ow, cout = B.dlf_net_layer_info(h, last)[:3]
+        out.append((-(-batch * oh * ow // item[0]) * -(-cout // item[1]), info["budget"], item, cfg))
+    B.dlf_plan_destroy(p)
+    B.dlf_net_destroy(h)
+    return out
+
+
+def test_launches_keep_to_their_budget():
+    """A workgroup per item, so items <= budget x occupancy (two workgroups per CU)."""
+    seen = 0
+    for net in (nets.resnet50(128), nets.resnet18(), nets.mobilenet_v1(), nets.vgg16(64)):
+        for batch in (1, 2, 4):
+            for mode, kw in ((B.TUNER_LAYERWISE, dict(fixed_budget=32)), (B.TUNER_LAYERWISE, dict(fixed_budget=64)),
+                             (B.TUNER_LAYERWISE, dict(fixed_budget=128)), (B.TUNER_GREEDY, dict(fixed_budget=32)),
+                             (B.TUNER_DP, {}), (B.TUNER_DP, dict(budgets=[16]))):
+                for wgs, budget, item, cfg in _split_k_groups(net, batch, mode=mode, **kw):
+                    seen += 1
+                    assert wgs <= 2 * budget, (net["name"], batch, mode, kw, wgs, budget, cfg)
+    assert seen > 100, seen
