@@ -1685,14 +1685,16 @@ uint64_t skc_cost_ps(const DlfSkcArgs& sk, int shape, int budget)
     return (uint64_t)(cycles * PS_PER_CYCLE);
 }
 
-bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, DlfSkcArgs& best, int& shape, uint64_t& cost)
+int skc_lds_bytes(const DlfSkcArgs& sk, int shape) { return sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024; }
+
+bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, int max_lds, DlfSkcArgs& best, int& shape, uint64_t& cost)
 {
     bool found = false;
     for (int sh = 0; sh < DLF_SKC_SHAPES; ++sh) {
         if (g_skc_force.shape >= 0 && sh != g_skc_force.shape) continue;
         DlfSkcArgs sk;
         skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
-        if (!sk_items_ok(sk.n_pg, sk.n_cg, budget)) continue;
+        if (!sk_items_ok(sk.n_pg, sk.n_cg, budget) || skc_lds_bytes(sk, sh) > max_lds) continue;
         const uint64_t c = skc_cost_ps(sk, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
     }
@@ -1742,14 +1744,16 @@ uint64_t skd_cost_ps(const DlfSkdArgs& sd, int shape, int budget)
     return (uint64_t)(cycles * PS_PER_CYCLE);
 }
 
-bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, DlfSkdArgs& best, int& shape, uint64_t& cost)
+int skd_lds_bytes(const DlfSkdArgs& sd, int shape) { return DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw); }
+
+bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, int max_lds, DlfSkdArgs& best, int& shape, uint64_t& cost)
 {
     bool found = false;
     for (int sh = 0; sh < DLF_SKD_SHAPES; ++sh) {
         if (g_skd_force.shape >= 0 && sh != g_skd_force.shape) continue;
         DlfSkdArgs sd;
         skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
-        if (!sk_items_ok(sd.n_pg, sd.n_cg, budget)) continue;
+        if (!sk_items_ok(sd.n_pg, sd.n_cg, budget) || skd_lds_bytes(sd, sh) > max_lds) continue;
         const uint64_t c = skd_cost_ps(sd, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }
@@ -2241,7 +2245,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
         DlfSkdArgs sd;
         int shape = 0;
         uint64_t cost = 0;
-        if (!skd_choose(L0, net.L[last], batch, budget, sd, shape, cost)) return s;
+        if (!skd_choose(L0, net.L[last], batch, budget, max_lds, sd, shape, cost)) return s;
         if (s == DLF_OK && g_skd_force.mode != 1 && g.cost <= cost) return s;
         g = GroupPlan();
         g.first = first; g.last = last; g.budget = budget;
@@ -2253,7 +2257,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
         g.occ = SK_OCC;
         g.grid = sd.n_pg * sd.n_cg;
         g.th = 1; g.tw = 16;
-        g.lds_bytes = DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw);
+        g.lds_bytes = skd_lds_bytes(sd, shape);
         return DLF_OK;
     }
     const Layer* conv = nullptr;
@@ -2275,7 +2279,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     DlfSkcArgs sk;
     int shape = 0;
     uint64_t cost = 0;
-    if (!skc_choose(*conv, proj, pool2, batch, budget, sk, shape, cost)) return s;
+    if (!skc_choose(*conv, proj, pool2, batch, budget, max_lds, sk, shape, cost)) return s;
     if (s == DLF_OK && g_skc_force.mode != 1 && g.cost <= cost) return s;
     g = GroupPlan();
     g.first = first; g.last = last; g.budget = budget;
@@ -2289,7 +2293,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     g.occ = SK_OCC;
     g.grid = sk.n_pg * sk.n_cg;
     g.th = 1; g.tw = 16 * SKC_TP[shape];
-    g.lds_bytes = sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024;
+    g.lds_bytes = skc_lds_bytes(sk, shape);
     return DLF_OK;
 }
 

@@ -96,3 +96,31 @@ def test_launches_keep_to_their_budget():
                     seen += 1
                     assert wgs <= 2 * budget, (net["name"], batch, mode, kw, wgs, budget, cfg)
     assert seen > 100, seen
+
+
+def test_launches_keep_to_the_lds_limit():
+    """max_lds_bytes is the limit of every group on the split-K kernels."""
+    seen = 0
+    for net in (nets.resnet50(), nets.mobilenet_v1(), nets.identical_chain(64, 32, 3)):
+        for limit in (4096, 16384, 65536):
+            for batch in (1, 4):
+                try:
+                    groups = _split_k_groups(net, batch, max_lds_bytes=limit)
+                except B.DlfError:
+                    continue                                       # (some layer fits no kernel)
+                for _, _, _, cfg in groups:
+                    seen += 1
+                    assert 0 < cfg["lds_bytes"] <= limit, (net["name"], batch, limit, cfg)
+    # one layer, every item shape asked for: 32 x 64 outputs need 32 KiB with four waves
+    for limit in (2048, 4096, 16384, 32768):
+        for shape in range(4):
+            B.dlf_debug_small_mode(1, shape, 0)
+            try:
+                cfg, _ = _plan([nets.conv(64, 64, 3, 1, 1, "relu")], 32, 32, 1, max_lds=limit)
+            except B.DlfError:
+                continue
+            finally:
+                B.dlf_debug_small_mode(0)
+            seen += 1
+            assert cfg["lds_bytes"] <= limit, (limit, shape, cfg)
+    assert seen > 60, seen
