@@ -2155,9 +2155,10 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
             if (have) c3c = c3_cost_ps(L0, pool2, batch, budget, cc);
         } else {
             have = c3_choose(L0, pool2, batch, budget, max_lds, cc, c3c);
-            // (not considered while a testing hook or a caller names another kernel's form)
+            // (not considered while a testing hook or a caller names another kernel's form, nor for layers that none of
+            // the others takes)
             const bool named = (force_tc && force_tc->th > 0) || pwm != 0 || g_force.th > 0 || g_dw_mode != 0;
-            if (!named && c3r_choose(L0, pool2, batch, budget, max_lds, cr, crc) && (!have || crc < c3c)) {
+            if (!named && (have || have_c3s || tiled) && c3r_choose(L0, pool2, batch, budget, max_lds, cr, crc) && (!have || crc < c3c)) {
                 have = reg = true;
                 cc = cr;
                 c3c = crc;
@@ -2186,7 +2187,7 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
         C3Cfg cc;
         uint64_t c = 0;
         const bool forced = c3f.shape >= 0;
-        if (c3r_stem_choose(L0, B, pool2, batch, budget, max_lds, cc, c, forced ? c3f.th : 0, forced ? c3f.tw : 0) && (!tiled || c3f.mode == 1 || c < cost)) {
+        if (c3r_stem_choose(L0, B, pool2, batch, budget, max_lds, cc, c, forced ? c3f.th : 0, forced ? c3f.tw : 0) && (c3f.mode == 1 || (tiled && c < cost))) {
             DlfC3Args& ca = g.ca;
             g.grid = c3_fill(B, pool2, batch, budget, B.d.act, true, cc, ca);
             ca.w = B.d_w; ca.bias = B.d_bias;
@@ -2229,7 +2230,8 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
     return DLF_OK;
 }
 
-// The group on the cheapest kernel: the one of make_group_tiled, or the split-K convolution kernel.
+// The group on the cheapest kernel: the one of make_group_tiled, or a split-K kernel in its place (layers that none of the
+// others takes, for their size or the LDS limit, stay infeasible).
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
                       GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
                       const C3Force* c3_force = nullptr)
@@ -2246,7 +2248,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
         int shape = 0;
         uint64_t cost = 0;
         if (!skd_choose(L0, net.L[last], batch, budget, max_lds, sd, shape, cost)) return s;
-        if (s == DLF_OK && g_skd_force.mode != 1 && g.cost <= cost) return s;
+        if (g_skd_force.mode != 1 && (s != DLF_OK || g.cost <= cost)) return s;
         g = GroupPlan();
         g.first = first; g.last = last; g.budget = budget;
         g.in_layer = L0.src;
@@ -2280,7 +2282,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     int shape = 0;
     uint64_t cost = 0;
     if (!skc_choose(*conv, proj, pool2, batch, budget, max_lds, sk, shape, cost)) return s;
-    if (s == DLF_OK && g_skc_force.mode != 1 && g.cost <= cost) return s;
+    if (g_skc_force.mode != 1 && (s != DLF_OK || g.cost <= cost)) return s;
     g = GroupPlan();
     g.first = first; g.last = last; g.budget = budget;
     g.in_layer = conv->src;

@@ -124,3 +124,18 @@ def test_launches_keep_to_the_lds_limit():
             seen += 1
             assert cfg["lds_bytes"] <= limit, (limit, shape, cfg)
     assert seen > 60, seen
+
+
+@pytest.mark.parametrize("layers,h,w,batch,max_lds", [
+    ([nets.conv(96, 88, 3, 1, 1, "relu"), nets.maxpool(88, 2, 2, 0)], 6, 8, 2, 4096),
+    ([nets.conv(256, 928, 5, 3, 4, "relu")], 33, 13, 1, 16384), ([nets.conv(352, 32, 3, 2, 1, "relu")], 37, 11, 1, 4096),
+    ([nets.conv(64, 64, 3, 1, 1, "relu")], 32, 32, 7, 2048),
+    ([nets.conv(128, 684380, 3, 1, 1, "relu")], 37, 36, 1, 0), ([nets.conv(1696, 966560, 3, 1, 1, "relu"), nets.maxpool(966560, 2, 2, 0)], 40, 22, 1, 32768)])
+def test_layers_that_fit_no_tile_stay_infeasible(layers, h, w, batch, max_lds):
+    """Layers that the tiled kernels refuse, for the LDS limit or their size, are refused by the library."""
+    n = B.dlf_net_create(layers, h, w, layers[0]["cin"])
+    assert B.dlf_group_cost(n, batch, 0, len(layers) - 1, 256, max_lds) is None
+    with pytest.raises(B.DlfError) as e:
+        _plan(layers, h, w, batch, max_lds=max_lds)
+    assert e.value.status == B.DLF_ERR_INFEASIBLE
+    B.dlf_net_destroy(n)
