@@ -340,7 +340,9 @@ const int64_t C3PW_OVERLAP_PCT = 60;         // two workgroups per CU: what a fu
 // split-K convolution kernel: a launch of one round trip, then the rate at which a CU takes operands in
 // (49 bytes per cycle for a workgroup alone on its CU, 34 if it gathers 32 pixels; several share the
 // first-level cache and its path to L2 and get 28 or 25 together).  Fitted to 10 layer shapes at batch 1, 2 and 4 in chains of 12 layers.
+// The residual operand: measured 0.02 - 0.12 us (64 - 512 channels, 7 x 7 to 56 x 56).
 const int64_t C_SKC_ITEM = -900;
+const int64_t C_SKC_RES = 150;
 const int64_t SKC_FEW_ITEMS = 128;
 const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
 const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
@@ -1667,15 +1669,22 @@ void skc_fill(const Layer& L, const Layer* proj, int pool2, int batch, int shape
     sk.taps_m = magic(L.d.kh * L.d.kw); sk.kw_m = magic(L.d.kw);
 }
 
-uint64_t skc_cost_ps(const DlfSkcArgs& sk, int shape, int budget)
+uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, int batch, int shape, int budget)
 {
     const int64_t items = (int64_t)sk.n_pg * sk.n_cg;
+    const int64_t has_res = L.d.residual_from >= 0 && !proj ? 1 : 0;
     const int64_t bytes = (int64_t)(sk.nk + sk.nk2) * (SKC_TP[shape] + SKC_TC[shape]) * 1024;
     int64_t intake = bytes / SKC_BYTES_PER_CYCLE[shape];
     // the taps of a 3x3 filter meet in the first-level cache, a long 1x1 row does not (2048 channels, 240 items: 12 us)
     if (shape == 3 && sk.kh * sk.kw == 1 && items > SKC_FEW_ITEMS) intake = bytes / SKC_SHARED_BYTES_PER_CYCLE[shape];
     if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
-    int64_t cycles = C_LAUNCH + C_SKC_ITEM + intake;
+    // ... and never faster than the tensors pass: the input pixels the filter meets, the output, the residual operand, the weights
+    const int64_t m = (int64_t)batch * L.out_h * L.out_w;
+    const int64_t in = std::min((int64_t)batch * L.in_h * L.in_w, m * L.d.kh * L.d.kw);
+    int64_t hbm = in * L.d.cin * 2 + (sk.pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
+    if (proj) hbm += m * proj->d.cin * 2 + (int64_t)proj->ncb * proj->nsteps * 1024;
+    const int64_t mem = hbm / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
+    int64_t cycles = C_LAUNCH + std::max(C_SKC_ITEM + intake + has_res * C_SKC_RES, mem);
     // 32 pixels x 64 channels on nearly every CU: 15 - 20 % above the fit (64 -> 64 3x3 at 32 x 32, batch 7, 224 items: 6.2 us, not 5.3)
     if (shape == 3 && items <= budget && items * 4 > (int64_t)budget * 3) cycles = cycles * 5 / 4;
     // The kernel is for launches of at most about one item per CU.  Beyond that the models of the
@@ -1695,7 +1704,7 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
         DlfSkcArgs sk;
         skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
         if (!sk_items_ok(sk.n_pg, sk.n_cg, budget) || skc_lds_bytes(sk, sh) > max_lds) continue;
-        const uint64_t c = skc_cost_ps(sk, sh, budget);
+        const uint64_t c = skc_cost_ps(L, proj, sk, batch, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
     }
     return found;
@@ -1736,12 +1745,14 @@ void skd_fill(const Layer& D, const Layer& P, int batch, int shape, int waves, D
     sd.n_cg_m = magic(sd.n_cg); sd.ow_m = magic(sd.ow); sd.oh_m = magic(sd.oh);
 }
 
-uint64_t skd_cost_ps(const DlfSkdArgs& sd, int shape, int budget)
+uint64_t skd_cost_ps(const Layer& D, const Layer& P, const DlfSkdArgs& sd, int shape, int budget)
 {
     const int64_t items = (int64_t)sd.n_pg * sd.n_cg;
     const int64_t rounds = (items + budget - 1) / budget;
     const int64_t cycles = std::max(C_SKD_LEAST, C_SKD_ITEM[shape] + sd.nk * C_SKD_STEP) + (rounds - 1) * (C_SKD_ROUND + sd.nk * C_SKD_ROUND_STEP);
-    return (uint64_t)(cycles * PS_PER_CYCLE);
+    const int64_t bytes = (int64_t)sd.in_bytes + (int64_t)sd.m * P.d.cout * 2 + (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
+    const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
+    return (uint64_t)(std::max(cycles, C_LAUNCH + mem) * PS_PER_CYCLE);
 }
 
 int skd_lds_bytes(const DlfSkdArgs& sd, int shape) { return DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw); }
@@ -1754,7 +1765,7 @@ bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, int max_l
         DlfSkdArgs sd;
         skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
         if (!sk_items_ok(sd.n_pg, sd.n_cg, budget) || skd_lds_bytes(sd, sh) > max_lds) continue;
-        const uint64_t c = skd_cost_ps(sd, sh, budget);
+        const uint64_t c = skd_cost_ps(D, P, sd, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }
     return found;

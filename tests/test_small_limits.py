@@ -43,14 +43,18 @@ def test_items_of_many_channels_are_divided_exactly():
     cases = [(32, 905432, 44, 20), (64, 561244, 64, 16), (32, 1 << 20, 40, 24)]
     cases += [(32 * rng.randint(1, 4), 4 * rng.randint(1 << 16, 1 << 18), rng.randint(2, 48), rng.randint(2, 48)) for _ in range(20)]
     seen = 0
-    for cin, cout, h, w in cases:
+    for t, (cin, cout, h, w) in enumerate(cases):
+        shape = 3 if t < 3 else t % 4
+        B.dlf_debug_small_mode(1, shape, 0)
         try:
             cfg, m = _plan([nets.conv(cin, cout, 1, 1, 0, "relu")], h, w, 1, budget)
         except B.DlfError:
             continue
+        finally:
+            B.dlf_debug_small_mode(0)
         if cfg["kind"] == 10 and cfg["variant"] >= 16:
             seen += 1
-            assert _items_divide_exactly(m, cout, CONV_ITEM[cfg["variant"] - 16]), (cin, cout, h, w, cfg)
+            assert _items_divide_exactly(m, cout, CONV_ITEM[shape]), (cin, cout, h, w, cfg)
     for shape in (0, 1):
         B.dlf_debug_small_pair_mode(1, shape, 0)
         try:
@@ -139,3 +143,36 @@ def test_layers_that_fit_no_tile_stay_infeasible(layers, h, w, batch, max_lds):
         _plan(layers, h, w, batch, max_lds=max_lds)
     assert e.value.status == B.DLF_ERR_INFEASIBLE
     B.dlf_net_destroy(n)
+
+
+def test_no_layer_is_priced_below_its_bytes():
+    """Whatever kernel a layer is planned on, its modelled cost covers the bytes it reads and writes once, residual operand
+    and weights included, at the rate a large copy reaches (5.2 TB/s)."""
+    rng = random.Random(11)
+    seen = 0
+    cases = [(32, 2048, 1, 58, 32, True), (32, 512, 1, 56, 40, True), (32, 256, 1, 40, 32, True), (2048, 512, 1, 7, 8, False)]
+    for _ in range(150):
+        k = rng.choice([1, 1, 3])
+        cases.append((32 * rng.randint(1, 8), 8 * rng.randint(1, 259), k, rng.randint(1, 64 // k), rng.randint(1, 32), rng.random() < 0.5))
+    for cin, cout, k, hw, batch, res in cases:
+        layers = [nets.conv(cin, cin, 1, 1, 0, "relu"), nets.conv(cin, cout, 1, 1, 0, "none"),
+                  nets.conv(cin, cout, k, 1, k // 2, "relu", input_from=0, residual_from=1 if res else -1)]
+        n = B.dlf_net_create(layers, hw, hw, cin)
+        m = batch * hw * hw
+        floor_ps = (m * cin + m * cout * (2 if res else 1) + k * k * cin * cout) * 2 / 5.2
+        for budget in (256, 64):
+            cost = B.dlf_group_cost(n, batch, 2, 2, budget)
+            seen += cost is not None
+            assert cost is None or cost >= floor_ps, (cin, cout, k, hw, batch, res, budget, cost, floor_ps)
+        B.dlf_net_destroy(n)
+    for c, cout, stride, hw, batch in ((32, 512, 1, 40, 16), (64, 64, 1, 64, 16), (512, 512, 1, 14, 32), (1024, 1024, 1, 7, 32)):
+        layers = [nets.dwconv(c, 3, stride, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")]
+        n = B.dlf_net_create(layers, hw, hw, c)
+        B.dlf_debug_small_pair_mode(1, 1, 0)
+        try:
+            cost = B.dlf_group_cost(n, batch, 0, 1, 1 << 16)
+        finally:
+            B.dlf_debug_small_pair_mode(0)
+        assert cost >= (batch * hw * hw * (c + cout) + c * cout) * 2 / 5.2, (c, cout, hw, batch, cost)
+        B.dlf_net_destroy(n)
+    assert seen > 250, seen
