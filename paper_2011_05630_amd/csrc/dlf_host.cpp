@@ -1684,7 +1684,7 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
     int64_t hbm = in * L.d.cin * 2 + (sk.pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
     if (proj) hbm += m * proj->d.cin * 2 + (int64_t)proj->ncb * proj->nsteps * 1024;
     const int64_t mem = hbm / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
-    int64_t cycles = C_LAUNCH + std::max(C_SKC_ITEM + intake + has_res * C_SKC_RES, mem);
+    int64_t cycles = C_LAUNCH + C_SKC_ITEM + std::max(intake + has_res * C_SKC_RES, mem);
     // 32 pixels x 64 channels on nearly every CU: 15 - 20 % above the fit (64 -> 64 3x3 at 32 x 32, batch 7, 224 items: 6.2 us, not 5.3)
     if (shape == 3 && items <= budget && items * 4 > (int64_t)budget * 3) cycles = cycles * 5 / 4;
     // The kernel is for launches of at most about one item per CU.  Beyond that the models of the
