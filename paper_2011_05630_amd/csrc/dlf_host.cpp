@@ -2241,17 +2241,58 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
     return DLF_OK;
 }
 
+// What the fused-group kernel (in one round of tiles, up to 64 channels, by number of layers) and the 3x3 -> 1x1 kernel are modelled at
+// beyond what they take, where the models of the kernels for single layers that came after them are within 10 %.  Chains of 2 / 3 / 4
+// layers of 32 and 64 channels, 14 x 14 to 56 x 56: 15.6 / 17.7 / 19.7 and 17.6 / 20.7 / 25.6 us modelled, 9.8 / 12.6 / 15.4 and
+// 12.0 / 15.6 / 20.3 measured; with 128 channels and more it is right.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
+// 4, 14.7 - 15.1 modelled, 8.5 - 9.2 measured, at 30 x 30, batch 32, 35.1 and 26; 256 channels 23.1 and 20.7.
+const int64_t C_FUSED_HIGH = 15000;
+const int64_t C_FUSED_HIGH_LAYER = 1900;
+const int64_t C_C3PW_HIGH = 10000;
+const int64_t C_C3PW_HIGH_256 = 2000;
+
+dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
+                      GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
+                      const C3Force* c3_force = nullptr);
+
+// A fused group whose layers would run on those kernels one by one: the older models compare fairly with one another but not
+// with theirs, so a group that is modelled above its layers' sum, but below it after that correction, is priced at the sum, and
+// the plan of fewer launches wins.  Nothing else in a plan changes by it: the layers one by one are a plan of that price.
+uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds, const GroupPlan& g)
+{
+    if (g.first == g.last || !((g.kind == GK_GROUP && g.ga.ntiles <= g.grid) || g.kind == GK_C3PW)) return g.cost;
+    const Layer& L0 = net.L[g.first];
+    int64_t high = L0.d.cin <= 128 ? C_C3PW_HIGH : C_C3PW_HIGH_256;
+    if (g.kind == GK_GROUP) high = std::max<int64_t>(0, C_FUSED_HIGH - g.ga.nstages * C_FUSED_HIGH_LAYER);
+    std::vector<StageSpec> specs;
+    std::string why;
+    int kind;
+    if (!group_stages(net, g.first, g.last, specs, kind, why) || specs.size() < 2) return g.cost;
+    for (const StageSpec& s : specs)
+        if (g.kind == GK_GROUP && std::max(net.L[s.layer].d.cin, net.L[s.layer].d.cout) > 64) return g.cost;
+    uint64_t sum = 0;
+    bool newer = false;
+    for (const StageSpec& s : specs) {
+        GroupPlan one;
+        if (make_group(net, batch, s.layer, s.pool2 ? s.pool_layer : s.layer, budget, max_lds, one) != DLF_OK) return g.cost;
+        newer = newer || one.kind == GK_SKC || one.kind == GK_C3R;
+        sum += one.cost;
+        if (sum >= g.cost) return g.cost;
+    }
+    return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)sum ? sum : g.cost;
+}
+
 // The group on the cheapest kernel: the one of make_group_tiled, or a split-K kernel in its place (layers that none of the
 // others takes, for their size or the LDS limit, stay infeasible).
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
-                      GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
-                      const C3Force* c3_force = nullptr)
+                      GroupPlan& g, const TileCfg* force_tc, int pw_mode, const C3Force* c3_force)
 {
     const dlf_status s = make_group_tiled(net, batch, first, last, budget, max_lds, g, force_tc, pw_mode, c3_force);
     // a caller or a testing hook that names another kernel's form gets that kernel
     const bool named = force_tc || pw_mode > 0 || c3_force || g_force.th > 0 || g_pw_mode != 0 || g_c3_force.mode != 0 ||
                        g_c3_force.shape >= 0 || g_dw_mode != 0;
     if (named && g_skc_force.mode != 1 && g_skd_force.mode != 1) return s;
+    if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g);
     if (first < 0 || last >= (int)net.L.size() || first > last || budget <= 0 || last > first + 1) return s;
     const Layer& L0 = net.L[first];
     if (g_skd_force.mode != 2 && !(named && g_skd_force.mode == 0) && last == first + 1 && skd_eligible(net, first, last, batch)) {
