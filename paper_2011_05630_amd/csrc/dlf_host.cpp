@@ -317,6 +317,7 @@ const int64_t C3S_SMALL_ITEMS = 128;
 const int64_t C_C3S_SMALL = 1200;
 const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
+const int64_t C_C3S_STEP_ONE = 125;          // ... tiles of one pixel block
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
 const int64_t C_C3S_EPI = 2500;
 // the fused 3x3 -> 1x1 kernel for small maps: per work item (decode, first loads), bytes per cycle of
@@ -1375,10 +1376,12 @@ uint64_t c3s_cost_ps(const Layer& L, int batch, int budget, const DlfC3sArgs& cs
     const int64_t wbytes = (int64_t)L.ncb * L.nsteps * 1024;
     const int64_t nitems = (int64_t)cs.ntiles * cs.nsl;
     const int64_t rounds = (nitems + budget - 1) / budget;
+    // tiles of one pixel block whose K is shared four ways, one round of them: the weights arrive faster than the model's other
+    // launches have it (512 channels at 9 x 9, batch 4: 9.6 us, 256 at 10 x 10, batch 6: 7.0)
+    const bool one_block = cs.taps == 9 && cs.tp <= 32 && cs.ksplit == 4 && rounds == 1;
     const int64_t item = C_C3S_ITEM + (rounds > 1 ? C_C3S_NEXT : 0) + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE +
                          (int64_t)(cs.nsteps / cs.ksplit) * (wbytes > C_C3S_BIG_BYTES ? C_C3S_STEP_BIG : C_C3S_STEP) *
-                             (cs.tp > 32 ? 4 : 3) / 4 +        // one pixel block: half the MFMAs, the same weights
-
+                             (cs.tp > 32 ? 4 : one_block ? 2 : 3) / 4 +        // one pixel block: half the MFMAs, the same weights
                          (cs.ksplit > 1 ? C_C3S_RED : 0) + C_C3S_EPI + (L.d.residual_from >= 0 ? C_PW_RES : 0);
     int64_t compute = C_LAT + rounds * item;
     // one round of items that share K four ways: most of its round trips are in C_LAUNCH already (512 channels at 5 x 5, batch 26:
@@ -1388,7 +1391,7 @@ uint64_t c3s_cost_ps(const Layer& L, int batch, int budget, const DlfC3sArgs& cs
     // rate a CU takes eight waves' weights in (183 cycles per step: 45 bytes per cycle), not at the
     // chip's matrix rate (256 channels at 14 x 14, batch 1 - 8: 8.3 - 8.5 us; 512 at 7 x 7: 11.4)
     if (nitems <= (cs.taps == 9 ? C3S_SMALL_ITEMS : C3S_SMALL_ITEMS / 2) && rounds == 1)
-        compute = C_C3S_SMALL + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE + (int64_t)(cs.nsteps / cs.ksplit) * (nitems > C3S_SMALL_ITEMS / 2 && cs.ksplit < 4 ? C_C3S_STEP_HALF : C_C3S_STEP_SMALL);
+        compute = C_C3S_SMALL + (int64_t)cs.rp * cs.cin * 2 / DWS_BYTES_PER_CYCLE + (int64_t)(cs.nsteps / cs.ksplit) * (nitems > C3S_SMALL_ITEMS / 2 && cs.ksplit < 4 ? C_C3S_STEP_HALF : one_block ? C_C3S_STEP_ONE : C_C3S_STEP_SMALL);
     const int64_t m = (int64_t)batch * L.out_h * L.out_w;
     const int64_t bytes = (int64_t)batch * L.in_h * L.in_w * L.d.cin * 2 + m * L.d.cout * 2 * (L.d.residual_from >= 0 ? 2 : 1) +
                           (int64_t)L.ncb * L.nsteps * 1024;

@@ -205,3 +205,12 @@ def test_bottleneck_pairs_keep_their_one_launch():
         h, groups = _default_plan(nets.resnet50(hw), batch)
         assert {(17, 18), (20, 21), (23, 24)} <= {g[:2] for g in groups}, (hw, batch, groups)
         B.dlf_net_destroy(h)
+
+
+@pytest.mark.parametrize("c,hw,batch,split", [(512, 9, 4, False), (512, 5, 12, False), (512, 10, 3, False), (256, 10, 8, False),
+                                              (512, 9, 2, True), (512, 7, 1, True), (256, 9, 4, True), (256, 14, 1, True)])
+def test_small_map_or_split_k(c, hw, batch, split):
+    """3x3 layers of 256 and 512 channels go to the faster of the small-map kernel (512 at 9 x 9, batch 4: 9.6 us against 10.9; 256
+    at 10 x 10, batch 8: 7.1 against 7.4) and the split-K kernel (512 at 9 x 9, batch 2: 8.4 against 9.4)."""
+    cfg, _ = _plan([nets.conv(c, c, 3, 1, 1, "relu")], hw, hw, batch)
+    assert cfg["kind"] == 10 and (cfg["variant"] >= 16) == split, cfg
