@@ -2247,10 +2247,10 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
 // What the fused-group kernel (in one round of tiles, up to 64 channels, by number of layers) and the 3x3 -> 1x1 kernel are modelled at
 // beyond what they take, where the models of the kernels for single layers that came after them are within 10 %.  Chains of 2 / 3 / 4
 // layers of 32 and 64 channels, 14 x 14 to 56 x 56: 15.6 / 17.7 / 19.7 and 17.6 / 20.7 / 25.6 us modelled, 9.8 / 12.6 / 15.4 and
-// 12.0 / 15.6 / 20.3 measured; with 128 channels and more it is right.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
+// 12.0 / 15.6 / 20.3 measured, two of 64 at 64 x 64, batch 13, 26.4 and 19.8; with 128 channels and more it is right.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
 // 4, 14.7 - 15.1 modelled, 8.5 - 9.2 measured, at 30 x 30, batch 32, 35.1 and 26; 256 channels 23.1 and 20.7.
-const int64_t C_FUSED_HIGH = 15000;
-const int64_t C_FUSED_HIGH_LAYER = 1900;
+const int64_t C_FUSED_HIGH = 17500;
+const int64_t C_FUSED_HIGH_LAYER = 2500;
 const int64_t C_C3PW_HIGH = 10000;
 const int64_t C_C3PW_HIGH_256 = 2000;
 

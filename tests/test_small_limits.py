@@ -205,6 +205,10 @@ def test_bottleneck_pairs_keep_their_one_launch():
         h, groups = _default_plan(nets.resnet50(hw), batch)
         assert {(17, 18), (20, 21), (23, 24)} <= {g[:2] for g in groups}, (hw, batch, groups)
         B.dlf_net_destroy(h)
+    # ResNet-18's first blocks: 19.8 us in one launch, 22.2 in two
+    h, groups = _default_plan(nets.resnet18(256), 13)
+    assert {(2, 3), (4, 5)} <= {g[:2] for g in groups}, groups
+    B.dlf_net_destroy(h)
 
 
 @pytest.mark.parametrize("c,hw,batch,split", [(512, 9, 4, False), (512, 5, 12, False), (512, 10, 3, False), (256, 10, 8, False),
