@@ -1028,7 +1028,7 @@ bool c3r_build(int pool2, int cin, int shape, int th, int tw, int max_lds, C3Cfg
     return c.lds_bytes <= max_lds;
 }
 
-uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3Cfg& c)
+uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3Cfg& c, bool stem = false)
 {
     const int64_t tiles = (int64_t)batch * ceil_div(L.out_h, c.th) * ceil_div(L.out_w, c.tw);
     const int64_t items = tiles * ceil_div(L.ncb, C3R_NCBW[c.shape]);
@@ -1044,10 +1044,11 @@ uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3C
     const int64_t bytes = m * L.d.cin * 2 + (pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
     const int64_t mem = bytes / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
     int64_t cycles = C_LAUNCH + std::max(compute, mem);
-    // With half of the chip idle (counted in items of 128 channels x 128 pixels, all of them used) a split of K is the better
-    // kernel, and the model of the fused-group kernel's is too high there (256 channels at 56 x 56 with the pool, batch
-    // 1: 12.8 us, modelled 18.3, here 15.2)
-    if (m * L.ncb <= C3R_FEW_ITEMS * 4 * 128) cycles = cycles * 4 / 3;
+    if (stem) cycles += items_cu * C_C3R_STEM;
+    // With half of the chip idle (counted in items of 128 channels x 128 pixels, all of them used; with the layer in front 64 x 512) a
+    // split of K is the better kernel, and the model of the fused-group kernel's is too high there (256 channels at 56 x 56 with
+    // the pool, batch 1: 12.8 us, modelled 18.3, here 15.2; VGG-16's first group, batch 1: 15.1 and 17.4)
+    if (m * L.ncb <= C3R_FEW_ITEMS * (stem ? 2 * 512 : 4 * 128)) cycles = cycles * 4 / 3;
     return (uint64_t)(cycles * PS_PER_CYCLE);
 }
 
@@ -1099,12 +1100,7 @@ bool c3r_stem_choose(const Layer& A, const Layer& B, int pool2, int batch, int b
             if (!c3r_build(pool2, 64, DLF_C3R_STEM_SHAPE, th, tw, max_lds, c, pw, vw)) continue;
             c.lds_bytes = std::max(c.na_i * 1024 + DLF_C3R_STEM_BYTES(th, tw, A.d.cin), (int)DLF_C3R_EPI_BYTES);
             if (c.lds_bytes > max_lds) continue;
-            const int64_t items = (int64_t)batch * ceil_div(B.out_h, th) * ceil_div(B.out_w, tw) * ceil_div(B.ncb, C3R_NCBW[DLF_C3R_STEM_SHAPE]);
-            const int64_t items_cu = (items + budget - 1) / budget;
-            uint64_t cc = c3r_cost_ps(B, pool2, batch, budget, c) + (uint64_t)(items_cu * C_C3R_STEM * PS_PER_CYCLE);
-            // (half of the chip idle, in items of 64 channels x 512 pixels: as in c3r_cost_ps; VGG-16 batch 1 17.4 us, the
-            // fused-group kernel 15.1)
-            if ((int64_t)batch * B.out_h * B.out_w * B.ncb <= C3R_FEW_ITEMS * 2 * 512) cc = cc * 4 / 3;
+            const uint64_t cc = c3r_cost_ps(B, pool2, batch, budget, c, true);
             if (!found || cc < cost) { found = true; cost = cc; best = c; }
         }
     return found;

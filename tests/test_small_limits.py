@@ -218,3 +218,17 @@ def test_small_map_or_split_k(c, hw, batch, split):
     at 10 x 10, batch 8: 7.1 against 7.4) and the split-K kernel (512 at 9 x 9, batch 2: 8.4 against 9.4)."""
     cfg, _ = _plan([nets.conv(c, c, 3, 1, 1, "relu")], hw, hw, batch)
     assert cfg["kind"] == 10 and (cfg["variant"] >= 16) == split, cfg
+
+
+def test_first_layer_pair_is_not_priced_lower_for_more_images():
+    """3 -> 64 -> 64 channels at 128 x 128 as one launch of the block kernel (forced): batches that leave half of the chip idle are all
+    priced by the same rule."""
+    costs = []
+    n = B.dlf_net_create([nets.conv(3, 64, 3, 1, 1, "relu"), nets.conv(64, 64, 3, 1, 1, "relu")], 128, 128, 3)
+    B.dlf_debug_block3x3_mode(1, 14, 14, 32)
+    try:
+        costs = [B.dlf_group_cost(n, b, 0, 1, 256) for b in (1, 2, 3, 4)]
+    finally:
+        B.dlf_debug_block3x3_mode(0)
+        B.dlf_net_destroy(n)
+    assert costs == sorted(costs), costs
