@@ -252,9 +252,10 @@ void dlf_i8conv_destroy(dlf_i8conv_t* layer);
 /* Tile (th x tw convolution pixels per work item; 1 x pixels for a 1x1 layer on the block kernel), kernel
  * shape index (5: the kernel for maps of many channels and few pixels; else ksize = 3: 0 .. 4, the block
  * kernel's shapes -- output channels x pixels per workgroup 128 x 256, 128 x 256 with 128-byte activation
- * blocks, 64 x 512, 64 x 512 with 128-byte blocks, 128 x 512; 0 .. 3 also stand for its form with the weights in
- * registers, of at most as many pixels --, ksize = 1: 3 = 128 x 128, 4 = 64 x 256), workgroups launched (that form's two
- * to a CU counted once), and the operation count of Eq. 1 for the whole batch.  Any out pointer may be NULL. */
+ * blocks, 64 x 512, 64 x 512 with 128-byte blocks, 128 x 512 --, 8 .. 13, its form with the weights in registers -- 128 x
+ * 224, 128 x 128, 64 x 448 and 64 x 256 with 128-byte blocks, 128 x 224 and 64 x 448 with 64-byte blocks --, ksize = 1:
+ * 3 = 128 x 128, 4 = 64 x 256), workgroups launched (shapes 8 .. 13 and ksize = 1: up to two to a compute unit), and the
+ * operation count of Eq. 1 for the whole batch.  Any out pointer may be NULL. */
 dlf_status dlf_i8conv_info(const dlf_i8conv_t* layer, int32_t* th, int32_t* tw, int32_t* shape, int32_t* grid,
                            uint64_t* op_count);
 /* One launch on hip_stream; asynchronous, allocates nothing.  DLF_ERR_NO_WEIGHTS on a shape-only layer. */

@@ -3480,10 +3480,8 @@ dlf_status dlf_i8conv_info(const dlf_i8conv_t* l, int32_t* th, int32_t* tw, int3
     if (!l) return fail(DLF_ERR_INVALID_ARG, "dlf_i8conv_info: null layer");
     if (th) *th = l->th;
     if (tw) *tw = l->tw;
-    // the block kernel with its weights in registers: the block shape of its channels and activation block; workgroups
-    // that share a CU count once
-    if (shape) *shape = !l->reg ? l->shape : (C3R_NCBW[l->shape] == 4 ? 0 : 2) + (C3R_ACH[l->shape] == 64 ? 1 : 0);
-    if (grid) *grid = !l->reg ? l->grid : std::max(8, l->grid / std::min(2, 160 * 1024 / l->lds_bytes) / 8 * 8);
+    if (shape) *shape = l->reg ? C3R_HOOK + l->shape : l->shape;
+    if (grid) *grid = l->grid;
     if (op_count) *op_count = l->ops;
     return DLF_OK;
 }

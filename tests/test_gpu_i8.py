@@ -222,7 +222,7 @@ def test_i8_vgg16_body_equals_oracle_chain():
             ref = oracle.maxpool2x2_i8(ref)
         assert np.array_equal(got, ref), "layer %d" % i
     assert got.shape == (2, 2, 2, 512) and got.max() > 20, (got.shape, int(got.max()))
-    assert 5 in kinds and any(k < 5 for k in kinds), kinds         # small-map and block kernels both take part
+    assert 5 in kinds and any(k != 5 for k in kinds), kinds        # small-map and block kernels both take part
 
 
 def test_i8_layers_captured_in_a_hip_graph_replay_to_the_oracle():

@@ -418,7 +418,9 @@ def test_i8conv_shape_only_layer_and_argument_checks():
     l = B.dlf_i8conv_create(16, 56, 56, 256, 256, 3, True)
     info = B.dlf_i8conv_info(l)
     assert info["op_count"] == 2 * 16 * 56 * 56 * 9 * 256 * 256        # Eq. 1 over the batch
-    assert info["th"] * info["tw"] <= 512 and info["grid"] % 8 == 0 and 8 <= info["grid"] <= 256
+    assert info["th"] * info["tw"] <= 512 and info["grid"] % 8 == 0 and 8 <= info["grid"] <= 2 * 256
+    # the kernel with the weights in registers: its own shape index, two workgroups to a compute unit
+    assert info["shape"] in range(8, 14) and info["grid"] == -(-16 * 7 * 2 * 2 // 8) * 8, info
     with pytest.raises(B.DlfError) as e:
         B.dlf_i8conv_run(l, 16, 16, None)
     assert e.value.status == B.DLF_ERR_NO_WEIGHTS
