@@ -187,18 +187,24 @@ const void* dlf_plan_layer_output(const dlf_plan_t* plan, int32_t layer);
  * 3 = 32x64 built for two workgroups per CU), for kind 3 the work-item form (0 = 64x64 and
  * 1 = 32x32 per wave, 2 = 64x64 with K split over four waves, 3 = 128x128 and 4 = 64x256 blocks
  * shared through LDS), for kind 4 the block shape (0 / 1 = 128 channels x 256 pixels, 2 / 3 =
- * 64 x 512, odd: activations 64 input channels at a time, even: 32; 4 = 128 x 512), 5 streaming
+ * 64 x 512, odd: activations 64 input channels at a time, even: 32; 4 = 128 x 512; 16 .. 21 its form with
+ * the weights in registers: 128 x 224, 128 x 128, 64 x 448 and 64 x 256 with 64 input channels at a time, 128 x 224
+ * and 64 x 448 with 32; 22 = 64 x 448 with a 3x3 layer of at most three input channels and 64 output channels in front, a
+ * group of two 3x3 layers), 5 streaming
  * depthwise kernel: a single depthwise 3x3 layer (variant = stride - 1), 6 fused depthwise 3x3 +
  * 1x1 kernel: a depthwise layer and the pointwise layer behind it, the depthwise result held in
- * registers (variant = 32-channel blocks of a wave's work item, 2 or 4), 7 depthwise + 1x1 tile
+ * registers (variant = 32-channel blocks of a wave's work item, 2 or 4; 16 and 17 the form for outputs of few
+ * pixels, 16 pixels x 32 or 64 channels per workgroup, K split over its waves), 7 depthwise + 1x1 tile
  * kernel: the same pair, the depthwise result of a pixel tile held in LDS (variant = stride - 1),
  * 8 two 1x1 convolutions into one output (the projection shortcut of a residual block and the
- * block's last layer, variant = block form as for kind 3; the group reads two tensors, reported by
+ * block's last layer, variant = block form as for kind 3, or 16 .. 19 as for kind 10; the group reads two tensors, reported by
  * dlf_plan_group_io as input = the last layer's input, residual = the projection's input),
  * 9 depthwise + 1x1 kernel for maps of 256 and more channels and few pixels (variant = 2 * (stride
  * - 1) + channel blocks per wave - 1), 10 small-map kernel: a single 3x3 layer (stride 1 or 2,
  * residual or not) or 1x1 layer on 256 .. 2048 input channels (variant = waves that share a channel
- * block's K: 1, 2 or 4; + 8 for a 1x1 layer), 11 a 3x3 layer of 64, 128 or 256 channels and the 1x1
+ * block's K: 1, 2 or 4; + 8 for a 1x1 layer; 16 .. 19 the kernel for outputs of few pixels: any single convolution of up
+ * to 25 taps on a multiple of 32 input channels, with its folded 2x2 pool or residual, 16 pixels x 16, 32 or 64 channels or 32 x
+ * 64 per workgroup, K split over its waves), 11 a 3x3 layer of 64, 128 or 256 channels and the 1x1
  * layer behind it (variant = 32-pixel blocks of a tile: 2 or 4), 12 a whole bottleneck block, 1x1 to
  * 64 channels -> 3x3 -> 1x1 with the block's input as residual operand, or its first two layers
  * (variant = the block's input channels; dlf_plan_group_io reports no residual tensor: the kernel
