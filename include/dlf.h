@@ -220,8 +220,8 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
 dlf_status dlf_plan_group_io(const dlf_plan_t* plan, int32_t g, int32_t* in_layer, int32_t* res_layer);
 /* Measured refinement of a plan, after the paper's search procedure that times candidates on the
  * hardware (Sec. V, the reduced brute-force search): for every fused group and every single 1x1 or
- * 3x3 layer, the top_k tilings by modelled cost (and each pointwise form, and the top_k block 3x3
- * shapes, that apply) are run
+ * 3x3 layer, the top_k tilings by modelled cost (and each pointwise form, the top_k block 3x3
+ * shapes with the weights in LDS and with the weights in registers, and each form for outputs of few pixels, that apply) are run
  * `reps` times on the group's real input (caches scrubbed, the input freshly written by the group
  * in front) and the fastest replaces the planned configuration if it is at least 10 % faster.  The partition into groups and the budgets stay as planned.
  * in_dev / out_dev: DEVICE, as for dlf_run; the workspace must be bound.  Runs the network once,

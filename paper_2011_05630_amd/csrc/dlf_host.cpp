@@ -1054,7 +1054,8 @@ uint64_t c3r_cost_ps(const Layer& L, int pool2, int batch, int budget, const C3C
 
 // Cheapest shape and tile (ties: the fewest work items, then as in c3_choose; 8 x 28 tiles of a 56 x 56 map take
 // 3 % less time than 7 x 28, the matrix pipes' power being the limit).
-bool c3r_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost)
+bool c3r_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost,
+                std::vector<std::pair<uint64_t, C3Cfg>>* all = nullptr)
 {
     bool found = false;
     int64_t items = 0;
@@ -1067,6 +1068,7 @@ bool c3r_choose(const Layer& L, int pool2, int batch, int budget, int max_lds, C
                 int pw, vw;
                 if (!c3r_build(pool2, L.d.cin, shape, th, tw, max_lds, c, pw, vw)) continue;
                 const uint64_t cc = c3r_cost_ps(L, pool2, batch, budget, c);
+                if (all) all->push_back(std::make_pair(cc, c));
                 const int64_t n = (int64_t)ceil_div(L.out_h, th) * ceil_div(L.out_w, tw) * ceil_div(L.ncb, C3R_NCBW[shape]);
                 if (!found || cc < cost || (cc == cost && n < items)) { found = true; cost = cc; best = c; items = n; }
             }
@@ -1088,7 +1090,8 @@ bool c3r_stem_eligible(const dlf_net_s& net, const std::vector<StageSpec>& specs
     return c3_eligible(net, second, batch) && B.d.cin == 64 && B.d.residual_from < 0;
 }
 
-bool c3r_stem_choose(const Layer& A, const Layer& B, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost, int fth = 0, int ftw = 0)
+bool c3r_stem_choose(const Layer& A, const Layer& B, int pool2, int batch, int budget, int max_lds, C3Cfg& best, uint64_t& cost, int fth = 0,
+                     int ftw = 0, std::vector<std::pair<uint64_t, C3Cfg>>* all = nullptr)
 {
     bool found = false;
     for (int th : TILE_H)
@@ -1101,6 +1104,7 @@ bool c3r_stem_choose(const Layer& A, const Layer& B, int pool2, int batch, int b
             c.lds_bytes = std::max(c.na_i * 1024 + DLF_C3R_STEM_BYTES(th, tw, A.d.cin), (int)DLF_C3R_EPI_BYTES);
             if (c.lds_bytes > max_lds) continue;
             const uint64_t cc = c3r_cost_ps(B, pool2, batch, budget, c, true);
+            if (all) all->push_back(std::make_pair(cc, c));
             if (!found || cc < cost) { found = true; cost = cc; best = c; }
         }
     return found;
@@ -1695,13 +1699,14 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
 
 int skc_lds_bytes(const DlfSkcArgs& sk, int shape) { return sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024; }
 
-bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, int max_lds, DlfSkcArgs& best, int& shape, uint64_t& cost)
+bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, int max_lds, const SkcForce& force,
+                DlfSkcArgs& best, int& shape, uint64_t& cost)
 {
     bool found = false;
     for (int sh = 0; sh < DLF_SKC_SHAPES; ++sh) {
-        if (g_skc_force.shape >= 0 && sh != g_skc_force.shape) continue;
+        if (force.shape >= 0 && sh != force.shape) continue;
         DlfSkcArgs sk;
-        skc_fill(L, proj, pool2, batch, sh, g_skc_force.waves, sk);
+        skc_fill(L, proj, pool2, batch, sh, force.waves, sk);
         if (!sk_items_ok(sk.n_pg, sk.n_cg, budget) || skc_lds_bytes(sk, sh) > max_lds) continue;
         const uint64_t c = skc_cost_ps(L, proj, sk, batch, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
@@ -1756,13 +1761,14 @@ uint64_t skd_cost_ps(const Layer& D, const Layer& P, const DlfSkdArgs& sd, int s
 
 int skd_lds_bytes(const DlfSkdArgs& sd, int shape) { return DLF_SKD_LDS_BYTES(sd.nw, 16 * SKD_TC[shape], sd.ksw); }
 
-bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, int max_lds, DlfSkdArgs& best, int& shape, uint64_t& cost)
+bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, int max_lds, const SkcForce& force, DlfSkdArgs& best, int& shape,
+                uint64_t& cost)
 {
     bool found = false;
     for (int sh = 0; sh < DLF_SKD_SHAPES; ++sh) {
-        if (g_skd_force.shape >= 0 && sh != g_skd_force.shape) continue;
+        if (force.shape >= 0 && sh != force.shape) continue;
         DlfSkdArgs sd;
-        skd_fill(D, P, batch, sh, g_skd_force.waves, sd);
+        skd_fill(D, P, batch, sh, force.waves, sd);
         if (!sk_items_ok(sd.n_pg, sd.n_cg, budget) || skd_lds_bytes(sd, sh) > max_lds) continue;
         const uint64_t c = skd_cost_ps(D, P, sd, sh, budget);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
@@ -2281,6 +2287,60 @@ uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds,
     return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)sum ? sum : g.cost;
 }
 
+// The group on the split-K kernel for a depthwise layer and the 1x1 layer behind it, or on the one for a single convolution, where
+// one of them takes it, in the forms that `pair` and `conv` name.
+bool small_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds, const SkcForce& conv_force,
+                 const SkcForce& pair_force, GroupPlan& g)
+{
+    if (first < 0 || last >= (int)net.L.size() || first > last || budget <= 0 || last > first + 1) return false;
+    const Layer& L0 = net.L[first];
+    int shape = 0;
+    uint64_t cost = 0;
+    if (pair_force.mode != 2 && last == first + 1 && skd_eligible(net, first, last, batch)) {
+        DlfSkdArgs sd;
+        if (!skd_choose(L0, net.L[last], batch, budget, max_lds, pair_force, sd, shape, cost)) return false;
+        g = GroupPlan();
+        g.in_layer = L0.src;
+        g.sd = sd;
+        g.kind = GK_SKD;
+        g.grid = sd.n_pg * sd.n_cg;
+        g.th = 1; g.tw = 16;
+        g.lds_bytes = skd_lds_bytes(sd, shape);
+    } else {
+        if (conv_force.mode == 2) return false;
+        const Layer* conv = &L0;
+        const Layer* proj = nullptr;
+        int pool2 = 0;
+        if (pw2_eligible(net, first, last, batch)) {
+            conv = &net.L[last];
+            proj = &L0;
+        } else {
+            std::vector<StageSpec> specs;
+            std::string why;
+            int kind;
+            if (!group_stages(net, first, last, specs, kind, why) || kind != GK_GROUP || specs.size() != 1) return false;
+            pool2 = specs[0].pool2;
+        }
+        if (!skc_layer_ok(*conv, batch) || (proj && !skc_layer_ok(*proj, batch))) return false;
+        DlfSkcArgs sk;
+        if (!skc_choose(*conv, proj, pool2, batch, budget, max_lds, conv_force, sk, shape, cost)) return false;
+        g = GroupPlan();
+        g.in_layer = conv->src;
+        if (proj) { g.res_layer = proj->src; g.res_stage = 0; }
+        else if (conv->d.residual_from >= 0) { g.res_layer = conv->d.residual_from; g.res_stage = 0; }
+        g.sk = sk;
+        g.kind = GK_SKC;
+        g.grid = sk.n_pg * sk.n_cg;
+        g.th = 1; g.tw = 16 * SKC_TP[shape];
+        g.lds_bytes = skc_lds_bytes(sk, shape);
+    }
+    g.first = first; g.last = last; g.budget = budget;
+    g.cost = cost;
+    g.variant = shape;
+    g.occ = SK_OCC;
+    return true;
+}
+
 // The group on the cheapest kernel: the one of make_group_tiled, or a split-K kernel in its place (layers that none of the
 // others takes, for their size or the LDS limit, stay infeasible).
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
@@ -2292,61 +2352,14 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
                        g_c3_force.shape >= 0 || g_dw_mode != 0;
     if (named && g_skc_force.mode != 1 && g_skd_force.mode != 1) return s;
     if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g);
-    if (first < 0 || last >= (int)net.L.size() || first > last || budget <= 0 || last > first + 1) return s;
-    const Layer& L0 = net.L[first];
-    if (g_skd_force.mode != 2 && !(named && g_skd_force.mode == 0) && last == first + 1 && skd_eligible(net, first, last, batch)) {
-        DlfSkdArgs sd;
-        int shape = 0;
-        uint64_t cost = 0;
-        if (!skd_choose(L0, net.L[last], batch, budget, max_lds, sd, shape, cost)) return s;
-        if (g_skd_force.mode != 1 && (s != DLF_OK || g.cost <= cost)) return s;
-        g = GroupPlan();
-        g.first = first; g.last = last; g.budget = budget;
-        g.in_layer = L0.src;
-        g.sd = sd;
-        g.kind = GK_SKD;
-        g.cost = cost;
-        g.variant = shape;
-        g.occ = SK_OCC;
-        g.grid = sd.n_pg * sd.n_cg;
-        g.th = 1; g.tw = 16;
-        g.lds_bytes = skd_lds_bytes(sd, shape);
-        return DLF_OK;
-    }
-    const Layer* conv = nullptr;
-    const Layer* proj = nullptr;
-    int pool2 = 0;
-    if (pw2_eligible(net, first, last, batch)) {
-        conv = &net.L[last];
-        proj = &L0;
-    } else {
-        std::vector<StageSpec> specs;
-        std::string why;
-        int kind;
-        if (!group_stages(net, first, last, specs, kind, why) || kind != GK_GROUP || specs.size() != 1) return s;
-        conv = &L0;
-        pool2 = specs[0].pool2;
-    }
-    if (g_skc_force.mode == 2 || (named && g_skc_force.mode == 0)) return s;
-    if (!skc_layer_ok(*conv, batch) || (proj && !skc_layer_ok(*proj, batch))) return s;
-    DlfSkcArgs sk;
-    int shape = 0;
-    uint64_t cost = 0;
-    if (!skc_choose(*conv, proj, pool2, batch, budget, max_lds, sk, shape, cost)) return s;
-    if (g_skc_force.mode != 1 && (s != DLF_OK || g.cost <= cost)) return s;
-    g = GroupPlan();
-    g.first = first; g.last = last; g.budget = budget;
-    g.in_layer = conv->src;
-    if (proj) { g.res_layer = proj->src; g.res_stage = 0; }
-    else if (conv->d.residual_from >= 0) { g.res_layer = conv->d.residual_from; g.res_stage = 0; }
-    g.sk = sk;
-    g.kind = GK_SKC;
-    g.cost = cost;
-    g.variant = shape;
-    g.occ = SK_OCC;
-    g.grid = sk.n_pg * sk.n_cg;
-    g.th = 1; g.tw = 16 * SKC_TP[shape];
-    g.lds_bytes = skc_lds_bytes(sk, shape);
+    const SkcForce never = {2, -1, 0};
+    GroupPlan small;
+    if (!small_group(net, batch, first, last, budget, max_lds, named && g_skc_force.mode == 0 ? never : g_skc_force,
+                     named && g_skd_force.mode == 0 ? never : g_skd_force, small))
+        return s;
+    const bool forced = (small.kind == GK_SKD ? g_skd_force : g_skc_force).mode == 1;
+    if (!forced && (s != DLF_OK || g.cost <= small.cost)) return s;
+    g = small;
     return DLF_OK;
 }
 
@@ -3140,22 +3153,38 @@ dlf_status dlf_plan_refine(dlf_plan_t* plan, const void* in_dev, void* out_dev, 
                     cands.push_back(gp);
             }
         }
-        if (c3_eligible(net, specs, plan->batch)) {
-            std::vector<std::pair<uint64_t, C3Cfg>> all;
-            C3Cfg cc;
-            uint64_t c = 0;
-            c3_choose(net.L[cur.first], specs[0].pool2, plan->batch, cur.budget, plan->max_lds, cc, c, &all);
+        // the block 3x3 kernel, with its weights in LDS or in registers, and the latter with a first layer in front
+        auto add_c3 = [&](std::vector<std::pair<uint64_t, C3Cfg>>& all, int first_shape, int pw_mode) {
             std::stable_sort(all.begin(), all.end(),
                              [](const std::pair<uint64_t, C3Cfg>& x, const std::pair<uint64_t, C3Cfg>& y) {
                                  return x.first < y.first;
                              });
             for (size_t i = 0; i < all.size() && (int)i < top_k; ++i) {
                 GroupPlan gp;
-                const C3Force f = {1, all[i].second.shape, all[i].second.th, all[i].second.tw};
-                if (make_group(net, plan->batch, cur.first, cur.last, cur.budget, plan->max_lds, gp, &none, 2,
+                const C3Force f = {1, first_shape + all[i].second.shape, all[i].second.th, all[i].second.tw};
+                if (make_group(net, plan->batch, cur.first, cur.last, cur.budget, plan->max_lds, gp, &none, pw_mode,
                                &f) == DLF_OK)
                     cands.push_back(gp);
             }
+        };
+        std::vector<std::pair<uint64_t, C3Cfg>> lds_forms, reg_forms;
+        C3Cfg cc;
+        uint64_t cost = 0;
+        if (c3_eligible(net, specs, plan->batch)) {
+            c3_choose(net.L[cur.first], specs[0].pool2, plan->batch, cur.budget, plan->max_lds, cc, cost, &lds_forms);
+            c3r_choose(net.L[cur.first], specs[0].pool2, plan->batch, cur.budget, plan->max_lds, cc, cost, &reg_forms);
+            add_c3(lds_forms, 0, 2);
+            add_c3(reg_forms, C3R_HOOK, 2);
+        } else if (c3r_stem_eligible(net, specs, plan->batch)) {
+            c3r_stem_choose(net.L[specs[0].layer], net.L[specs[1].layer], specs[1].pool2, plan->batch, cur.budget, plan->max_lds, cc, cost,
+                            0, 0, &reg_forms);
+            add_c3(reg_forms, C3R_HOOK + DLF_C3R_SHAPES - DLF_C3R_STEM_SHAPE, 0);
+        }
+        // the kernels for outputs of few pixels
+        for (int sh = 0; sh < std::max(DLF_SKC_SHAPES, DLF_SKD_SHAPES); ++sh) {
+            GroupPlan gp;
+            const SkcForce one = {1, sh, 0};
+            if (small_group(net, plan->batch, cur.first, cur.last, cur.budget, plan->max_lds, one, one, gp)) cands.push_back(gp);
         }
         if (cur.first == cur.last && pw_eligible(net.L[cur.first], plan->batch)) {
             for (int sh = 0; sh < PW_SHAPES; ++sh) {
