@@ -1620,7 +1620,7 @@ SkcForce g_skc_force = {0, -1, 0};
 const int SKC_TP[DLF_SKC_SHAPES] = {1, 1, 1, 2};        // 16-pixel blocks of an item
 const int SKC_TC[DLF_SKC_SHAPES] = {1, 2, 4, 4};        // 16-channel blocks of an item
 
-// A convolution the kernel can run, alone or with the 2x2 pool behind it, or a fully connected layer.
+// A convolution the kernel can run, alone or with the 2x2 pool behind it.
 bool skc_layer_ok(const Layer& L, int batch)
 {
     const dlf_layer_desc& d = L.d;
@@ -3004,11 +3004,11 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
             if (sk.nk2 > 0) sk.in2 = res;
             else sk.res = res;
         }
-        e = dlf_launch_skc ? dlf_launch_skc(&sk, G.variant, stream) : (int)hipErrorInvalidDeviceFunction;
+        e = dlf_launch_skc(&sk, G.variant, stream);
     } else if (G.kind == GK_SKD) {
         DlfSkdArgs sd = G.sd;
         sd.in = in; sd.out = out;
-        e = dlf_launch_skd ? dlf_launch_skd(&sd, G.variant, stream) : (int)hipErrorInvalidDeviceFunction;
+        e = dlf_launch_skd(&sd, G.variant, stream);
     } else if (G.kind == GK_DWS) {
         DlfDwsArgs ds = G.ds;
         ds.in = in; ds.out = out;
@@ -3025,7 +3025,7 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
             ca.res = res;
         }
         if (G.kind == GK_C3) e = dlf_launch_c3(&ca, G.variant, G.grid, G.lds_bytes, stream);
-        else e = dlf_launch_c3r ? dlf_launch_c3r(&ca, G.variant, 0, G.grid, G.lds_bytes, stream) : (int)hipErrorInvalidDeviceFunction;
+        else e = dlf_launch_c3r(&ca, G.variant, 0, G.grid, G.lds_bytes, stream);
     } else {
         DlfGroupArgs ga = G.ga;
         ga.in = in; ga.out = out;
@@ -3537,7 +3537,7 @@ dlf_status dlf_i8conv_run(const dlf_i8conv_t* l, const void* in_dev, void* out_d
         DlfC3Args ca = l->ca;
         ca.in = in_dev; ca.out = out_dev;
         if (!l->reg) e = dlf_launch_c3_i8(&ca, l->shape, l->grid, l->lds_bytes, hip_stream);
-        else e = dlf_launch_c3r ? dlf_launch_c3r(&ca, l->shape, 1, l->grid, l->lds_bytes, hip_stream) : (int)hipErrorInvalidDeviceFunction;
+        else e = dlf_launch_c3r(&ca, l->shape, 1, l->grid, l->lds_bytes, hip_stream);
     }
     if (e != 0) return fail(DLF_ERR_HIP, "launch of the int8 layer failed: %s", hipGetErrorString((hipError_t)e));
     return DLF_OK;

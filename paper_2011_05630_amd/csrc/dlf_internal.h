@@ -380,10 +380,10 @@ struct DlfBnArgs {
 };
 
 // One convolution (any filter of up to 25 taps, any stride; optionally with the 2x2 max pool behind
-// it folded in, a residual operand, or a second 1x1 operand pair added before the activation), or a
-// fully connected layer, for outputs so small that the latency of one workgroup is the launch: a
-// workgroup of `nw` waves computes 16 * TP pixels x 16 * TC channels, each wave over its own share of
-// K with all of its operands requested at once; the partial sums meet in LDS.
+// it folded in, a residual operand, or a second 1x1 operand pair added before the activation) for
+// outputs so small that the latency of one workgroup is the launch: a workgroup of `nw` waves computes
+// 16 * TP pixels x 16 * TC channels, each wave over its own share of K with a ring of its operands in
+// flight; the partial sums meet in LDS.
 #define DLF_SKC_SHAPES 4             // (TP, TC): 0 = (1, 1), 1 = (1, 2), 2 = (1, 4), 3 = (2, 4)
 #define DLF_SKC_MAX_TAPS 25
 struct DlfSkcArgs {
@@ -395,7 +395,7 @@ struct DlfSkcArgs {
     const void* w2;       // packed fragments of the second pair
     const float* bias;    // padded to ncb * 32
     const float* bias2;   // ... of the second pair
-    uint32_t in_bytes, in2_bytes, res_bytes;  // sizes of the tensors read (below 2 GiB each)
+    uint32_t in_bytes, in2_bytes;  // sizes of the tensors read (below 2 GiB each)
     int32_t h, w_, oh, ow, cin, cout, ncb;
     int32_t kw, kh, stride, pad, act, pool2;
     int32_t nk, nk2;      // 32-channel K steps of the first / second pair (cin / 32 * taps, cin2 / 32)
@@ -447,8 +447,8 @@ int dlf_launch_fc(const DlfFcArgs* a, void* stream);
 int dlf_launch_gap(const DlfGapArgs* a, void* stream);
 int dlf_launch_pw(const DlfPwArgs* a, int shape, int grid, void* stream);
 int dlf_launch_c3(const DlfC3Args* a, int shape, int grid, int lds_bytes, void* stream);
-// (weak, as dlf_launch_skc below) `i8`: the quantised form
-__attribute__((weak)) int dlf_launch_c3r(const DlfC3Args* a, int shape, int i8, int grid, int lds_bytes, void* stream);
+// `i8`: the quantised form
+int dlf_launch_c3r(const DlfC3Args* a, int shape, int i8, int grid, int lds_bytes, void* stream);
 int dlf_launch_pw_i8(const DlfPwArgs* a, int shape, int grid, void* stream);
 int dlf_launch_c3_i8(const DlfC3Args* a, int shape, int grid, int lds_bytes, void* stream);
 int dlf_launch_dw(const DlfDwArgs* a, int grid, void* stream);
@@ -458,9 +458,8 @@ int dlf_launch_dws(const DlfDwsArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_c3s(const DlfC3sArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_c3pw(const DlfC3PwArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, void* stream);
-// (weak: a host-only build of the planner, which launches nothing, links without it)
-__attribute__((weak)) int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream);
-__attribute__((weak)) int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream);
+int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream);
+int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream);
 int dlf_kernels_init(void);
 // Attaches a start / stop event pair (hipEvent_t, either may be null) to this thread's next launch.
 void dlf_next_launch_events(void* start, void* stop);

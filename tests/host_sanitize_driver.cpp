@@ -43,6 +43,9 @@ int dlf_launch_dws(const DlfDwsArgs*, int, int, void*) { return unreachable_laun
 int dlf_launch_c3s(const DlfC3sArgs*, int, int, void*) { return unreachable_launch("c3s"); }
 int dlf_launch_c3pw(const DlfC3PwArgs*, int, int, void*) { return unreachable_launch("c3pw"); }
 int dlf_launch_bneck(const DlfBnArgs*, int, int, void*) { return unreachable_launch("bneck"); }
+int dlf_launch_c3r(const DlfC3Args*, int, int, int, int, void*) { return unreachable_launch("c3r"); }
+int dlf_launch_skc(const DlfSkcArgs*, int, void*) { return unreachable_launch("skc"); }
+int dlf_launch_skd(const DlfSkdArgs*, int, void*) { return unreachable_launch("skd"); }
 int dlf_kernels_init(void) { return unreachable_launch("init"); }
 void dlf_next_launch_events(void*, void*) { (void)unreachable_launch("events"); }
 }

@@ -35,6 +35,16 @@ def driver(tmp_path_factory):
     return exe
 
 
+def test_driver_replaces_every_launcher():
+    """Each launcher the host code may call has a stand-in that aborts (and none may be left undefined: no weak declarations)."""
+    with open(os.path.join(ROOT, "paper_2011_05630_amd", "csrc", "dlf_internal.h")) as f:
+        header = f.read()
+    with open(os.path.join(ROOT, "tests", "host_sanitize_driver.cpp")) as f:
+        stand_ins = set(re.findall(r"int (dlf_launch_\w+)\(", f.read()))
+    assert set(re.findall(r"int (dlf_launch_\w+)\(", header)) == stand_ins and len(stand_ins) >= 17
+    assert "weak" not in header
+
+
 def _net_lines(net):
     out = ["net %d %d %d %d" % (net["in_h"], net["in_w"], net["in_c"], len(net["layers"]))]
     for L in net["layers"]:
