@@ -258,7 +258,7 @@ const int64_t C_C3R_EDGE[DLF_C3R_SHAPES] = {7000, 4000, 9000, 6000, 7000, 9000};
 const int64_t C_C3R_ITEM[DLF_C3R_SHAPES] = {4000, 2000, 6500, 3500, 4000, 6500};
 const int64_t C3R_MMA_ALONE[DLF_C3R_SHAPES] = {160, 140, 160, 150, 160, 160};
 const int64_t C3R_MMA_SHARED = 142;
-const int64_t C3R_FEW_ITEMS = 128;
+const int64_t C3R_FEW_ITEMS = 128;            // items of a launch that leaves half of the chip idle (see c3r_cost_ps)
 const int64_t C_C3R_STEM = 4000;             // an item's layer in front
 
 // streaming depthwise kernel: per work item (decode, weights, first rows of the window), per output

@@ -2377,9 +2377,12 @@ __device__ __forceinline__ void stem_region(const DlfC3Args& a, int n, int ty0, 
 // Bank conflicts: part q of the halo pixel (r, c) lies at q ^ ((r * vw + c) >> SH), rows of `pw` pixels.  LDS serves
 // 16 lanes per cycle; with vw = tw the permutation runs through consecutive integers for consecutive tile
 // pixels whatever the tap and across row breaks, and pw = tw + 2 (128-byte pixels) or tw + 4 (64-byte pixels)
-// keeps the pixels' own bank halves (quarters) in step: no conflicts in the K loop's reads (counted over the tiles in use;
-// with the halo index in the permutation 1.4 cycles per read at 28-wide tiles, 2 with the pool's quads).  The
-// pool's order (2x2 windows in quads) wants the rows of a window 8 parts apart: vw = 8 mod 16.
+// keeps the pixels' own bank halves (quarters) in step; with the halo index in the permutation a read took 1.4
+// cycles at 28-wide tiles, 2 with the pool's quads.  The pool's order (2x2 windows in quads) wants the rows of a
+// window 8 parts apart: vw = 8 mod 16.  Counted (SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE): 8 x 28 tiles 5 % at 256
+// channels, 9 % at 128, and 14 x 32 tiles with the pool 2 %: the epilogue's alone (the same number whatever K is: its
+// 80-byte rows meet two ways), none in the K loop.  Left in the K loop: 7 x 28 tiles 7 % (lanes without a pixel read
+// pixel 0), and 28-wide tiles with the pool, 29 %, a third more cycles per read: a row of 14 windows breaks inside a pixel block.
 // Fragment reads are a ring of FP registers, each refilled for the next K step behind the MFMA that used it, and
 // waited for by count (see k_c3b), two pixel blocks at a time: a wave alone on its SIMD issues one instruction per
 // matrix instruction's eight passes, so what stands beside the MFMAs (4.2 instructions each, 8 in the first form) is

@@ -9,7 +9,7 @@ from gpu_util import compare, announce
 pytestmark = pytest.mark.gpu
 
 
-def _run(net, batch, lasts, shape, waves, kinds):
+def _run(net, batch, lasts, shape, waves, kinds, budget=256):
     from oracle import oracle as o
     from paper_2011_05630_amd import binding as B
     from paper_2011_05630_amd.runner import Session
@@ -17,7 +17,7 @@ def _run(net, batch, lasts, shape, waves, kinds):
     ref = o.run_net(net, x, ws, bs)
     B.dlf_debug_small_mode(1, shape, waves)
     try:
-        s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=list(lasts), group_budget=[256] * len(lasts))
+        s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=list(lasts), group_budget=[budget] * len(lasts))
     finally:
         B.dlf_debug_small_mode(0)
     try:
@@ -61,3 +61,20 @@ def test_residual_pool_and_projection(shape):
                   nets.conv(64, 136, 1, stride, 0, "none", input_from=0),
                   nets.conv(32, 136, 1, 1, 0, "relu", input_from=2, residual_from=3)]
         _run(_mk(layers, hw, hw + 2, 64), 3, [0, 1, 2, 4], shape, 0, [10, 10, 10, 8])
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+def test_rectangular_filters(shape):
+    """Filters of unequal sides, up to 25 taps, with and without padding, stride 2."""
+    announce("small rectangular", shape)
+    for kh, kw, stride, pad, h, w, batch in ((1, 7, 1, 0, 5, 12, 2), (5, 3, 2, 1, 11, 8, 3), (3, 8, 1, 2, 4, 9, 1), (25, 1, 1, 0, 27, 3, 2), (2, 5, 2, 4, 6, 7, 2)):
+        layer = dict(nets.conv(64, 72, 1, stride, pad, "relu"), kh=kh, kw=kw)
+        _run(_mk([layer], h, w, 64), batch, [0], shape, 0, [10])
+
+
+@pytest.mark.parametrize("shape,channels,pixels,h,w", [(0, 72, 16, 40, 40), (1, 40, 16, 63, 64), (2, 100, 16, 63, 64), (3, 64, 32, 126, 125)])
+def test_as_many_items_as_the_budget_allows(shape, channels, pixels, h, w):
+    """Launches of just under two workgroups per compute unit of the whole chip, and of exactly two on a budget of eight."""
+    announce("small, budget", shape, channels, h, w)
+    _run(_mk([nets.conv(32, channels, 3, 1, 1, "relu")], h, w, 32), 1, [0], shape, 0, [10])
+    _run(_mk([nets.conv(96, 16, 1, 1, 0, "relu")], 4, 4 * pixels, 96), 1, [0], shape, 0, [10], budget=8)
