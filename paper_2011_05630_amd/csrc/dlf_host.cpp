@@ -3,12 +3,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <deque>
 #include <limits>
+#include <map>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -2256,14 +2258,18 @@ const int64_t C_FUSED_HIGH_LAYER = 2500;
 const int64_t C_C3PW_HIGH = 10000;
 const int64_t C_C3PW_HIGH_256 = 2000;
 
+// Layers as groups of their own, by (layer, layer or folded pool, budget): a plan's search meets each of them in every range.
+struct OneLayer { bool ok, newer; uint64_t cost; };
+typedef std::map<std::array<int, 3>, OneLayer> OneLayers;
+
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
                       GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
-                      const C3Force* c3_force = nullptr);
+                      const C3Force* c3_force = nullptr, OneLayers* known = nullptr);
 
 // A fused group whose layers would run on those kernels one by one: the older models compare fairly with one another but not
 // with theirs, so a group that is modelled above its layers' sum, but below it after that correction, is priced at the sum, and
 // the plan of fewer launches wins.  Nothing else in a plan changes by it: the layers one by one are a plan of that price.
-uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds, const GroupPlan& g)
+uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds, const GroupPlan& g, OneLayers& known)
 {
     if (g.first == g.last || !((g.kind == GK_GROUP && g.ga.ntiles <= g.grid) || g.kind == GK_C3PW)) return g.cost;
     const Layer& L0 = net.L[g.first];
@@ -2278,10 +2284,16 @@ uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds,
     uint64_t sum = 0;
     bool newer = false;
     for (const StageSpec& s : specs) {
-        GroupPlan one;
-        if (make_group(net, batch, s.layer, s.pool2 ? s.pool_layer : s.layer, budget, max_lds, one) != DLF_OK) return g.cost;
-        newer = newer || one.kind == GK_SKC || one.kind == GK_C3R;
-        sum += one.cost;
+        const std::array<int, 3> key = {s.layer, s.pool2 ? s.pool_layer : s.layer, budget};
+        auto at = known.find(key);
+        if (at == known.end()) {
+            GroupPlan one;
+            const bool ok = make_group(net, batch, key[0], key[1], budget, max_lds, one) == DLF_OK;
+            at = known.insert({key, OneLayer{ok, one.kind == GK_SKC || one.kind == GK_C3R, one.cost}}).first;
+        }
+        if (!at->second.ok) return g.cost;
+        newer = newer || at->second.newer;
+        sum += at->second.cost;
         if (sum >= g.cost) return g.cost;
     }
     return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)sum ? sum : g.cost;
@@ -2344,14 +2356,15 @@ bool small_group(const dlf_net_s& net, int batch, int first, int last, int budge
 // The group on the cheapest kernel: the one of make_group_tiled, or a split-K kernel in its place (layers that none of the
 // others takes, for their size or the LDS limit, stay infeasible).
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
-                      GroupPlan& g, const TileCfg* force_tc, int pw_mode, const C3Force* c3_force)
+                      GroupPlan& g, const TileCfg* force_tc, int pw_mode, const C3Force* c3_force, OneLayers* known)
 {
     const dlf_status s = make_group_tiled(net, batch, first, last, budget, max_lds, g, force_tc, pw_mode, c3_force);
     // a caller or a testing hook that names another kernel's form gets that kernel
     const bool named = force_tc || pw_mode > 0 || c3_force || g_force.th > 0 || g_pw_mode != 0 || g_c3_force.mode != 0 ||
                        g_c3_force.shape >= 0 || g_dw_mode != 0;
     if (named && g_skc_force.mode != 1 && g_skd_force.mode != 1) return s;
-    if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g);
+    OneLayers here;
+    if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g, known ? *known : here);
     const SkcForce never = {2, -1, 0};
     GroupPlan small;
     if (!small_group(net, batch, first, last, budget, max_lds, named && g_skc_force.mode == 0 ? never : g_skc_force,
@@ -2671,6 +2684,7 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
         const int nb = (int)budgets.size();
         // (a range that cannot be a group does not end the scan: longer ranges starting at the same
         // layer may still be, e.g. conv + pool + conv)
+        OneLayers known;
         std::deque<GroupPlan> table;                               // the groups that exist ...
         std::vector<int> at((size_t)n * n * nb, -1);               // ... and where a range's group is
         auto idx = [&](int f, int l, int b) { return ((size_t)f * n + l) * nb + b; };
@@ -2678,7 +2692,7 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
             for (int l = f; l < n; ++l)
                 for (int b = 0; b < nb; ++b) {
                     table.emplace_back();
-                    if (make_group(*net, batch, f, l, budgets[b], max_lds, table.back()) == DLF_OK)
+                    if (make_group(*net, batch, f, l, budgets[b], max_lds, table.back(), nullptr, -1, nullptr, &known) == DLF_OK)
                         at[idx(f, l, b)] = (int)table.size() - 1;
                     else
                         table.pop_back();
