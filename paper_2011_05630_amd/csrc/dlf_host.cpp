@@ -2258,13 +2258,24 @@ const int64_t C_FUSED_HIGH_LAYER = 2500;
 const int64_t C_C3PW_HIGH = 10000;
 const int64_t C_C3PW_HIGH_256 = 2000;
 
-// Layers as groups of their own, by (layer, layer or folded pool, budget): a plan's search meets each of them in every range.
-struct OneLayer { bool ok, newer; uint64_t cost; };
+// Layers as groups of their own, by (first, last, budget): a plan's search meets each of them in every range.
+struct OneLayer { dlf_status status; GroupPlan plan; };
 typedef std::map<std::array<int, 3>, OneLayer> OneLayers;
 
 dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds,
                       GroupPlan& g, const TileCfg* force_tc = nullptr, int pw_mode = -1,
                       const C3Force* c3_force = nullptr, OneLayers* known = nullptr);
+
+const OneLayer& one_layer(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds, OneLayers& known)
+{
+    const std::array<int, 3> key = {first, last, budget};
+    auto at = known.find(key);
+    if (at == known.end()) {
+        at = known.insert({key, OneLayer()}).first;
+        at->second.status = make_group(net, batch, first, last, budget, max_lds, at->second.plan);
+    }
+    return at->second;
+}
 
 // A fused group whose layers would run on those kernels one by one: the older models compare fairly with one another but not
 // with theirs, so a group that is modelled above its layers' sum, but below it after that correction, is priced at the sum, and
@@ -2284,16 +2295,10 @@ uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds,
     uint64_t sum = 0;
     bool newer = false;
     for (const StageSpec& s : specs) {
-        const std::array<int, 3> key = {s.layer, s.pool2 ? s.pool_layer : s.layer, budget};
-        auto at = known.find(key);
-        if (at == known.end()) {
-            GroupPlan one;
-            const bool ok = make_group(net, batch, key[0], key[1], budget, max_lds, one) == DLF_OK;
-            at = known.insert({key, OneLayer{ok, one.kind == GK_SKC || one.kind == GK_C3R, one.cost}}).first;
-        }
-        if (!at->second.ok) return g.cost;
-        newer = newer || at->second.newer;
-        sum += at->second.cost;
+        const OneLayer& one = one_layer(net, batch, s.layer, s.pool2 ? s.pool_layer : s.layer, budget, max_lds, known);
+        if (one.status != DLF_OK) return g.cost;
+        newer = newer || one.plan.kind == GK_SKC || one.plan.kind == GK_C3R;
+        sum += one.plan.cost;
         if (sum >= g.cost) return g.cost;
     }
     return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)sum ? sum : g.cost;
@@ -2692,10 +2697,16 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
             for (int l = f; l < n; ++l)
                 for (int b = 0; b < nb; ++b) {
                     table.emplace_back();
-                    if (make_group(*net, batch, f, l, budgets[b], max_lds, table.back(), nullptr, -1, nullptr, &known) == DLF_OK)
-                        at[idx(f, l, b)] = (int)table.size() - 1;
-                    else
-                        table.pop_back();
+                    dlf_status st;
+                    if (f == l) {
+                        const OneLayer& one = one_layer(*net, batch, f, f, budgets[b], max_lds, known);
+                        st = one.status;
+                        table.back() = one.plan;
+                    } else {
+                        st = make_group(*net, batch, f, l, budgets[b], max_lds, table.back(), nullptr, -1, nullptr, &known);
+                    }
+                    if (st == DLF_OK) at[idx(f, l, b)] = (int)table.size() - 1;
+                    else table.pop_back();
                 }
         // best[i] = best plan for the suffix starting at layer i under the total order
         // (cost, number of groups, group_last lexicographic, budgets lexicographic)
