@@ -144,7 +144,9 @@ dlf_status dlf_run(const dlf_plan_t* plan, const void* in_dev, void* out_dev, vo
  * on until the process ends; no workspace has to be bound, and a bound one is not used.  in_dev /
  * out_dev as for dlf_run (DEVICE, caller-owned).  Calls no hipMalloc / hipFree and creates no
  * stream or event; every group runs in order on hip_stream (dlf_plan_set_overlap is ignored).
- * DLF_ERR_OOM if dlf_plan_workspace_bytes(plan) exceeds the static size.  All calls on one GPU share
+ * Where dlf_plan_workspace_bytes(plan) exceeds the static size, a DLF_TUNER_DP plan runs its layers in the
+ * cheapest groups found whose tensors fit (as dlf_plan laid them down; dlf_plan_refine does not change them);
+ * DLF_ERR_OOM if there are none, and for the other modes.  All calls on one GPU share
  * that GPU's array, whatever the plan: two calls whose kernels overlap in time on one GPU (different
  * streams or threads) race; calls on one stream are ordered and safe.  Nothing in the array has to
  * start at zero: every byte a kernel reads was written earlier in the same call. */

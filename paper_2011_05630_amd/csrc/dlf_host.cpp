@@ -2389,6 +2389,10 @@ struct dlf_plan_s {
     std::vector<GroupPlan> G;
     std::vector<size_t> layer_off;   // workspace offset of each layer's output, or SIZE_MAX
     size_t ws_bytes = 0;
+    // what dlf_run_noalloc runs where the plan's workspace is larger than the static one: the cheapest
+    // grouping found whose tensors fit, or empty
+    std::vector<GroupPlan> compact;
+    std::vector<size_t> compact_off;
     char* ws = nullptr;
     int max_lds = 160 * 1024;
     // Branches: a group that does not read the output of the group in front of it (the projection
@@ -2414,6 +2418,35 @@ struct dlf_plan_s {
 namespace {
 
 const int DEFAULT_BUDGETS[4] = {32, 64, 128, 256};
+
+size_t slot_bytes(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+
+// Bytes of workspace that a group's output and scratch take.
+size_t group_slots(const dlf_net_s& net, int batch, const GroupPlan& G)
+{
+    const Layer& L = net.L[G.last];
+    const size_t out = G.last + 1 < (int)net.L.size() ? slot_bytes((size_t)batch * L.out_h * L.out_w * L.out_c * 2) : 0;
+    return out + slot_bytes(G.scratch_bytes);
+}
+
+// Workspace of a list of groups: the output of each group except the last, then the scratch areas, 256-byte
+// aligned slots.  Returns its size.
+size_t lay_out(const dlf_net_s& net, int batch, std::vector<GroupPlan>& groups, std::vector<size_t>& layer_off)
+{
+    layer_off.assign(net.L.size(), (size_t)-1);
+    size_t off = 0;
+    for (size_t g = 0; g + 1 < groups.size(); ++g) {
+        const Layer& L = net.L[groups[g].last];
+        layer_off[groups[g].last] = off;
+        off += slot_bytes((size_t)batch * L.out_h * L.out_w * L.out_c * 2);
+    }
+    for (GroupPlan& G : groups)
+        if (G.scratch_bytes > 0) {
+            G.scratch_off = off;
+            off += slot_bytes(G.scratch_bytes);
+        }
+    return off;
+}
 
 // Algorithm 1 of the paper (greedy joint fusion + MP pass).  Where the printed algorithm is silent
 // or inconsistent: the running mean of the per-layer MP is kept as a sum and a count; the threshold
@@ -2668,7 +2701,7 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
     else budgets.assign(DEFAULT_BUDGETS, DEFAULT_BUDGETS + 4);
     for (int b : budgets) if (b <= 0) return fail(DLF_ERR_INVALID_ARG, "budgets must be positive");
 
-    std::vector<GroupPlan> groups;
+    std::vector<GroupPlan> groups, compact;
     if (o.mode == DLF_TUNER_MANUAL) {
         if (!o.manual_group_last || !o.manual_budget || o.manual_n <= 0)
             return fail(DLF_ERR_INVALID_ARG, "manual plan needs group_last[], budget[] and a count");
@@ -2748,6 +2781,44 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
             groups.push_back(table[at[idx(first, last, bi)]]);
             first = last + 1;
         }
+        // Where these groups need more than the static workspace: a grouping for dlf_run_noalloc, from the same table, cost and
+        // bytes weighed against each other by the smallest weight found (in picoseconds per KiB) at which it fits.
+        size_t need = 0;
+        for (const GroupPlan& G : groups) need += group_slots(*net, batch, G);
+        if (need > DLF_STATIC_WS_BYTES) {
+            std::vector<uint64_t> value(n + 1);
+            std::vector<int> pick(n + 1);
+            auto weighed = [&](uint64_t weight, std::vector<GroupPlan>& out) {
+                value[n] = 0;
+                for (int i = n - 1; i >= 0; --i) {
+                    value[i] = INF;
+                    for (int l = i; l < n; ++l)
+                        for (int b = 0; b < nb && value[l + 1] != INF; ++b) {
+                            const int k = at[idx(i, l, b)];
+                            if (k < 0) continue;
+                            const uint64_t v = table[k].cost + weight * (group_slots(*net, batch, table[k]) >> 10) + value[l + 1];
+                            if (v < value[i]) { value[i] = v; pick[i] = k; }
+                        }
+                }
+                out.clear();
+                size_t bytes = 0;
+                for (int i = 0; i < n; i = out.back().last + 1) {
+                    out.push_back(table[pick[i]]);
+                    bytes += group_slots(*net, batch, out.back());
+                }
+                return bytes <= DLF_STATIC_WS_BYTES;
+            };
+            std::vector<GroupPlan> trial;
+            if (weighed((uint64_t)1 << 30, compact)) {           // (the fewest bytes, whatever they cost)
+                for (int lo = 0, hi = 30; hi - lo > 1;) {
+                    const int mid = (lo + hi) / 2;
+                    if (weighed((uint64_t)1 << mid, trial)) { hi = mid; compact = trial; }
+                    else lo = mid;
+                }
+            } else {
+                compact.clear();
+            }
+        }
     } else if (o.mode == DLF_TUNER_GREEDY) {
         const double alpha = (o.alpha == 0 && o.beta == 0) ? 0.316 : o.alpha;
         const double beta = (o.alpha == 0 && o.beta == 0) ? 0.659 : o.beta;
@@ -2815,21 +2886,9 @@ dlf_status dlf_plan(const dlf_net_t* net, int32_t batch, const dlf_tuner_opts* o
     plan->batch = batch;
     plan->G = groups;
     plan->max_lds = max_lds;
-    // workspace: the output of each group except the last, 256-byte aligned slots
-    plan->layer_off.assign(n, (size_t)-1);
-    size_t off = 0;
-    for (size_t g = 0; g + 1 < groups.size(); ++g) {
-        const Layer& L = net->L[groups[g].last];
-        const size_t bytes = (size_t)batch * L.out_h * L.out_w * L.out_c * 2;
-        plan->layer_off[groups[g].last] = off;
-        off += (bytes + 255) & ~(size_t)255;
-    }
-    for (GroupPlan& G : plan->G)
-        if (G.scratch_bytes > 0) {
-            G.scratch_off = off;
-            off += (G.scratch_bytes + 255) & ~(size_t)255;
-        }
-    plan->ws_bytes = off;
+    plan->ws_bytes = lay_out(*net, batch, plan->G, plan->layer_off);
+    plan->compact = compact;
+    (void)lay_out(*net, batch, plan->compact, plan->compact_off);
     {
         const size_t ng = groups.size();
         std::vector<int> owner(n, -1);               // group that produces a layer's output
@@ -3574,19 +3633,22 @@ dlf_status dlf_run_noalloc(const dlf_plan_t* plan, const void* in_dev, void* out
 {
     if (!plan || !in_dev || !out_dev) return fail(DLF_ERR_INVALID_ARG, "dlf_run_noalloc: null argument");
     if (!plan->net->has_weights) return fail(DLF_ERR_NO_WEIGHTS, "network was created without weights");
-    if (plan->ws_bytes > DLF_STATIC_WS_BYTES)
+    const bool fits = plan->ws_bytes <= DLF_STATIC_WS_BYTES;
+    const std::vector<GroupPlan>& groups = fits ? plan->G : plan->compact;
+    const std::vector<size_t>& layer_off = fits ? plan->layer_off : plan->compact_off;
+    if (groups.empty())
         return fail(DLF_ERR_OOM, "dlf_run_noalloc: the plan needs %zu bytes of workspace, the static one holds %zu",
                     plan->ws_bytes, (size_t)DLF_STATIC_WS_BYTES);
     char* ws = nullptr;
     dlf_status s = static_workspace(&ws);
     if (s != DLF_OK) return s;
     // every group in order on the caller's stream: nothing here creates a stream or an event
-    const size_t ng = plan->G.size();
+    const size_t ng = groups.size();
     for (size_t g = 0; g < ng; ++g) {
-        const GroupPlan& G = plan->G[g];
-        const void* in = G.in_layer < 0 ? in_dev : ws + plan->layer_off[G.in_layer];
-        const void* res = G.res_stage < 0 ? nullptr : G.res_layer < 0 ? in_dev : ws + plan->layer_off[G.res_layer];
-        void* out = (g + 1 == ng) ? out_dev : (void*)(ws + plan->layer_off[G.last]);
+        const GroupPlan& G = groups[g];
+        const void* in = G.in_layer < 0 ? in_dev : ws + layer_off[G.in_layer];
+        const void* res = G.res_stage < 0 ? nullptr : G.res_layer < 0 ? in_dev : ws + layer_off[G.res_layer];
+        void* out = (g + 1 == ng) ? out_dev : (void*)(ws + layer_off[G.last]);
         s = launch_one(plan, G, in, res, out, hip_stream, ws);
         if (s != DLF_OK) return s;
     }
