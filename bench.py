@@ -112,8 +112,8 @@ PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>",
 SKC_NAME = {16: "k_skc<1,1,4>", 17: "k_skc<1,2,4>", 18: "k_skc<1,4,3>", 19: "k_skc<2,4,3>"}
 DW_NAME = {0: "k_dw<1>", 1: "k_dw<2>"}
 C3_NAME = {0: "k_c3b<2,32,2>", 1: "k_c3b<2,64,2>", 2: "k_c3b<1,32,2>", 3: "k_c3b<1,64,2>", 4: "k_c3b<2,32,4>",
-           16: "k_c3r<4,7,64>", 17: "k_c3r<4,4,64>", 18: "k_c3r<2,7,64>", 19: "k_c3r<2,4,64>", 20: "k_c3r<4,7,32>",
-           21: "k_c3r<2,7,32>", 22: "k_c3r<2,7,64,stem>"}
+           16: "k_c3r<4,7,64,10>", 17: "k_c3r<4,4,64,6>", 18: "k_c3r<2,7,64,17>", 19: "k_c3r<2,4,64,11>",
+           20: "k_c3r<4,7,32,6>", 21: "k_c3r<2,7,32,9>", 22: "k_c3r<2,7,64,17,false,true>"}
 
 
 def workloads():
