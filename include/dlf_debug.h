@@ -69,7 +69,7 @@ void dlf_debug_block3x3_mode(int32_t mode, int32_t shape, int32_t th, int32_t tw
 /* Testing hook: how a single convolution (with the 2x2 max pool folded behind it, a residual operand, or
  * together with the projection shortcut in front of it) chooses between the other kernels and the split-K
  * convolution kernel for outputs of few pixels: mode 0 = by modelled cost, 1 = that kernel wherever it
- * applies, 2 = never.  In mode 1 shape 0 .. 3 fixes an item's pixels x channels (16 x 16, 16 x 32, 16 x 64,
+ * applies (its items within two workgroups per compute unit of the budget, its LDS within the limit), 2 = never.  In mode 1 shape 0 .. 3 fixes an item's pixels x channels (16 x 16, 16 x 32, 16 x 64,
  * 32 x 64; -1: by cost) and waves (1, 2, 4 or 8; 0: automatic) the waves K is dealt to.  In mode 0 the
  * kernel is not considered while another hook names a kernel.  Process-wide, not thread-safe. */
 void dlf_debug_small_mode(int32_t mode, int32_t shape, int32_t waves);

@@ -232,3 +232,22 @@ def test_first_layer_pair_is_not_priced_lower_for_more_images():
         B.dlf_debug_block3x3_mode(0)
         B.dlf_net_destroy(n)
     assert costs == sorted(costs), costs
+
+
+def test_kernels_of_the_evaluated_networks():
+    """The kernels that the networks' plans are known to hold, so that a silent change of the planner's choice (and with it of what
+    the parity tests of these networks cover) shows."""
+    def forms(net, batch):
+        h = B.dlf_net_create(net["layers"], net["in_h"], net["in_w"], net["in_c"])
+        p = B.dlf_plan(h, batch)
+        out = [(c["kind"], c["variant"]) for c in (B.dlf_plan_group_config(p, g) for g in range(B.dlf_plan_num_groups(p)))]
+        B.dlf_plan_destroy(p)
+        B.dlf_net_destroy(h)
+        return out
+    vgg = forms(nets.vgg16(), 16)                        # register-weight kernel, with the first layer in front; small-map kernel
+    assert {(4, 16), (4, 17), (4, 22)} <= set(vgg) and any(k == 10 and v < 16 for k, v in vgg) and len(vgg) <= 16, vgg
+    res = forms(nets.resnet50(), 1)                      # split-K kernel, with projections; 3x3 -> 1x1 pairs; bottleneck blocks
+    assert sum(k == 10 and v >= 16 for k, v in res) >= 20 and any(k == 8 and v >= 16 for k, v in res), res
+    assert sum(k == 11 for k, _ in res) == 3 and any(k == 12 for k, _ in res) and len(res) <= 43, res
+    mob = forms(nets.mobilenet_v1(), 1)                  # split-K depthwise pairs
+    assert sum(k == 6 and v >= 16 for k, v in mob) >= 8 and len(mob) <= 14, mob
