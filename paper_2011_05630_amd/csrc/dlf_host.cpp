@@ -359,15 +359,21 @@ const int64_t C_SKD_ROUND = 700;
 const int64_t C_SKD_ROUND_STEP = 700;
 // ... and on the same pairs the other depthwise kernels in launches that leave places free (C_LAUNCH holds most of
 // such a launch's round trips; in per cent): the tile kernel with one tile per CU at most (5.0 - 7.4 us, 11 - 14
-// without this), the small-map kernel with one item (8.5 / 10.6 / 13.4 / 17.8, 14.7 -
-// 25.2; batch 18 10.0 and 13.1, 15.8 and 18.8), a streaming layer
-// of one item per SIMD (4.4 - 6.0, 8.0)
+// without this; from 5 MiB on it is slower), the small-map kernel with one item per CU at most: 256 / 512 / 1024 channels 7.4 - 9.2 /
+// 10.2 - 12.9 / 17.8 - 21.9 us at batch 1 - 48, 14.7 / 17 / 25 without this; per MB beyond ten (512 channels at 28 x 28, batch 8 /
+// 12 / 16: 12.8 / 17.1 / 18.9)
 const int64_t DWT_ONE_PCT = 30;
 const int64_t DWT_ONE_BYTES = 5 << 20;
-const int64_t DWS_SMALL_BYTES = 10 << 20;
 const int64_t DWS_SMALL_PCT = 92;
 const int64_t C_DWS_SMALL = 8000;
-const int64_t DW_ONE_PCT = 30;
+const int64_t DWS_SMALL_BYTES = 10 << 20;
+const int64_t C_DWS_SMALL_MB = 540;
+// ... a streaming layer of one item per SIMD at most: by rows of an item, less than nothing at few, and by bytes; 7 x 7 maps 3.9 -
+// 6.1 us, 14 x 14 and larger 5.5 - 7.2 at 1 MB, 7.5 - 8.5 at 10 MB, 9 at 25 (64 - 1024 channels, batch 1 - 48)
+const int64_t C_DW_ONE = -4700;
+const int64_t C_DW_ONE_ROW = 800;
+const int64_t C_DW_ONE_LEAST = 500;
+const int64_t C_DW_ONE_MB = 215;
 
 struct StageSpec {   // one stage, before tiling
     int layer;
@@ -1171,7 +1177,7 @@ uint64_t dw_cost_ps(const Layer& L, int batch, int budget, const DlfDwArgs& da)
     const int64_t items_simd = ((int64_t)da.nitems + (int64_t)budget * 4 - 1) / ((int64_t)budget * 4);
     int64_t compute = C_LAT + items_simd * (C_DW_ITEM / (DW_WAVES_PER_CU / 4) + rows * C_DW_ROW);
     const int64_t bytes = (int64_t)da.in_bytes + (int64_t)batch * L.out_h * L.out_w * L.out_c * 2 + (int64_t)L.cin_pad * 22;
-    if (items_simd <= 1 && bytes <= DWS_SMALL_BYTES) compute = compute * DW_ONE_PCT / 100;
+    if (items_simd <= 1) compute = std::min(compute, std::max(C_DW_ONE_LEAST, C_DW_ONE + rows * C_DW_ONE_ROW) + bytes * C_DW_ONE_MB / 1000000);
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
 }
@@ -1833,7 +1839,8 @@ uint64_t dws_cost_ps(const Layer& D, const Layer& P, int batch, int budget, cons
     const int64_t m = (int64_t)batch * D.out_h * D.out_w;
     const int64_t bytes = (int64_t)batch * D.in_h * D.in_w * D.in_c * 2 + m * P.d.cout * 2 +
                           (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
-    if (nitems <= budget && bytes <= DWS_SMALL_BYTES) compute = std::max<int64_t>(0, compute * DWS_SMALL_PCT / 100 - C_DWS_SMALL);
+    if (nitems <= budget)
+        compute = std::min(compute, std::max<int64_t>(0, compute * DWS_SMALL_PCT / 100 - C_DWS_SMALL) + std::max<int64_t>(0, bytes - DWS_SMALL_BYTES) * C_DWS_SMALL_MB / 1000000);
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
 }

@@ -251,3 +251,19 @@ def test_kernels_of_the_evaluated_networks():
     assert sum(k == 11 for k, _ in res) == 3 and any(k == 12 for k, _ in res) and len(res) <= 43, res
     mob = forms(nets.mobilenet_v1(), 1)                  # split-K depthwise pairs
     assert sum(k == 6 and v >= 16 for k, v in mob) >= 8 and len(mob) <= 14, mob
+
+
+def test_depthwise_layers_have_no_step_in_their_price():
+    """A streaming depthwise layer's price grows with the batch as its time does (512 channels at 14 x 14: 6.9 us at batch 1, 8.3 at 25 and
+    32), and MobileNet-v1's pairs stay pairs (217 x 217, batch 25: 12.1 us a pair, 19.1 as two launches)."""
+    for c, hw, measured in ((512, 14, {1: 6.9, 8: 7.4, 16: 7.6, 25: 8.3, 32: 8.3, 48: 8.7}), (256, 28, {1: 7.1, 4: 7.2, 12: 8.0, 16: 8.3, 32: 9.0}),
+                            (1024, 7, {1: 4.6, 16: 5.1, 32: 5.8, 48: 6.1})):
+        n = B.dlf_net_create([nets.dwconv(c, 3, 1, "relu")], hw, hw, c)
+        costs = {b: B.dlf_group_cost(n, b, 0, 0, 256) / 1e6 for b in range(1, 49)}
+        B.dlf_net_destroy(n)
+        assert all(costs[b] <= costs[b + 1] <= costs[b] + 0.75 for b in range(1, 32)), costs  # (256 channels: a second item from 33 on)
+        assert all(abs(costs[b] - us) <= 0.15 * us for b, us in measured.items()), {b: (costs[b], us) for b, us in measured.items()}
+    for hw, batch in ((217, 25), (224, 16), (224, 64)):
+        h, groups = _default_plan(nets.mobilenet_v1(hw), batch)
+        assert {(13, 14), (15, 16), (17, 18), (19, 20), (21, 22)} <= {g[:2] for g in groups}, (hw, batch, groups)
+        B.dlf_net_destroy(h)
