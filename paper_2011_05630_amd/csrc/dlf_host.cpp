@@ -2258,12 +2258,20 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
 // What the fused-group kernel (in one round of tiles, up to 64 channels, by number of layers) and the 3x3 -> 1x1 kernel are modelled at
 // beyond what they take, where the models of the kernels for single layers that came after them are within 10 %.  Chains of 2 / 3 / 4
 // layers of 32 and 64 channels, 14 x 14 to 56 x 56: 15.6 / 17.7 / 19.7 and 17.6 / 20.7 / 25.6 us modelled, 9.8 / 12.6 / 15.4 and
-// 12.0 / 15.6 / 20.3 measured, two of 64 at 64 x 64, batch 13, 26.4 and 19.8; with 128 channels and more it is right.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
+// 12.0 / 15.6 / 20.3 measured, two of 64 at 64 x 64, batch 13, 26.4 and 19.8.  3x3 chains of 96 and 128 channels at 2300 - 3200 pixels:
+// 19.5 / 23.6 / 30.5 and 21.5 / 26.5 / 35.4 us modelled, 13.3 / 17.3 / 22.8 - 25.5 and 15.6 / 20.0 / 27.5 - 32.1 measured; from 129 channels
+// on the layers one by one are the faster plan.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
 // 4, 14.7 - 15.1 modelled, 8.5 - 9.2 measured, at 30 x 30, batch 32, 35.1 and 26; 256 channels 23.1 and 20.7.
 const int64_t C_FUSED_HIGH = 17500;
 const int64_t C_FUSED_HIGH_LAYER = 2500;
+const int64_t C_FUSED_HIGH_128 = 11000;
+const int64_t C_FUSED_HIGH_128_LAYER = 800;
 const int64_t C_C3PW_HIGH = 10000;
 const int64_t C_C3PW_HIGH_256 = 2000;
+// ... and what a 3x3 layer on the split-K kernel's items of 32 pixels x 64 channels takes, above SKC_FEW_ITEMS, by K steps: 5.3 - 5.4 /
+// 5.9 - 6.1 / 6.4 - 6.6 / 7.3 - 7.5 us with 9 / 18 / 27 / 36, 4.5 / 5.3 / 6.0 - 7.5 / 6.8 - 8.5 modelled.
+const int64_t C_SKC_FAIR = 1000;
+const int64_t C_SKC_FAIR_STEP = 156;
 
 // Layers as groups of their own, by (first, last, budget): a plan's search meets each of them in every range.
 struct OneLayer { dlf_status status; GroupPlan plan; };
@@ -2292,23 +2300,35 @@ uint64_t fused_cost_ps(const dlf_net_s& net, int batch, int budget, int max_lds,
     if (g.first == g.last || !((g.kind == GK_GROUP && g.ga.ntiles <= g.grid) || g.kind == GK_C3PW)) return g.cost;
     const Layer& L0 = net.L[g.first];
     int64_t high = L0.d.cin <= 128 ? C_C3PW_HIGH : C_C3PW_HIGH_256;
-    if (g.kind == GK_GROUP) high = std::max<int64_t>(0, C_FUSED_HIGH - g.ga.nstages * C_FUSED_HIGH_LAYER);
     std::vector<StageSpec> specs;
     std::string why;
     int kind;
     if (!group_stages(net, g.first, g.last, specs, kind, why) || specs.size() < 2) return g.cost;
-    for (const StageSpec& s : specs)
-        if (g.kind == GK_GROUP && std::max(net.L[s.layer].d.cin, net.L[s.layer].d.cout) > 64) return g.cost;
-    uint64_t sum = 0;
+    int most = 0;
+    bool c3 = true;
+    for (const StageSpec& s : specs) {
+        const dlf_layer_desc& d = net.L[s.layer].d;
+        most = std::max(most, (int)std::max(d.cin, d.cout));
+        c3 = c3 && d.op == DLF_CONV && d.kw == 3 && d.kh == 3 && d.stride == 1 && !s.pool2;
+    }
+    const bool wide = g.kind == GK_GROUP && most > 64;
+    if (wide && (most > 128 || !c3)) return g.cost;
+    if (g.kind == GK_GROUP)
+        high = wide ? C_FUSED_HIGH_128 + g.ga.nstages * C_FUSED_HIGH_128_LAYER
+                    : std::max<int64_t>(0, C_FUSED_HIGH - g.ga.nstages * C_FUSED_HIGH_LAYER);
+    uint64_t sum = 0, fair = 0;
     bool newer = false;
     for (const StageSpec& s : specs) {
         const OneLayer& one = one_layer(net, batch, s.layer, s.pool2 ? s.pool_layer : s.layer, budget, max_lds, known);
         if (one.status != DLF_OK) return g.cost;
+        if (wide && one.plan.kind != GK_SKC) return g.cost;
         newer = newer || one.plan.kind == GK_SKC || one.plan.kind == GK_C3R;
         sum += one.plan.cost;
         if (sum >= g.cost) return g.cost;
+        const bool few = one.plan.kind == GK_SKC && one.plan.variant == 3 && c3 && one.plan.grid > SKC_FEW_ITEMS && one.plan.grid <= budget;
+        fair += few ? (uint64_t)((C_LAUNCH + C_SKC_FAIR + one.plan.sk.nk * C_SKC_FAIR_STEP) * PS_PER_CYCLE) : one.plan.cost;
     }
-    return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)sum ? sum : g.cost;
+    return newer && (int64_t)g.cost - high * PS_PER_CYCLE <= (int64_t)fair ? sum : g.cost;
 }
 
 // The group on the split-K kernel for a depthwise layer and the 1x1 layer behind it, or on the one for a single convolution, where

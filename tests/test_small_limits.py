@@ -267,3 +267,30 @@ def test_depthwise_layers_have_no_step_in_their_price():
         h, groups = _default_plan(nets.mobilenet_v1(hw), batch)
         assert {(13, 14), (15, 16), (17, 18), (19, 20), (21, 22)} <= {g[:2] for g in groups}, (hw, batch, groups)
         B.dlf_net_destroy(h)
+
+
+@pytest.mark.parametrize("c,hw,batch,depth", [
+    (64, 27, 8, 4),      # 19.4 us as one launch, 23.4 as four
+    (64, 29, 5, 4),
+    (32, 69, 1, 2),      # 9.8, 10.8
+    (96, 28, 4, 3),      # 16.9, 19.4
+    (96, 28, 3, 4),      # 22.9, 25.9
+    (128, 28, 3, 4),     # 27.6, 29.7
+    (128, 28, 4, 3),     # 19.0, 22.0
+])
+def test_chains_above_128_items_keep_one_launch(c, hw, batch, depth):
+    h, groups = _default_plan(nets.identical_chain(c, hw, depth), batch)
+    assert [g[:2] for g in groups] == [(0, depth - 1)], groups
+    B.dlf_net_destroy(h)
+
+
+@pytest.mark.parametrize("c,hw,batch,depth", [
+    (96, 28, 4, 2),      # 13.0 us as two launches, 13.3 as one
+    (128, 28, 4, 2),     # 15.0, 15.7
+    (192, 28, 3, 4),     # 37.6, 47.1
+    (64, 28, 3, 4),      # 17.4, 18.6
+])
+def test_chains_that_are_faster_layer_by_layer_are_not_fused(c, hw, batch, depth):
+    h, groups = _default_plan(nets.identical_chain(c, hw, depth), batch)
+    assert [g[:2] for g in groups] == [(i, i) for i in range(depth)], groups
+    B.dlf_net_destroy(h)
