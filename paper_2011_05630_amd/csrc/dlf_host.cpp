@@ -351,12 +351,12 @@ const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
 const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
 
 // depthwise + 1x1 pair for outputs of few pixels: a whole launch of one item per CU (at least; by shape; per 32-channel step
-// of K), and what a further item per CU adds.  Fitted to MobileNet-v1's nine pairs at batch 1, 2 and 4 in chains of six.
+// of K), and what a further item per CU adds.  Fitted to pairs of 128 - 1024 channels at batch 1 and 2 in chains of six.
 const int64_t C_SKD_LEAST = 10800;
-const int64_t C_SKD_ITEM[DLF_SKD_SHAPES] = {7000, 7800};
-const int64_t C_SKD_STEP = 565;
+const int64_t C_SKD_ITEM[DLF_SKD_SHAPES] = {8500, 9100};
+const int64_t C_SKD_STEP = 237;
 const int64_t C_SKD_ROUND = 700;
-const int64_t C_SKD_ROUND_STEP = 700;
+const int64_t C_SKD_ROUND_STEP = 205;
 // ... and on the same pairs the other depthwise kernels in launches that leave places free (C_LAUNCH holds most of
 // such a launch's round trips; in per cent): the tile kernel with one tile per CU at most (5.0 - 7.4 us, 11 - 14
 // without this; from 5 MiB on it is slower), the small-map kernel with one item per CU at most: 256 / 512 / 1024 channels 7.4 - 9.2 /
@@ -1748,9 +1748,9 @@ void skd_fill(const Layer& D, const Layer& P, int batch, int shape, int waves, D
     sd.m = batch * D.out_h * D.out_w;
     sd.n_pg = ceil_div(sd.m, 16);
     sd.n_cg = ceil_div(P.d.cout, 16 * SKD_TC[shape]);
-    // two waves, four from 8 steps on (measured at 1, 2 and 4: 256 channels 8.2 / 6.2 / 6.1 us, 512 11.8 / 8.4 / 7.5, 1024
-    // 20.5 / 12.6 / 11.7; at 128 channels 7.3 / 7.6 / 9.3)
-    sd.nw = waves > 0 ? std::min(waves, DLF_SKD_MAX_WAVES) : sd.nk >= 8 ? 4 : 2;
+    // two waves, four from 8 steps on, eight from 32 on (measured at 2, 4 and 8 waves, the better item shape: 256 channels 5.7 / 5.1 /
+    // 5.7 us, 512 7.7 / 5.7 / 5.9, 1024 12.2 / 8.5 / 7.2)
+    sd.nw = waves > 0 ? std::min(waves, DLF_SKD_MAX_WAVES) : sd.nk >= 32 ? 8 : sd.nk >= 8 ? 4 : 2;
     while (sd.nw > 1 && sd.nw / 2 >= sd.nk) sd.nw /= 2;
     sd.ksw = ceil_div(sd.nk, sd.nw);
     auto magic = [](int d) { return 0xFFFFFFFFu / (unsigned)d + 1u; };
@@ -3012,7 +3012,7 @@ void dlf_debug_small_mode(int32_t mode, int32_t shape, int32_t waves)
 void dlf_debug_small_pair_mode(int32_t mode, int32_t shape, int32_t waves)
 {
     g_skd_force = SkcForce{(mode >= 0 && mode <= 2) ? mode : 0, shape < DLF_SKD_SHAPES ? shape : -1,
-                           waves == 1 || waves == 2 || waves == 4 ? waves : 0};
+                           waves == 1 || waves == 2 || waves == 4 || waves == 8 ? waves : 0};
 }
 
 void dlf_debug_force_ksplit(int32_t ksplit) { g_force.ksplit = ksplit > 0 ? ksplit : 1; }

@@ -410,9 +410,9 @@ struct DlfSkcArgs {
 // A depthwise 3x3 layer and the 1x1 layer behind it for outputs of few pixels (k_skd): a workgroup of `nw` waves
 // computes 16 pixels x 16 * TC channels, each wave over its own share of the depthwise layer's channels.
 #define DLF_SKD_SHAPES 2             // TC = 2, 4
-#define DLF_SKD_MAX_WAVES 4
-// partial sums, and each wave's depthwise weights and biases (9 halfs and a float per channel of its share)
-#define DLF_SKD_LDS_BYTES(NW, C, KSW) ((NW) * (16 * (C) * 4 + (KSW) * 32 * 22))
+#define DLF_SKD_MAX_WAVES 8
+// partial sums, each wave's depthwise weights and biases (9 halfs and a float per channel of its share), its turning space
+#define DLF_SKD_LDS_BYTES(NW, C, KSW) ((NW) * (16 * (C) * 4 + (KSW) * 32 * 22 + 1024))
 struct DlfSkdArgs {
     const void* in;       // [batch][h][w][c] fp16
     void* out;            // [batch][oh][ow][cout] fp16
@@ -425,7 +425,7 @@ struct DlfSkdArgs {
     int32_t cout, ncb, nk;          // nk: 32-channel steps = c / 32
     int32_t m;            // output pixels = batch * oh * ow
     int32_t n_pg, n_cg;   // groups of 16 pixels, of 16 * TC channels
-    int32_t nw, ksw;      // waves per workgroup (1, 2 or 4), steps per wave
+    int32_t nw, ksw;      // waves per workgroup (1, 2, 4 or 8), steps per wave
     uint32_t n_cg_m, ow_m, oh_m;    // reciprocals for division by n_cg, ow, oh
 };
 

@@ -4656,15 +4656,17 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
 // A depthwise 3x3 layer (pad 1, stride 1 or 2) and the 1x1 layer behind it for outputs of few pixels: the pairs of
 // MobileNet-style networks at small batch, which k_dwt / k_dws need more pixels for.
 // Built as k_skc: work item = 16 pixels x 16 * TC channels of the 1x1 layer, K -- the depthwise layer's channels -- dealt to
-// the waves in shares of 32-channel steps, partial sums in LDS.  In a step a lane computes the depthwise result of its pixel
+// the waves in shares of 32-channel steps, partial sums in LDS.  In a step a lane computes the depthwise result of a pixel
 // and 8 channels in registers (nine 16-byte loads through a buffer resource whose range check supplies the padding, the
-// order of sums and the rounding of k_dw): that is the MFMA "B" operand as it stands.  Every channel group computes it
-// again: 72 multiply-adds a step.  What bounds an item is the CU's vector-memory path, (9 + TC) KiB a step; the depthwise
-// weights and biases of a share go through LDS (fetched per step they were 11 KiB more: 512 -> 512 channels at 14 x 14 8.3 ->
-// 7.5 us).  Operands of step s + 1 are requested ahead of the arithmetic of step s; three or four steps at a time is slower
-// (8.5 us: requests beyond a share cost the path what real ones do).
-// Batch 1 against the faster of k_dwt and k_dws: 256 -> 256 at 28 x 28 7.3 -> 6.1 us, 256 -> 512 stride 2 8.6 -> 5.6, 512 -> 512 at
-// 14 x 14 10.6 -> 7.5, 512 -> 1024 stride 2 13.5 -> 7.4; on the maps in front k_dwt is ahead (128 at 56 x 56: 5.2 against 6.6).
+// order of sums and the rounding of k_dw).  Every channel group computes it again: 72 multiply-adds a step.
+// The lanes load and filter as memory lies, four consecutive lanes a pixel's 64 bytes, and the result turns to the MFMA "B"
+// operand's order (sixteen consecutive lanes sixteen pixels) through 1 KiB of LDS of the wave.  Loaded in the operand's order four
+// consecutive lanes touch four cache lines, which the CU's vector-memory path takes at 16 bytes per cycle instead of 45 (61 with
+// eight waves), and that path is what bounds an item, (9 + TC) KiB a step: 512 -> 512 channels at 14 x 14 7.5 -> 5.7 us,
+// 1024 -> 1024 at 7 x 7 11.7 -> 8.5 and with eight waves 7.2 (as two launches 8.6), 256 -> 256 at 28 x 28 6.0 -> 5.1.
+// The depthwise weights and biases of a share go through LDS: fetched per step they were 11 KiB more.  Operands of step s + 1 are
+// requested ahead of the arithmetic of step s; three or four steps at a time is slower (requests beyond a share cost the path
+// what real ones do).  On the maps in front k_dwt is level (128 at 56 x 56: 5.0 us).
 template <int TC>
 __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs a)
 {
@@ -4696,7 +4698,7 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
         // the lane's pixel: byte offsets of its nine taps' 16 bytes of the first step, or out of range
         int voff[9];
         {
-            const int px = pg * P + r16;
+            const int px = pg * P + (lane >> 2);
             const int row = div_by(px, a.ow_m), n = div_by(row, a.oh_m);
             const int ox = px - row * a.ow, oy = row - n * a.oh;
             const int iy = oy * a.stride - 1, ix = ox * a.stride - 1;
@@ -4704,7 +4706,7 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
             for (int t = 0; t < 9; ++t) {
                 const int y = iy + t / 3, x = ix + t % 3;
                 const bool ok = px < a.m && y >= 0 && y < a.h && x >= 0 && x < a.w_;
-                voff[t] = ok ? ((n * a.h + y) * a.w_ + x) * a.c * 2 + q * 16 : DLF_OOB;
+                voff[t] = ok ? ((n * a.h + y) * a.w_ + x) * a.c * 2 + (lane & 3) * 16 : DLF_OOB;
             }
         }
         const unsigned lo_d = act_lo(a.act_dw), hi_d = act_hi(a.act_dw);
@@ -4713,6 +4715,8 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
         // the share's depthwise weights [tap][channel] and biases, in the wave's own part of LDS: a vector of them serves
         // sixteen pixels, and requested per step the eleven would take more of the CU's path than the inputs
         half_t* const wl = (half_t*)(part + a.nw * (P * C)) + wave * (a.ksw * 32 * 11);
+        // the wave's 1 KiB between the two lane orders: 64 bytes per pixel, part g of pixel p at g ^ (p / 4) % 4 (no bank conflicts)
+        char* const turn = (char*)((half_t*)(part + a.nw * (P * C)) + a.nw * (a.ksw * 32 * 11)) + wave * 1024;
         const int row = a.ksw * 4, nparts = 9 * row, n = nparts + 2 * row;
         const unsigned row_m = div_magic(row);
         auto weight = [&](int i) __attribute__((always_inline)) {      // 16-byte part i: nine rows of weights, two of biases
@@ -4735,8 +4739,8 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
                 A[d][c] = __builtin_bit_cast(h8, raw_buffer_load_x4(rwp, ok ? aoff[c] : DLF_OOB, (int)((cb[c] * (unsigned)a.nk + (unsigned)s) * 2048u), 0));
         };
         auto multiply = [&](int s, int d) __attribute__((always_inline)) {
-            const half_t* const ws = wl + (s - k0) * 32 + q * 8;
-            const float* const bs = (const float*)(wl + 9 * a.ksw * 32) + (s - k0) * 32 + q * 8;
+            const half_t* const ws = wl + (s - k0) * 32 + (lane & 3) * 8;
+            const float* const bs = (const float*)(wl + 9 * a.ksw * 32) + (s - k0) * 32 + (lane & 3) * 8;
             const f4v b0 = *(const f4v*)bs, b1 = *(const f4v*)(bs + 4);
             float v[8];
 #pragma unroll
@@ -4748,9 +4752,12 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
             hv.y = pk_min(pk_max(cvt_pk(v[2], v[3]), lo_d), hi_d);
             hv.z = pk_min(pk_max(cvt_pk(v[4], v[5]), lo_d), hi_d);
             hv.w = pk_min(pk_max(cvt_pk(v[6], v[7]), lo_d), hi_d);
+            // to the lanes that multiply it
+            *(u4v*)(turn + (lane >> 2) * 64 + ((lane ^ (lane >> 4)) & 3) * 16) = hv;
+            __builtin_amdgcn_wave_barrier();
+            const h8 bf = *(const h8*)(turn + r16 * 64 + ((q ^ (r16 >> 2)) & 3) * 16);
 #pragma unroll
-            for (int c = 0; c < TC; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], __builtin_bit_cast(h8, hv), acc[c], 0, 0, 0);
+            for (int c = 0; c < TC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], bf, acc[c], 0, 0, 0);
         };
         request(k0, 0);
 #pragma unroll
