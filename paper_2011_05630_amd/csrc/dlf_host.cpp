@@ -340,14 +340,19 @@ const int64_t C_BN_CHANNEL = 150;
 const int64_t C_BN_LAST = 5000;              // ... less without the last layer
 const int64_t C3PW_OVERLAP_PCT = 60;         // two workgroups per CU: what a further round of items adds, in per cent of an item
 
-// split-K convolution kernel: a launch of one round trip, then the rate at which a CU takes operands in
-// (49 bytes per cycle for a workgroup alone on its CU, 34 if it gathers 32 pixels; several share the
-// first-level cache and its path to L2 and get 28 or 25 together).  Fitted to 10 layer shapes at batch 1, 2 and 4 in chains of 12 layers.
+// split-K convolution kernel: a launch of one round trip, then the rate at which a CU takes operands in (52 to 70 bytes per cycle
+// for a workgroup alone on its CU, fitted to 22 layer shapes in chains of 8 layers, within 6 % but for 1x1 layers of 64 K steps, 13 %
+// high).  Launches of several items per CU are priced as before the activations came in by whole lines: the kernels they compete
+// with are priced high there, and what the rates below give them is what kept the choices right.
 // The residual operand: measured 0.02 - 0.12 us (64 - 512 channels, 7 x 7 to 56 x 56).
-const int64_t C_SKC_ITEM = -900;
+const int64_t C_SKC_ITEM[DLF_SKC_SHAPES] = {-1750, -1800, -2400, 1000};
+const int64_t C_SKC_LOAD[DLF_SKC_SHAPES] = {0, 0, 15, 0};       // ... and per item of the launch (256 channels: 52 items 6.1 us, 196 6.9)
+const int64_t C_SKC_MANY = -900;             // ... more than one item per CU
 const int64_t C_SKC_RES = 150;
 const int64_t SKC_FEW_ITEMS = 128;
-const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
+const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {52, 60, 65, 62};
+const int64_t SKC_BYTES_PER_CYCLE_8 = 70;    // eight waves
+const int64_t SKC_MANY_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
 const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
 
 // depthwise + 1x1 pair for outputs of few pixels: a whole launch of one item per CU (at least; by shape; per 32-channel step
@@ -1667,10 +1672,10 @@ void skc_fill(const Layer& L, const Layer* proj, int pool2, int batch, int shape
     sk.m = batch * L.out_h * L.out_w;
     sk.n_pg = ceil_div(sk.m, 16 * SKC_TP[shape]);
     sk.n_cg = ceil_div(L.d.cout, 16 * SKC_TC[shape]);
-    // Waves per workgroup: four, two for short K (measured at 1, 2, 4, 8: K of 8 or 16 steps 0.2 us
-    // faster on two waves than on four, 64 steps and more 0.5 - 2 us slower; eight never pay: the
-    // operands' path into the CU is the limit, not the number of loads in flight).
-    sk.nw = waves > 0 ? waves : sk.nk + sk.nk2 <= 16 ? 2 : 4;
+    // Waves per workgroup: four, two for short K (K of 8 or 16 steps 0.2 us faster on two waves than on four, 64 steps and more
+    // 0.5 - 2 us slower), eight for the smallest items from 64 steps on (256 channels 3x3 4.66 -> 4.42 us, 512 5.97 -> 5.40; the
+    // larger items' operands fill the CU's path with four: 256 channels at 16 x 32 4.96 and 5.33 us).
+    sk.nw = waves > 0 ? waves : sk.nk + sk.nk2 <= 16 ? 2 : shape == 0 && sk.nk + sk.nk2 >= 64 ? 8 : 4;
     while (sk.nw > 1 && sk.nw / 2 >= sk.nk + sk.nk2) sk.nw /= 2;
     sk.ksw = ceil_div(sk.nk + sk.nk2, sk.nw);
     sk.pw = pool2 ? L.out_w / 2 : L.out_w;
@@ -1685,7 +1690,7 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
     const int64_t items = (int64_t)sk.n_pg * sk.n_cg;
     const int64_t has_res = L.d.residual_from >= 0 && !proj ? 1 : 0;
     const int64_t bytes = (int64_t)(sk.nk + sk.nk2) * (SKC_TP[shape] + SKC_TC[shape]) * 1024;
-    int64_t intake = bytes / SKC_BYTES_PER_CYCLE[shape];
+    int64_t intake = items > budget ? bytes / SKC_MANY_BYTES_PER_CYCLE[shape] : bytes / (sk.nw == 8 ? SKC_BYTES_PER_CYCLE_8 : SKC_BYTES_PER_CYCLE[shape]);
     // the taps of a 3x3 filter meet in the first-level cache, a long 1x1 row does not (2048 channels, 240 items: 12 us)
     if (shape == 3 && sk.kh * sk.kw == 1 && items > SKC_FEW_ITEMS) intake = bytes / SKC_SHARED_BYTES_PER_CYCLE[shape];
     if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
@@ -1695,7 +1700,7 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
     int64_t hbm = in * L.d.cin * 2 + (sk.pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
     if (proj) hbm += m * proj->d.cin * 2 + (int64_t)proj->ncb * proj->nsteps * 1024;
     const int64_t mem = hbm / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
-    int64_t cycles = C_LAUNCH + C_SKC_ITEM + std::max(intake + has_res * C_SKC_RES, mem);
+    int64_t cycles = C_LAUNCH + (items > budget ? C_SKC_MANY : C_SKC_ITEM[shape] + items * C_SKC_LOAD[shape]) + std::max(intake + has_res * C_SKC_RES, mem);
     // 32 pixels x 64 channels on nearly every CU: 15 - 20 % above the fit (64 -> 64 3x3 at 32 x 32, batch 7, 224 items: 6.2 us, not 5.3)
     if (shape == 3 && items <= budget && items * 4 > (int64_t)budget * 3) cycles = cycles * 5 / 4;
     // The kernel is for launches of at most about one item per CU.  Beyond that the models of the
@@ -1705,7 +1710,7 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
     return (uint64_t)(cycles * PS_PER_CYCLE);
 }
 
-int skc_lds_bytes(const DlfSkcArgs& sk, int shape) { return sk.nw * SKC_TP[shape] * SKC_TC[shape] * 1024; }
+int skc_lds_bytes(const DlfSkcArgs& sk, int shape) { return sk.nw * DLF_SKC_WAVE_BYTES(SKC_TP[shape], SKC_TC[shape]); }
 
 bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int budget, int max_lds, const SkcForce& force,
                 DlfSkcArgs& best, int& shape, uint64_t& cost)
@@ -2266,7 +2271,7 @@ const int64_t C_FUSED_HIGH = 17500;
 const int64_t C_FUSED_HIGH_LAYER = 2500;
 const int64_t C_FUSED_HIGH_128 = 11000;
 const int64_t C_FUSED_HIGH_128_LAYER = 800;
-const int64_t C_C3PW_HIGH = 10000;
+const int64_t C_C3PW_HIGH = 11500;
 const int64_t C_C3PW_HIGH_256 = 2000;
 // ... and what a 3x3 layer on the split-K kernel's items of 32 pixels x 64 channels takes, above SKC_FEW_ITEMS, by K steps: 5.3 - 5.4 /
 // 5.9 - 6.1 / 6.4 - 6.6 / 7.3 - 7.5 us with 9 / 18 / 27 / 36, 4.5 / 5.3 / 6.0 - 7.5 / 6.8 - 8.5 modelled.

@@ -386,6 +386,8 @@ struct DlfBnArgs {
 // flight; the partial sums meet in LDS.
 #define DLF_SKC_SHAPES 4             // (TP, TC): 0 = (1, 1), 1 = (1, 2), 2 = (1, 4), 3 = (2, 4)
 #define DLF_SKC_MAX_TAPS 25
+// LDS of a wave: its ring of activations (four steps) or its partial sums, whichever is larger
+#define DLF_SKC_WAVE_BYTES(TP, TC) ((TP) * 4096 > (TP) * (TC) * 1024 ? (TP) * 4096 : (TP) * (TC) * 1024)
 struct DlfSkcArgs {
     const void* in;       // [batch][h][w][cin] fp16
     const void* in2;      // second operand pair: [batch][h2][w2][cin2] fp16, or null

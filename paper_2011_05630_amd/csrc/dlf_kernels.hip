@@ -4482,25 +4482,29 @@ __global__ __launch_bounds__(256) void k_fc_fin(const DlfFcArgs a)
 // batch 1: 16 workgroups, 8.3 us; 1024 -> 256 1x1: 16 workgroups, 8.5 us; a launch that reads and writes
 // one value takes 4.1).
 //
-// Work item = 16 * TP pixels x 16 * TC channels, one workgroup of up to four waves, an item per CU where the
+// Work item = 16 * TP pixels x 16 * TC channels, one workgroup of up to eight waves, an item per CU where the
 // layer has that many; K is dealt to the waves in contiguous shares of 32-channel steps, each wave keeps D
-// steps' operands in flight, and the partial sums meet in LDS.  No operand passes through LDS: the waves
-// share none.  What bounds an item is the CU's vector-memory path: it takes in (TP + TC) KiB per step at
-// 49 bytes per cycle of 2.15 GHz (of the path's 64), so the planner prices the shapes by that.  Deeper
-// rings (up to 18 steps) and 8 or 16 waves were measured and are slower: the loads beyond a share cost
-// issue slots though they fetch nothing, a workgroup of 16 waves takes 0.5 us longer to start, and streaming
-// hints on the weights cost 0.3 - 2 us (the second item of an XCD finds them in its L2).
-// Measured at batch 1 (us per layer in a chain of 12, before -> after): 256 -> 256 3x3 at 14 x 14 8.3 -> 5.4;
-// 512 -> 512 3x3 at 7 x 7 11.6 -> 7.2, at 14 x 14 11.4 -> 8.4; 128 -> 128 3x3 at 28 x 28 8.7 -> 4.7; 1x1 pairs
-// 256 -> 1024 -> 256 at 14 x 14 6.6 -> 4.1, 512 -> 2048 -> 512 at 7 x 7 6.8 -> 4.5.
+// steps' operands in flight, and the partial sums meet in LDS.  The waves share no operand.  What bounds an item is the CU's
+// vector-memory path, (TP + TC) KiB per step; it takes in 52 - 65 bytes per cycle, 70 with eight waves, and the planner prices the
+// shapes by that.  For that rate four consecutive lanes have to fetch a pixel's 64 bytes: the "B" operand's own order, sixteen
+// consecutive lanes sixteen pixels, touches a cache line per lane and passes at 16 bytes per cycle.  So the activations come in
+// by direct loads into a ring in the wave's LDS and are read from there in the operand's order (weights, runs of 256 bytes, go to
+// registers).  Deeper rings are slower (four steps instead of three at 64 channels: 6.5 -> 6.9 us on K of 36 and 72 steps): the
+// loads beyond a share cost issue slots though they fetch nothing; so are eight waves for the larger items.
+// Measured at batch 1 (us per layer in chains; as 16 loads of 64 bytes in the operand's order -> now): 256 -> 256 3x3 at 14 x 14
+// 5.4 -> 4.4; 512 -> 512 3x3 at 7 x 7 7.2 -> 5.4, at 14 x 14 8.4 -> 6.8; 128 -> 128 3x3 at 28 x 28 4.7 -> 4.2; 1x1 pairs
+// 256 -> 1024 -> 256 at 14 x 14 4.1 -> 3.7, 512 -> 2048 -> 512 at 7 x 7 4.5 -> 3.8.  A launch that reads and writes one value
+// takes 3.4 - 4.
 //
 // v_mfma_f32_16x16x32_f16: its "A" operand is half of the rows of two consecutive packed 32-channel
-// fragments (runs of 256 bytes), its "B" operand 64 contiguous bytes of each of 16 pixels, gathered
+// fragments (runs of 256 bytes), its "B" operand 64 contiguous bytes of each of 16 pixels, requested
 // through a buffer resource whose range check supplies the padding.
 template <int TP, int TC, int D, bool P2>
 __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
 {
     constexpr int P = 16 * TP, C = 16 * TC;
+    constexpr int WB = DLF_SKC_WAVE_BYTES(TP, TC);       // a wave's LDS: its ring of "B" operands, then its partial sums
+    static_assert(D * TP * 1024 <= WB && P * C * 4 <= WB, "a wave's LDS");
     float* const part = (float*)lds;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4;
@@ -4525,13 +4529,11 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
         for (int p = 0; p < TP; ++p) acc[c][p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 
     if (k0 < k1) {
-        const i32x4 rin = make_rsrc(a.in, a.in_bytes);
+        const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc((void*)a.in, 0, (int)a.in_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rin2 = __builtin_amdgcn_make_buffer_rsrc((void*)(P2 ? a.in2 : a.in), 0, (int)(P2 ? a.in2_bytes : a.in_bytes), 0x00020000);
         const i32x4 rw = make_rsrc(a.w, (unsigned)a.ncb * (unsigned)a.nk * 2048u);
-        i32x4 rin2 = rin, rw2 = rw;
-        if (P2) {
-            rin2 = make_rsrc(a.in2, a.in2_bytes);
-            rw2 = make_rsrc(a.w2, (unsigned)a.ncb * (unsigned)a.nk2 * 2048u);
-        }
+        i32x4 rw2 = rw;
+        if (P2) rw2 = make_rsrc(a.w2, (unsigned)a.ncb * (unsigned)a.nk2 * 2048u);
         // "A": 16 channels = half a 32-channel block; lane (row r16, K quarter q)
         int aoff[TC];
         unsigned cb[TC];
@@ -4541,26 +4543,31 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
             cb[c] = (unsigned)min(sc >> 1, a.ncb - 1);
             aoff[c] = (q >> 1) * 1024 + ((q & 1) * 32 + (sc & 1) * 16 + r16) * 16;
         }
-        // "B": the lane's pixel: byte offset of its first tap, a bit per tap inside the image
+        // "B" comes in as memory lies, four consecutive lanes a pixel's 64 bytes, part g of pixel p to the place g ^ (p / 4) % 4
+        // of its 64 bytes in LDS (the reads' sixteen pixels fall into different banks); the pixel the lane fetches from: byte offset of
+        // its first tap, a bit per tap inside the image
+        const int part16 = ((lane ^ (lane >> 4)) & 3) * 16;
         int boff[TP], boff2[TP];
         unsigned mask[TP];
 #pragma unroll
         for (int p = 0; p < TP; ++p) {
-            const int pi = pg * P + p * 16 + r16;
+            const int pi = pg * P + p * 16 + (lane >> 2);
             const int px = a.pool2 ? pi >> 2 : pi;
             const int row = div_by(px, a.pw_m), n = div_by(row, a.ph_m);
             int ox = px - row * a.pw, oy = row - n * a.ph;
             if (a.pool2) { oy = 2 * oy + ((pi >> 1) & 1); ox = 2 * ox + (pi & 1); }
             const int iy = oy * a.stride - a.pad, ix = ox * a.stride - a.pad;
-            boff[p] = ((n * a.h + iy) * a.w_ + ix) * a.cin * 2 + q * 16;
+            boff[p] = ((n * a.h + iy) * a.w_ + ix) * a.cin * 2 + part16;
             unsigned cols = 0, mk = 0;
             for (int t = 0; t < a.kw; ++t) cols |= (unsigned)(ix + t >= 0 && ix + t < a.w_) << t;
             for (int t = 0; t < a.kh; ++t) mk |= (iy + t >= 0 && iy + t < a.h) ? cols << (t * a.kw) : 0u;
             mask[p] = pi < a.m ? mk : 0u;
             boff2[p] = 0;
-            if (P2) boff2[p] = pi < a.m ? ((n * a.h2 + oy * a.stride2) * a.w2_ + ox * a.stride2) * a.cin2 * 2 + q * 16 : DLF_OOB;
+            if (P2) boff2[p] = pi < a.m ? ((n * a.h2 + oy * a.stride2) * a.w2_ + ox * a.stride2) * a.cin2 * 2 + part16 : DLF_OOB;
         }
-        h8 A[D][TC], B[D][TP];
+        h8 A[D][TC];
+        half_t* const ring = lds + wave * (WB / 2);
+        const unsigned from = (unsigned)(wave * WB + r16 * 64 + ((q ^ (r16 >> 2)) & 3) * 16);
         // The requests of a wave run through its share of K in order; what names the next one is
         // kept as running scalars: the step, its tap, the tap's column, the tap's byte offset, the
         // chunk's.  (Finding them by division cost two dozen scalar instructions and four branches a step.)
@@ -4578,51 +4585,50 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
         auto request = [&](int d) __attribute__((always_inline)) {
             const bool ok = s_ < k1, second = P2 && s_ >= a.nk;
             const int s1 = second ? s_ - a.nk : s_;
+            const unsigned bit = ok ? 1u << tap : 0u;
+            // (the activations first: when the step's weights are there, so are they)
+#pragma unroll
+            for (int p = 0; p < TP; ++p) {
+                const int b1 = (mask[p] & bit) ? boff[p] + toff : DLF_OOB;
+                if (P2 && second) dma16b(rin2, ring + (d * TP + p) * 512, (unsigned)(ok ? boff2[p] : DLF_OOB), s1 * 64);
+                else dma16b(rin, ring + (d * TP + p) * 512, (unsigned)b1, coff);
+            }
             const i32x4 rwx = second ? rw2 : rw;
 #pragma unroll
             for (int c = 0; c < TC; ++c)
                 A[d][c] = __builtin_bit_cast(h8, raw_buffer_load_x4(rwx, ok ? aoff[c] : DLF_OOB,
                                                                     (int)((cb[c] * (unsigned)(second ? a.nk2 : a.nk) + (unsigned)s1) * 2048u), 0));
-            if (P2) {
-                const i32x4 rinx = second ? rin2 : rin;
-                const unsigned bit = ok ? 1u << tap : 0u;
-#pragma unroll
-                for (int p = 0; p < TP; ++p) {
-                    const int b1 = (mask[p] & bit) ? boff[p] + toff : DLF_OOB, b2 = ok ? boff2[p] : DLF_OOB;
-                    B[d][p] = __builtin_bit_cast(h8, raw_buffer_load_x4(rinx, second ? b2 : b1, second ? s1 * 64 : coff, 0));
-                }
-            } else {
-                const unsigned bit = ok ? 1u << tap : 0u;
-#pragma unroll
-                for (int p = 0; p < TP; ++p)
-                    B[d][p] = __builtin_bit_cast(h8, raw_buffer_load_x4(rin, (mask[p] & bit) ? boff[p] + toff : DLF_OOB, coff, 0));
-            }
             ++s_; ++tap; ++tx; toff += step_x;
             if (tx == a.kw) { tx = 0; toff += step_y; }
             if (tap == taps) { tap = 0; toff = 0; coff += 64; }
+            __builtin_amdgcn_sched_barrier(0);       // the requests stay in order: they are waited for by count
         };
-        auto multiply = [&](int d) __attribute__((always_inline)) {
+        // (`later`: the steps behind it that are in flight)
+        auto multiply = [&](auto dc, auto later) __attribute__((always_inline)) {
+            constexpr int d = decltype(dc)::value;
+            wait_vmcnt<decltype(later)::value * (TP + TC)>();
+            h8 B[TP];
+            static_for<0, TP>([&](auto pc) __attribute__((always_inline)) { B[decltype(pc)::value] = lds_read16<(d * TP + decltype(pc)::value) * 1024>(from); });
+            static_for<0, TP>([&](auto pc) __attribute__((always_inline)) { lds_arrive1<TP - 1 - decltype(pc)::value>(B[decltype(pc)::value]); });
 #pragma unroll
             for (int c = 0; c < TC; ++c)
 #pragma unroll
                 for (int p = 0; p < TP; ++p)
-                    acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], B[d][p], acc[c][p], 0, 0, 0);
+                    acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][c], B[p], acc[c][p], 0, 0, 0);
         };
 #pragma unroll
         for (int d = 0; d < D; ++d) request(d);
         for (int s = k0; s + D < k1; s += D) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                multiply(d);
-                request(d);
-            }
+            static_for<0, D>([&](auto dc) __attribute__((always_inline)) {
+                multiply(dc, std::integral_constant<int, D - 1>());
+                request(decltype(dc)::value);
+            });
         }
-#pragma unroll
-        for (int d = 0; d < D; ++d) multiply(d);
+        static_for<0, D>([&](auto dc) __attribute__((always_inline)) { multiply(dc, std::integral_constant<int, D - 1 - decltype(dc)::value>()); });
     }
 
     // partial sums: [wave][pixel][channel]; lane (pixel r16, channels 4q .. 4q + 3)
-    float* const mine = part + wave * (P * C);
+    float* const mine = part + wave * (WB / 4);
 #pragma unroll
     for (int c = 0; c < TC; ++c)
 #pragma unroll
@@ -4634,7 +4640,7 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
         const int rp = pg * P + e / (C / 4);
         if (a.res != nullptr && e != tid) rv = *(const u2v*)(rsrc + (size_t)min(rp, a.m - 1) * a.cout);
         f4v sum = bv;
-        for (int w = 0; w < a.nw; ++w) sum += *(const f4v*)(part + w * (P * C) + e * 4);
+        for (int w = 0; w < a.nw; ++w) sum += *(const f4v*)(part + w * (WB / 4) + e * 4);
         u2v o = {cvt_pk(sum.x, sum.y), cvt_pk(sum.z, sum.w)};
         if (a.res != nullptr) { o.x = pk_add(o.x, rv.x); o.y = pk_add(o.y, rv.y); }
         o.x = pk_min(pk_max(o.x, lo), hi);
@@ -5215,7 +5221,7 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
     static const int px[DLF_SKC_SHAPES] = {16, 16, 16, 32}, ch[DLF_SKC_SHAPES] = {16, 32, 64, 64};
     if ((int64_t)a->n_pg * a->n_cg * a->n_cg >= (int64_t)1 << 32) return (int)hipErrorInvalidValue;      // div_by of an item
     if (shape < 0 || shape >= DLF_SKC_SHAPES || (a->nw != 1 && a->nw != 2 && a->nw != 4 && a->nw != 8)) return (int)hipErrorInvalidValue;
-    launch(k[a->nk2 > 0 ? 1 : 0][shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * px[shape] * ch[shape] * 4,
+    launch(k[a->nk2 > 0 ? 1 : 0][shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * DLF_SKC_WAVE_BYTES(px[shape] / 16, ch[shape] / 16),
            (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
