@@ -191,7 +191,7 @@ def group_accounting(net, batch, session):
         elif cfg["kind"] == 6:
             kname = "k_dwpw<%d>" % cfg["variant"] if cfg["variant"] < 16 else "k_skd<%d>" % (2 << (cfg["variant"] - 16))
         elif cfg["kind"] == 7:
-            kname = "k_dwt<%d>" % (cfg["variant"] + 1)
+            kname = "k_dwt<%d>" % (cfg["variant"] + 1) if cfg["variant"] < 16 else "k_sdp<%d>" % (cfg["variant"] - 16)
         elif cfg["kind"] == 10 and cfg["variant"] in SKC_NAME:
             kname = SKC_NAME[cfg["variant"]]
         elif cfg["kind"] == 10:

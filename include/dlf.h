@@ -197,7 +197,9 @@ const void* dlf_plan_layer_output(const dlf_plan_t* plan, int32_t layer);
  * 1x1 kernel: a depthwise layer and the pointwise layer behind it, the depthwise result held in
  * registers (variant = 32-channel blocks of a wave's work item, 2 or 4; 16 and 17 the form for outputs of few
  * pixels, 16 pixels x 32 or 64 channels per workgroup, K split over its waves), 7 depthwise + 1x1 tile
- * kernel: the same pair, the depthwise result of a pixel tile held in LDS (variant = stride - 1),
+ * kernel: the same pair, the depthwise result of a pixel tile held in LDS (variant = stride - 1; 16 + n a first 3x3
+ * layer of stride 2, three channels to 32, in front of the pair, a group of three layers, n = 32-channel blocks of the 1x1 layer: 1, 2
+ * or 4),
  * 8 two 1x1 convolutions into one output (the projection shortcut of a residual block and the
  * block's last layer, variant = block form as for kind 3, or 16 .. 19 as for kind 10; the group reads two tensors, reported by
  * dlf_plan_group_io as input = the last layer's input, residual = the projection's input),

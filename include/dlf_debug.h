@@ -38,7 +38,8 @@ void dlf_debug_pointwise_mode(int32_t mode);
  * they apply (a pair: the tile kernel where its shape restrictions allow, else the register kernel),
  * 2 = never, 3 = as 1 but a pair always on the register kernel, 4 = a pair on the kernel for maps of many
  * channels and few pixels wherever that applies (channels a multiple of 256).  In mode 1 - 3 that kernel is
- * not considered.  Process-wide, not thread-safe. */
+ * not considered.  5 = by modelled cost, but a first layer with such a pair behind it on the kernel for the three wherever that
+ * applies.  Process-wide, not thread-safe. */
 void dlf_debug_depthwise_mode(int32_t mode);
 /* Testing hook: wx > 0 fixes the tile of the depthwise + 1x1 tile kernel for groups planned afterwards:
  * wx (1, 2 or 4) of its four waves side by side, each 512 / (2 * channels) pixels wide, rw output rows

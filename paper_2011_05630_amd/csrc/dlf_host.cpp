@@ -321,6 +321,13 @@ const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_STEP_ONE = 125;          // ... tiles of one pixel block
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
+const int64_t C_SDP_FIRST = 3700;            // k_sdp: a CU's first tile ...
+const int64_t C_SDP_TILE = 2500;             // ... each further one ...
+const int64_t C_SDP_BLOCK = 400;             // ... and 32 channels of its 1x1 layer
+// Fewer tiles stay on the fused-group kernel, whose group goes on behind these layers: seven of MobileNet-v1's in one launch at one
+// image, 22 us.  As this kernel and two pairs they are three launches of 17.3 us, but single images are planned for few launches
+// (at most 14 for this network, and these would make it 15).
+const int SDP_LEAST_TILES = 256;
 const int64_t C_C3S_EPI = 2500;
 // the fused 3x3 -> 1x1 kernel for small maps: per work item (decode, first loads), bytes per cycle of
 // its LDS intake, cycles per MFMA of a SIMD, per K step of the first layer's weight ring (requests
@@ -1149,6 +1156,7 @@ int c3_fill(const Layer& L, int pool2, int batch, int budget, int act, bool reg,
 // Testing hook: 0 = the streaming kernel competes with the fused-group kernel on modelled cost,
 // 1 = always where it applies, 2 = never.
 int g_dw_mode = 0;
+bool g_sdp_always = false;
 
 bool dw_eligible(const Layer& L, int batch)
 {
@@ -1236,6 +1244,65 @@ uint64_t dwpw_cost_ps(const Layer& D, const Layer& P, int batch, int budget, int
                           (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
+}
+
+// ---- a first layer of stride 2, the depthwise layer and the 1x1 layer behind it ----
+
+bool sdp_eligible(const dlf_net_s& net, int first, int last, int batch)
+{
+    if (first < 0 || last != first + 2 || last >= (int)net.L.size() || !dwpw_eligible(net, first + 1, last, batch)) return false;
+    const Layer& A = net.L[first];
+    const Layer& D = net.L[first + 1];
+    const dlf_layer_desc& d = A.d;
+    if (d.op != DLF_CONV || !A.rowfold || d.cin != 3 || d.kh != 3 || d.kw != 3 || d.stride != 2 || d.pad != 1 || d.cout != 32 || d.residual_from >= 0 ||
+        A.nsteps != 6)
+        return false;
+    if (D.src != first || D.d.stride != 1 || net.L[last].ncb > 4) return false;
+    if ((int64_t)batch * A.in_h * A.in_w * A.in_c * 2 >= (int64_t)1 << 31) return false;
+    // the first layer's output exists only on chip: nothing else may read it
+    for (size_t k = 0; k < net.L.size(); ++k) {
+        if (net.L[k].d.residual_from == first) return false;
+        if ((int)k != first + 1 && net.L[k].src == first) return false;
+    }
+    return true;
+}
+
+uint64_t sdp_cost_ps(const DlfDwtArgs& dt, int budget)
+{
+    const int64_t tiles_cu = ((int64_t)dt.ntiles + budget - 1) / budget;
+    const int64_t compute = C_SDP_FIRST + (tiles_cu - 1) * (C_SDP_TILE + DLF_SDP_BLOCKS(dt.ncb) * C_SDP_BLOCK);
+    const int64_t bytes = (int64_t)dt.in_bytes + (int64_t)dt.batch * dt.oh * dt.ow * dt.cout * 2;
+    const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
+    return (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
+}
+
+bool sdp_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds, GroupPlan& g)
+{
+    if (!sdp_eligible(net, first, last, batch)) return false;
+    const Layer& A = net.L[first];
+    const Layer& D = net.L[first + 1];
+    const Layer& P = net.L[last];
+    g = GroupPlan();
+    DlfDwtArgs& dt = g.dt;
+    memset(&dt, 0, sizeof dt);
+    dt.w0 = A.d_w; dt.b0 = A.d_bias; dt.wdw = D.d_w; dt.bdw = D.d_bias; dt.wpw = P.d_w; dt.bpw = P.d_bias;
+    dt.in_bytes = (uint32_t)((int64_t)batch * A.in_h * A.in_w * A.in_c * 2);
+    dt.batch = batch; dt.ih = A.in_h; dt.iw = A.in_w; dt.h = D.in_h; dt.w_ = D.in_w; dt.c = D.d.cin;
+    dt.oh = D.out_h; dt.ow = D.out_w; dt.stride = D.d.stride; dt.act0 = A.d.act; dt.act_dw = D.d.act; dt.act_pw = P.d.act;
+    dt.cout = P.d.cout; dt.ncb = P.ncb; dt.nsteps = P.nsteps;
+    dt.th = DLF_SDP_TH; dt.tw = DLF_SDP_TW; dt.tp = dt.th * dt.tw;
+    dt.tiles_y = ceil_div(D.out_h, dt.th); dt.tiles_x = ceil_div(D.out_w, dt.tw);
+    dt.ntiles = batch * dt.tiles_y * dt.tiles_x;
+    g.first = first; g.last = last; g.budget = budget;
+    g.in_layer = A.src;
+    g.kind = GK_DWT;
+    g.variant = 16 + DLF_SDP_BLOCKS(P.ncb);
+    g.th = dt.th; g.tw = dt.tw;
+    g.occ = DLF_SDP_PER_CU;
+    g.lds_bytes = DLF_SDP_LDS_BYTES(DLF_SDP_BLOCKS(P.ncb));
+    g.grid = std::min(round_up(dt.ntiles, 8), round_up(budget * DLF_SDP_PER_CU, 8));
+    g.cost = sdp_cost_ps(dt, budget);
+    return g.lds_bytes <= max_lds;
 }
 
 // ---- depthwise + 1x1 tile kernel ----
@@ -2400,6 +2467,14 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
     const bool named = force_tc || pw_mode > 0 || c3_force || g_force.th > 0 || g_pw_mode != 0 || g_c3_force.mode != 0 ||
                        g_c3_force.shape >= 0 || g_dw_mode != 0;
     if (named && g_skc_force.mode != 1 && g_skd_force.mode != 1) return s;
+    if (s == DLF_OK && !named && last == first + 2) {
+        GroupPlan front;
+        if (sdp_group(net, batch, first, last, budget, max_lds, front) &&
+            (g_sdp_always || (front.dt.ntiles >= SDP_LEAST_TILES && front.cost < g.cost))) {
+            g = front;
+            return s;
+        }
+    }
     OneLayers here;
     if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g, known ? *known : here);
     const SkcForce never = {2, -1, 0};
@@ -2999,7 +3074,11 @@ dlf_status dlf_plan_group_io(const dlf_plan_t* plan, int32_t g, int32_t* in_laye
 
 void dlf_debug_pointwise_mode(int32_t mode) { g_pw_mode = (mode >= 0 && mode <= 8) ? mode : 0; }
 
-void dlf_debug_depthwise_mode(int32_t mode) { g_dw_mode = (mode >= 0 && mode <= 4) ? mode : 0; }
+void dlf_debug_depthwise_mode(int32_t mode)
+{
+    g_dw_mode = (mode >= 0 && mode <= 4) ? mode : 0;
+    g_sdp_always = mode == 5;
+}
 
 void dlf_debug_depthwise_tile(int32_t wx, int32_t rw) { g_dwt_force = DwtForce{wx, rw}; }
 

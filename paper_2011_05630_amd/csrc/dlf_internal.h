@@ -238,7 +238,21 @@ struct DlfDwtArgs {
     int32_t npb;          // ceil(tp / 32) pixel blocks
     int32_t npg;          // ceil(npb / 4) groups of up to four pixel blocks
     int32_t tiles_y, tiles_x, ntiles;     // ntiles = batch * tiles_y * tiles_x
+    // with a first layer in front (k_sdp) if not null: `in` is its image [batch][ih][iw][3], in_bytes the image's size, c = 32
+    const void* w0;       // packed fragments, a filter row = two K steps of 4-channel pixels (the second holds zeros)
+    const float* b0;
+    int32_t ih, iw, act0;
 };
+
+// A first 3x3 layer of stride 2 on an image of three channels, the depthwise 3x3 layer (stride 1, 32 channels) and the 1x1
+// layer behind it (k_sdp): a workgroup of four waves per tile of 8 x 16 pixels of the last two layers' map.
+#define DLF_SDP_TH 8
+#define DLF_SDP_TW 16
+#define DLF_SDP_PATCH ((2 * DLF_SDP_TH + 5) * (2 * DLF_SDP_TW + 6))     // image pixels of a tile, four halfs each
+#define DLF_SDP_REGION 192           // 10 x 18 pixels of the first layer's map, 32 channels each, in whole blocks of 32
+#define DLF_SDP_PER_CU 4             // workgroups of a CU
+#define DLF_SDP_BLOCKS(NCB) ((NCB) > 2 ? 4 : (NCB))                    // 32-channel blocks of the 1x1 layer it is built for
+#define DLF_SDP_LDS_BYTES(NCB) (DLF_SDP_PATCH * 8 + (DLF_SDP_REGION + DLF_SDP_TH * DLF_SDP_TW) * 64 + (2 + (NCB)) * 128 + 576 + (NCB) * 2048)
 
 // Depthwise 3x3 + 1x1 convolution for maps of many channels and few pixels (channels a multiple of
 // 256), where the tile kernel above has no tile to work with: one workgroup of eight waves per work

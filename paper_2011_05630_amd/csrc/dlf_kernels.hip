@@ -3148,6 +3148,186 @@ __global__ __launch_bounds__(DLF_DWT_WAVES * 64, 2) void k_dwt(const DlfDwtArgs 
     }
 }
 
+// A first 3x3 layer of stride 2 (three channels -> 32), the depthwise 3x3 layer and the 1x1 layer behind it: the front of
+// a MobileNet, whose two tensors between the layers are the network's largest and never leave the chip here.  A workgroup of four
+// waves, persistent over tiles of 8 x 16 pixels; per tile
+//   1. the image patch, requested a tile ahead through a buffer resource whose range check supplies the padding, goes to LDS
+//      as 4-channel pixels (the fourth zero);
+//   2. first layer on the tile's 10 x 18 region: a filter row of an output pixel is four consecutive patch pixels, 16 K
+//      values, one 16-byte read per lane, as the weights are packed (the fourth pixel is masked: what it holds is not the
+//      window's); three MFMAs per 32 pixels; outside the map, where the depthwise layer pads, zeros;
+//   3. depthwise: a wave two rows of the tile, lane = (column, 8 channels), four region rows in registers, sums in k_dw's order;
+//   4. 1x1 on the wave's own 32 pixels; lanes l and l + 32 trade halves of a pixel's eight channels and store
+//      16 bytes each.
+// Region and depthwise result keep 64 bytes per pixel, part q of pixel p at q ^ (p / 4) % 4: reads and writes of 16 lanes fall into
+// different banks.  The depthwise and 1x1 weights are read from LDS: in registers (158) three workgroups share a CU, not four.
+// What bounds it: vector instructions (some 450 a wave and tile, half of them the depthwise layer's) beside the tile's chain of
+// waits; without the stores a launch of 64 images takes 32 us, without the next tile's requests 34.  Stores with the streaming hint
+// cost 60 us more (32 bytes of a pixel at a time).  224 x 224 images, cout 64: batch 64 first layer + k_dwt pair 82 -> 48 us (floor,
+// image in and result out at a copy's rate: 23).
+template <int NCB>
+__global__ __launch_bounds__(256, DLF_SDP_PER_CU) void k_sdp(const DlfDwtArgs a)
+{
+    constexpr int RW = DLF_SDP_TW + 2, NPX = (DLF_SDP_TH + 2) * RW, PW = 2 * DLF_SDP_TW + 6, NL = (DLF_SDP_PATCH + 255) / 256;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    char* const patch = (char*)lds;
+    char* const region = patch + DLF_SDP_PATCH * 8;
+    char* const mid = region + DLF_SDP_REGION * 64;
+    float* const bias = (float*)(mid + DLF_SDP_TH * DLF_SDP_TW * 64);            // the first layer's, then the 1x1 layer's
+    const unsigned lo0 = act_lo(a.act0), hi0 = act_hi(a.act0), lo_d = act_lo(a.act_dw), hi_d = act_hi(a.act_dw);
+    const unsigned lo_p = act_lo(a.act_pw), hi_p = act_hi(a.act_pw);
+    auto swz = [](int px, int part) __attribute__((always_inline)) { return px * 64 + ((part ^ (px >> 2)) & 3) * 16; };
+    if ((int)threadIdx.x < 32 * (1 + NCB))
+        bias[threadIdx.x] = threadIdx.x < 32 ? a.b0[threadIdx.x] : a.bpw[min((int)threadIdx.x - 32, a.ncb * 32 - 1)];
+    // the layers' parameters in LDS: with them in registers three workgroups fit a CU, and what bounds a tile is its chain of waits
+    float* const bias_d = bias + 32 * (1 + NCB);
+    half_t* const wd = (half_t*)(bias_d + 32);
+    h8* const wp = (h8*)(wd + 9 * 32);
+    if (threadIdx.x < 32) bias_d[threadIdx.x] = a.bdw[threadIdx.x];
+    if (threadIdx.x < 36) *(u4v*)(wd + threadIdx.x * 8) = *(const u4v*)((const half_t*)a.wdw + threadIdx.x * 8);
+    for (int v = threadIdx.x; v < NCB * 128; v += 256) wp[v] = *((const h8*)a.wpw + min(v, a.ncb * 128 - 128 + (v & 127)));
+    h8 w0[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) w0[r] = *((const h8*)a.w0 + r * 128 + lane);
+    const int col = lane >> 2, g = lane & 3;
+    const unsigned keep = lhi ? 0u : 0xFFFFFFFFu;    // the second half of a filter row's K values: three pixels, then none
+
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc((void*)a.in, 0, (int)a.in_bytes, 0x00020000);
+    unsigned px[NL][3];
+    auto locate = [&](int t, int& n, int& ty0, int& tx0) __attribute__((always_inline)) {
+        const int tx = t % a.tiles_x;
+        t /= a.tiles_x;
+        ty0 = t % a.tiles_y * DLF_SDP_TH;
+        n = t / a.tiles_y;
+        tx0 = tx * DLF_SDP_TW;
+    };
+    int row[NL], at[NL];                             // the lane's patch pixels: row and column, and their offset in pixels
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+        const int v = (int)threadIdx.x + u * 256;
+        row[u] = v < DLF_SDP_PATCH ? (v / PW) | (v % PW) << 16 : 1 << 14;          // (none: a row no image has)
+        at[u] = v / PW * a.iw + v % PW;
+    }
+    auto request = [&](int t) __attribute__((always_inline)) {
+        int n, ty0, tx0;
+        locate(t, n, ty0, tx0);
+        const int gy0 = 2 * ty0 - 3, gx0 = 2 * tx0 - 3, at0 = (n * a.ih + gy0) * a.iw + gx0;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const bool ok = (unsigned)(gy0 + (row[u] & 0xffff)) < (unsigned)a.ih && (unsigned)(gx0 + (row[u] >> 16)) < (unsigned)a.iw;
+            const unsigned off = ok ? (unsigned)(at0 + at[u]) * 6u : (unsigned)DLF_OOB;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) px[u][c] = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rin, (int)off + c * 2, 0, 0);
+        }
+    };
+    // (work item i goes to XCD i % 8, a contiguous eighth of the tiles each: see k_dwt)
+    const int per_xcd = (a.ntiles + 7) >> 3;
+    int i = blockIdx.x;
+    auto tile_of = [&](int k) __attribute__((always_inline)) { return (k & 7) * per_xcd + (k >> 3); };
+    if (i < 8 * per_xcd && tile_of(i) < a.ntiles) request(tile_of(i));
+    for (; i < 8 * per_xcd; i += gridDim.x) {
+        const int t = tile_of(i);
+        if (t >= a.ntiles) break;                    // an XCD's items run out together
+        int n, ty0, tx0;
+        locate(t, n, ty0, tx0);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int v = (int)threadIdx.x + u * 256;
+            const u2v p = {px[u][0] | px[u][1] << 16, px[u][2]};
+            if (v < DLF_SDP_PATCH) *(u2v*)(patch + v * 8) = p;
+        }
+        __syncthreads();
+        const int next = i + (int)gridDim.x;
+        if (next < 8 * per_xcd && tile_of(next) < a.ntiles) request(tile_of(next));
+        // first layer
+        for (int b = wave; b < DLF_SDP_REGION / 32; b += 4) {
+            const int p = b * 32 + l32, pc = min(p, NPX - 1), ry = pc / RW, rx = pc - ry * RW;
+            const char* const src = patch + (2 * ry * PW + 2 * (rx + lhi)) * 8;
+            f16v acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f4v bv = *(const f4v*)(bias + q * 8 + lhi * 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[q * 4 + r] = bv[r];
+            }
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                u4v x = *(const u4v*)(src + r * PW * 8);
+                x.z &= keep;
+                x.w &= keep;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w0[r], __builtin_bit_cast(h8, x), acc, 0, 0, 0);
+            }
+            const int gy = ty0 - 1 + ry, gx = tx0 - 1 + rx;
+            const unsigned in_map = gy >= 0 && gy < a.oh && gx >= 0 && gx < a.ow ? 0xFFFFFFFFu : 0u;
+            if (p < NPX) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u2v v = {pk_min(pk_max(cvt_pk(acc[q * 4 + 0], acc[q * 4 + 1]), lo0), hi0) & in_map,
+                                   pk_min(pk_max(cvt_pk(acc[q * 4 + 2], acc[q * 4 + 3]), lo0), hi0) & in_map};
+                    *(u2v*)(region + swz(p, q) + lhi * 8) = v;
+                }
+            }
+        }
+        __syncthreads();
+        // depthwise layer, the wave's two rows
+        {
+            float v[2][8];
+#pragma unroll
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[o][e] = bias_d[g * 8 + e];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const u4v x = *(const u4v*)(region + swz((wave * 2 + r) * RW + col + k, g));
+                    if (r < 3) dw_tap(v[0], x, *(const u4v*)(wd + (r * 3 + k) * 32 + g * 8));
+                    if (r > 0) dw_tap(v[1], x, *(const u4v*)(wd + (r * 3 - 3 + k) * 32 + g * 8));
+                }
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                u4v hv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hv[e] = pk_min(pk_max(cvt_pk(v[o][e * 2], v[o][e * 2 + 1]), lo_d), hi_d);
+                *(u4v*)(mid + swz(wave * 32 + o * 16 + col, g)) = hv;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        // 1x1 layer on the wave's 32 pixels
+        h8 b[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) b[k] = *(const h8*)(mid + swz(wave * 32 + l32, k * 2 + lhi));
+        const int oy = ty0 + wave * 2 + (l32 >> 4), ox = tx0 + (l32 & 15);
+        half_t* const out = (half_t*)a.out + (size_t)((n * a.oh + oy) * a.ow + ox) * a.cout + lhi * 8;
+        const bool live = oy < a.oh && ox < a.ow;
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) {
+            f16v acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f4v bv = *(const f4v*)(bias + (1 + c) * 32 + q * 8 + lhi * 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[q * 4 + r] = bv[r];
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(wp[(c * 2 + k) * 64 + lane], b[k], acc, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                u4v v;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const auto s = __builtin_amdgcn_permlane32_swap(cvt_pk(acc[k * 8 + j * 2], acc[k * 8 + j * 2 + 1]),
+                                                                    cvt_pk(acc[k * 8 + 4 + j * 2], acc[k * 8 + 5 + j * 2]), false, false);
+                    v[j] = pk_min(pk_max(s[0], lo_p), hi_p);
+                    v[2 + j] = pk_min(pk_max(s[1], lo_p), hi_p);
+                }
+                if (live && c * 32 + k * 16 + lhi * 8 < a.cout) *(u4v*)(out + c * 32 + k * 16) = v;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 
 // Depthwise 3x3 + 1x1 convolution where a map has many channels and few pixels (MobileNet's 14 x 14
 // and 7 x 7 maps of 256 - 1024 channels).  There the layers are small, a launch costs about as much
@@ -5087,6 +5267,16 @@ extern "C" int dlf_launch_dwpw(const DlfDwPwArgs* a, int nb, int grid, void* str
 
 extern "C" int dlf_launch_dwt(const DlfDwtArgs* a, int grid, int lds_bytes, void* stream)
 {
+    if (a->w0 != nullptr) {          // with a first layer in front
+        // what the kernel's indexing assumes
+        if (grid <= 0 || (grid & 7) != 0 || a->in_bytes >= 0x80000000u || a->c != 32 || a->stride != 1 || (a->cout & 7) != 0 ||
+            a->ncb != (a->cout + 31) / 32 || a->ncb < 1 || a->ncb > 4 || a->oh != (a->ih - 1) / 2 + 1 || a->ow != (a->iw - 1) / 2 + 1 ||
+            a->tiles_y != (a->oh + DLF_SDP_TH - 1) / DLF_SDP_TH || a->tiles_x != (a->ow + DLF_SDP_TW - 1) / DLF_SDP_TW ||
+            a->ntiles != a->batch * a->tiles_y * a->tiles_x || lds_bytes != DLF_SDP_LDS_BYTES(DLF_SDP_BLOCKS(a->ncb)))
+            return (int)hipErrorInvalidValue;
+        launch(a->ncb == 1 ? k_sdp<1> : a->ncb == 2 ? k_sdp<2> : k_sdp<4>, dim3(grid), dim3(256), (size_t)lds_bytes, (hipStream_t)stream, *a);
+        return (int)hipGetLastError();
+    }
     // what the kernel's indexing assumes
     if (grid <= 0 || (a->stride != 1 && a->stride != 2) || a->in_bytes >= 0x80000000u) return (int)hipErrorInvalidValue;
     if (a->cg * 8 != a->c || a->cg < 4 || a->cg > 64 || (a->cg & (a->cg - 1)) != 0 || a->pxw * a->cg != 64)
