@@ -218,8 +218,8 @@ const int64_t C_STAGE = 1200;                // per VALU stage
 const int64_t C_STORE_VEC = 80;             // per 512 stored 16-byte vectors
 const int64_t C_STORE = 1600;
 const int64_t MFMA_CYCLES = 32;             // one 32x32x16 MFMA on one SIMD
-const int64_t FC_BYTES_PER_CYCLE = 1400;    // weight streaming rate of the FC kernel
-const int64_t FC_SPLIT_HBM_BYTES_PER_CYCLE = 1900;   // the same with K split over all CUs
+const int64_t FC_SPLIT_HBM_BYTES_PER_CYCLE = 1900;   // weight streaming rate of the FC kernels
+const int64_t FC_CU_BYTES_PER_CYCLE = 50;   // ... and what one CU takes in, weights and activations
 const int64_t GAP_BYTES_PER_CYCLE = 1000;
 // pointwise kernel, per item shape: register tile (FC x FP blocks of 32), operand ring depth,
 // independent waves per CU
@@ -1933,14 +1933,17 @@ bool dws_choose(const Layer& D, const Layer& P, int batch, int budget, int max_l
 }
 
 // force_tc / pw_mode: explicit values for the two testing hooks (null / -1: the process-wide ones)
-// Fully connected layer: one workgroup per 32 output channels streaming all of K, or, where that is
-// cheaper, pairs of channel blocks with K split 2, 4 or 8 ways (at most 256 workgroups), a second
+// Fully connected layer: one workgroup per 16 output channels and 16 or 32 images with all of K, or, where that is
+// cheaper, pairs of 32-channel blocks with K split 2, 4 or 8 ways (at most 256 workgroups), a second
 // launch adding the slices: what a workgroup then takes in per K step is 3 KiB for two MFMAs.
 uint64_t fc_cost_ps(const Layer& L, int batch, int& ksplit)
 {
     const int64_t nbb = ceil_div(batch, 32);
     const int64_t wbytes = (int64_t)L.ncb * L.nsteps * 1024 * nbb;
-    uint64_t best = (uint64_t)((C_LAUNCH + C_LAT + wbytes / FC_BYTES_PER_CYCLE) * PS_PER_CYCLE);
+    const int64_t blocks = batch > 16 ? 2 : 1, groups = ceil_div(batch, 16 * (int)blocks);
+    const int64_t rounds = (ceil_div(L.d.cout, 16) * groups + 255) / 256;
+    const int64_t all = rounds * (L.nsteps / 2) * (1 + blocks) * 1024 / FC_CU_BYTES_PER_CYCLE;
+    uint64_t best = (uint64_t)((C_LAUNCH + C_LAT + std::max(all, wbytes / FC_SPLIT_HBM_BYTES_PER_CYCLE)) * PS_PER_CYCLE);
     ksplit = 1;
     for (int ks = 2; ks <= 8; ks *= 2) {
         if (ceil_div(L.ncb, 2) * ks > 256 || L.nsteps < 64 * ks) continue;
@@ -2009,6 +2012,7 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
             ksplit = force.nslices;                     // testing hook
         fa.ksplit = ksplit;
         g.scratch_bytes = ksplit > 1 ? (size_t)ksplit * ceil_div(batch, 32) * L0.ncb * 4096 : 0;
+        g.variant = ksplit > 1 ? 3 : DLF_FC_SHAPE(batch, L0.nsteps);
         g.grid = L0.ncb;
         g.th = g.tw = 1;
         return DLF_OK;

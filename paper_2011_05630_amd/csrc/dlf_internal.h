@@ -72,6 +72,9 @@ struct DlfGroupArgs {
     DlfStage st[DLF_MAX_STAGES];
 };
 
+#define DLF_FC_WAVES 8
+// k_fc's forms: 0 / 1 = 16 images, 4 / 8 turns of 64 K values ahead (a wave's share is up to 4 turns / longer), 2 = 32 images, 4 turns
+#define DLF_FC_SHAPE(BATCH, NSTEPS) ((BATCH) > 16 ? 2 : (NSTEPS) > 16 * DLF_FC_WAVES ? 1 : 0)
 struct DlfFcArgs {
     const void* x;        // [batch][k] fp16
     void* y;              // [batch][cout] fp16

@@ -4463,9 +4463,7 @@ __global__ __launch_bounds__(DLF_BN_WAVES * 64, 2) void k_bneck(const DlfBnArgs 
 extern "C" int dlf_launch_dw(const DlfDwArgs* a, int grid, void* stream);
 
 // Fully connected layer (Eq. 2 with M = batch): y[n][co] = act(bias[co] + sum_k x[n][k] w[co][k]).
-// One workgroup per 32 output channels; its 8 waves split K, each streaming a contiguous share
-// of the packed weight fragments from HBM exactly once; partial sums meet in LDS.
-#define DLF_FC_WAVES 8
+// k_fc, further down, in one launch; k_fc_sk with K split over workgroups.
 #define DLF_FC_BROW 144                                      // bytes of an activation row in LDS: 4 K steps + 16
 #define DLF_FC_BBYTES (32 * DLF_FC_BROW)                     // per wave
 
@@ -4557,42 +4555,6 @@ __device__ __forceinline__ void fc_steps(const DlfFcArgs& a, const h8* const (&w
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-    }
-}
-
-__global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
-{
-    // the waves' activation rows during the K loop, their partial sums behind it
-    __shared__ __align__(16) char smem[DLF_FC_WAVES * DLF_FC_BBYTES];
-    static_assert(sizeof(smem) >= DLF_FC_WAVES * 16 * 64 * 4, "partial sums");
-    float (*const red)[16][64] = (float (*)[16][64])smem;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cb = blockIdx.x;
-    half_t* y = (half_t*)a.y;
-    const h8* const wp[1] = {(const h8*)a.w + (size_t)cb * a.nsteps * 64 + lane};
-    // each wave a contiguous eighth of the K steps, whole groups of four
-    const int per = ((a.nsteps + DLF_FC_WAVES - 1) / DLF_FC_WAVES + 3) & ~3;
-    const int t0 = min(wave * per, a.nsteps), t1 = min(a.nsteps, t0 + per);
-    for (int nb = 0; nb < a.batch; nb += 32) {
-        f16v acc[1];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[0][i] = 0.0f;
-        fc_steps<1>(a, wp, nb, t0, t1, smem + wave * DLF_FC_BBYTES, lane, acc);
-        __syncthreads();                                     // the sums take the rows' place
-#pragma unroll
-        for (int i = 0; i < 16; ++i) red[wave][i][lane] = acc[0][i];
-        __syncthreads();
-        for (int e = tid; e < 16 * 64; e += DLF_FC_WAVES * 64) {
-            const int i = e >> 6, ln = e & 63;
-            float s = 0.0f;
-#pragma unroll
-            for (int w = 0; w < DLF_FC_WAVES; ++w) s += red[w][i][ln];
-            const int co = cb * 32 + (i >> 2) * 8 + (ln >> 5) * 4 + (i & 3);
-            const int im = nb + (ln & 31);
-            if (co < a.cout && im < a.batch)
-                y[(size_t)im * a.cout + co] = (half_t)apply_act(s + a.bias[co], a.act);
-        }
-        __syncthreads();
     }
 }
 
@@ -4839,6 +4801,104 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
     }
 }
 
+// Fully connected layer in one launch: 16 output channels per workgroup, so that 4096 outputs are one workgroup per CU, and 16 * TP images;
+// K dealt to eight waves in contiguous shares of 64, partial sums through LDS.  What bounds the layer is how many bytes of weights are
+// in flight: each wave keeps D turns of 64 K values, weights in registers ("A": half of the rows of packed 32-channel fragments, runs of
+// 256 bytes), activations by direct loads in the wave's LDS.  There eight consecutive lanes fetch the 128 bytes of a row (by
+// 64 bytes, a step of the matrix instruction, each line is fetched twice: 25088 -> 4096 42.5 us at batch 16, not 36.8); part g of row r lies at the place
+// g ^ r % 8 ^ r / 8 of its 128 bytes, so that the sixteen rows of an operand read lie in different banks.  Both resources begin at the workgroup's own
+// channels and images; rows beyond the batch and pieces beyond K are not fetched and read as zeros.
+// Per launch, as one workgroup per 32 channels or k_fc_sk and k_fc_fin -> now: 25088 -> 4096 45.0 -> 31.3 us at batch 1 (6.6 TB/s of
+// weights, part of them from the last-level cache), 48.9 -> 36.8 at 16, 54.2 -> 47.1 at 32; 9216 -> 4096 21.7 -> 12.4 and 22.8 -> 14.9;
+// 4096 -> 4096 at batch 16 10.2 -> 6.7; 4096 -> 1000 at batch 64 12.4 -> 6.8 (6.7 is the host's time per call).
+template <int TP, int D>
+__global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
+{
+    constexpr int P = 16 * TP, WB = D * TP * 2048;           // a wave's LDS: its ring of "B" operands, then its partial sums
+    static_assert(WB >= P * 16 * 4, "partial sums");
+    float* const part = (float*)lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q = lane >> 4;
+    // the image groups of 16 channels on one XCD (workgroups i, i + 8, ...): its L2 has their weights
+    const int n_pg = (a.batch + P - 1) / P, n_cg = (a.cout + 15) >> 4;
+    const int j = (int)blockIdx.x >> 3, pg = j % n_pg, cg = (j / n_pg) * 8 + ((int)blockIdx.x & 7);
+    if (cg >= n_cg) return;
+    const int nk = (a.nsteps + 3) >> 2, ksw = (nk + DLF_FC_WAVES - 1) / DLF_FC_WAVES;
+    const int k0 = wave * ksw, k1 = min(k0 + ksw, nk);
+    f4v acc[TP];
+#pragma unroll
+    for (int p = 0; p < TP; ++p) acc[p] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    if (k0 < k1) {
+        const int images = min(P, a.batch - pg * P);
+        const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc((void*)((const half_t*)a.x + (size_t)pg * P * a.k), 0,
+                                                                             images * a.k * 2, 0x00020000);
+        const i32x4 rw = make_rsrc((const char*)a.w + (size_t)(cg >> 1) * a.nsteps * 1024, (unsigned)a.nsteps * 1024u);
+        const int aoff = (q >> 1) * 1024 + ((q & 1) * 32 + (cg & 1) * 16 + r16) * 16;
+        int boff[TP][2], piece[2];                           // the lane's row and 16-byte piece of it in the loads of rows 0 - 7 and 8 - 15
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            piece[h] = ((lane ^ (lane >> 3) ^ h) & 7) * 16;
+#pragma unroll
+            for (int p = 0; p < TP; ++p) {
+                const int row = p * 16 + h * 8 + (lane >> 3);
+                boff[p][h] = row < images ? row * a.k * 2 + piece[h] : DLF_OOB;
+            }
+        }
+        h8 A[D][2];
+        half_t* const ring = lds + wave * (WB / 2);
+        const unsigned row0 = (unsigned)(wave * WB + r16 * 128), place = (unsigned)(q ^ (r16 & 7) ^ (r16 >> 3));
+        const unsigned from[2] = {row0 + place * 16, row0 + (place ^ 4) * 16};
+        int s_ = k0;
+        auto request = [&](int d) __attribute__((always_inline)) {       // beyond the wave's share nothing is fetched
+            const bool ok = s_ < k1;
+#pragma unroll
+            for (int p = 0; p < TP; ++p)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    dma16b(rin, ring + ((d * TP + p) * 2 + h) * 512, (unsigned)(ok && s_ * 128 + piece[h] < a.k * 2 ? boff[p][h] : DLF_OOB), s_ * 128);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                A[d][e] = __builtin_bit_cast(h8, raw_buffer_load_x4(rw, ok && s_ * 4 + e * 2 < a.nsteps ? aoff : DLF_OOB, s_ * 4096 + e * 2048, 2));
+            ++s_;
+            __builtin_amdgcn_sched_barrier(0);               // the requests stay in order: they are waited for by count
+        };
+        auto multiply = [&](auto dc, auto later) __attribute__((always_inline)) {
+            constexpr int d = decltype(dc)::value;
+            wait_vmcnt<decltype(later)::value * (TP + 1) * 2>();
+            h8 B[TP * 2];
+            static_for<0, TP * 2>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                B[i] = lds_read16<(d * TP + (i >> 1)) * 2048>(from[i & 1]);
+            });
+            static_for<0, TP * 2>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                lds_arrive1<TP * 2 - 1 - i>(B[i]);
+                acc[i >> 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[d][i & 1], B[i], acc[i >> 1], 0, 0, 0);
+            });
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) request(d);
+        for (int s = k0; s + D < k1; s += D) {
+            static_for<0, D>([&](auto dc) __attribute__((always_inline)) {
+                multiply(dc, std::integral_constant<int, D - 1>());
+                request(decltype(dc)::value);
+            });
+        }
+        static_for<0, D>([&](auto dc) __attribute__((always_inline)) { multiply(dc, std::integral_constant<int, D - 1 - decltype(dc)::value>()); });
+    }
+    // partial sums: [wave][image][channel]; lane (image r16, channels 4q .. 4q + 3); added in the order of the waves
+#pragma unroll
+    for (int p = 0; p < TP; ++p) *(f4v*)(part + wave * (WB / 4) + (p * 16 + r16) * 16 + q * 4) = acc[p];
+    __syncthreads();
+    const int im = pg * P + (tid >> 4), co = cg * 16 + (tid & 15);
+    if (tid < P * 16 && co < a.cout && im < a.batch) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < DLF_FC_WAVES; ++w) s += part[w * (WB / 4) + tid];
+        ((half_t*)a.y)[(size_t)im * a.cout + co] = (half_t)apply_act(s + a.bias[co], a.act);
+    }
+}
+
 // A depthwise 3x3 layer (pad 1, stride 1 or 2) and the 1x1 layer behind it for outputs of few pixels: the pairs of
 // MobileNet-style networks at small batch, which k_dwt / k_dws need more pixels for.
 // Built as k_skc: work item = 16 pixels x 16 * TC channels of the 1x1 layer, K -- the depthwise layer's channels -- dealt to
@@ -5077,6 +5137,9 @@ template <bool I8> static c3_kernel_t c3r_kernel(int shape)
     }
 }
 
+typedef void (*FcKernel)(const DlfFcArgs);
+static FcKernel fc_kernel(int shape) { return shape == 0 ? k_fc<1, 4> : shape == 1 ? k_fc<1, 8> : k_fc<2, 4>; }
+
 extern "C" int dlf_kernels_init(void)
 {
     {
@@ -5125,6 +5188,10 @@ extern "C" int dlf_kernels_init(void)
         }
     }
     {
+        for (int v = 0; v < 3; ++v) {
+            hipError_t e = hipFuncSetAttribute((const void*)fc_kernel(v), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return (int)e;
+        }
         const void* ks[4] = {(const void*)k_dws<1, 1>, (const void*)k_dws<1, 2>, (const void*)k_dws<2, 1>, (const void*)k_dws<2, 2>};
         for (const void* k : ks) {
             hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -5194,7 +5261,11 @@ extern "C" int dlf_launch_fc(const DlfFcArgs* a, void* stream)
         launch(k_fc_fin, dim3(a->ncb * ((a->batch + 31) / 32)), dim3(256), 0, (hipStream_t)stream, *a);
         return (int)hipGetLastError();
     }
-    launch(k_fc, dim3(a->ncb), dim3(DLF_FC_WAVES * 64), 0, (hipStream_t)stream, *a);
+    if (a->nsteps & 1) return (int)hipErrorInvalidValue;     // whole 32-channel chunks of K
+    const int shape = DLF_FC_SHAPE(a->batch, a->nsteps), images = shape == 2 ? 32 : 16;
+    const int grid = ((a->cout + 15) / 16 + 7) / 8 * 8 * ((a->batch + images - 1) / images);
+    const int ring = DLF_FC_WAVES * 1024 * (shape == 0 ? 8 : 16);
+    launch(fc_kernel(shape), dim3(grid), dim3(DLF_FC_WAVES * 64), ring, (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
 

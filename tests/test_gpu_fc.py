@@ -1,0 +1,32 @@
+"""GPU parity of the fully connected kernel in one launch, against the CPU oracle: K shorter than one wave's turn, odd numbers of
+32-channel chunks, shares just above the ring's length; ragged channel groups; one image to more than two groups of 32."""
+import pytest
+
+from synth import nets, gen
+from gpu_util import compare, announce
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [1, 15, 16, 17, 32, 33, 70])
+@pytest.mark.parametrize("k,cout", [(8, 1), (24, 17), (72, 33), (512, 130), (2056, 16), (4096, 47), (4136, 1000), (8200, 129)])
+def test_fc(k, cout, batch):
+    from oracle import oracle as o
+    from paper_2011_05630_amd import binding as B
+    from paper_2011_05630_amd.runner import Session
+    announce("fc", k, cout, batch)
+    act = ("none", "relu", "relu6")[(k + batch) % 3]
+    net = dict(name="t", layers=[nets.fc(k, cout, act)], in_h=1, in_w=1, in_c=k, input_dist="normal")
+    x, ws, bs = gen.make_params(net, batch, 31)
+    B.dlf_debug_force_config(1, 1, 0, 1, 0, 0, 32)       # K not split over workgroups
+    try:
+        s = Session(net, batch, ws, bs)
+    finally:
+        B.dlf_debug_force_config(0, 0, 0, 1, 0, 0, 32)
+    try:
+        cfg = B.dlf_plan_group_config(s.plan, 0)
+        assert (cfg["kind"], cfg["variant"]) == (1, 2 if batch > 16 else 1 if (k + 31) // 32 * 2 > 128 else 0), cfg
+        got = s.run_numpy(x)
+    finally:
+        s.close()
+    compare(got, o.run_net(net, x, ws, bs), "fc")
