@@ -75,9 +75,13 @@ void dlf_debug_block3x3_mode(int32_t mode, int32_t shape, int32_t th, int32_t tw
  * kernel is not considered while another hook names a kernel.  Process-wide, not thread-safe. */
 void dlf_debug_small_mode(int32_t mode, int32_t shape, int32_t waves);
 /* Testing hook: the same for a depthwise 3x3 layer with the 1x1 layer behind it and the split-K kernel for such
- * pairs: in mode 1 shape 0 or 1 fixes an item's channels (32, 64; 16 pixels), waves is 1, 2, 4 or 0.  Process-wide,
- * not thread-safe. */
+ * pairs: in mode 1 shape 0 or 1 fixes an item's channels (32, 64; 16 pixels), waves is 1, 2, 4, 8 or 0.
+ * Process-wide, not thread-safe. */
 void dlf_debug_small_pair_mode(int32_t mode, int32_t shape, int32_t waves);
+
+/* Testing hook: puts every group of the plan through its launcher's checks and launches nothing; DLF_ERR_HIP if one
+ * refuses its arguments.  Needs neither a GPU nor weights. */
+dlf_status dlf_debug_check_launches(const dlf_plan_t* plan);
 
 #ifdef __cplusplus
 }

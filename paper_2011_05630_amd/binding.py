@@ -123,6 +123,8 @@ def lib():
     L.dlf_debug_small_mode.restype = None
     L.dlf_debug_small_pair_mode.argtypes = [i32, i32, i32]
     L.dlf_debug_small_pair_mode.restype = None
+    L.dlf_debug_check_launches.argtypes = [vp]
+    L.dlf_debug_check_launches.restype = i32
     L.dlf_plan_set_overlap.argtypes = [vp, i32]
     L.dlf_plan_set_overlap.restype = i32
     L.dlf_plan_group_stream.argtypes = [vp, i32]
@@ -405,6 +407,11 @@ def dlf_debug_small_mode(mode=0, shape=-1, waves=0):
 def dlf_debug_small_pair_mode(mode=0, shape=-1, waves=0):
     """Testing hook: as dlf_debug_small_mode, for a depthwise layer with the 1x1 layer behind it (shape 0, 1)."""
     lib().dlf_debug_small_pair_mode(mode, shape, waves)
+
+
+def dlf_debug_check_launches(plan):
+    """Testing hook: every group of the plan through its launcher's checks, nothing launched (no GPU needed)."""
+    _check(lib().dlf_debug_check_launches(plan))
 
 
 def dlf_debug_force_config(th=0, tw=0, variant=0, nslices=1, slice_c=0, stream0=0, kc=0):

@@ -1800,6 +1800,7 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
 SkcForce g_skd_force = {0, -1, 0};
 const int SKD_TC[DLF_SKD_SHAPES] = {2, 4};          // 16-channel blocks of an item
 
+// (up to 1376 channels, the limit of dwpw_eligible: at most 73 KiB of LDS)
 bool skd_eligible(const dlf_net_s& net, int first, int last, int batch)
 {
     if (!dwpw_eligible(net, first, last, batch)) return false;
@@ -1807,7 +1808,7 @@ bool skd_eligible(const dlf_net_s& net, int first, int last, int batch)
     // pixels and rows are divided as 32-bit products (items: skd_choose)
     const int64_t m = (int64_t)batch * P.out_h * P.out_w;
     return m <= 1 << 17 && m * std::max(P.out_h, P.out_w) < (int64_t)1 << 31 && (int64_t)P.ncb * P.nsteps * 1024 < (int64_t)1 << 31 &&
-           net.L[first].d.cin <= 2048;                             // (the weights' place in LDS)
+           net.L[first].d.cin <= 2048;
 }
 
 void skd_fill(const Layer& D, const Layer& P, int batch, int shape, int waves, DlfSkdArgs& sd)
@@ -3132,15 +3133,18 @@ const void* dlf_plan_layer_output(const dlf_plan_t* plan, int32_t layer)
 
 static std::once_flag g_kernels_once;
 static int g_kernels_rc = 0;
+__thread int dlf_launch_dry = 0;
 
 // ws: base of the workspace this run uses (the plan's bound one, or the static array)
 static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const void* in, const void* res,
                              void* out, void* stream, char* ws)
 {
     int e = 0;
-    std::call_once(g_kernels_once, [] { g_kernels_rc = dlf_kernels_init(); });
-    if (g_kernels_rc != 0)
-        return fail(DLF_ERR_HIP, "kernel setup failed: %s", hipGetErrorString((hipError_t)g_kernels_rc));
+    if (!dlf_launch_dry) {
+        std::call_once(g_kernels_once, [] { g_kernels_rc = dlf_kernels_init(); });
+        if (g_kernels_rc != 0)
+            return fail(DLF_ERR_HIP, "kernel setup failed: %s", hipGetErrorString((hipError_t)g_kernels_rc));
+    }
     if (G.kind == GK_FC) {
         DlfFcArgs fa = G.fa;
         fa.x = in; fa.y = out;
@@ -3234,10 +3238,29 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
         }
         e = dlf_launch_group(&ga, G.variant, G.grid, G.lds_bytes, stream);
     }
+    if (dlf_launch_dry && e != (int)hipErrorInvalidValue) e = 0;     // (without a GPU the runtime's last error is that there is none)
     if (e != 0) return fail(DLF_ERR_HIP, "launch of group [%d,%d] failed: %s", G.first, G.last,
                             hipGetErrorString((hipError_t)e));
     (void)plan;
     return DLF_OK;
+}
+
+dlf_status dlf_debug_check_launches(const dlf_plan_t* plan)
+{
+    if (!plan) return fail(DLF_ERR_INVALID_ARG, "null plan");
+    char* const some = (char*)4096;                // looked at for null only: nothing is launched
+    auto check = [&](GroupPlan G) {                // a shape-only network has no parameters to name
+        if (G.kind == GK_DWT && G.variant >= 16 && !G.dt.w0) G.dt.w0 = some;
+        if (G.kind == GK_PW2 && !G.wa.w2) { G.wa.w2 = some; G.wa.bias2 = (const float*)some; }
+        if (G.kind == GK_C3R && G.ca.cin0 > 0 && !G.ca.w0) G.ca.w0 = some;
+        return launch_one(plan, G, some, some, some, nullptr, some);
+    };
+    dlf_launch_dry = 1;
+    dlf_status s = DLF_OK;
+    for (const GroupPlan& G : plan->G) if (s == DLF_OK) s = check(G);
+    for (const GroupPlan& G : plan->compact) if (s == DLF_OK) s = check(G);
+    dlf_launch_dry = 0;
+    return s;
 }
 
 dlf_status dlf_run_group(const dlf_plan_t* plan, int32_t g, const void* in_dev, const void* res_dev,

@@ -482,6 +482,8 @@ int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream);
 int dlf_kernels_init(void);
 // Attaches a start / stop event pair (hipEvent_t, either may be null) to this thread's next launch.
 void dlf_next_launch_events(void* start, void* stop);
+// While set, this thread's launchers check their arguments and launch nothing.
+extern __thread int dlf_launch_dry;
 #ifdef __cplusplus
 }
 #endif

@@ -5065,6 +5065,7 @@ extern "C" void dlf_next_launch_events(void* start, void* stop)
 template <typename K, typename A>
 static void launch(K k, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream, const A& a)
 {
+    if (dlf_launch_dry) return;
     if (g_ev_start != nullptr || g_ev_stop != nullptr) {
         hipExtLaunchKernelGGL(k, grid, block, lds_bytes, stream, g_ev_start, g_ev_stop, 0, a);
         g_ev_start = g_ev_stop = nullptr;
@@ -5140,6 +5141,8 @@ template <bool I8> static c3_kernel_t c3r_kernel(int shape)
 typedef void (*FcKernel)(const DlfFcArgs);
 static FcKernel fc_kernel(int shape) { return shape == 0 ? k_fc<1, 4> : shape == 1 ? k_fc<1, 8> : k_fc<2, 4>; }
 
+static void (*skd_kernel(int shape))(const DlfSkdArgs) { return shape == 0 ? k_skd<2> : k_skd<4>; }
+
 extern "C" int dlf_kernels_init(void)
 {
     {
@@ -5190,6 +5193,10 @@ extern "C" int dlf_kernels_init(void)
     {
         for (int v = 0; v < 3; ++v) {
             hipError_t e = hipFuncSetAttribute((const void*)fc_kernel(v), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return (int)e;
+        }
+        for (int v = 0; v < DLF_SKD_SHAPES; ++v) {
+            hipError_t e = hipFuncSetAttribute((const void*)skd_kernel(v), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return (int)e;
         }
         const void* ks[4] = {(const void*)k_dws<1, 1>, (const void*)k_dws<1, 2>, (const void*)k_dws<2, 1>, (const void*)k_dws<2, 2>};
@@ -5489,12 +5496,11 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
 
 extern "C" int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream)
 {
-    static void (*const k[DLF_SKD_SHAPES])(const DlfSkdArgs) = {k_skd<2>, k_skd<4>};
     if ((int64_t)a->n_pg * a->n_cg * a->n_cg >= (int64_t)1 << 32) return (int)hipErrorInvalidValue;      // div_by of an item
-    if (DLF_SKD_LDS_BYTES(a->nw, 64, a->ksw) > 64 * 1024) return (int)hipErrorInvalidValue;
     if (shape < 0 || shape >= DLF_SKD_SHAPES || a->ksw < 1 || a->nw < 1 || a->nw > DLF_SKD_MAX_WAVES || (a->nw & (a->nw - 1)) != 0) return (int)hipErrorInvalidValue;
-    launch(k[shape], dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), DLF_SKD_LDS_BYTES(a->nw, 32 << shape, a->ksw),
-           (hipStream_t)stream, *a);
+    const int lds_bytes = DLF_SKD_LDS_BYTES(a->nw, 32 << shape, a->ksw);
+    if (lds_bytes > 160 * 1024) return (int)hipErrorInvalidValue;
+    launch(skd_kernel(shape), dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), lds_bytes, (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
 

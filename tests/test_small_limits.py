@@ -178,6 +178,47 @@ def test_no_layer_is_priced_below_its_bytes():
     assert seen > 250, seen
 
 
+@pytest.mark.parametrize("c", range(32, 2049, 32))
+def test_depthwise_pairs_pass_their_launcher(c):
+    """Whatever the planner chooses for a depthwise layer and the 1x1 layer behind it, and every form of the split-K kernel that the
+    testing hook names, is a launch that the kernel's launcher takes (1056 to 1376 channels: eight waves of five or six steps, 51
+    to 73 KiB of LDS; wider pairs are two launches)."""
+    for cout, hw, batch, stride in ((8, 7, 1, 1), (320, 14, 1, 2), (c, 7, 2, 1)):
+        layers = [nets.dwconv(c, 3, stride, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")]
+        n = B.dlf_net_create(layers, hw, hw, c)
+        one = dict(mode=B.TUNER_MANUAL, group_last=[1], group_budget=[256])
+        forms = [(0, -1, 0)] + [(1, shape, waves) for shape in (0, 1) for waves in (0, 1, 2, 4, 8)]
+        for mode, shape, waves in forms if c <= 1376 else forms[:1]:
+            for kw in ([{}] if mode == 0 else []) + ([one] if c <= 1376 else []):
+                B.dlf_debug_small_pair_mode(mode, shape, waves)
+                try:
+                    p = B.dlf_plan(n, batch, **kw)
+                finally:
+                    B.dlf_debug_small_pair_mode(0)
+                B.dlf_debug_check_launches(p)
+                cfg = B.dlf_plan_group_config(p, 0)
+                assert mode == 0 or (cfg["kind"], cfg["variant"]) == (6, 16 + shape), (c, cout, shape, waves, cfg)
+                B.dlf_plan_destroy(p)
+        B.dlf_net_destroy(n)
+
+
+def test_plans_pass_their_launchers():
+    """Every group of the networks' plans, and of the plans under an LDS limit, is a launch that its launcher takes."""
+    for net in (nets.vgg16(), nets.resnet18(173), nets.resnet50(), nets.mobilenet_v1(), nets.alexnet(), nets.identical_chain(64, 56, 4)):
+        for batch in (1, 5, 32):
+            for limit in (0, 65536, 16384):
+                for mode in (B.TUNER_DP, B.TUNER_LAYERWISE):
+                    h = B.dlf_net_create(net["layers"], net["in_h"], net["in_w"], net["in_c"])
+                    try:
+                        p = B.dlf_plan(h, batch, mode=mode, max_lds_bytes=limit)
+                        B.dlf_debug_check_launches(p)
+                        B.dlf_plan_destroy(p)
+                    except B.DlfError as e:
+                        assert limit > 0 and e.status == B.DLF_ERR_INFEASIBLE, (net["name"], batch, limit, e)
+                    finally:
+                        B.dlf_net_destroy(h)
+
+
 def _default_plan(net, batch):
     h = B.dlf_net_create(net["layers"], net["in_h"], net["in_w"], net["in_c"])
     p = B.dlf_plan(h, batch)
