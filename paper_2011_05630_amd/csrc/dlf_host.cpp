@@ -369,6 +369,15 @@ const int64_t C_SKD_ITEM[DLF_SKD_SHAPES] = {8500, 9100};
 const int64_t C_SKD_STEP = 237;
 const int64_t C_SKD_ROUND = 700;
 const int64_t C_SKD_ROUND_STEP = 205;
+// ... with eight waves, which fill a CU, so that a further item runs behind the first and not beside it (1024 channels at 7 x 7, items
+// of 64: 256 items 8.6 us, 304 15.1), and per MB of input beyond 1.5 (1152 -> 320 stride 2: 4.5 MB 10.3 us, 7.2 12.0).  Fitted to
+// 1024 - 1376 channels, 150 - 512 items, within 8 %.
+const int64_t C_SKD_ITEM_8[DLF_SKD_SHAPES] = {6100, 7800};
+const int64_t C_SKD_STEP_8[DLF_SKD_SHAPES] = {300, 327};
+const int64_t C_SKD_ROUND_8[DLF_SKD_SHAPES] = {4500, 7600};
+const int64_t C_SKD_ROUND_STEP_8 = 218;
+const int64_t C_SKD_MB_8 = 1000;
+const int64_t SKD_FREE_BYTES_8 = 3 << 19;
 // ... and on the same pairs the other depthwise kernels in launches that leave places free (C_LAUNCH holds most of
 // such a launch's round trips; in per cent): the tile kernel with one tile per CU at most (5.0 - 7.4 us, 11 - 14
 // without this; from 5 MiB on it is slower), the small-map kernel with one item per CU at most: 256 / 512 / 1024 channels 7.4 - 9.2 /
@@ -1834,7 +1843,10 @@ uint64_t skd_cost_ps(const Layer& D, const Layer& P, const DlfSkdArgs& sd, int s
 {
     const int64_t items = (int64_t)sd.n_pg * sd.n_cg;
     const int64_t rounds = (items + budget - 1) / budget;
-    const int64_t cycles = std::max(C_SKD_LEAST, C_SKD_ITEM[shape] + sd.nk * C_SKD_STEP) + (rounds - 1) * (C_SKD_ROUND + sd.nk * C_SKD_ROUND_STEP);
+    int64_t cycles = std::max(C_SKD_LEAST, C_SKD_ITEM[shape] + sd.nk * C_SKD_STEP) + (rounds - 1) * (C_SKD_ROUND + sd.nk * C_SKD_ROUND_STEP);
+    if (sd.nw == 8)
+        cycles = C_SKD_ITEM_8[shape] + sd.nk * C_SKD_STEP_8[shape] + (rounds - 1) * (C_SKD_ROUND_8[shape] + sd.nk * C_SKD_ROUND_STEP_8) +
+                 std::max<int64_t>(0, (int64_t)sd.in_bytes - SKD_FREE_BYTES_8) * C_SKD_MB_8 / (1 << 20);
     const int64_t bytes = (int64_t)sd.in_bytes + (int64_t)sd.m * P.d.cout * 2 + (int64_t)P.ncb * P.nsteps * 1024 + (int64_t)D.d.cin * 22;
     const int64_t mem = bytes / std::min<int64_t>(DW_HBM_BYTES_PER_CYCLE, (int64_t)budget * DW_CU_BYTES_PER_CYCLE);
     return (uint64_t)(std::max(cycles, C_LAUNCH + mem) * PS_PER_CYCLE);
@@ -2488,6 +2500,14 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
                      named && g_skd_force.mode == 0 ? never : g_skd_force, small))
         return s;
     const bool forced = (small.kind == GK_SKD ? g_skd_force : g_skc_force).mode == 1;
+    // A pair of at most 128 output channels whose pixels make more than one split-K item per CU, but whole rounds of the XCDs in
+    // tiles, stays on the tile kernel, whose price is 1.3 us high there: 64 -> 64 channels 4.25 us against 4.9, 128 -> 128 4.65
+    // against 5.6, 256 -> 128 5.5 against 6.6 (at other tile counts 6.0, 6.8 and 8.4; at 256 outputs 5.8 - 7.1 against 5.7 - 6.6).
+    if (!forced && s == DLF_OK && small.kind == GK_SKD && g.kind == GK_DWT && small.grid > budget && g.dt.ntiles <= budget &&
+        g.dt.ntiles % 8 == 0 && net.L[first].d.cin >= 64 && net.L[last].d.cout <= 128) {
+        g.cost = std::min(g.cost, small.cost);
+        return s;
+    }
     if (!forced && (s != DLF_OK || g.cost <= small.cost)) return s;
     g = small;
     return DLF_OK;

@@ -261,6 +261,25 @@ def test_small_map_or_split_k(c, hw, batch, split):
     assert cfg["kind"] == 10 and (cfg["variant"] >= 16) == split, cfg
 
 
+@pytest.mark.parametrize("c,cout,hw,batch,kinds", [
+    # eight waves fill a CU: one item per CU at most (1024 channels at 7 x 7: batch 4 8.5 us against 10.2 in two launches, batch 6 15.1
+    # against 13.6; 1280 at 7 x 7: batch 2 9.4 and 10.6, batch 4 16.4 and 12.5; 1376 at 10 x 10, batch 2 17.8 and 14.0)
+    (1024, 1024, 7, 4, [6]), (1024, 1024, 7, 6, [5, 10]), (1024, 1024, 7, 8, [5, 10]), (1280, 1280, 7, 2, [6]), (1280, 1280, 7, 4, [5, 10]),
+    (1376, 1376, 10, 2, [5, 10]),
+    # four waves: a second item runs beside the first (512 channels at 14 x 14, batch 2 and 4: 6.2 and 8.8 us against 10.8 and 10.9)
+    (512, 512, 14, 2, [6]), (512, 512, 14, 4, [6]),
+    # the tile kernel, in whole rounds of the XCDs (168 - 224 tiles), and not otherwise (180)
+    (128, 128, 56, 1, [7]), (128, 128, 28, 3, [7]), (64, 64, 28, 6, [7]), (256, 128, 14, 12, [7]), (256, 128, 20, 6, [6]), (256, 256, 20, 3, [6])])
+def test_pairs_beyond_one_item_per_cu(c, cout, hw, batch, kinds):
+    """Depthwise + 1x1 pairs go to the split-K kernel only where it is the faster plan."""
+    n = B.dlf_net_create([nets.dwconv(c, 3, 1, "relu"), nets.conv(c, cout, 1, 1, 0, "relu")], hw, hw, c)
+    p = B.dlf_plan(n, batch)
+    got = [B.dlf_plan_group_config(p, g)["kind"] for g in range(B.dlf_plan_num_groups(p))]
+    B.dlf_plan_destroy(p)
+    B.dlf_net_destroy(n)
+    assert got == kinds
+
+
 def test_first_layer_pair_is_not_priced_lower_for_more_images():
     """3 -> 64 -> 64 channels at 128 x 128 as one launch of the block kernel (forced): batches that leave half of the chip idle are all
     priced by the same rule."""
