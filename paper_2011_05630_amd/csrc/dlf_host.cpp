@@ -348,16 +348,26 @@ const int64_t C_BN_LAST = 5000;              // ... less without the last layer
 const int64_t C3PW_OVERLAP_PCT = 60;         // two workgroups per CU: what a further round of items adds, in per cent of an item
 
 // split-K convolution kernel: a launch of one round trip, then the rate at which a CU takes operands in (52 to 70 bytes per cycle
-// for a workgroup alone on its CU, fitted to 22 layer shapes in chains of 8 layers, within 6 % but for 1x1 layers of 64 K steps, 13 %
-// high).  Launches of several items per CU are priced as before the activations came in by whole lines: the kernels they compete
+// for a workgroup alone on its CU; 1x1 layers, whose rows no second tap meets in the first-level cache, less on the larger items).
+// Fitted to 460 launches of one item per CU at most (1x1 and 3x3, 32 - 2048 channels, in chains of 8 layers), within 6 % for 9 of 10.
+// Launches of several items per CU are priced as before the activations came in by whole lines: the kernels they compete
 // with are priced high there, and what the rates below give them is what kept the choices right.
 // The residual operand: measured 0.02 - 0.12 us (64 - 512 channels, 7 x 7 to 56 x 56).
-const int64_t C_SKC_ITEM[DLF_SKC_SHAPES] = {-1750, -1800, -2400, 1000};
-const int64_t C_SKC_LOAD[DLF_SKC_SHAPES] = {0, 0, 15, 0};       // ... and per item of the launch (256 channels: 52 items 6.1 us, 196 6.9)
+const int64_t C_SKC_ITEM[DLF_SKC_SHAPES] = {-2150, -2000, -2400, 600};
+const int64_t C_SKC_ITEM_1X1[DLF_SKC_SHAPES] = {-2700, -2500, -1750, 1000};
+const int64_t C_SKC_EIGHT = 500;             // ... more with eight waves
+const int64_t C_SKC_LOAD[DLF_SKC_SHAPES] = {0, 0, 15, 0};       // ... and per item of the launch (the small-map kernel is priced high beside it)
+const int64_t C_SKC_LOAD_1X1[DLF_SKC_SHAPES] = {0, 0, 8, 0};
 const int64_t C_SKC_MANY = -900;             // ... more than one item per CU
 const int64_t C_SKC_RES = 150;
 const int64_t SKC_FEW_ITEMS = 128;
-const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {52, 60, 65, 62};
+// 1x1 layers of more than that many of the largest items: their rows share no cache lines (512 channels, 152 items 5.5 us; 1024, 160 items
+// 6.6), and inputs above that size are read anew by every XCD (1024 -> 256, 2.7 MB, 164 items 7.5 us; 2048 -> 512, 2.3 MB, 144 items 9.4)
+const int64_t C_SKC_ROWS = 200;
+const int64_t SKC_ROWS_BYTES_PER_CYCLE = 34;
+const int64_t SKC_ROWS_BYTES = 2 << 20;
+const int64_t SKC_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {52, 60, 65, 52};
+const int64_t SKC_BYTES_PER_CYCLE_1X1[DLF_SKC_SHAPES] = {52, 60, 52, 43};
 const int64_t SKC_BYTES_PER_CYCLE_8 = 70;    // eight waves
 const int64_t SKC_MANY_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {49, 49, 49, 34};
 const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
@@ -1766,17 +1776,25 @@ uint64_t skc_cost_ps(const Layer& L, const Layer* proj, const DlfSkcArgs& sk, in
     const int64_t items = (int64_t)sk.n_pg * sk.n_cg;
     const int64_t has_res = L.d.residual_from >= 0 && !proj ? 1 : 0;
     const int64_t bytes = (int64_t)(sk.nk + sk.nk2) * (SKC_TP[shape] + SKC_TC[shape]) * 1024;
-    int64_t intake = items > budget ? bytes / SKC_MANY_BYTES_PER_CYCLE[shape] : bytes / (sk.nw == 8 ? SKC_BYTES_PER_CYCLE_8 : SKC_BYTES_PER_CYCLE[shape]);
-    // the taps of a 3x3 filter meet in the first-level cache, a long 1x1 row does not (2048 channels, 240 items: 12 us)
-    if (shape == 3 && sk.kh * sk.kw == 1 && items > SKC_FEW_ITEMS) intake = bytes / SKC_SHARED_BYTES_PER_CYCLE[shape];
-    if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
-    // ... and never faster than the tensors pass: the input pixels the filter meets, the output, the residual operand, the weights
     const int64_t m = (int64_t)batch * L.out_h * L.out_w;
     const int64_t in = std::min((int64_t)batch * L.in_h * L.in_w, m * L.d.kh * L.d.kw);
+    const bool row = sk.kh * sk.kw == 1;
+    int64_t intake = bytes / (sk.nw == 8 ? SKC_BYTES_PER_CYCLE_8 : (row ? SKC_BYTES_PER_CYCLE_1X1 : SKC_BYTES_PER_CYCLE)[shape]);
+    int64_t item = (row ? C_SKC_ITEM_1X1 : C_SKC_ITEM)[shape] + (sk.nw == 8 ? C_SKC_EIGHT : 0) + items * (row ? C_SKC_LOAD_1X1 : C_SKC_LOAD)[shape];
+    if (row && shape == 3 && items > SKC_FEW_ITEMS) {
+        intake = bytes / (in * L.d.cin * 2 > SKC_ROWS_BYTES ? SKC_SHARED_BYTES_PER_CYCLE[shape] : SKC_ROWS_BYTES_PER_CYCLE);
+        item += C_SKC_ROWS;
+    }
+    if (items > budget) {
+        intake = bytes / (row && shape == 3 ? SKC_SHARED_BYTES_PER_CYCLE : SKC_MANY_BYTES_PER_CYCLE)[shape];
+        item = C_SKC_MANY;
+    }
+    if (items > budget) intake = std::max(intake, items * bytes / (budget * SKC_SHARED_BYTES_PER_CYCLE[shape]));
+    // ... and never faster than the tensors pass: the input pixels the filter meets, the output, the residual operand, the weights
     int64_t hbm = in * L.d.cin * 2 + (sk.pool2 ? m / 4 : m) * L.d.cout * 2 * (1 + has_res) + (int64_t)L.ncb * L.nsteps * 1024;
     if (proj) hbm += m * proj->d.cin * 2 + (int64_t)proj->ncb * proj->nsteps * 1024;
     const int64_t mem = hbm / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
-    int64_t cycles = C_LAUNCH + (items > budget ? C_SKC_MANY : C_SKC_ITEM[shape] + items * C_SKC_LOAD[shape]) + std::max(intake + has_res * C_SKC_RES, mem);
+    int64_t cycles = C_LAUNCH + item + std::max(intake + has_res * C_SKC_RES, mem);
     // 32 pixels x 64 channels on nearly every CU: 15 - 20 % above the fit (64 -> 64 3x3 at 32 x 32, batch 7, 224 items: 6.2 us, not 5.3)
     if (shape == 3 && items <= budget && items * 4 > (int64_t)budget * 3) cycles = cycles * 5 / 4;
     // The kernel is for launches of at most about one item per CU.  Beyond that the models of the

@@ -261,6 +261,19 @@ def test_small_map_or_split_k(c, hw, batch, split):
     assert cfg["kind"] == 10 and (cfg["variant"] >= 16) == split, cfg
 
 
+@pytest.mark.parametrize("cin,cout,k,hw,batch,forms", [
+    # short K: items of few channels (256 1x1 at 7 x 7 2.9 us, 3.6 on items of 64 channels; 32 3x3 at 14 x 14 3.2 and 3.7)
+    (256, 256, 1, 7, 1, (16, 17)), (192, 192, 1, 9, 1, (16, 17)), (128, 128, 1, 14, 1, (16, 17)), (32, 32, 3, 14, 1, (16, 17)),
+    # long K on items of 32 x 64: the small-map kernel (256 3x3 at 9 x 9, batch 16 7.1 us against 8.6; 512 at 20 x 20, batch 2 11.3 and 12.5)
+    (256, 256, 3, 9, 16, (4,)), (512, 512, 3, 20, 2, (4,)), (512, 512, 3, 12, 4, (4,)), (2048, 512, 1, 9, 7, (12,)),
+    # 1x1 layers of at most 192 such items (512 channels at 7 x 7, batch 12 5.5 us against 6.2; 1024 at batch 6 6.6 and 8.4)
+    (512, 512, 1, 7, 12, (19,)), (1024, 1024, 1, 7, 6, (19,))])
+def test_split_k_form_of_a_layer(cin, cout, k, hw, batch, forms):
+    """Single convolutions on the faster of the split-K kernel's item shapes and the small-map kernel."""
+    cfg, _ = _plan([nets.conv(cin, cout, k, 1, k // 2, "relu")], hw, hw, batch)
+    assert cfg["kind"] == 10 and cfg["variant"] in forms, cfg
+
+
 @pytest.mark.parametrize("c,cout,hw,batch,kinds", [
     # eight waves fill a CU: one item per CU at most (1024 channels at 7 x 7: batch 4 8.5 us against 10.2 in two launches, batch 6 15.1
     # against 13.6; 1280 at 7 x 7: batch 2 9.4 and 10.6, batch 4 16.4 and 12.5; 1376 at 10 x 10, batch 2 17.8 and 14.0)
