@@ -359,6 +359,7 @@ const int64_t C_SKC_EIGHT = 500;             // ... more with eight waves
 const int64_t C_SKC_LOAD[DLF_SKC_SHAPES] = {0, 0, 15, 0};       // ... and per item of the launch (the small-map kernel is priced high beside it)
 const int64_t C_SKC_LOAD_1X1[DLF_SKC_SHAPES] = {0, 0, 8, 0};
 const int64_t C_SKC_MANY = -900;             // ... more than one item per CU
+const int64_t C_SKC_ALONE = 170;             // ... a step more in a wave's share, where the LDS limit holds fewer waves (512 channels 3x3: 4, 2 and 1 waves 6.0, 8.9 and 15.2 us)
 const int64_t C_SKC_RES = 150;
 const int64_t SKC_FEW_ITEMS = 128;
 // 1x1 layers of more than that many of the largest items: their rows share no cache lines (512 channels, 152 items 5.5 us; 1024, 160 items
@@ -377,6 +378,7 @@ const int64_t SKC_SHARED_BYTES_PER_CYCLE[DLF_SKC_SHAPES] = {28, 28, 28, 25};
 const int64_t C_SKD_LEAST = 10800;
 const int64_t C_SKD_ITEM[DLF_SKD_SHAPES] = {8500, 9100};
 const int64_t C_SKD_STEP = 237;
+const int64_t C_SKD_ALONE = 950;             // ... and a step more in a wave's share, where the LDS limit holds fewer waves
 const int64_t C_SKD_ROUND = 700;
 const int64_t C_SKD_ROUND_STEP = 205;
 // ... with eight waves, which fill a CU, so that a further item runs behind the first and not beside it (1024 channels at 7 x 7, items
@@ -1814,8 +1816,10 @@ bool skc_choose(const Layer& L, const Layer* proj, int pool2, int batch, int bud
         if (force.shape >= 0 && sh != force.shape) continue;
         DlfSkcArgs sk;
         skc_fill(L, proj, pool2, batch, sh, force.waves, sk);
+        const int ksw = sk.ksw;
+        while (force.waves <= 0 && sk.nw > 1 && skc_lds_bytes(sk, sh) > max_lds) skc_fill(L, proj, pool2, batch, sh, sk.nw / 2, sk);
         if (!sk_items_ok(sk.n_pg, sk.n_cg, budget) || skc_lds_bytes(sk, sh) > max_lds) continue;
-        const uint64_t c = skc_cost_ps(L, proj, sk, batch, sh, budget);
+        const uint64_t c = skc_cost_ps(L, proj, sk, batch, sh, budget) + (uint64_t)((sk.ksw - ksw) * C_SKC_ALONE * PS_PER_CYCLE);
         if (!found || c < cost) { found = true; cost = c; best = sk; shape = sh; }
     }
     return found;
@@ -1880,8 +1884,10 @@ bool skd_choose(const Layer& D, const Layer& P, int batch, int budget, int max_l
         if (force.shape >= 0 && sh != force.shape) continue;
         DlfSkdArgs sd;
         skd_fill(D, P, batch, sh, force.waves, sd);
+        const int ksw = sd.ksw;
+        while (force.waves <= 0 && sd.nw > 1 && skd_lds_bytes(sd, sh) > max_lds) skd_fill(D, P, batch, sh, sd.nw / 2, sd);
         if (!sk_items_ok(sd.n_pg, sd.n_cg, budget) || skd_lds_bytes(sd, sh) > max_lds) continue;
-        const uint64_t c = skd_cost_ps(D, P, sd, sh, budget);
+        const uint64_t c = skd_cost_ps(D, P, sd, sh, budget) + (uint64_t)((sd.ksw - ksw) * C_SKD_ALONE * PS_PER_CYCLE);
         if (!found || c < cost) { found = true; cost = c; best = sd; shape = sh; }
     }
     return found;

@@ -130,6 +130,17 @@ def test_launches_keep_to_the_lds_limit():
     assert seen > 60, seen
 
 
+@pytest.mark.parametrize("layers,hw,max_lds", [
+    ([nets.conv(512, 512, 1, 1, 0, "relu")], 7, 4096),           # 3.9 us with one wave, 5.4 on the pointwise kernel
+    ([nets.conv(256, 256, 3, 1, 1, "relu")], 14, 4096),          # 8.9, 11.5 on the fused-group kernel
+    ([nets.conv(512, 512, 3, 1, 1, "relu")], 7, 16384),          # 6.0 with four waves, 17.7
+    ([nets.dwconv(256, 3, 1, "relu"), nets.conv(256, 256, 1, 1, 0, "relu")], 14, 16384)])
+def test_fewer_waves_under_an_lds_limit(layers, hw, max_lds):
+    """Where an LDS limit does not hold the waves a split-K launch has otherwise, it has fewer."""
+    cfg, _ = _plan(layers, hw, hw, 1, max_lds=max_lds)
+    assert cfg["kind"] in (6, 10) and cfg["variant"] >= 16 and 0 < cfg["lds_bytes"] <= max_lds, cfg
+
+
 @pytest.mark.parametrize("layers,h,w,batch,max_lds", [
     ([nets.conv(96, 88, 3, 1, 1, "relu"), nets.maxpool(88, 2, 2, 0)], 6, 8, 2, 4096),
     ([nets.conv(256, 928, 5, 3, 4, "relu")], 33, 13, 1, 16384), ([nets.conv(352, 32, 3, 2, 1, "relu")], 37, 11, 1, 4096),
