@@ -110,7 +110,8 @@ PW_NAME = {0: "k_pw<2,2,6,2>", 1: "k_pw<1,1,8,4>", 2: "k_pw_sk", 3: "k_pwb<2,2>"
 PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>", 17: "k_skc<1,2,4,true>",
             18: "k_skc<1,4,3,true>", 19: "k_skc<2,4,3,true>"}
 SKC_NAME = {16: "k_skc<1,1,4>", 17: "k_skc<1,2,4>", 18: "k_skc<1,4,3>", 19: "k_skc<2,4,3>"}
-FC_NAME = {0: "k_fc<1,4>", 1: "k_fc<1,8>", 2: "k_fc<2,4>", 3: "k_fc_sk"}
+FC_NAME = {0: "k_fc<1,4>", 1: "k_fc<1,8>", 2: "k_fc<2,4>", 3: "k_fc_sk", 4: "k_fc<1,2>", 5: "k_fc<1,1>", 6: "k_fc_few<4>",
+           7: "k_fc_few<2>", 8: "k_fc_few<1>", 9: "k_fc<2,2>", 10: "k_fc<2,1>"}
 DW_NAME = {0: "k_dw<1>", 1: "k_dw<2>"}
 C3_NAME = {0: "k_c3b<2,32,2>", 1: "k_c3b<2,64,2>", 2: "k_c3b<1,32,2>", 3: "k_c3b<1,64,2>", 4: "k_c3b<2,32,4>",
            16: "k_c3r<4,7,64,10>", 17: "k_c3r<4,4,64,6>", 18: "k_c3r<2,7,64,17>", 19: "k_c3r<2,4,64,11>",

@@ -183,7 +183,8 @@ dlf_status dlf_run_group(const dlf_plan_t* plan, int32_t g, const void* in_dev, 
 const void* dlf_plan_layer_output(const dlf_plan_t* plan, int32_t layer);
 
 /* Kernel configuration chosen for group g: kind (0 fused-group kernel, 1 FC (variant 0 / 1 = 16 images per workgroup, K short /
- * long, 2 = 32 images, 3 = K split over workgroups, two launches), 2 global avgpool,
+ * long, 2 = 32 images, 3 = K split over workgroups, two launches; under an LDS limit 4 .. 8 = 16 images in 32, 16, 8, 4
+ * and 2 KiB, 9 and 10 = 32 images in 64 and 32 KiB), 2 global avgpool,
  * 3 pointwise-convolution kernels: a single 1x1 layer, 4 block 3x3 kernel: a single 3x3 stride-1
  * pad-1 layer, with its folded 2x2 pool or residual); variant: for kind 0 the register tile
  * (per-wave accumulator tile, output channels x pixels: 0 = 64x64, 1 = 32x128, 2 = 32x64,

@@ -219,7 +219,8 @@ const int64_t C_STORE_VEC = 80;             // per 512 stored 16-byte vectors
 const int64_t C_STORE = 1600;
 const int64_t MFMA_CYCLES = 32;             // one 32x32x16 MFMA on one SIMD
 const int64_t FC_SPLIT_HBM_BYTES_PER_CYCLE = 1900;   // weight streaming rate of the FC kernels
-const int64_t FC_CU_BYTES_PER_CYCLE = 50;   // ... and what one CU takes in, weights and activations
+const int64_t FC_CU_BYTES_PER_CYCLE = 50;   // ... and what one CU takes in, weights and activations, with weights of at least
+const int64_t FC_RING_BYTES = 20480;        // that size in flight
 const int64_t GAP_BYTES_PER_CYCLE = 1000;
 // pointwise kernel, per item shape: register tile (FC x FP blocks of 32), operand ring depth,
 // independent waves per CU
@@ -1972,17 +1973,27 @@ bool dws_choose(const Layer& D, const Layer& P, int batch, int budget, int max_l
 // force_tc / pw_mode: explicit values for the two testing hooks (null / -1: the process-wide ones)
 // Fully connected layer: one workgroup per 16 output channels and 16 or 32 images with all of K, or, where that is
 // cheaper, pairs of 32-channel blocks with K split 2, 4 or 8 ways (at most 256 workgroups), a second
-// launch adding the slices: what a workgroup then takes in per K step is 3 KiB for two MFMAs.
-uint64_t fc_cost_ps(const Layer& L, int batch, int& ksplit)
+// launch adding the slices: what a workgroup then takes in per K step is 3 KiB for two MFMAs.  The budget limits the workgroups
+// of neither (nor those of the global average pool).  Under an LDS limit the rings are shorter, at 16 images, and below eight of the shortest the waves are fewer: `form`, or -1.
+uint64_t fc_cost_ps(const Layer& L, int batch, int max_lds, int& ksplit, int& form)
 {
     const int64_t nbb = ceil_div(batch, 32);
     const int64_t wbytes = (int64_t)L.ncb * L.nsteps * 1024 * nbb;
-    const int64_t blocks = batch > 16 ? 2 : 1, groups = ceil_div(batch, 16 * (int)blocks);
-    const int64_t rounds = (ceil_div(L.d.cout, 16) * groups + 255) / 256;
-    const int64_t all = rounds * (L.nsteps / 2) * (1 + blocks) * 1024 / FC_CU_BYTES_PER_CYCLE;
-    uint64_t best = (uint64_t)((C_LAUNCH + C_LAT + std::max(all, wbytes / FC_SPLIT_HBM_BYTES_PER_CYCLE)) * PS_PER_CYCLE);
     ksplit = 1;
-    for (int ks = 2; ks <= 8; ks *= 2) {
+    form = DLF_FC_FORM(batch, L.nsteps);
+    static const int lesser[2][6] = {{0, 4, 5, 6, 7, 8}, {9, 10, 5, 6, 7, 8}};
+    for (const int f : lesser[batch > 16 ? 1 : 0])
+        if (DLF_FC_LDS[form] > max_lds) form = f;
+    if (DLF_FC_LDS[form] > max_lds) form = -1;
+    uint64_t best = UINT64_MAX;
+    if (form >= 0) {
+        const int64_t images = DLF_FC_IMAGES(form), groups = ceil_div(batch, (int)images);
+        const int64_t rounds = (ceil_div(L.d.cout, 16) * groups + 255) / 256;
+        const int64_t rate = FC_CU_BYTES_PER_CYCLE * std::min<int64_t>(DLF_FC_LDS[form] * 16 / images, FC_RING_BYTES) / FC_RING_BYTES;
+        const int64_t all = rounds * (L.nsteps / 2) * (1 + images / 16) * 1024 / rate;
+        best = (uint64_t)((C_LAUNCH + C_LAT + std::max(all, wbytes / FC_SPLIT_HBM_BYTES_PER_CYCLE)) * PS_PER_CYCLE);
+    }
+    for (int ks = 2; ks <= 8 && DLF_FC_LDS[DLF_FC_SPLIT] <= max_lds; ks *= 2) {
         if (ceil_div(L.ncb, 2) * ks > 256 || L.nsteps < 64 * ks) continue;
         const int64_t intake = 3 * (int64_t)ceil_div(L.nsteps, ks) * 1024 * nbb / PW_BYTES_PER_CYCLE;
         const int64_t hbm = wbytes / FC_SPLIT_HBM_BYTES_PER_CYCLE;
@@ -2044,13 +2055,17 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
         fa.batch = batch; fa.k = L0.d.cin; fa.cout = L0.d.cout; fa.ncb = L0.ncb;
         fa.nsteps = L0.nsteps; fa.act = L0.d.act;
         int ksplit = 1;
-        g.cost = fc_cost_ps(L0, batch, ksplit);
+        g.cost = fc_cost_ps(L0, batch, max_lds, ksplit, fa.form);
         if (force.th > 0 && (force.nslices == 1 || force.nslices == 2 || force.nslices == 4 || force.nslices == 8))
             ksplit = force.nslices;                     // testing hook
+        const int form = ksplit > 1 ? DLF_FC_SPLIT : fa.form;
+        if (form < 0 || DLF_FC_LDS[form] > max_lds)
+            return fail(DLF_ERR_INFEASIBLE, "layer %d: no fully connected kernel within %d bytes of LDS", first, max_lds);
         fa.ksplit = ksplit;
         g.scratch_bytes = ksplit > 1 ? (size_t)ksplit * ceil_div(batch, 32) * L0.ncb * 4096 : 0;
-        g.variant = ksplit > 1 ? 3 : DLF_FC_SHAPE(batch, L0.nsteps);
-        g.grid = L0.ncb;
+        g.variant = form;
+        g.lds_bytes = DLF_FC_LDS[form];
+        g.grid = ksplit > 1 ? ceil_div(L0.ncb, 2) * ksplit : DLF_FC_GRID(batch, L0.d.cout, form);
         g.th = g.tw = 1;
         return DLF_OK;
     }

@@ -73,8 +73,17 @@ struct DlfGroupArgs {
 };
 
 #define DLF_FC_WAVES 8
-// k_fc's forms: 0 / 1 = 16 images, 4 / 8 turns of 64 K values ahead (a wave's share is up to 4 turns / longer), 2 = 32 images, 4 turns
-#define DLF_FC_SHAPE(BATCH, NSTEPS) ((BATCH) > 16 ? 2 : (NSTEPS) > 16 * DLF_FC_WAVES ? 1 : 0)
+// k_fc's forms: 0 / 1 = 16 images, 4 / 8 turns of 64 K values ahead (a wave's share is up to 4 turns / longer), 2 = 32 images, 4 turns,
+// 3 = K split over workgroups (k_fc_sk); under an LDS limit 4 / 5 = 16 images, 2 / 1 turns, 6 / 7 / 8 = 1 turn, four, two and one wave,
+// 9 / 10 = 32 images, 2 / 1 turns
+#define DLF_FC_FORMS 11
+#define DLF_FC_SPLIT 3
+#define DLF_FC_FORM(BATCH, NSTEPS) ((BATCH) > 16 ? 2 : (NSTEPS) > 16 * DLF_FC_WAVES ? 1 : 0)
+static constexpr int DLF_FC_FORM_WAVES[DLF_FC_FORMS] = {8, 8, 8, 8, 8, 8, 4, 2, 1, 8, 8};
+static constexpr int DLF_FC_LDS[DLF_FC_FORMS] = {65536, 131072, 131072, 36864, 32768, 16384, 8192, 4096, 2048, 65536, 32768};
+#define DLF_FC_IMAGES(FORM) ((FORM) == 2 || (FORM) > 8 ? 32 : 16)
+// workgroups: 16 channels, a multiple of eight of them (the XCDs), by the image groups
+#define DLF_FC_GRID(BATCH, COUT, FORM) (((COUT) + 127) / 128 * 8 * (((BATCH) + DLF_FC_IMAGES(FORM) - 1) / DLF_FC_IMAGES(FORM)))
 struct DlfFcArgs {
     const void* x;        // [batch][k] fp16
     void* y;              // [batch][cout] fp16
@@ -83,6 +92,7 @@ struct DlfFcArgs {
     int32_t batch, k, cout, ncb, nsteps, act;
     int32_t ksplit;       // > 1: K is split over ksplit workgroups per pair of channel blocks ...
     float* part;          // ... which leave fp32 partial sums here: [batch block][ksplit][ncb][16][64]
+    int32_t form;         // of DLF_FC_FORMS, if not split
 };
 
 // Pointwise (1x1, pad 0) convolution run without tiles or barriers: every wave owns work items

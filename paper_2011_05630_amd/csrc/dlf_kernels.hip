@@ -4811,8 +4811,9 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
 // Per launch, as one workgroup per 32 channels or k_fc_sk and k_fc_fin -> now: 25088 -> 4096 45.0 -> 31.3 us at batch 1 (6.6 TB/s of
 // weights, part of them from the last-level cache), 48.9 -> 36.8 at 16, 54.2 -> 47.1 at 32; 9216 -> 4096 21.7 -> 12.4 and 22.8 -> 14.9;
 // 4096 -> 4096 at batch 16 10.2 -> 6.7; 4096 -> 1000 at batch 64 12.4 -> 6.8 (6.7 is the host's time per call).
-template <int TP, int D>
-__global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
+// The rings are what an LDS limit shortens (25088 -> 4096 at batch 1 with 128 / 32 / 16 / 8 / 4 / 2 KiB: 32 / 30 / 36 / 58 / 101 / 189 us).
+template <int TP, int D, int W>
+__device__ __forceinline__ void fc_item(const DlfFcArgs& a)
 {
     constexpr int P = 16 * TP, WB = D * TP * 2048;           // a wave's LDS: its ring of "B" operands, then its partial sums
     static_assert(WB >= P * 16 * 4, "partial sums");
@@ -4823,7 +4824,7 @@ __global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
     const int n_pg = (a.batch + P - 1) / P, n_cg = (a.cout + 15) >> 4;
     const int j = (int)blockIdx.x >> 3, pg = j % n_pg, cg = (j / n_pg) * 8 + ((int)blockIdx.x & 7);
     if (cg >= n_cg) return;
-    const int nk = (a.nsteps + 3) >> 2, ksw = (nk + DLF_FC_WAVES - 1) / DLF_FC_WAVES;
+    const int nk = (a.nsteps + 3) >> 2, ksw = (nk + W - 1) / W;
     const int k0 = wave * ksw, k1 = min(k0 + ksw, nk);
     f4v acc[TP];
 #pragma unroll
@@ -4890,13 +4891,28 @@ __global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
 #pragma unroll
     for (int p = 0; p < TP; ++p) *(f4v*)(part + wave * (WB / 4) + (p * 16 + r16) * 16 + q * 4) = acc[p];
     __syncthreads();
-    const int im = pg * P + (tid >> 4), co = cg * 16 + (tid & 15);
-    if (tid < P * 16 && co < a.cout && im < a.batch) {
+#pragma unroll
+    for (int e = tid; e < P * 16; e += W * 64) {
+        const int im = pg * P + (e >> 4), co = cg * 16 + (e & 15);
+        if (co >= a.cout || im >= a.batch) continue;
         float s = 0.0f;
 #pragma unroll
-        for (int w = 0; w < DLF_FC_WAVES; ++w) s += part[w * (WB / 4) + tid];
+        for (int w = 0; w < W; ++w) s += part[w * (WB / 4) + e];
         ((half_t*)a.y)[(size_t)im * a.cout + co] = (half_t)apply_act(s + a.bias[co], a.act);
     }
+}
+
+template <int TP, int D>
+__global__ __launch_bounds__(DLF_FC_WAVES * 64) void k_fc(const DlfFcArgs a)
+{
+    fc_item<TP, D, DLF_FC_WAVES>(a);
+}
+
+// ... on fewer waves, for an LDS limit below eight rings of one turn (2 KiB each)
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_fc_few(const DlfFcArgs a)
+{
+    fc_item<1, 1, W>(a);
 }
 
 // A depthwise 3x3 layer (pad 1, stride 1 or 2) and the 1x1 layer behind it for outputs of few pixels: the pairs of
@@ -5139,7 +5155,22 @@ template <bool I8> static c3_kernel_t c3r_kernel(int shape)
 }
 
 typedef void (*FcKernel)(const DlfFcArgs);
-static FcKernel fc_kernel(int shape) { return shape == 0 ? k_fc<1, 4> : shape == 1 ? k_fc<1, 8> : k_fc<2, 4>; }
+static FcKernel fc_kernel(int form)
+{
+    switch (form) {
+    case 0: return k_fc<1, 4>;
+    case 1: return k_fc<1, 8>;
+    case 2: return k_fc<2, 4>;
+    case 4: return k_fc<1, 2>;
+    case 5: return k_fc<1, 1>;
+    case 6: return k_fc_few<4>;
+    case 7: return k_fc_few<2>;
+    case 8: return k_fc_few<1>;
+    case 9: return k_fc<2, 2>;
+    case 10: return k_fc<2, 1>;
+    default: return nullptr;
+    }
+}
 
 static void (*skd_kernel(int shape))(const DlfSkdArgs) { return shape == 0 ? k_skd<2> : k_skd<4>; }
 
@@ -5258,6 +5289,7 @@ extern "C" int dlf_launch_group(const DlfGroupArgs* a, int variant, int grid, in
 extern "C" int dlf_launch_fc(const DlfFcArgs* a, void* stream)
 {
     if (a->ksplit > 1) {
+        static_assert(DLF_FC_WAVES * DLF_FC_BBYTES == DLF_FC_LDS[DLF_FC_SPLIT], "k_fc_sk's LDS");
         if (a->part == nullptr) return (int)hipErrorInvalidValue;
         // a stop event requested for "the next launch" belongs to the second of the two
         hipEvent_t stop = g_ev_stop;
@@ -5269,10 +5301,9 @@ extern "C" int dlf_launch_fc(const DlfFcArgs* a, void* stream)
         return (int)hipGetLastError();
     }
     if (a->nsteps & 1) return (int)hipErrorInvalidValue;     // whole 32-channel chunks of K
-    const int shape = DLF_FC_SHAPE(a->batch, a->nsteps), images = shape == 2 ? 32 : 16;
-    const int grid = ((a->cout + 15) / 16 + 7) / 8 * 8 * ((a->batch + images - 1) / images);
-    const int ring = DLF_FC_WAVES * 1024 * (shape == 0 ? 8 : 16);
-    launch(fc_kernel(shape), dim3(grid), dim3(DLF_FC_WAVES * 64), ring, (hipStream_t)stream, *a);
+    if (a->form < 0 || a->form >= DLF_FC_FORMS || a->form == DLF_FC_SPLIT) return (int)hipErrorInvalidValue;
+    launch(fc_kernel(a->form), dim3(DLF_FC_GRID(a->batch, a->cout, a->form)), dim3(DLF_FC_FORM_WAVES[a->form] * 64), DLF_FC_LDS[a->form],
+           (hipStream_t)stream, *a);
     return (int)hipGetLastError();
 }
 

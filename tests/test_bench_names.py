@@ -14,6 +14,6 @@ def test_kernel_names_are_the_librarys():
             names.add(bench.kernel_short_name(line[line.index(" k_") + 1:].replace("__device_stub__", "")))
         elif "__device_stub__k_" in line:
             names.add(bench.kernel_short_name(line[line.index("__device_stub__") + 15:]))
-    for table in (bench.VARIANT_NAME, bench.PW_NAME, bench.PW2_NAME, bench.SKC_NAME, bench.DW_NAME, bench.C3_NAME):
+    for table in (bench.VARIANT_NAME, bench.PW_NAME, bench.PW2_NAME, bench.SKC_NAME, bench.FC_NAME, bench.DW_NAME, bench.C3_NAME):
         for name in table.values():
             assert name in names, (name, sorted(n for n in names if n.startswith(name.split("<")[0])))

@@ -30,3 +30,27 @@ def test_fc(k, cout, batch):
     finally:
         s.close()
     compare(got, o.run_net(net, x, ws, bs), "fc")
+
+
+@pytest.mark.parametrize("limit,few,many", [(131071, 0, 9), (65536, 0, 9), (36863, 4, 10), (16384, 5, 5), (8192, 6, 6), (4096, 7, 7), (2048, 8, 8)])
+@pytest.mark.parametrize("k,cout,batch", [(8, 1, 1), (72, 33, 17), (520, 130, 16), (2056, 47, 33), (8200, 129, 5)])
+def test_fc_under_an_lds_limit(k, cout, batch, limit, few, many):
+    """The forms of a smaller LDS limit: shorter rings, fewer waves; shares longer than the ring and waves without one."""
+    from oracle import oracle as o
+    from paper_2011_05630_amd import binding as B
+    from paper_2011_05630_amd.runner import Session
+    announce("fc limit", k, cout, batch, limit)
+    net = dict(name="t", layers=[nets.fc(k, cout, "relu")], in_h=1, in_w=1, in_c=k, input_dist="normal")
+    x, ws, bs = gen.make_params(net, batch, 43)
+    B.dlf_debug_force_config(1, 1, 0, 1, 0, 0, 32)       # K not split over workgroups
+    try:
+        s = Session(net, batch, ws, bs, max_lds_bytes=limit)
+    finally:
+        B.dlf_debug_force_config(0, 0, 0, 1, 0, 0, 32)
+    try:
+        cfg = B.dlf_plan_group_config(s.plan, 0)
+        assert (cfg["kind"], cfg["variant"]) == (1, many if batch > 16 else few) and cfg["lds_bytes"] <= limit, cfg
+        got = s.run_numpy(x)
+    finally:
+        s.close()
+    compare(got, o.run_net(net, x, ws, bs), "fc limit %d" % limit)

@@ -130,6 +130,23 @@ def test_launches_keep_to_the_lds_limit():
     assert seen > 60, seen
 
 
+@pytest.mark.parametrize("k,cout", [(24, 17), (2048, 1000), (25088, 4096), (25088, 96)])
+@pytest.mark.parametrize("batch", [1, 16, 17, 70])
+def test_fully_connected_layers_keep_to_the_lds_limit(k, cout, batch):
+    """max_lds_bytes is the limit of fully connected layers too: shorter rings, then fewer waves, K split over workgroups only where its
+    36 KiB fit; below 2 KiB there is none."""
+    layers = [nets.fc(k, cout, "relu")]
+    for limit in (0, 163840, 131071, 65536, 36864, 36863, 32768, 16384, 8192, 4096, 2048):
+        cfg, _ = _plan(layers, 1, 1, batch, max_lds=limit)
+        assert cfg["kind"] == 1 and 0 < cfg["lds_bytes"] <= (limit or 163840), (limit, cfg)
+        want = {0: 65536, 1: 131072, 2: 131072, 3: 36864, 4: 32768, 5: 16384, 6: 8192, 7: 4096, 8: 2048,
+                9: 65536, 10: 32768}[cfg["variant"]]
+        assert cfg["lds_bytes"] == want and (limit > 0 or cfg["variant"] <= 3), (limit, cfg)
+    n = B.dlf_net_create(layers, 1, 1, k)
+    assert B.dlf_group_cost(n, batch, 0, 0, 256, 2047) is None
+    B.dlf_net_destroy(n)
+
+
 @pytest.mark.parametrize("layers,hw,max_lds", [
     ([nets.conv(512, 512, 1, 1, 0, "relu")], 7, 4096),           # 3.9 us with one wave, 5.4 on the pointwise kernel
     ([nets.conv(256, 256, 3, 1, 1, "relu")], 14, 4096),          # 8.9, 11.5 on the fused-group kernel
