@@ -54,3 +54,28 @@ def test_fc_under_an_lds_limit(k, cout, batch, limit, few, many):
     finally:
         s.close()
     compare(got, o.run_net(net, x, ws, bs), "fc limit %d" % limit)
+
+
+@pytest.mark.parametrize("ksplit", [2, 4, 8])
+@pytest.mark.parametrize("k,cout,batch", [(2056, 72, 17), (4136, 33, 40), (8200, 129, 5)])
+def test_split_k_on_ragged_k(k, cout, batch, ksplit):
+    """K split over workgroups where K is no multiple of 32: the last step is half beyond K (read from a stand-in address and replaced
+    by zeros), slices and waves' shares are uneven or empty; an odd number of channel blocks, two blocks of images."""
+    from oracle import oracle as o
+    from paper_2011_05630_amd import binding as B
+    from paper_2011_05630_amd.runner import Session
+    announce("fc split K", k, cout, batch, ksplit)
+    net = dict(name="t", layers=[nets.fc(k, cout, "none")], in_h=1, in_w=1, in_c=k, input_dist="normal")
+    x, ws, bs = gen.make_params(net, batch, 47)
+    B.dlf_debug_force_config(1, 1, 0, ksplit, 0, 0, 32)
+    try:
+        s = Session(net, batch, ws, bs)
+    finally:
+        B.dlf_debug_force_config(0, 0, 0, 1, 0, 0, 32)
+    try:
+        cfg = B.dlf_plan_group_config(s.plan, 0)
+        assert (cfg["kind"], cfg["variant"]) == (1, 3), cfg
+        got = s.run_numpy(x)
+    finally:
+        s.close()
+    compare(got, o.run_net(net, x, ws, bs), "fc K in %d slices" % ksplit)

@@ -513,14 +513,14 @@ def test_fc_and_global_avgpool():
     compare(got, ref, "conv-gap-fc")
     layers = [nets.fc(7 * 7 * 32, 200, "relu"), nets.fc(200, 40, "none")]
     net = _mk(layers, 7, 7, 32)
-    got, ref, _ = _run(net, 37)          # batch above 32: two passes in the FC kernel
+    got, ref, _ = _run(net, 37)          # batch above 32: two groups of images
     compare(got, ref, "fc-fc batch 37")
 
 
 def test_fc_long_ragged_k_in_one_workgroup():
-    """K = 2056: 129 K steps, so each wave's operand ring turns without tests before its last
-    turns, and the last step is half beyond K (its activation vector is read from a stand-in
-    address and replaced by zero).  K slices forced to 1: the plain kernel, not the split one."""
+    """K = 2056: 33 turns of 64 K values, five to a wave, so that the seventh wave has three and the eighth none, and the last turn is
+    mostly beyond K (pieces beyond it are not fetched and read as zeros).  K slices forced to 1: the one-launch kernel, not
+    the split one."""
     from paper_2011_05630_amd import binding as B
     from paper_2011_05630_amd.runner import Session
     from oracle import oracle as o
