@@ -363,7 +363,8 @@ def dlf_debug_force_ksplit(ksplit=1):
 
 def dlf_debug_depthwise_mode(mode=0):
     """Testing hook: 0 = depthwise kernels chosen by modelled cost, 1 = wherever they apply, 2 = never,
-    3 = wherever they apply, a depthwise + 1x1 pair always on the register kernel."""
+    3 = wherever they apply, a depthwise + 1x1 pair always on the register kernel, 4 = a pair on the kernel for maps of
+    many channels and few pixels, 5 = by modelled cost, but a first layer with a pair behind it on the kernel for the three."""
     lib().dlf_debug_depthwise_mode(mode)
 
 

@@ -322,7 +322,7 @@ const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_STEP_ONE = 125;          // ... tiles of one pixel block
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
-const int64_t C_SDP_FIRST = 3700;            // k_sdp: a CU's first tile ...
+const int64_t C_SDP_FIRST = 3700;            // k_sdp (10 % low at 64 images: 42.7 us, it takes 47.7): a CU's first tile ...
 const int64_t C_SDP_TILE = 2500;             // ... each further one ...
 const int64_t C_SDP_BLOCK = 400;             // ... and 32 channels of its 1x1 layer
 // Fewer tiles stay on the fused-group kernel, whose group goes on behind these layers: seven of MobileNet-v1's in one launch at one
@@ -2539,9 +2539,10 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
                      named && g_skd_force.mode == 0 ? never : g_skd_force, small))
         return s;
     const bool forced = (small.kind == GK_SKD ? g_skd_force : g_skc_force).mode == 1;
-    // A pair of at most 128 output channels whose pixels make more than one split-K item per CU, but whole rounds of the XCDs in
-    // tiles, stays on the tile kernel, whose price is 1.3 us high there: 64 -> 64 channels 4.25 us against 4.9, 128 -> 128 4.65
-    // against 5.6, 256 -> 128 5.5 against 6.6 (at other tile counts 6.0, 6.8 and 8.4; at 256 outputs 5.8 - 7.1 against 5.7 - 6.6).
+    // A pair of at most 128 output channels whose pixels make more than one split-K item per CU stays on the tile kernel, whose price
+    // is 1.3 us high there, where its tiles are a multiple of eight, one per workgroup: 64 -> 64 channels 4.25 us against 4.9,
+    // 128 -> 128 4.65 against 5.6, 256 -> 128 5.5 against 6.6 (at other counts some workgroups have two, and it takes 6.0, 6.8 and
+    // 8.4; at 256 output channels 5.8 - 7.1 against 5.7 - 6.6).
     if (!forced && s == DLF_OK && small.kind == GK_SKD && g.kind == GK_DWT && small.grid > budget && g.dt.ntiles <= budget &&
         g.dt.ntiles % 8 == 0 && net.L[first].d.cin >= 64 && net.L[last].d.cout <= 128) {
         g.cost = std::min(g.cost, small.cost);
