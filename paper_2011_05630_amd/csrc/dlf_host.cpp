@@ -2187,7 +2187,7 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
             g.cost = dc;
             g.variant = L0.d.stride - 1;
             g.occ = occ;
-            g.grid = std::min(budget * occ, dt.ntiles);
+            g.grid = std::min(budget * occ, round_up(dt.ntiles, 8));     // (an XCD's items: with fewer, some workgroups have two)
             g.th = dt.th; g.tw = dt.tw;
             g.lds_bytes = (int)DLF_DWT_LDS_BYTES(dt.tp, dt.c);
             return DLF_OK;
@@ -2539,12 +2539,11 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
                      named && g_skd_force.mode == 0 ? never : g_skd_force, small))
         return s;
     const bool forced = (small.kind == GK_SKD ? g_skd_force : g_skc_force).mode == 1;
-    // A pair of at most 128 output channels whose pixels make more than one split-K item per CU stays on the tile kernel, whose price
-    // is 1.3 us high there, where its tiles are a multiple of eight, one per workgroup: 64 -> 64 channels 4.25 us against 4.9,
-    // 128 -> 128 4.65 against 5.6, 256 -> 128 5.5 against 6.6 (at other counts some workgroups have two, and it takes 6.0, 6.8 and
-    // 8.4; at 256 output channels 5.8 - 7.1 against 5.7 - 6.6).
+    // A pair of at most 128 output channels whose pixels make more than one split-K item per CU, but at most one tile, stays on the
+    // tile kernel, whose price is 1.3 us high there: 64 -> 64 channels 4.25 us against 4.9, 128 -> 128 4.65 against 5.6, 256 -> 128
+    // 5.5 against 6.6 (256 -> 256 6.8 - 7.1 against 6.5 - 6.7).
     if (!forced && s == DLF_OK && small.kind == GK_SKD && g.kind == GK_DWT && small.grid > budget && g.dt.ntiles <= budget &&
-        g.dt.ntiles % 8 == 0 && net.L[first].d.cin >= 64 && net.L[last].d.cout <= 128) {
+        net.L[first].d.cin >= 64 && net.L[last].d.cout <= 128) {
         g.cost = std::min(g.cost, small.cost);
         return s;
     }
