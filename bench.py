@@ -110,6 +110,17 @@ PW_NAME = {0: "k_pw<2,2,6,2>", 1: "k_pw<1,1,8,4>", 2: "k_pw_sk", 3: "k_pwb<2,2>"
 PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>", 17: "k_skc<1,2,4,true>",
             18: "k_skc<1,4,3,true>", 19: "k_skc<2,4,3,true>"}
 SKC_NAME = {16: "k_skc<1,1,4>", 17: "k_skc<1,2,4>", 18: "k_skc<1,4,3>", 19: "k_skc<2,4,3>"}
+
+
+def skc_name(name, kh, kw, pad, alone):
+    """The split-K kernel's name for a filter: 1x1 (without padding or a pool behind it) and 3x3 have builds of their own."""
+    if kh == kw == 1 and pad == 0 and alone:
+        return name[:-1] + (",true>" if name.endswith(",true>") else ",false,true>")
+    if kh == kw == 3:
+        return name[:-1] + (",false,true>" if name.endswith(",true>") else ",false,false,true>")
+    return name
+
+
 FC_NAME = {0: "k_fc<1,4>", 1: "k_fc<1,8>", 2: "k_fc<2,4>", 3: "k_fc_sk", 4: "k_fc<1,2>", 5: "k_fc<1,1>", 6: "k_fc_few<4>",
            7: "k_fc_few<2>", 8: "k_fc_few<1>", 9: "k_fc<2,2>", 10: "k_fc<2,1>"}
 DW_NAME = {0: "k_dw<1>", 1: "k_dw<2>"}
@@ -195,7 +206,8 @@ def group_accounting(net, batch, session):
         elif cfg["kind"] == 7:
             kname = "k_dwt<%d>" % (cfg["variant"] + 1) if cfg["variant"] < 16 else "k_sdp<%d>" % (cfg["variant"] - 16)
         elif cfg["kind"] == 10 and cfg["variant"] in SKC_NAME:
-            kname = SKC_NAME[cfg["variant"]]
+            L = net["layers"][f]
+            kname = skc_name(SKC_NAME[cfg["variant"]], L["kh"], L["kw"], L["pad"], f == l)
         elif cfg["kind"] == 10:
             kname = "k_c3s<%d,%d,%d>" % (1 if cfg["variant"] >= 8 else 9, net["layers"][f]["stride"],
                                          2 if info["tile_h"] * info["tile_w"] > 32 else 1)
@@ -207,6 +219,8 @@ def group_accounting(net, batch, session):
             kname = "k_dws<%d,%d>" % (cfg["variant"] // 2 + 1, cfg["variant"] % 2 + 1)
         elif cfg["kind"] == 8:
             kname = PW2_NAME[cfg["variant"]]         # the same kernel, built for a second operand pair
+            if kname.startswith("k_skc"):
+                kname = skc_name(kname, net["layers"][l]["kh"], net["layers"][l]["kw"], net["layers"][l]["pad"], True)
         else:
             kname = VARIANT_NAME[cfg["variant"]]
         out.append(dict(first=f, last=l, budget=info["budget"], flops=flops, bytes=byts, flops3x3=flops3x3,

@@ -78,3 +78,14 @@ def test_as_many_items_as_the_budget_allows(shape, channels, pixels, h, w):
     announce("small, budget", shape, channels, h, w)
     _run(_mk([nets.conv(32, channels, 3, 1, 1, "relu")], h, w, 32), 1, [0], shape, 0, [10])
     _run(_mk([nets.conv(96, 16, 1, 1, 0, "relu")], 4, 4 * pixels, 96), 1, [0], shape, 0, [10], budget=8)
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+def test_pointwise_build(shape):
+    """The 1x1 build: a residual operand over one to eight turns of the reducing threads, ragged pixels; stride 2 on odd maps."""
+    announce("small 1x1", shape)
+    for waves in (1, 2, 4, 8):
+        _run(_mk([nets.conv(64, 160, 1, 1, 0, "relu"), nets.conv(160, 160, 1, 1, 0, "relu", residual_from=0)], 7, 9, 64),
+             2, [0, 1], shape, waves, [10, 10])
+    for h, w, batch in ((1, 1, 3), (7, 9, 2), (12, 5, 3)):
+        _run(_mk([nets.conv(96, 72, 1, 2, 0, "relu6")], h, w, 96), batch, [0], shape, 0, [10])
