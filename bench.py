@@ -104,7 +104,7 @@ def csrc_sha1():
     return h.hexdigest()
 
 
-VARIANT_NAME = {0: "k_group<2,2,2>", 1: "k_group<1,4,2>", 2: "k_group<1,2,2>", 3: "k_group<1,2,4>"}
+VARIANT_NAME = {0: "k_group<2,2,2>", 1: "k_group<1,4,2>", 2: "k_group<1,2,2>", 3: "k_group<1,2,4>", 16: "k_stem"}
 # pointwise kernels by item shape
 PW_NAME = {0: "k_pw<2,2,6,2>", 1: "k_pw<1,1,8,4>", 2: "k_pw_sk", 3: "k_pwb<2,2>", 4: "k_pwb<1,4>"}
 PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>", 17: "k_skc<1,2,4,true>",

@@ -158,7 +158,7 @@ dlf_status pack_and_upload(Layer& L)
 // Fusion groups
 // ------------------------------------------------------------------------------------------
 
-enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13, GK_C3R = 14, GK_SKD = 15 };
+enum { GK_GROUP = 0, GK_FC = 1, GK_GAP = 2, GK_PW = 3, GK_C3 = 4, GK_DW = 5, GK_DWPW = 6, GK_DWT = 7, GK_PW2 = 8, GK_DWS = 9, GK_C3S = 10, GK_C3PW = 11, GK_BNECK = 12, GK_SKC = 13, GK_C3R = 14, GK_SKD = 15, GK_STEM = 16 };
 
 struct TileCfg {
     int th, tw;      // tile of the group's final output tensor
@@ -188,7 +188,7 @@ struct GroupPlan {
     DlfDwPwArgs dp;
     DlfDwtArgs dt;
     DlfDwsArgs ds;
-    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn; DlfSkcArgs sk; DlfSkdArgs sd;
+    DlfC3sArgs cs; DlfC3PwArgs cp; DlfBnArgs bn; DlfSkcArgs sk; DlfSkdArgs sd; DlfStemArgs sm;
 };
 
 const int VAR_FC[DLF_NUM_VARIANTS] = {2, 1, 1, 1};
@@ -322,6 +322,9 @@ const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_STEP_ONE = 125;          // ... tiles of one pixel block
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
+const int64_t C_STEM_FIRST = 1000;           // k_stem (as measured: 6.3 us at 224 x 224, 25.6 at 32 images): the filter and the first patch ...
+const int64_t C_STEM_TILE = 5100;            // ... a tile's patch, barriers and pool ...
+const int64_t C_STEM_TURN = 1350;            // ... 32 pixels of the convolution on every wave of one of the CU's workgroups
 const int64_t C_SDP_FIRST = 3700;            // k_sdp (10 % low at 64 images: 42.7 us, it takes 47.7): a CU's first tile ...
 const int64_t C_SDP_TILE = 2500;             // ... each further one ...
 const int64_t C_SDP_BLOCK = 400;             // ... and 32 channels of its 1x1 layer
@@ -1325,6 +1328,67 @@ bool sdp_group(const dlf_net_s& net, int batch, int first, int last, int budget,
     g.grid = std::min(round_up(dt.ntiles, 8), round_up(budget * DLF_SDP_PER_CU, 8));
     g.cost = sdp_cost_ps(dt, budget);
     return g.lds_bytes <= max_lds;
+}
+
+// ---- 7x7 stride 2 layer on three channels and the 3x3 max pool behind it ----
+
+bool stem_eligible(const dlf_net_s& net, int first, int last, int batch)
+{
+    if (first < 0 || last != first + 1 || last >= (int)net.L.size()) return false;
+    const Layer& A = net.L[first];
+    const Layer& M = net.L[last];
+    const dlf_layer_desc& d = A.d;
+    const dlf_layer_desc& p = M.d;
+    if (d.op != DLF_CONV || !A.rowfold || d.cin != 3 || d.cout != 64 || d.kh != 7 || d.kw != 7 || d.stride != 2 || d.pad != 3 ||
+        d.residual_from >= 0 || A.nsteps != 14)
+        return false;
+    if (p.op != DLF_MAXPOOL || p.kh != 3 || p.kw != 3 || p.stride != 2 || p.pad != 1 || M.src != first || p.act != DLF_ACT_NONE) return false;
+    if ((int64_t)batch * A.in_h * A.in_w * 3 >= (int64_t)1 << 31 || (int64_t)batch * M.out_h * M.out_w * 64 >= (int64_t)1 << 31) return false;
+    for (size_t k = 0; k < net.L.size(); ++k)      // the convolution's output exists only on chip
+        if (net.L[k].d.residual_from == first || ((int)k != last && net.L[k].src == first)) return false;
+    return true;
+}
+
+bool stem_group(const dlf_net_s& net, int batch, int first, int last, int budget, int max_lds, GroupPlan& best)
+{
+    if (!stem_eligible(net, first, last, batch)) return false;
+    const Layer& A = net.L[first];
+    const Layer& M = net.L[last];
+    bool found = false;
+    auto magic = [](int d) { return 0xFFFFFFFFu / (unsigned)d + 1u; };
+    for (int th = 1; th <= 8; ++th)
+        for (int tw = 1; tw <= 8; ++tw) {
+            const int lds_bytes = DLF_STEM_LDS_BYTES(th, tw);
+            if ((4 * th + 7) * (4 * tw + 8) > DLF_STEM_IN_PIXELS || lds_bytes > max_lds) continue;
+            const int ty = ceil_div(M.out_h, th), tx = ceil_div(M.out_w, tw);
+            const int64_t tiles = (int64_t)batch * ty * tx;
+            if (tiles * std::max(tx, ty) >= (int64_t)1 << 31) continue;
+            const int64_t turns = ceil_div(ceil_div((2 * th + 1) * (2 * tw + 1), 32), 4);        // of the wave that has most
+            const int64_t per_cu = (tiles + budget - 1) / budget, rounds = (per_cu + DLF_STEM_PER_CU - 1) / DLF_STEM_PER_CU;
+            const int64_t share = std::min<int64_t>(per_cu, DLF_STEM_PER_CU);
+            const int64_t compute = C_STEM_FIRST + rounds * (C_STEM_TILE + turns * C_STEM_TURN * share);
+            const int64_t bytes = (int64_t)batch * (A.in_h * A.in_w * 6 + M.out_h * M.out_w * 128);
+            const int64_t mem = bytes / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
+            const uint64_t cost = (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
+            if (found && cost >= best.cost) continue;
+            found = true;
+            best = GroupPlan();
+            DlfStemArgs& sm = best.sm;
+            memset(&sm, 0, sizeof sm);
+            sm.w = A.d_w; sm.bias = A.d_bias;
+            sm.batch = batch; sm.h = A.in_h; sm.w_ = A.in_w; sm.ch = A.out_h; sm.cw = A.out_w; sm.oh = M.out_h; sm.ow = M.out_w; sm.act = A.d.act;
+            sm.th = th; sm.tw = tw; sm.tiles_y = ty; sm.tiles_x = tx; sm.ntiles = (int)tiles;
+            sm.iw_m = magic(4 * tw + 8); sm.cw_m = magic(2 * tw + 1); sm.tw_m = magic(tw); sm.tx_m = magic(tx); sm.ty_m = magic(ty);
+            best.first = first; best.last = last; best.budget = budget;
+            best.in_layer = A.src;
+            best.kind = GK_STEM;
+            best.th = th; best.tw = tw;
+            best.occ = DLF_STEM_PER_CU;
+            best.lds_bytes = lds_bytes;
+            best.grid = (int)std::min<int64_t>(tiles, (int64_t)budget * DLF_STEM_PER_CU);
+            best.cost = cost;
+        }
+    return found;
 }
 
 // ---- depthwise + 1x1 tile kernel ----
@@ -2531,6 +2595,13 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
             return s;
         }
     }
+    if (s == DLF_OK && !named && last == first + 1) {
+        GroupPlan stem;
+        if (stem_group(net, batch, first, last, budget, max_lds, stem) && stem.cost < g.cost) {
+            g = stem;
+            return s;
+        }
+    }
     OneLayers here;
     if (s == DLF_OK && !named) g.cost = fused_cost_ps(net, batch, budget, max_lds, g, known ? *known : here);
     const SkcForce never = {2, -1, 0};
@@ -3117,8 +3188,9 @@ dlf_status dlf_plan_group_config(const dlf_plan_t* plan, int32_t g, int32_t* kin
     // one of the two-operand kind
     // ..., the block kernel with the weights in registers as a form of the block kernel
     // ..., the depthwise pair for few pixels as a form of the register kernel
-    if (kind) *kind = G.kind == GK_C3R ? GK_C3 : G.kind == GK_SKD ? GK_DWPW : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
-    if (variant) *variant = G.kind != GK_SKC && G.kind != GK_C3R && G.kind != GK_SKD ? G.variant
+    // ..., the first layers' kernel as a form of the fused-group kernel
+    if (kind) *kind = G.kind == GK_STEM ? GK_GROUP : G.kind == GK_C3R ? GK_C3 : G.kind == GK_SKD ? GK_DWPW : G.kind != GK_SKC ? G.kind : G.sk.nk2 > 0 ? GK_PW2 : GK_C3S;
+    if (variant) *variant = G.kind == GK_STEM ? 16 : G.kind != GK_SKC && G.kind != GK_C3R && G.kind != GK_SKD ? G.variant
                             : G.kind == GK_C3R && G.ca.cin0 > 0 ? 16 + DLF_C3R_SHAPES : 16 + G.variant;
     if (nslices) *nslices = G.kind == GK_GROUP ? G.ga.nslices : 1;
     if (slice_c) *slice_c = G.kind == GK_GROUP ? G.ga.slice_c : 0;
@@ -3216,6 +3288,13 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
         DlfGapArgs pa = G.pa;
         pa.x = in; pa.y = out;
         e = dlf_launch_gap(&pa, stream);
+    } else if (G.kind == GK_STEM) {
+        DlfStemArgs sm = G.sm;
+        sm.in = in; sm.out = out;
+        DlfGroupArgs ga;
+        memset(&ga, 0, sizeof ga);
+        ga.stem = &sm;
+        e = dlf_launch_group(&ga, 0, G.grid, G.lds_bytes, stream);
     } else if (G.kind == GK_PW2) {
         DlfPwArgs wa = G.wa;
         wa.in = in; wa.out = out;

@@ -55,6 +55,7 @@ struct DlfStage {
     int32_t ks_off;       // an LDS area at this offset (halfs): [wave][FC * FP * 16][64] fp32
 };
 
+struct DlfStemArgs;
 struct DlfGroupArgs {
     const void* in;       // group input tensor (HBM)
     void* out;            // group output tensor (HBM)
@@ -70,6 +71,7 @@ struct DlfGroupArgs {
     int32_t ntiles;       // batch * tiles_y * tiles_x * nslices
     int32_t out_h, out_w, out_c;      // group output tensor shape
     DlfStage st[DLF_MAX_STAGES];
+    const DlfStemArgs* stem;     // not null: the launch is k_stem's, with these arguments (looked at by the launcher only)
 };
 
 #define DLF_FC_WAVES 8
@@ -456,6 +458,23 @@ struct DlfSkdArgs {
     int32_t n_pg, n_cg;   // groups of 16 pixels, of 16 * TC channels
     int32_t nw, ksw;      // waves per workgroup (1, 2, 4 or 8), steps per wave
     uint32_t n_cg_m, ow_m, oh_m;    // reciprocals for division by n_cg, ow, oh
+};
+
+// A 7x7 layer of stride 2 (pad 3) on three input channels, 64 output channels, and the 3x3 max pool of stride 2 (pad 1) behind it
+// (k_stem): a tile of th x tw pooled pixels, its (2 th + 1) x (2 tw + 1) pixels of the convolution, its (4 th + 7) x (4 tw + 8)
+// input pixels (one column more than the filter reaches: K runs in steps of four filter columns).
+#define DLF_STEM_IN_PIXELS 1536      // six per thread
+#define DLF_STEM_ROW 72              // halfs per convolution pixel in LDS
+#define DLF_STEM_LDS_BYTES(TH, TW) ((4 * (TH) + 7) * (4 * (TW) + 8) * 8 + (2 * (TH) + 1) * (2 * (TW) + 1) * DLF_STEM_ROW * 2 + 256)
+#define DLF_STEM_PER_CU 2
+struct DlfStemArgs {
+    const void* in;       // [batch][h][w][3] fp16
+    void* out;            // [batch][oh][ow][64] fp16
+    const void* w;        // packed fragments, K step = (filter row, half of its 32 columns x channels)
+    const float* bias;
+    int32_t batch, h, w_, ch, cw, oh, ow, act;      // input, convolution and pooled map
+    int32_t th, tw, tiles_y, tiles_x, ntiles;       // ntiles = batch * tiles_y * tiles_x
+    uint32_t iw_m, cw_m, tw_m, tx_m, ty_m;          // reciprocals for division by 4 tw + 8, 2 tw + 1, tw, tiles_x, tiles_y
 };
 
 struct DlfGapArgs {

@@ -5100,6 +5100,132 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
     }
 }
 
+// ResNet's first layers, 7x7 stride 2 on three channels and the 3x3 max pool of stride 2, in one pass.  Work item = tile of pooled
+// pixels, workgroups of four waves, two to a CU, that walk through the tiles.
+//   The whole filter (14 K steps x two channel blocks, 28 fragments) stays in a wave's registers.  The input patch lies in LDS as
+// 4-channel pixels (stage_rowfold's form: a filter row is one K of 32, eight pixels x four channels); the pixels of the next tile are
+// requested ahead of the multiplies of this one.  32 pixels of the convolution per wave and turn go to LDS in fp16, pixels outside
+// the map as -inf; then a thread takes the maximum of nine for one pooled pixel and eight channels.
+// Per launch, as a group of the fused-group kernel -> now: 224 x 224 batch 1 11.1 -> 5.0 us, batch 32 35.8 -> 25.6; 173 x 173 batch 5
+// 11.1 -> 6.6.  What bounds it at 32 images is the sum of a tile's phases (4.9 us: multiplies 2.1 of 0.75 at the matrix pipes' rate,
+// pool 1.2, the patch and barriers 1.6): rows as direct loads with a second pass in LDS, or three workgroups to a CU with a channel block
+// per wave, take as long.
+template <typename T> __device__ __forceinline__ T load_unaligned(const char* p)
+{
+    T v;
+    __builtin_memcpy(&v, p, sizeof v);
+    return v;
+}
+__global__ __launch_bounds__(256, DLF_STEM_PER_CU) void k_stem(const DlfStemArgs a)
+{
+    constexpr int STEPS = 14, U = DLF_STEM_IN_PIXELS / 256, ROW = DLF_STEM_ROW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    const int iw = 4 * a.tw + 8, n_in = (4 * a.th + 7) * iw, cwt = 2 * a.tw + 1, npix = (2 * a.th + 1) * cwt, nblk = (npix + 31) >> 5;
+    half_t* const in_t = lds;
+    half_t* const conv_t = lds + n_in * 4;
+    float* const bias_t = (float*)(conv_t + npix * ROW);      // (fetched per turn it would wait behind the next patch)
+    if (tid < 64) bias_t[tid] = a.bias[tid];
+    const char* const in = (const char*)a.in;
+    h8 wr[STEPS][2];
+    {
+        const i32x4 rw = make_rsrc(a.w, 2 * STEPS * 1024);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) wr[s][c] = wfrag(rw, lane * 16, (c * STEPS + s) * 1024);
+    }
+    // (the tile's patch row and column of the thread's pixels: the same for every tile)
+    int row[U], col[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int v = min(tid + u * 256, n_in - 1);
+        row[u] = div_by(v, a.iw_m);
+        col[u] = v - row[u] * iw;
+    }
+    u2v px[U];
+    int n, y0, x0;                                        // image and first pooled pixel of the tile whose patch was requested last
+    auto request = [&](int t) __attribute__((always_inline)) {
+        const int q = div_by(t, a.tx_m);
+        n = div_by(q, a.ty_m);
+        x0 = (t - q * a.tiles_x) * a.tw;
+        y0 = (q - n * a.tiles_y) * a.th;
+        const int iy = 4 * y0 - 5, ix = 4 * x0 - 5;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // every lane loads, from the nearest pixel inside the image where it has nothing to fetch
+            const int gy = iy + row[u], gx = ix + col[u];
+            const char* const p = in + (size_t)((n * a.h + min(max(gy, 0), a.h - 1)) * a.w_ + min(max(gx, 0), a.w_ - 1)) * 6;
+            px[u] = u2v{load_unaligned<unsigned>(p), load_unaligned<unsigned short>(p + 4)};
+        }
+    };
+    const unsigned lo_a = act_lo(a.act), hi_a = act_hi(a.act);
+    int t = blockIdx.x;
+    if (t >= a.ntiles) return;
+    request(t);
+    for (;;) {
+        const int cn = n, cy0 = 2 * y0 - 1, cx0 = 2 * x0 - 1, py0 = y0, px0 = x0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int gy = 4 * y0 - 5 + row[u], gx = 4 * x0 - 5 + col[u];
+            const bool ok = gy >= 0 && gy < a.h && gx >= 0 && gx < a.w_;
+            const u2v z = {0, 0};
+            if (tid + u * 256 < n_in) *(u2v*)(in_t + (tid + u * 256) * 4) = ok ? px[u] : z;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        t += gridDim.x;
+        if (t < a.ntiles) request(t);
+        for (int b = wave; b < nblk; b += 4) {
+            const int pix = min(b * 32 + l32, npix - 1), oy = div_by(pix, a.cw_m), ox = pix - oy * cwt;
+            const half_t* const src = in_t + ((2 * oy) * iw + 2 * ox + 2 * lhi) * 4;
+            f16v acc[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f4v bv = *(const f4v*)(bias_t + c * 32 + q * 8 + lhi * 4);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[c][q * 4 + r] = bv[r];
+                }
+#pragma unroll
+            for (int r = 0; r < 7; ++r)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const h8 bf = *(const h8*)(src + r * iw * 4 + h * 16);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wr[2 * r + h][c], bf, acc[c], 0, 0, 0);
+                }
+            const bool inside = cy0 + oy >= 0 && cy0 + oy < a.ch && cx0 + ox >= 0 && cx0 + ox < a.cw;
+            const unsigned lo = inside ? lo_a : 0xFC00FC00u, hi = inside ? hi_a : 0xFC00FC00u;
+            half_t* const dst = conv_t + pix * ROW + lhi * 4;
+            if (b * 32 + l32 < npix) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const u2v uu = {pk_min(pk_max(cvt_pk(acc[c][q * 4], acc[c][q * 4 + 1]), lo), hi),
+                                        pk_min(pk_max(cvt_pk(acc[c][q * 4 + 2], acc[c][q * 4 + 3]), lo), hi)};
+                        *(u2v*)(dst + c * 32 + q * 8) = uu;
+                    }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int e = tid; e < a.th * a.tw * 8; e += 256) {
+            const int pp = e >> 3, part = e & 7, y = div_by(pp, a.tw_m), x = pp - y * a.tw;
+            const half_t* const src = conv_t + (2 * y * cwt + 2 * x) * ROW + part * 8;
+            u4v m = *(const u4v*)src;
+#pragma unroll
+            for (int k = 1; k < 9; ++k) {
+                const u4v v = *(const u4v*)(src + ((k / 3) * cwt + k % 3) * ROW);
+                m = u4v{pk_max(m.x, v.x), pk_max(m.y, v.y), pk_max(m.z, v.z), pk_max(m.w, v.w)};
+            }
+            if (py0 + y < a.oh && px0 + x < a.ow)
+                *(u4v*)((half_t*)a.out + ((size_t)(cn * a.oh + py0 + y) * a.ow + px0 + x) * 64 + part * 8) = m;
+        }
+        if (t >= a.ntiles) break;
+    }
+}
+
 // Global average pooling: fp32 sum over H*W, mean, fp16.
 __global__ __launch_bounds__(256) void k_gap(const DlfGapArgs a)
 {
@@ -5321,9 +5447,24 @@ extern "C" int dlf_launch_c3_i8(const DlfC3Args* a, int shape, int grid, int lds
     return (int)hipGetLastError();
 }
 
+static int launch_stem(const DlfStemArgs* a, int grid, int lds_bytes, void* stream)
+{
+    // what the kernel's indexing assumes
+    if (grid <= 0 || a->th < 1 || a->th > 8 || a->tw < 1 || a->tw > 8 || (4 * a->th + 7) * (4 * a->tw + 8) > DLF_STEM_IN_PIXELS ||
+        a->ch != (a->h - 1) / 2 + 1 || a->cw != (a->w_ - 1) / 2 + 1 || a->oh != (a->ch - 1) / 2 + 1 || a->ow != (a->cw - 1) / 2 + 1 ||
+        a->tiles_y != (a->oh + a->th - 1) / a->th || a->tiles_x != (a->ow + a->tw - 1) / a->tw ||
+        a->ntiles != a->batch * a->tiles_y * a->tiles_x || (int64_t)a->ntiles * a->tiles_x >= (int64_t)1 << 32 ||
+        (int64_t)a->batch * a->tiles_y * a->tiles_y >= (int64_t)1 << 32 || (int64_t)a->batch * a->h * a->w_ * 3 >= (int64_t)1 << 31 ||
+        lds_bytes != DLF_STEM_LDS_BYTES(a->th, a->tw))
+        return (int)hipErrorInvalidValue;
+    launch(k_stem, dim3(grid), dim3(256), (size_t)lds_bytes, (hipStream_t)stream, *a);
+    return (int)hipGetLastError();
+}
+
 extern "C" int dlf_launch_group(const DlfGroupArgs* a, int variant, int grid, int lds_bytes,
                                 void* stream)
 {
+    if (a->stem != nullptr) return launch_stem(a->stem, grid, lds_bytes, stream);
     const bool ksplit = a->nstages == 1 && a->st[0].kind == DLF_ST_CONV && a->st[0].ksplit > 1;
     group_kernel_t k = group_kernel(variant, ksplit);
     if (k == nullptr || grid <= 0) return (int)hipErrorInvalidValue;
