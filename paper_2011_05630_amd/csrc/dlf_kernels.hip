@@ -5239,6 +5239,38 @@ __global__ __launch_bounds__(256) void k_gap(const DlfGapArgs a)
     ((half_t*)a.y)[idx] = (half_t)(s / (float)a.hw);
 }
 
+// ... of whole vectors: a workgroup takes 256 channels of an image, eight threads share the pixels of 8 channels, with seven loads in
+// flight each (49 pixels: one trip to memory in place of seven), and their sums meet in LDS in a fixed order.
+// 2048 channels at 7 x 7: batch 1 4.7 -> 3.4 us, batch 32 6.2 -> 4.7; 1024 channels batch 1 3.8 -> 2.8.
+__global__ __launch_bounds__(256) void k_gap8(const DlfGapArgs a)
+{
+    constexpr int PARTS = 8, U = 7;
+    float* const sums = (float*)lds;                          // [part][256]
+    const int tid = threadIdx.x, part = tid >> 5, groups = (a.c + 255) >> 8;
+    const int n = blockIdx.x / groups, c0 = (blockIdx.x - n * groups) * 256, c = min(c0 + (tid & 31) * 8, a.c - 8);
+    const half_t* const p = (const half_t*)a.x + (size_t)n * a.hw * a.c + c;
+    float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i0 = part; i0 < a.hw; i0 += PARTS * U) {
+        h8 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *(const h8*)(p + (size_t)min(i0 + u * PARTS, a.hw - 1) * a.c);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * PARTS < a.hw) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[e] += (float)v[u][e];
+            }
+    }
+    *(f4v*)(sums + part * 256 + (tid & 31) * 8) = f4v{s[0], s[1], s[2], s[3]};
+    *(f4v*)(sums + part * 256 + (tid & 31) * 8 + 4) = f4v{s[4], s[5], s[6], s[7]};
+    __syncthreads();
+    if (c0 + tid >= a.c) return;
+    float t = 0.0f;
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) t += sums[k * 256 + tid];
+    ((half_t*)a.y)[(size_t)n * a.c + c0 + tid] = (half_t)(t / (float)a.hw);
+}
+
 // Profiling: a start / stop event pair attached to the next launch of this thread.  The runtime
 // stamps such events with the dispatch's own begin and end, so their difference is the kernel's
 // duration (what a kernel trace reports), free of the gaps around events recorded on the stream.
@@ -5731,6 +5763,10 @@ extern "C" int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream)
 
 extern "C" int dlf_launch_gap(const DlfGapArgs* a, void* stream)
 {
+    if ((a->c & 7) == 0 && ((size_t)a->x & 15) == 0) {
+        launch(k_gap8, dim3(a->batch * ((a->c + 255) / 256)), dim3(256), 8 * 256 * sizeof(float), (hipStream_t)stream, *a);
+        return (int)hipGetLastError();
+    }
     const int total = a->batch * a->c;
     launch(k_gap, dim3((total + 255) / 256), dim3(256), 0, (hipStream_t)stream, *a);
     return (int)hipGetLastError();

@@ -1,0 +1,25 @@
+"""GPU parity of global average pooling against the CPU oracle: whole vectors and odd channel counts, the last group of 256 channels
+ragged, one pixel, a trip's worth of pixels per thread and one more."""
+import pytest
+
+from synth import nets, gen
+from gpu_util import compare, announce
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("c,h,w,batch", [(8, 1, 1, 1), (264, 7, 7, 3), (2048, 7, 8, 2), (512, 3, 19, 5), (1000, 12, 11, 1), (20, 7, 7, 2), (13, 9, 5, 3)])
+def test_global_average_pool(c, h, w, batch):
+    from oracle import oracle as o
+    from paper_2011_05630_amd import binding as B
+    from paper_2011_05630_amd.runner import Session
+    announce("gap", c, h, w, batch)
+    net = dict(name="t", layers=[nets.gavgpool(c)], in_h=h, in_w=w, in_c=c, input_dist="normal")
+    x, ws, bs = gen.make_params(net, batch, 33)
+    s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=[0], group_budget=[256])
+    try:
+        got = s.run_numpy(x)
+        assert got.shape == (batch, 1, 1, c)
+    finally:
+        s.close()
+    compare(got, o.run_net(net, x, ws, bs), "gap %d" % c)
