@@ -4182,15 +4182,17 @@ __global__ __launch_bounds__(DLF_C3PW_WAVES(C) * 64, C == 64 ? 2 : 1) void k_c3p
 //      weight fragments in registers; bias, activation, zero for pixels outside the map (they are
 //      the second layer's padding), fp16 into a second region [pixel][64] with the permutation the
 //      3x3 loop reads by.
-//   3. Second layer: waves 0 and 1 one channel block x the tile's two pixel blocks each, K through a
-//      register ring of 9 steps, as in k_c3pw; result to an LDS tile [pixel][64 + 8].
+//   3. Second layer: a channel block x 32 pixels per wave, K through a register ring of 9 steps;
+//      result to an LDS tile [pixel][64 + 8].  (On waves 0 and 1 alone, both pixel blocks each, the
+//      layer ran on two of a CU's four SIMDs: batch 1 9.5 -> 8.4 and 8.6 -> 7.8 us; at batch 32,
+//      47 us a launch, the phases of the CU's two workgroups covered it.)
 //   4. Last layer: every wave two channel blocks, all of K in registers, 32 pixels at a time through
 //      the wave's transpose buffer; + the input's centre pixels from the first region (fp16 + fp16),
 //      activation, a pixel's 2 x 64 bytes stored by adjacent instructions.
 template <int CIN0>
 __global__ __launch_bounds__(DLF_BN_WAVES * 64, 2) void k_bneck(const DlfBnArgs a)
 {
-    constexpr int D = 9, ROW = 32 + 8, C = 64, W = DLF_BN_WAVES, FP = 2, cs = C + 8;
+    constexpr int D = 9, ROW = 32 + 8, C = 64, W = DLF_BN_WAVES, cs = C + 8;
     static_assert(CIN0 == 64 || CIN0 == 128 || CIN0 == 256 || CIN0 == 512, "channels of the block's input");
     constexpr int pp0 = CIN0 == 64 ? 3 : (CIN0 == 128 ? 4 : (CIN0 == 256 ? 5 : 6));   // log2 of the input's 16-byte parts per pixel
     constexpr int PERM0 = CIN0 == 64 ? 7 : 15;               // the permutation stays inside a pixel
@@ -4255,8 +4257,8 @@ __global__ __launch_bounds__(DLF_BN_WAVES * 64, 2) void k_bneck(const DlfBnArgs 
     const int cb0 = (sl * W + wave) * 2;
     const bool live = cb0 < a.ncb2;                          // uniform
     if (last) bl[lane] = a.b2[min(cb0 * 32 + lane, a.ncb2 * 32 - 1)];
-    // the last layer's weights of this wave (both channel blocks, all of K) and, on the two waves of
-    // the second layer, the first turn of its ring: everything is requested before the first wait
+    // the last layer's weights of this wave (both channel blocks, all of K), the second layer's bias and
+    // the first turn of its ring: everything is requested before the first wait
     constexpr int nsteps1 = 2 * 18, nsteps2 = C / 16;
     h8 a2[2][nsteps2];
     if (last) {
@@ -4269,14 +4271,22 @@ __global__ __launch_bounds__(DLF_BN_WAVES * 64, 2) void k_bneck(const DlfBnArgs 
         }
     }
     const i32x4 rw1 = make_rsrc(a.w1, 0xffffffffu);
-    const unsigned wo = (unsigned)__builtin_amdgcn_readfirstlane((wave & 1) * nsteps1 * 1024);
+    const unsigned wo = (unsigned)__builtin_amdgcn_readfirstlane(cb_a * nsteps1 * 1024);
     int pf_ks = 0;
     h8 ar[D];
     auto request = [&](int slot) __attribute__((always_inline)) {
         ar[slot] = wfrag(rw1, lane16, wo + (unsigned)min(pf_ks, nsteps1 - 1) * 1024u);   // past the end: re-read, never used
         ++pf_ks;
     };
-    if (wave < 2) {
+    const bool second = (wave >> 1) * 32 < a.tp;             // uniform: has the wave pixels of the second layer
+    constexpr bool EARLY = CIN0 < 512;                       // (the first layer's 512 channels leave no registers for it)
+    f4v bias1[4];
+    auto load_bias1 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias1[q] = *(const f4v*)(a.b1 + cb_a * 32 + q * 8 + lhi * 4);
+    };
+    if (second) {
+        if (EARLY) load_bias1();
 #pragma unroll
         for (int d = 0; d < D; ++d) request(d);
     }
@@ -4314,60 +4324,49 @@ __global__ __launch_bounds__(DLF_BN_WAVES * 64, 2) void k_bneck(const DlfBnArgs 
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the second region is complete
 
-    // ---- step 3: the second layer ----
-    if (wave < 2) {
-        f4v bias1[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bias1[q] = *(const f4v*)(a.b1 + wave * 32 + q * 8 + lhi * 4);
-        int bt[9][FP], ft[9][FP];
-#pragma unroll
-        for (int p = 0; p < FP; ++p) {
-            const int px_ = min(p * 32 + l32, a.tp - 1);
-            const int py = div_by(px_, tw_m), pxx = px_ - py * a.tw;
+    // ---- step 3: the second layer, a channel block x 32 pixels per wave ----
+    if (second) {
+        if (!EARLY) load_bias1();
+        const int px_ = (wave >> 1) * 32 + l32, pc = min(px_, a.tp - 1);
+        int bt[9], ft[9];
+        {
+            const int py = div_by(pc, tw_m), pxx = pc - py * a.tw;
 #pragma unroll
             for (int t = 0; t < 9; ++t) {
                 const int ry = py + t / 3, rx = pxx + t % 3;
-                bt[t][p] = (ry * a.rw + rx) * C * 2;
-                ft[t][p] = (((ry * a.tw + rx) & 7) ^ lhi) << 4;
+                bt[t] = (ry * a.rw + rx) * C * 2;
+                ft[t] = (((ry * a.tw + rx) & 7) ^ lhi) << 4;
             }
         }
-        f16v acc[FP];
+        f16v acc;
 #pragma unroll
-        for (int p = 0; p < FP; ++p)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[p][q] = bias1[q >> 2][q & 3];
+        for (int q = 0; q < 16; ++q) acc[q] = bias1[q >> 2][q & 3];
         const char* const region = ma;
-        h8 bf[2][FP];
-#pragma unroll
-        for (int p = 0; p < FP; ++p) bf[0][p] = *(const h8*)(region + bt[0][p] + ft[0][p]);
+        h8 bf[3];
+        bf[0] = *(const h8*)(region + bt[0] + ft[0]);
+        bf[1] = *(const h8*)(region + bt[0] + (32 ^ ft[0]));
 #pragma unroll 1
         for (int c = 0; c < 2; ++c) {
             const int q16 = c * 64, q16n = min(c + 1, 1) * 64;
 #pragma unroll
             for (int j = 0; j < 18; ++j) {
-                const int jn = (j + 1) % 18, tn = jn >> 1;
-                const int qn = (j == 17 ? q16n : q16) + (jn & 1) * 32;
-#pragma unroll
-                for (int p = 0; p < FP; ++p) bf[(j + 1) & 1][p] = *(const h8*)(region + bt[tn][p] + (qn ^ ft[tn][p]));
-#pragma unroll
-                for (int p = 0; p < FP; ++p)
-                    acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ar[j % D], bf[j & 1][p], acc[p], 0, 0, 0);
+                // (two fragments ahead: a wave's step is one MFMA)
+                const int jn = (j + 2) % 18, tn = jn >> 1;
+                const int qn = (j >= 16 ? q16n : q16) + (jn & 1) * 32;
+                bf[(j + 2) % 3] = *(const h8*)(region + bt[tn] + (qn ^ ft[tn]));
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ar[j % D], bf[j % 3], acc, 0, 0, 0);
                 request(j % D);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
-        for (int p = 0; p < FP; ++p) {
-            const int px_ = p * 32 + l32;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                unsigned u0 = cvt_pk(acc[p][q * 4 + 0], acc[p][q * 4 + 1]);
-                unsigned u1 = cvt_pk(acc[p][q * 4 + 2], acc[p][q * 4 + 3]);
-                u0 = pk_min(pk_max(u0, lo1), hi1);
-                u1 = pk_min(pk_max(u1, lo1), hi1);
-                const u2v uu = {u0, u1};
-                if (px_ < a.tp) *(u2v*)(mid + px_ * cs + wave * 32 + q * 8 + lhi * 4) = uu;
-            }
+        for (int q = 0; q < 4; ++q) {
+            unsigned u0 = cvt_pk(acc[q * 4 + 0], acc[q * 4 + 1]);
+            unsigned u1 = cvt_pk(acc[q * 4 + 2], acc[q * 4 + 3]);
+            u0 = pk_min(pk_max(u0, lo1), hi1);
+            u1 = pk_min(pk_max(u1, lo1), hi1);
+            const u2v uu = {u0, u1};
+            if (px_ < a.tp) *(u2v*)(mid + px_ * cs + cb_a * 32 + q * 8 + lhi * 4) = uu;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
