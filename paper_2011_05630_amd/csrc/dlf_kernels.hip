@@ -1098,7 +1098,14 @@ __global__ __launch_bounds__(DLF_WG_THREADS, MINW) void k_group(const DlfGroupAr
                     else if (kind == 1) conv_stage<FC, FP, true, 1, (MINW >= 4), false>(a, st, n, ty0, tx0, slice, last);
                     else conv_stage<FC, FP, true, 0, (MINW >= 4), false>(a, st, n, ty0, tx0, slice, last);
                 } else {
-                    if (kind == 9) conv_stage<FC, FP, false, 9, (MINW >= 4), KSP>(a, st, n, ty0, tx0, slice, last);
+                    // A stage of one channel block and at most two work items (128 pixels) takes items of half the pixels: two layers of
+                    // 16 channels on 32 x 32, batch 1, 9.8 -> 9.05 us; three of 32 at 39 x 39, batch 5, 12.5 -> 12.0 (up to four items:
+                    // four layers of 16 at 56 x 56, batch 8, 16.75 -> 17.25).  With more channel blocks every further wave brings a
+                    // weight stream of its own, and those set the pace (64 -> 128 -> 128 channels: 18.2 -> 20.2).
+                    const bool half = FC == 1 && FP == 2 && MINW < 4 && kind == 9 && st.ncb == 1 && ((st.rh * st.rw + 63) >> 6) <= DLF_WAVES / 4 &&
+                                      (!KSP || st.ksplit <= 1);
+                    if (half) conv_stage<FC, FC == 1 && FP == 2 && MINW < 4 ? 1 : FP, false, 9, (MINW >= 4), false>(a, st, n, ty0, tx0, slice, last);
+                    else if (kind == 9) conv_stage<FC, FP, false, 9, (MINW >= 4), KSP>(a, st, n, ty0, tx0, slice, last);
                     else if (kind == 1) conv_stage<FC, FP, false, 1, (MINW >= 4), KSP>(a, st, n, ty0, tx0, slice, last);
                     else conv_stage<FC, FP, false, 0, (MINW >= 4), KSP>(a, st, n, ty0, tx0, slice, last);
                 }
