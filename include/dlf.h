@@ -188,7 +188,8 @@ const void* dlf_plan_layer_output(const dlf_plan_t* plan, int32_t layer);
  * 3 pointwise-convolution kernels: a single 1x1 layer, 4 block 3x3 kernel: a single 3x3 stride-1
  * pad-1 layer, with its folded 2x2 pool or residual); variant: for kind 0 the register tile
  * (per-wave accumulator tile, output channels x pixels: 0 = 64x64, 1 = 32x128, 2 = 32x64,
- * 3 = 32x64 built for two workgroups per CU), for kind 3 the work-item form (0 = 64x64 and
+ * 3 = 32x64 built for two workgroups per CU; 16 = the kernel for a 7x7 layer of stride 2, three channels to 64, and the 3x3
+ * max pool of stride 2 behind it, a group of two layers), for kind 3 the work-item form (0 = 64x64 and
  * 1 = 32x32 per wave, 2 = 64x64 with K split over four waves, 3 = 128x128 and 4 = 64x256 blocks
  * shared through LDS), for kind 4 the block shape (0 / 1 = 128 channels x 256 pixels, 2 / 3 =
  * 64 x 512, odd: activations 64 input channels at a time, even: 32; 4 = 128 x 512; 16 .. 21 its form with
