@@ -196,7 +196,7 @@ def group_accounting(net, batch, session):
         elif cfg["kind"] == 3:
             kname = PW_NAME[cfg["variant"]]
         elif cfg["kind"] == 2:
-            kname = "k_gap"
+            kname = "k_gap8" if cfg["lds_bytes"] > 0 else "k_gap"
         elif cfg["kind"] == 4:
             kname = C3_NAME[cfg["variant"]]
         elif cfg["kind"] == 5:

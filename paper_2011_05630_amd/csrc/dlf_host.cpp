@@ -2137,9 +2137,12 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
         DlfGapArgs& pa = g.pa;
         memset(&pa, 0, sizeof pa);
         pa.batch = batch; pa.hw = L0.in_h * L0.in_w; pa.c = L0.d.cin;
+        // the kernel of whole vectors (2048 channels at 7 x 7, batch 1: 3.4 us against 4.7) where its sums have room in LDS
+        pa.vectors = pa.c % 8 == 0 && DLF_GAP_LDS_BYTES <= max_lds;
         const int64_t bytes = (int64_t)batch * pa.hw * pa.c * 2;
         g.cost = (uint64_t)((C_LAUNCH + C_LAT + bytes / GAP_BYTES_PER_CYCLE) * PS_PER_CYCLE);
-        g.grid = ceil_div(batch * pa.c, 256);
+        g.lds_bytes = pa.vectors ? DLF_GAP_LDS_BYTES : 0;
+        g.grid = pa.vectors ? batch * ceil_div(pa.c, 256) : ceil_div(batch * pa.c, 256);
         g.th = L0.in_h; g.tw = L0.in_w;
         return DLF_OK;
     }

@@ -477,10 +477,12 @@ struct DlfStemArgs {
     uint32_t iw_m, cw_m, tw_m, tx_m, ty_m;          // reciprocals for division by 4 tw + 8, 2 tw + 1, tw, tiles_x, tiles_y
 };
 
+#define DLF_GAP_LDS_BYTES (8 * 256 * 4)      // k_gap8: [part of the pixels][channel] fp32
 struct DlfGapArgs {
     const void* x;        // [batch][hw][c]
     void* y;              // [batch][c]
     int32_t batch, hw, c;
+    int32_t vectors;      // 1: k_gap8 (c a multiple of 8; where x is not at a multiple of 16 bytes the launcher takes k_gap)
 };
 
 #ifdef __cplusplus

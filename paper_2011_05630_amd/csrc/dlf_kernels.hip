@@ -5251,6 +5251,7 @@ __global__ __launch_bounds__(256) void k_gap(const DlfGapArgs a)
 __global__ __launch_bounds__(256) void k_gap8(const DlfGapArgs a)
 {
     constexpr int PARTS = 8, U = 7;
+    static_assert(PARTS * 256 * sizeof(float) == DLF_GAP_LDS_BYTES, "k_gap8's LDS");
     float* const sums = (float*)lds;                          // [part][256]
     const int tid = threadIdx.x, part = tid >> 5, groups = (a.c + 255) >> 8;
     const int n = blockIdx.x / groups, c0 = (blockIdx.x - n * groups) * 256, c = min(c0 + (tid & 31) * 8, a.c - 8);
@@ -5769,8 +5770,9 @@ extern "C" int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream)
 
 extern "C" int dlf_launch_gap(const DlfGapArgs* a, void* stream)
 {
-    if ((a->c & 7) == 0 && ((size_t)a->x & 15) == 0) {
-        launch(k_gap8, dim3(a->batch * ((a->c + 255) / 256)), dim3(256), 8 * 256 * sizeof(float), (hipStream_t)stream, *a);
+    if (a->vectors != 0 && (a->c & 7) != 0) return (int)hipErrorInvalidValue;
+    if (a->vectors != 0 && ((size_t)a->x & 15) == 0) {
+        launch(k_gap8, dim3(a->batch * ((a->c + 255) / 256)), dim3(256), DLF_GAP_LDS_BYTES, (hipStream_t)stream, *a);
         return (int)hipGetLastError();
     }
     const int total = a->batch * a->c;

@@ -1,5 +1,5 @@
 """GPU parity of global average pooling against the CPU oracle: whole vectors and odd channel counts, the last group of 256 channels
-ragged, one pixel, a trip's worth of pixels per thread and one more."""
+ragged, one pixel, a trip's worth of pixels per thread and one more, an LDS limit that holds no partial sums."""
 import pytest
 
 from synth import nets, gen
@@ -8,16 +8,18 @@ from gpu_util import compare, announce
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("max_lds", [0, 4096])
 @pytest.mark.parametrize("c,h,w,batch", [(8, 1, 1, 1), (264, 7, 7, 3), (2048, 7, 8, 2), (512, 3, 19, 5), (1000, 12, 11, 1), (20, 7, 7, 2), (13, 9, 5, 3)])
-def test_global_average_pool(c, h, w, batch):
+def test_global_average_pool(c, h, w, batch, max_lds):
     from oracle import oracle as o
     from paper_2011_05630_amd import binding as B
     from paper_2011_05630_amd.runner import Session
-    announce("gap", c, h, w, batch)
+    announce("gap", c, h, w, batch, max_lds)
     net = dict(name="t", layers=[nets.gavgpool(c)], in_h=h, in_w=w, in_c=c, input_dist="normal")
     x, ws, bs = gen.make_params(net, batch, 33)
-    s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=[0], group_budget=[256])
+    s = Session(net, batch, ws, bs, mode=B.TUNER_MANUAL, group_last=[0], group_budget=[256], max_lds_bytes=max_lds)
     try:
+        assert B.dlf_plan_group_config(s.plan, 0)["lds_bytes"] == (8192 if max_lds == 0 and c % 8 == 0 else 0)
         got = s.run_numpy(x)
         assert got.shape == (batch, 1, 1, c)
     finally:

@@ -147,6 +147,14 @@ def test_fully_connected_layers_keep_to_the_lds_limit(k, cout, batch):
     B.dlf_net_destroy(n)
 
 
+@pytest.mark.parametrize("c", [8, 13, 512, 2048])
+def test_global_average_pools_keep_to_the_lds_limit(c):
+    """max_lds_bytes is the limit of global average pools: the kernel of whole vectors, 8 KiB, only where it has them; the other takes none."""
+    for limit in (0, 163840, 8192, 8191, 4096, 1):
+        cfg, _ = _plan([nets.gavgpool(c)], 7, 7, 3, max_lds=limit)
+        assert cfg["kind"] == 2 and cfg["lds_bytes"] == (8192 if c % 8 == 0 and (limit or 163840) >= 8192 else 0), (limit, cfg)
+
+
 @pytest.mark.parametrize("layers,hw,max_lds", [
     ([nets.conv(512, 512, 1, 1, 0, "relu")], 7, 4096),           # 3.9 us with one wave, 5.4 on the pointwise kernel
     ([nets.conv(256, 256, 3, 1, 1, "relu")], 14, 4096),          # 8.9, 11.5 on the fused-group kernel
