@@ -1367,7 +1367,7 @@ bool stem_group(const dlf_net_s& net, int batch, int first, int last, int budget
             const int64_t per_cu = (tiles + budget - 1) / budget, rounds = (per_cu + DLF_STEM_PER_CU - 1) / DLF_STEM_PER_CU;
             const int64_t share = std::min<int64_t>(per_cu, DLF_STEM_PER_CU);
             const int64_t compute = C_STEM_FIRST + rounds * (C_STEM_TILE + turns * C_STEM_TURN * share);
-            const int64_t bytes = (int64_t)batch * (A.in_h * A.in_w * 6 + M.out_h * M.out_w * 128);
+            const int64_t bytes = (int64_t)batch * ((int64_t)A.in_h * A.in_w * 6 + (int64_t)M.out_h * M.out_w * 128);
             const int64_t mem = bytes / std::min<int64_t>(PW_HBM_BYTES_PER_CYCLE, (int64_t)budget * CU_BYTES_PER_CYCLE);
             const uint64_t cost = (uint64_t)((C_LAUNCH + std::max(compute, mem)) * PS_PER_CYCLE);
             if (found && cost >= best.cost) continue;
