@@ -173,7 +173,7 @@ def test_random_and_malformed_nets_under_sanitizers(driver):
 
 def test_large_first_layers_under_sanitizers(driver):
     """A first 7x7 layer with its max pool on images whose pooled map is just below 2^31 values: their bytes do not fit 32 bits."""
-    lines, sizes = [], ((18000, 18000, 1), (23000, 23000, 1), (23100, 22900, 1)))
+    lines, sizes = [], ((18000, 18000, 1), (23000, 23000, 1), (23100, 22900, 1))
     for h, w, batch in sizes:
         net = dict(in_h=h, in_w=w, in_c=3, layers=[nets.conv(3, 64, 7, 2, 3, "relu"), nets.maxpool(64, 3, 2, 1)])
         lines += _net_lines(net) + ["manual %d 1 1 256" % batch]
