@@ -3294,10 +3294,7 @@ static dlf_status launch_one(const dlf_plan_s* plan, const GroupPlan& G, const v
     } else if (G.kind == GK_STEM) {
         DlfStemArgs sm = G.sm;
         sm.in = in; sm.out = out;
-        DlfGroupArgs ga;
-        memset(&ga, 0, sizeof ga);
-        ga.stem = &sm;
-        e = dlf_launch_group(&ga, 0, G.grid, G.lds_bytes, stream);
+        e = dlf_launch_stem(&sm, G.grid, G.lds_bytes, stream);
     } else if (G.kind == GK_PW2) {
         DlfPwArgs wa = G.wa;
         wa.in = in; wa.out = out;

@@ -55,7 +55,6 @@ struct DlfStage {
     int32_t ks_off;       // an LDS area at this offset (halfs): [wave][FC * FP * 16][64] fp32
 };
 
-struct DlfStemArgs;
 struct DlfGroupArgs {
     const void* in;       // group input tensor (HBM)
     void* out;            // group output tensor (HBM)
@@ -71,7 +70,6 @@ struct DlfGroupArgs {
     int32_t ntiles;       // batch * tiles_y * tiles_x * nslices
     int32_t out_h, out_w, out_c;      // group output tensor shape
     DlfStage st[DLF_MAX_STAGES];
-    const DlfStemArgs* stem;     // not null: the launch is k_stem's, with these arguments (looked at by the launcher only)
 };
 
 #define DLF_FC_WAVES 8
@@ -510,6 +508,7 @@ int dlf_launch_c3pw(const DlfC3PwArgs* a, int grid, int lds_bytes, void* stream)
 int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream);
 int dlf_launch_skd(const DlfSkdArgs* a, int shape, void* stream);
+int dlf_launch_stem(const DlfStemArgs* a, int grid, int lds_bytes, void* stream);
 int dlf_kernels_init(void);
 // Attaches a start / stop event pair (hipEvent_t, either may be null) to this thread's next launch.
 void dlf_next_launch_events(void* start, void* stop);

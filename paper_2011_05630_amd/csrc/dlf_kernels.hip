@@ -5486,7 +5486,7 @@ extern "C" int dlf_launch_c3_i8(const DlfC3Args* a, int shape, int grid, int lds
     return (int)hipGetLastError();
 }
 
-static int launch_stem(const DlfStemArgs* a, int grid, int lds_bytes, void* stream)
+extern "C" int dlf_launch_stem(const DlfStemArgs* a, int grid, int lds_bytes, void* stream)
 {
     // what the kernel's indexing assumes
     if (grid <= 0 || a->th < 1 || a->th > 8 || a->tw < 1 || a->tw > 8 || (4 * a->th + 7) * (4 * a->tw + 8) > DLF_STEM_IN_PIXELS ||
@@ -5503,7 +5503,6 @@ static int launch_stem(const DlfStemArgs* a, int grid, int lds_bytes, void* stre
 extern "C" int dlf_launch_group(const DlfGroupArgs* a, int variant, int grid, int lds_bytes,
                                 void* stream)
 {
-    if (a->stem != nullptr) return launch_stem(a->stem, grid, lds_bytes, stream);
     const bool ksplit = a->nstages == 1 && a->st[0].kind == DLF_ST_CONV && a->st[0].ksplit > 1;
     group_kernel_t k = group_kernel(variant, ksplit);
     if (k == nullptr || grid <= 0) return (int)hipErrorInvalidValue;

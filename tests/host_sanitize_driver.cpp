@@ -46,6 +46,7 @@ int dlf_launch_bneck(const DlfBnArgs*, int, int, void*) { return unreachable_lau
 int dlf_launch_c3r(const DlfC3Args*, int, int, int, int, void*) { return unreachable_launch("c3r"); }
 int dlf_launch_skc(const DlfSkcArgs*, int, void*) { return unreachable_launch("skc"); }
 int dlf_launch_skd(const DlfSkdArgs*, int, void*) { return unreachable_launch("skd"); }
+int dlf_launch_stem(const DlfStemArgs*, int, int, void*) { return unreachable_launch("stem"); }
 int dlf_kernels_init(void) { return unreachable_launch("init"); }
 void dlf_next_launch_events(void*, void*) { (void)unreachable_launch("events"); }
 }

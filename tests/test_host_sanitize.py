@@ -36,13 +36,16 @@ def driver(tmp_path_factory):
 
 
 def test_driver_replaces_every_launcher():
-    """Each launcher the host code may call has a stand-in that aborts (and none may be left undefined: no weak declarations)."""
+    """Each launcher the host code may call has a stand-in that aborts (and none may be left undefined: no weak declarations), and no
+    kernel's launcher hides behind another's."""
     with open(os.path.join(ROOT, "paper_2011_05630_amd", "csrc", "dlf_internal.h")) as f:
         header = f.read()
     with open(os.path.join(ROOT, "tests", "host_sanitize_driver.cpp")) as f:
         stand_ins = set(re.findall(r"int (dlf_launch_\w+)\(", f.read()))
     assert set(re.findall(r"int (dlf_launch_\w+)\(", header)) == stand_ins and len(stand_ins) >= 17
     assert "weak" not in header
+    with open(os.path.join(ROOT, "paper_2011_05630_amd", "csrc", "dlf_kernels.hip")) as f:
+        assert set(re.findall(r"int (\w*launch\w*)\(const Dlf", f.read())) == stand_ins
 
 
 def _net_lines(net):
