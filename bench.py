@@ -107,17 +107,17 @@ def csrc_sha1():
 VARIANT_NAME = {0: "k_group<2,2,2>", 1: "k_group<1,4,2>", 2: "k_group<1,2,2>", 3: "k_group<1,2,4>", 16: "k_stem"}
 # pointwise kernels by item shape
 PW_NAME = {0: "k_pw<2,2,6,2>", 1: "k_pw<1,1,8,4>", 2: "k_pw_sk", 3: "k_pwb<2,2>", 4: "k_pwb<1,4>"}
-PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true>", 17: "k_skc<1,2,4,true>",
-            18: "k_skc<1,4,3,true>", 19: "k_skc<2,4,3,true>"}
+PW2_NAME = {3: "k_pwb<2,2,true>", 4: "k_pwb<1,4,true>", 16: "k_skc<1,1,4,true,true>", 17: "k_skc<1,2,4,true,true>",
+            18: "k_skc<1,4,3,true,true>", 19: "k_skc<2,4,3,true,true>"}
 SKC_NAME = {16: "k_skc<1,1,4>", 17: "k_skc<1,2,4>", 18: "k_skc<1,4,3>", 19: "k_skc<2,4,3>"}
 
 
 def skc_name(name, kh, kw, pad, alone):
-    """The split-K kernel's name for a filter: 1x1 (without padding or a pool behind it) and 3x3 have builds of their own."""
+    """The split-K convolution's name for a filter: 1x1 (without padding or a pool behind it) and 3x3 have builds of their own."""
     if kh == kw == 1 and pad == 0 and alone:
-        return name[:-1] + (",true>" if name.endswith(",true>") else ",false,true>")
+        return name[:-1] + ",false,true>"
     if kh == kw == 3:
-        return name[:-1] + (",false,true>" if name.endswith(",true>") else ",false,false,true>")
+        return name[:-1] + ",false,false,true>"
     return name
 
 
@@ -219,8 +219,6 @@ def group_accounting(net, batch, session):
             kname = "k_dws<%d,%d>" % (cfg["variant"] // 2 + 1, cfg["variant"] % 2 + 1)
         elif cfg["kind"] == 8:
             kname = PW2_NAME[cfg["variant"]]         # the same kernel, built for a second operand pair
-            if kname.startswith("k_skc"):
-                kname = skc_name(kname, net["layers"][l]["kh"], net["layers"][l]["kw"], net["layers"][l]["pad"], True)
         else:
             kname = VARIANT_NAME[cfg["variant"]]
         out.append(dict(first=f, last=l, budget=info["budget"], flops=flops, bytes=byts, flops3x3=flops3x3,

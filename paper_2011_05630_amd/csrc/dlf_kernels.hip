@@ -4655,6 +4655,7 @@ __global__ __launch_bounds__(256) void k_fc_fin(const DlfFcArgs a)
 template <int TP, int TC, int D, bool P2, bool K1, bool K3>
 __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
 {
+    static_assert(!P2 || K1, "a second operand pair comes with 1x1 filters only");
     constexpr int KW = K1 ? 1 : K3 ? 3 : 0;
     constexpr int P = 16 * TP, C = 16 * TC;
     constexpr int WB = DLF_SKC_WAVE_BYTES(TP, TC);       // a wave's LDS: its ring of "B" operands, then its partial sums
@@ -4740,7 +4741,6 @@ __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
             for (int t = 0; t < kh; ++t) mk |= (iy + t >= 0 && iy + t < a.h) ? cols << (t * kw) : 0u;
             mask[p] = pi < a.m ? mk : 0u;
             boff2[p] = 0;
-            if (P2) boff2[p] = pi < a.m ? ((n * a.h2 + oy * a.stride2) * a.w2_ + ox * a.stride2) * a.cin2 * 2 + part16 : DLF_OOB;
         }
         h8 A[D][TC];
         half_t* const ring = lds + wave * (WB / 2);
@@ -5736,13 +5736,12 @@ extern "C" int dlf_launch_bneck(const DlfBnArgs* a, int grid, int lds_bytes, voi
     return (int)hipGetLastError();
 }
 
-template <bool K1, bool K3>
-static void (*skc_kernel(int shape, bool second))(const DlfSkcArgs)
+template <bool P2, bool K1, bool K3>
+static void (*skc_kernel(int shape))(const DlfSkcArgs)
 {
-    static void (*const k[2][DLF_SKC_SHAPES])(const DlfSkcArgs) = {
-        {k_skc<1, 1, 4, false, K1, K3>, k_skc<1, 2, 4, false, K1, K3>, k_skc<1, 4, 3, false, K1, K3>, k_skc<2, 4, 3, false, K1, K3>},
-        {k_skc<1, 1, 4, true, K1, K3>, k_skc<1, 2, 4, true, K1, K3>, k_skc<1, 4, 3, true, K1, K3>, k_skc<2, 4, 3, true, K1, K3>}};
-    return k[second ? 1 : 0][shape];
+    static void (*const k[DLF_SKC_SHAPES])(const DlfSkcArgs) = {
+        k_skc<1, 1, 4, P2, K1, K3>, k_skc<1, 2, 4, P2, K1, K3>, k_skc<1, 4, 3, P2, K1, K3>, k_skc<2, 4, 3, P2, K1, K3>};
+    return k[shape];
 }
 
 extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
@@ -5751,7 +5750,9 @@ extern "C" int dlf_launch_skc(const DlfSkcArgs* a, int shape, void* stream)
     if ((int64_t)a->n_pg * a->n_cg * a->n_cg >= (int64_t)1 << 32) return (int)hipErrorInvalidValue;      // div_by of an item
     if (shape < 0 || shape >= DLF_SKC_SHAPES || (a->nw != 1 && a->nw != 2 && a->nw != 4 && a->nw != 8)) return (int)hipErrorInvalidValue;
     const bool second = a->nk2 > 0, k1 = a->kh == 1 && a->kw == 1 && a->pad == 0 && a->pool2 == 0, k3 = a->kh == 3 && a->kw == 3;
-    launch(k1 ? skc_kernel<true, false>(shape, second) : k3 ? skc_kernel<false, true>(shape, second) : skc_kernel<false, false>(shape, second),
+    if (second && !k1) return (int)hipErrorInvalidValue;
+    launch(second ? skc_kernel<true, true, false>(shape) : k1 ? skc_kernel<false, true, false>(shape)
+                  : k3 ? skc_kernel<false, false, true>(shape) : skc_kernel<false, false, false>(shape),
            dim3(a->n_pg * a->n_cg), dim3(a->nw * 64), a->nw * DLF_SKC_WAVE_BYTES(px[shape] / 16, ch[shape] / 16),
            (hipStream_t)stream, *a);
     return (int)hipGetLastError();
