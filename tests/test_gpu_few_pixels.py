@@ -33,6 +33,10 @@ def test_few_pixels(channels, h, w, batch, th, tw):
         finally:
             B.dlf_debug_force_config(0)
         try:
+            # the kernel and the register tile (32 x 64) that hold the half items, on the tile asked for
+            cfg, g = B.dlf_plan_group_config(s.plan, 0), B.dlf_plan_groups(s.plan)[0]
+            assert (cfg["kind"], cfg["variant"], cfg["nslices"]) == (0, 2, 1), cfg
+            assert (g["tile_h"], g["tile_w"]) == (th, tw) if th > 0 else g["tile_h"] * g["tile_w"] <= 128, g
             got = s.run_numpy(x)
         finally:
             s.close()
