@@ -1,5 +1,6 @@
 """GPU parity of global average pooling against the CPU oracle: whole vectors and odd channel counts, the last group of 256 channels
-ragged, one pixel, a trip's worth of pixels per thread and one more, an LDS limit that holds no partial sums."""
+ragged, one pixel, a trip's worth of pixels per thread and one more, an LDS limit that holds no partial sums,
+a tensor that is not on a 16-byte line."""
 import pytest
 
 from synth import nets, gen
@@ -25,3 +26,22 @@ def test_global_average_pool(c, h, w, batch, max_lds):
     finally:
         s.close()
     compare(got, o.run_net(net, x, ws, bs), "gap %d" % c)
+
+
+def test_tensor_off_the_vectors_line():
+    import numpy as np
+    import torch
+    from oracle import oracle as o
+    from paper_2011_05630_amd.runner import Session
+    net = dict(name="t", layers=[nets.gavgpool(264)], in_h=7, in_w=5, in_c=264, input_dist="normal")
+    x, ws, bs = gen.make_params(net, 3, 33)
+    s = Session(net, 3, ws, bs)
+    room = torch.zeros(x.size + 8, dtype=torch.float16, device="cuda")
+    try:
+        for off in (1, 4, 8):
+            announce("gap, offset", off)
+            xd = room[off:off + x.size].view(x.shape)
+            xd.copy_(torch.from_numpy(np.ascontiguousarray(x, dtype=np.float16)))
+            compare(s.run(xd).cpu().numpy(), o.run_net(net, x, ws, bs), "gap, offset %d" % off)
+    finally:
+        s.close()

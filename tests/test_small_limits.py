@@ -170,6 +170,7 @@ def test_fewer_waves_under_an_lds_limit(layers, hw, max_lds):
     ([nets.conv(96, 88, 3, 1, 1, "relu"), nets.maxpool(88, 2, 2, 0)], 6, 8, 2, 4096),
     ([nets.conv(256, 928, 5, 3, 4, "relu")], 33, 13, 1, 16384), ([nets.conv(352, 32, 3, 2, 1, "relu")], 37, 11, 1, 4096),
     ([nets.conv(64, 64, 3, 1, 1, "relu")], 32, 32, 7, 2048),
+    ([nets.conv(3, 64, 7, 2, 3, "relu"), nets.maxpool(64, 3, 2, 1)], 64, 64, 1, 9408),
     ([nets.conv(128, 684380, 3, 1, 1, "relu")], 37, 36, 1, 0), ([nets.conv(1696, 966560, 3, 1, 1, "relu"), nets.maxpool(966560, 2, 2, 0)], 40, 22, 1, 32768)])
 def test_layers_that_fit_no_tile_stay_infeasible(layers, h, w, batch, max_lds):
     """Layers that the tiled kernels refuse, for the LDS limit or their size, are refused by the library."""
