@@ -322,7 +322,7 @@ const int64_t C_C3S_ONE = 6500;
 const int64_t C_C3S_STEP_SMALL = 183;
 const int64_t C_C3S_STEP_ONE = 125;          // ... tiles of one pixel block
 const int64_t C_C3S_STEP_HALF = 236;         // ... from 64 items on, where fewer than four waves share a channel block (256 channels, 120 items: 13.1 us)
-const int64_t C_STEM_FIRST = 1000;           // k_stem (as measured: 6.3 us at 224 x 224, 25.6 at 32 images): the filter and the first patch ...
+const int64_t C_STEM_FIRST = 1000;           // k_stem (at 224 x 224 priced 7.6 us, 8.3 at 4 and 24.2 at 32 images; it takes 4.9, 6.5 and 24.3): the filter and the first patch ...
 const int64_t C_STEM_TILE = 5100;            // ... a tile's patch, barriers and pool ...
 const int64_t C_STEM_TURN = 1350;            // ... 32 pixels of the convolution on every wave of one of the CU's workgroups
 const int64_t C_SDP_FIRST = 3700;            // k_sdp (10 % low at 64 images: 42.7 us, it takes 47.7): a CU's first tile ...
@@ -2453,7 +2453,10 @@ dlf_status make_group_tiled(const dlf_net_s& net, int batch, int first, int last
 // What the fused-group kernel (in one round of tiles, up to 64 channels, by number of layers) and the 3x3 -> 1x1 kernel are modelled at
 // beyond what they take, where the models of the kernels for single layers that came after them are within 10 %.  Chains of 2 / 3 / 4
 // layers of 32 and 64 channels, 14 x 14 to 56 x 56: 15.6 / 17.7 / 19.7 and 17.6 / 20.7 / 25.6 us modelled, 9.8 / 12.6 / 15.4 and
-// 12.0 / 15.6 / 20.3 measured, two of 64 at 64 x 64, batch 13, 26.4 and 19.8.  3x3 chains of 96 and 128 channels at 2300 - 3200 pixels:
+// 12.0 / 15.6 / 20.3 measured, two of 64 at 64 x 64, batch 13, 26.4 and 19.8.  The correction is fitted to these; since then stages of
+// one channel block and few pixels take items of half the pixels, and the chains of 32 channels 8.2 - 8.8 / 10.5 - 11.1 / 12.8 - 14.2 (of 64
+// channels 10.9 - 11.3 / 14.0 - 14.9 / 17.7 - 20.3 on the same card): three layers at up to 32 x 32, batch 1, are planned as layers, 11.3
+// - 11.7 us, and would take 10.6 as one launch, four 15.3 and 12.9.  3x3 chains of 96 and 128 channels at 2300 - 3200 pixels:
 // 19.5 / 23.6 / 30.5 and 21.5 / 26.5 / 35.4 us modelled, 13.3 / 17.3 / 22.8 - 25.5 and 15.6 / 20.0 / 27.5 - 32.1 measured; from 129 channels
 // on the layers one by one are the faster plan.  The 3x3 -> 1x1 kernel: 128 channels at 16 x 16 to 32 x 32, batch
 // 4, 14.7 - 15.1 modelled, 8.5 - 9.2 measured, at 30 x 30, batch 32, 35.1 and 26; 256 channels 23.1 and 20.7.
@@ -2598,7 +2601,7 @@ dlf_status make_group(const dlf_net_s& net, int batch, int first, int last, int 
             return s;
         }
     }
-    if (s == DLF_OK && !named && last == first + 1) {
+    if (s == DLF_OK && !named && last == first + 1) {       // (a limit below 9424 bytes, which the fused-group kernel needs, stays refused)
         GroupPlan stem;
         if (stem_group(net, batch, first, last, budget, max_lds, stem) && stem.cost < g.cost) {
             g = stem;

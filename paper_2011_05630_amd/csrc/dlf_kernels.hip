@@ -4190,9 +4190,10 @@ __global__ __launch_bounds__(DLF_C3PW_WAVES(C) * 64, C == 64 ? 2 : 1) void k_c3p
 //      the second layer's padding), fp16 into a second region [pixel][64] with the permutation the
 //      3x3 loop reads by.
 //   3. Second layer: a channel block x 32 pixels per wave, K through a register ring of 9 steps;
-//      result to an LDS tile [pixel][64 + 8].  (On waves 0 and 1 alone, both pixel blocks each, the
-//      layer ran on two of a CU's four SIMDs: batch 1 9.5 -> 8.4 and 8.6 -> 7.8 us; at batch 32,
-//      47 us a launch, the phases of the CU's two workgroups covered it.)
+//      result to an LDS tile [pixel][64 + 8].  (Waves 0 and 1 alone used to take both pixel blocks.  Tiles
+//      of at most 32 pixels keep to those two waves, but no longer multiply a second block that holds
+//      no pixel: batch 1, 4 x 5 tiles, 8.7 -> 7.8 us a launch.  Larger ones have all four SIMDs: batch
+//      4, 7 x 7, 12.0 -> 10.8; batch 32, 8 x 7, 48.7 -> 47.7, the CU's other workgroup covered it.)
 //   4. Last layer: every wave two channel blocks, all of K in registers, 32 pixels at a time through
 //      the wave's transpose buffer; + the input's centre pixels from the first region (fp16 + fp16),
 //      activation, a pixel's 2 x 64 bytes stored by adjacent instructions.
@@ -4651,7 +4652,8 @@ __global__ __launch_bounds__(256) void k_fc_fin(const DlfFcArgs a)
 // K1: the filter is 1x1 without padding (and no pool), K3: it is 3x3.  A wave's way to its first request is what the launch
 // waits for beside the round trip itself (0.5 of 2.2 - 3 us): built for the filter, the tap masks need no loops and a 1x1
 // layer of stride 1 no divisions.  With the residual operand of all of a thread's turns requested at the start, ResNet-50 batch 1
-// 206.6 -> 197.0 us, ResNet-18 at 173 x 173 batch 5 124.8 -> 120.2, VGG-16 batch 1 159.3 -> 157.1.
+// 206.6 -> 197.0 us, ResNet-18 at 173 x 173 batch 5 124.8 -> 120.2, VGG-16 batch 1 159.3 -> 157.1 (of that the 3x3 builds, with the
+// general one in their place: 0.8, 2.2 and 0.7).  A second operand pair comes with 1x1 filters only.
 template <int TP, int TC, int D, bool P2, bool K1, bool K3>
 __global__ __launch_bounds__(512) void k_skc(const DlfSkcArgs a)
 {
@@ -5112,8 +5114,8 @@ __global__ __launch_bounds__(DLF_SKD_MAX_WAVES * 64) void k_skd(const DlfSkdArgs
 // 4-channel pixels (stage_rowfold's form: a filter row is one K of 32, eight pixels x four channels); the pixels of the next tile are
 // requested ahead of the multiplies of this one.  32 pixels of the convolution per wave and turn go to LDS in fp16, pixels outside
 // the map as -inf; then a thread takes the maximum of nine for one pooled pixel and eight channels.
-// Per launch, as a group of the fused-group kernel -> now: 224 x 224 batch 1 11.1 -> 5.0 us, batch 32 35.8 -> 25.6; 173 x 173 batch 5
-// 11.1 -> 6.6.  What bounds it at 32 images is the sum of a tile's phases (4.9 us: multiplies 2.1 of 0.75 at the matrix pipes' rate,
+// Per launch, as a group of the fused-group kernel -> now: 224 x 224 batch 1 10.5 -> 4.9 us, batch 4 12.5 -> 6.5, batch 32 35.8 -> 24.3 (another
+// card 25.6); 173 x 173 batch 5 11.1 -> 6.4.  What bounds it at 32 images is the sum of a tile's phases (4.9 us: multiplies 2.1 of 0.75 at the matrix pipes' rate,
 // pool 1.2, the patch and barriers 1.6): rows as direct loads with a second pass in LDS, or three workgroups to a CU with a channel block
 // per wave, take as long.
 template <typename T> __device__ __forceinline__ T load_unaligned(const char* p)
